@@ -2203,42 +2203,93 @@ __global__ __launch_bounds__(256) void k_pack_w(const uint16_t *__restrict__ wt,
     dst[d] = wt[(int64_t)col * in + k];
 }
 
-// Writes an adapter's packed form (see the top of this file).  One thread per destination element.
-// A: [in][r] row-major -> dst of r8*in elements.
-__global__ __launch_bounds__(256) void k_pack_a(const uint16_t *__restrict__ A, int in, int r, int r8,
-                                                uint16_t *__restrict__ dst)
+// ------------------------------------------------------------------------------------------------
+// Writes an adapter's packed form (see the top of this file), both matrices in one launch: the first n_a
+// work groups (of one wavefront) take A, the others B.  An adapter is at most a few megabytes and a launch
+// lasts as long as its shortest chain of trips to memory, so what counts is that there is one launch and not
+// two, and that every load is requested at once.  A thread reads an 8 x 8 block with eight 16-byte loads of
+// consecutive columns, turns it in registers and writes eight 16-byte pieces: for A (8 k of 8 rank rows)
+// they are 128 consecutive bytes of a row block, for B (8 rank rows of 8 columns) one piece of each of the
+// strip's eight sub-blocks, 16 threads side by side.  Where a 16-byte load is not possible (A's rows start
+// at multiples of 2 r bytes: r not a multiple of 8; or a source that is not 16-byte aligned) a thread
+// gathers one 16-byte piece with eight 2-byte loads.  16 adapters of ranks 8 .. 128 at 4096 -> 4096, one call
+// each: 109 us with a launch per matrix and a thread per element, 68 us this way.
+// ------------------------------------------------------------------------------------------------
+constexpr int kPackThreads = 64;
+
+// words of row i of the transpose of the 8 x 8 block of 16-bit values whose rows are `in`
+static __device__ __forceinline__ uint4 block_column(const uint4 (&in)[8], int i)
 {
-    const int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (d >= (int64_t)r8 * in) return;
-    const int jb = (int)(d / (16 * (int64_t)in));
-    const int h = min(16, r8 - 16 * jb);
-    const int64_t idx = d - (int64_t)jb * 16 * in;
-    const int s = (int)(idx / (32 * h));
-    const int rem = (int)(idx % (32 * h));
-    const int kq = rem / (8 * h);
-    const int n = (rem % (8 * h)) / 8;
-    const int e = rem % 8;
-    const int j = 16 * jb + n;
-    const int k = 32 * s + 8 * kq + e;
-    dst[d] = j < r ? A[(int64_t)k * r + j] : (uint16_t)0;
+    auto word = [&](const uint4 &v) __attribute__((always_inline)) {
+        return (i >> 1) == 0 ? v.x : (i >> 1) == 1 ? v.y : (i >> 1) == 2 ? v.z : v.w;
+    };
+    auto pair = [&](const uint4 &lo, const uint4 &hi) __attribute__((always_inline)) {
+        return (i & 1) ? (word(lo) >> 16) | (word(hi) & 0xFFFF0000u) : (word(lo) & 0xFFFFu) | (word(hi) << 16);
+    };
+    return uint4{pair(in[0], in[1]), pair(in[2], in[3]), pair(in[4], in[5]), pair(in[6], in[7])};
 }
 
-// B: [r][out] row-major -> dst of out*r8 elements.
-__global__ __launch_bounds__(256) void k_pack_b(const uint16_t *__restrict__ B, int out, int r, int r8,
-                                                uint16_t *__restrict__ dst)
+__global__ __launch_bounds__(kPackThreads) void k_pack_adapter(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
+                                                               int in, int out, int r, int r8, int vec_a, int vec_b,
+                                                               unsigned n_a, uint16_t *__restrict__ dst_a,
+                                                               uint16_t *__restrict__ dst_b)
 {
-    const int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (d >= (int64_t)out * r8) return;
-    const int strip = (int)(d / (128 * r8));
-    const int idx = (int)(d % (128 * r8));
-    const int b = idx / (16 * r8);
-    const int rem = idx % (16 * r8);
-    const int kp = rem / 128;
-    const int n = (rem % 128) / 8;
-    const int e = rem % 8;
-    const int c = 128 * strip + 8 * n + b;
-    const int j = 8 * kp + e;
-    dst[d] = j < r ? B[(int64_t)j * out + c] : (uint16_t)0;
+    const uint4 zero = {0u, 0u, 0u, 0u};
+    const int octets = r8 >> 3;
+    if (blockIdx.x < n_a) {
+        const unsigned t = blockIdx.x * kPackThreads + threadIdx.x;
+        if (vec_a) {
+            // octet jo of the rank rows (r = r8 here), octet ko of k
+            const int jo = (int)(t % (unsigned)octets), ko = (int)(t / (unsigned)octets);
+            if (ko >= in >> 3) return;
+            uint4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = ld16_stream(A + (int64_t)(8 * ko + i) * r + 8 * jo);
+            const int jb = jo >> 1, h = min(16, r8 - 16 * jb);
+            uint16_t *d = dst_a + (int64_t)16 * jb * in + (int64_t)(ko >> 2) * 32 * h + ((ko & 3) * h + 8 * (jo & 1)) * 8;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) *reinterpret_cast<uint4 *>(d + 8 * i) = block_column(v, i);
+        } else {
+            // one 16-byte piece: 8 k of rank row j
+            const int j = (int)(t % (unsigned)r8), ko = (int)(t / (unsigned)r8);
+            if (ko >= in >> 3) return;
+            uint32_t e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = A[(int64_t)(8 * ko + i) * r + min(j, r - 1)];
+            const int jb = j >> 4, h = min(16, r8 - 16 * jb);
+            const uint4 p = {e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+            *reinterpret_cast<uint4 *>(dst_a + (int64_t)16 * jb * in + (int64_t)(ko >> 2) * 32 * h +
+                                       ((ko & 3) * h + (j & 15)) * 8) = j < r ? p : zero;
+        }
+        return;
+    }
+    const unsigned t = (blockIdx.x - n_a) * kPackThreads + threadIdx.x;
+    if (vec_b) {
+        // columns 8 co .. + 7 of rank rows 8 kp .. + 7
+        const int co = (int)(t % (unsigned)(out >> 3)), kp = (int)(t / (unsigned)(out >> 3));
+        if (kp >= octets) return;
+        uint4 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = ld16_stream(B + (int64_t)min(8 * kp + i, r - 1) * out + 8 * co);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (8 * kp + i >= r) v[i] = zero;
+        uint16_t *d = dst_b + (int64_t)128 * (co >> 4) * r8 + (kp * 16 + (co & 15)) * 8;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) *reinterpret_cast<uint4 *>(d + (int64_t)b * octets * 128) = block_column(v, b);
+    } else {
+        // one 16-byte piece: 8 rank rows of column c
+        const int c = (int)(t % (unsigned)out), kp = (int)(t / (unsigned)out);
+        if (kp >= octets) return;
+        uint32_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = B[(int64_t)min(8 * kp + i, r - 1) * out + c];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (8 * kp + i >= r) e[i] = 0u;
+        *reinterpret_cast<uint4 *>(dst_b + (int64_t)128 * (c >> 7) * r8 + (((c & 7) * octets + kp) * 16 + ((c & 127) >> 3)) * 8) =
+            uint4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2455,9 +2506,13 @@ hipError_t static_scratch(void **ptr)
 hipError_t launch_pack_adapter(const uint16_t *A, const uint16_t *B, int in, int out, int r, int r8,
                                uint16_t *dst_a, uint16_t *dst_b, hipStream_t stream)
 {
-    const int64_t na = (int64_t)r8 * in, nb = (int64_t)out * r8;
-    hipLaunchKernelGGL(k_pack_a, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, stream, A, in, r, r8, dst_a);
-    hipLaunchKernelGGL(k_pack_b, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, stream, B, out, r, r8, dst_b);
+    // threads: one per 8 x 8 block, or (no 16-byte loads) one per 16-byte piece
+    const int vec_a = r % 8 == 0 && (uintptr_t)A % 16 == 0, vec_b = (uintptr_t)B % 16 == 0;
+    const int64_t ta = (int64_t)(in / 8) * (vec_a ? r8 / 8 : r8), tb = (int64_t)(r8 / 8) * (vec_b ? out / 8 : out);
+    const int64_t ga = (ta + kPackThreads - 1) / kPackThreads, gb = (tb + kPackThreads - 1) / kPackThreads;
+    if (ga + gb > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_pack_adapter, dim3((unsigned)(ga + gb)), dim3(kPackThreads), 0, stream, A, B, in, out, r, r8, vec_a,
+                       vec_b, (unsigned)ga, dst_a, dst_b);
     return hipGetLastError();
 }
 
