@@ -348,15 +348,16 @@ lora_status_t lora_apply(const lora_pool_t *pool, const lora_segments_t *seg, co
  * frozen layer plus the low-rank pair of Background, "Low-Rank Adaptation", computed together as a
  * serving system does for each adapted projection (Motivation, Fig. 3).  y is written once and never
  * read, where lora_apply reads and re-writes what a separate base GEMM wrote.  Launches: the shrink of
- * lora_apply (v into the workspace), then one GEMM kernel over 256 x 128 tiles of y whose rows follow
- * the segment object's grouping (x is gathered and y scattered through it; no copy of either).
+ * lora_apply (s v into the workspace), then one GEMM kernel over tiles of y (256 x 256, 64 x 64 or smaller, by
+ * the batch) whose rows follow the segment object's grouping (x is gathered and y scattered through it; no
+ * copy of either).
  *   w_packed: the base weight in the kernel's operand order, made once by lora_linear_pack_weight from
  *             W^T [out][in] row-major bf16 (the layout of a linear layer's weight), in_features *
  *             out_features * 2 bytes of device memory, 256-byte aligned, owned by the caller;
  *   x, y, workspace, stream: as for lora_apply (workspace size: lora_apply_workspace_bytes); y need not be
  *             initialised.  Single-pool segment objects only.
- * fp32 accumulation of x W and of the delta (each in one accumulator, the delta scaled once), one
- * rounding to bf16. */
+ * fp32 accumulation of x W and of the delta, one rounding to bf16; v is scaled in fp32 before it is split
+ * into bf16 hi + lo. */
 lora_status_t lora_linear_pack_weight(const void *wt_out_by_in, int32_t in_features, int32_t out_features,
                                       void *dev_packed, void *stream);
 lora_status_t lora_linear(const lora_pool_t *pool, const lora_segments_t *seg, const void *x, int64_t ldx,

@@ -16,7 +16,7 @@
 #include <unordered_map>
 #include <vector>
 
-using lora::LinBlock;
+using lora::LinPiece;
 using lora::SegRec;
 using lora::Unit;
 
@@ -94,11 +94,13 @@ struct lora_segments {
     std::vector<Unit> shrink_units, prefill_units, expand_units, expand_big_units;
     // the one-launch decode form's own lists, by place in the launch (empty places have ntok == 0)
     std::vector<Unit> fused_shrink, fused_expand;
-    // the adapted layer's row order (lora_linear): batch row of every place (-1: none) and the adapter of
-    // every 16 places; all T tokens are in it, the ones without adapter last
+    // the adapted layer's row order (lora_linear): batch row of every place (-1: none), behind them where
+    // every block of 16 places has its first piece, and the pieces of one adapter each; all T tokens are in
+    // it, the ones without adapter last
     std::vector<int32_t> lin_rows;
-    std::vector<LinBlock> lin_blocks;
-    size_t off_lin_rows, off_lin_blocks;
+    std::vector<LinPiece> lin_pieces;
+    int lin_front;  // places of the small groups start here
+    size_t off_lin_rows, off_lin_pieces;
     // device table: [perm | shrink units | prefill shrink units | expand units | arrival counters,
     // ready counters, time-out flag]
     char *dev;
@@ -741,6 +743,9 @@ static void order_heavy_units_by_xcd(std::vector<Unit> &units)
     units.swap(out);
 }
 
+// groups of at least this many tokens go to the front of the adapted layer's row order (lora_linear)
+static const int kLinFillingGroup = 16;
+
 static int g_compute_units = 256;  // of the chip: a whole-k launch within this many units is one round
 static int opt_big_runs_max_units(const lora_segments *sg)
 {
@@ -782,8 +787,8 @@ static void layout_table(lora_segments *sg)
     sg->off_fused_shrink = round_up_sz(sg->off_expand_big + sg->expand_big_units.size() * sizeof(Unit), 256);
     sg->off_fused_expand = round_up_sz(sg->off_fused_shrink + sg->fused_shrink.size() * sizeof(Unit), 256);
     sg->off_lin_rows = round_up_sz(sg->off_fused_expand + sg->fused_expand.size() * sizeof(Unit), 256);
-    sg->off_lin_blocks = round_up_sz(sg->off_lin_rows + sg->lin_rows.size() * sizeof(int32_t), 256);
-    sg->off_sync = round_up_sz(sg->off_lin_blocks + sg->lin_blocks.size() * sizeof(LinBlock), 256);
+    sg->off_lin_pieces = round_up_sz(sg->off_lin_rows + sg->lin_rows.size() * sizeof(int32_t), 256);
+    sg->off_sync = round_up_sz(sg->off_lin_pieces + sg->lin_pieces.size() * sizeof(LinPiece), 256);
     sg->table_bytes = round_up_sz(sg->off_sync + (size_t)(2 * sg->n_sync + 4 + 2 * 256) * sizeof(unsigned), 256);
 }
 
@@ -1179,37 +1184,43 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         finish_decode_fused(sg, pool->in_features);
     else
         sg->decode_fused = false;
-    // row order of the adapted layer: groups in table order, each padded to a multiple of 16 places, then
-    // the tokens without adapter, the whole padded to a multiple of the kernel's row tile
+    // row order of the adapted layer: groups that fill blocks of 16 rows, the tokens without adapter, then the
+    // small groups (the kernel's large tiles take rows from the front, and a block of many adapters costs
+    // them most), the whole padded to a multiple of the kernel's row tile
     sg->lin_rows.clear();
-    sg->lin_blocks.clear();
+    sg->lin_pieces.clear();
     if (n_projections == 1 && T > 0) {
-        auto add_group = [&](const int32_t *toks, int n, const SegRec *r) {
-            for (int t0 = 0; t0 < n; t0 += 16) {
-                LinBlock b;
-                memset(&b, 0, sizeof b);
-                b.ntok = std::min(16, n - t0);
-                if (r) {
-                    b.b_off = r->b_off;
-                    b.v_off = r->v_off + (int64_t)t0 * r->r8;
-                    b.r8 = r->r8;
-                    b.scale = r->scale;
+        const size_t places = ((size_t)T + lora::kLinTileM - 1) / lora::kLinTileM * lora::kLinTileM;
+        sg->lin_rows.reserve(places + places / 16 + 1);
+        std::vector<int32_t> per_block(places / 16 + 1, 0);
+        auto add_groups = [&](bool filling) {
+            for (const SegRec &r : sg->segs) {
+                if ((r.ntok >= kLinFillingGroup) != filling) continue;
+                int32_t at = (int32_t)sg->lin_rows.size();
+                const int32_t first = at, end = at + r.ntok;
+                sg->lin_rows.insert(sg->lin_rows.end(), sg->perm.begin() + r.tok_start, sg->perm.begin() + r.tok_start + r.ntok);
+                while (at < end) {
+                    LinPiece q;
+                    memset(&q, 0, sizeof q);
+                    q.place = at;
+                    q.ntok = std::min(end, at / 16 * 16 + 16) - at;
+                    q.b_off = r.b_off;
+                    q.v_off = r.v_off + (int64_t)(at - first) * r.r8;
+                    q.r8 = r.r8;
+                    sg->lin_pieces.push_back(q);
+                    ++per_block[at / 16 + 1];
+                    at += q.ntok;
                 }
-                sg->lin_blocks.push_back(b);
-                for (int q = 0; q < 16; ++q) sg->lin_rows.push_back(q < b.ntok ? toks[t0 + q] : -1);
             }
         };
-        for (const SegRec &r : sg->segs) add_group(sg->perm.data() + r.tok_start, r.ntok, &r);
-        std::vector<int32_t> none;
+        add_groups(true);
         for (int32_t t = 0; t < T; ++t)
-            if (ta[t] < 0) none.push_back(t);
-        add_group(none.data(), (int)none.size(), nullptr);
-        while (sg->lin_rows.size() % lora::kLinTileM) {
-            LinBlock b;
-            memset(&b, 0, sizeof b);
-            sg->lin_blocks.push_back(b);
-            sg->lin_rows.insert(sg->lin_rows.end(), 16, -1);
-        }
+            if (ta[t] < 0) sg->lin_rows.push_back(t);
+        sg->lin_front = (int)sg->lin_rows.size();
+        add_groups(false);
+        sg->lin_rows.resize(places, -1);
+        for (size_t b = 1; b < per_block.size(); ++b) per_block[b] += per_block[b - 1];
+        sg->lin_rows.insert(sg->lin_rows.end(), per_block.begin(), per_block.end());
     }
     layout_table(sg);
     return LORA_OK;
@@ -1443,7 +1454,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
     sg->fused_expand.clear();
     sg->fused_grid = 0;
     sg->lin_rows.clear();
-    sg->lin_blocks.clear();
+    sg->lin_pieces.clear();
     layout_table(sg);
     return LORA_OK;
 }
@@ -1579,8 +1590,8 @@ static lora_status_t upload_table(lora_segments *sg, hipStream_t s)
         memcpy(sg->staging + sg->off_fused_expand, sg->fused_expand.data(), sg->fused_expand.size() * sizeof(Unit));
     if (!sg->lin_rows.empty())
         memcpy(sg->staging + sg->off_lin_rows, sg->lin_rows.data(), sg->lin_rows.size() * sizeof(int32_t));
-    if (!sg->lin_blocks.empty())
-        memcpy(sg->staging + sg->off_lin_blocks, sg->lin_blocks.data(), sg->lin_blocks.size() * sizeof(LinBlock));
+    if (!sg->lin_pieces.empty())
+        memcpy(sg->staging + sg->off_lin_pieces, sg->lin_pieces.data(), sg->lin_pieces.size() * sizeof(LinPiece));
     memset(sg->staging + sg->off_sync, 0, sg->table_bytes - sg->off_sync);
     sg->launches = 0;
     if (sg->table_bytes) HIP_TRY(hipMemcpyAsync(sg->dev, sg->staging, sg->table_bytes, hipMemcpyHostToDevice, s));
@@ -1881,6 +1892,7 @@ static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_f
     c.n_units = (int)list.size();
     c.in_features = in_features;
     c.out_features = out_features;
+    c.scale_v = 0;
     return c;
 }
 
@@ -2204,8 +2216,9 @@ try {
     sa.epoch = 0;
     sa.spin_limit = opt_spin_limit(sg);
     if (sg->n_active > 0) {
-        // the shrink half of lora_apply's separate-launch forms: v complete as bf16 hi + lo in the workspace
-        const lora::LaunchCtx cs = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, kPrefill);
+        // the shrink half of lora_apply's separate-launch forms: s_a v complete as bf16 hi + lo in the workspace
+        lora::LaunchCtx cs = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, kPrefill);
+        cs.scale_v = cp.scale_v = 1;
         if (opt_merged(sg) && sg->has_big_units && !sg->wide && cs.n_units > 0) {
             HIP_TRY(lora::launch_shrink_mixed(cp, sg->n_prefill_hi, cs, (const uint16_t *)x, ldx, sg->k_slice_len, parts, nsl,
                                               stride, &sa, s));
@@ -2219,8 +2232,10 @@ try {
                 HIP_TRY(lora::launch_shrink(cs, (const uint16_t *)x, ldx, sg->k_slice_len, parts, nsl, stride, &sa, s));
         }
     }
-    HIP_TRY(lora::launch_linear_lora((const int32_t *)(sg->dev + sg->off_lin_rows),
-                                     (const LinBlock *)(sg->dev + sg->off_lin_blocks), (int)sg->lin_rows.size(), pool->arena,
+    const int32_t *rows = (const int32_t *)(sg->dev + sg->off_lin_rows);
+    const size_t places = ((size_t)sg->T + lora::kLinTileM - 1) / lora::kLinTileM * lora::kLinTileM;
+    const lora::LinBlock blocks = {rows + places, (const LinPiece *)(sg->dev + sg->off_lin_pieces), sg->lin_front};
+    HIP_TRY(lora::launch_linear_lora(rows, &blocks, sg->T, pool->arena,
                                      (const uint16_t *)w_packed, (const uint16_t *)x, ldx, in, out, sa.v_hi, sa.v_lo,
                                      (uint16_t *)y, ldy, s));
     return LORA_OK;

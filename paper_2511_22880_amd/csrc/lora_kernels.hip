@@ -17,7 +17,10 @@
 // takes one unit.  No unit ever depends on another adapter's rank.
 #include "lora_internal.h"
 
+#include <algorithm>
 #include <atomic>
+#include <cmath>
+#include <type_traits>
 
 namespace lora {
 
@@ -92,6 +95,7 @@ struct Sync {
     unsigned epoch;
     unsigned spin_limit;
     int wait;                 // expand units poll `ready` (single launch) or not (expand launched after shrink)
+    int scale_v;              // shrink: v_hi / v_lo receive s_a v, not v
 };
 
 static __device__ __forceinline__ void st_through_f32x4(float *p, f32x4 v)
@@ -310,11 +314,12 @@ static __device__ __forceinline__ void shrink_body(const Unit &u, const uint16_t
                 if (lane == 0) atomicExch(sy.counters + u.sync_idx, 0u);
                 const int64_t tile_off = u.v_off - u.p0;
                 const int tasks = ntok * (u.r8 >> 3);
+                const float vs = sy.scale_v ? u.scale : 1.f;
                 for (int task = lane; task < tasks; task += 64) {
                     f32x4 f0, f1;
                     sum_slices(v_out + tile_off + 8 * task, n_slices, slice_stride, f0, f1);
                     uint4 ph, pl;
-                    split_bf16(f0, f1, ph, pl);
+                    split_bf16(vs * f0, vs * f1, ph, pl);
                     st_through_u16x8(sy.v_hi + tile_off + 8 * task, ph);
                     st_through_u16x8(sy.v_lo + tile_off + 8 * task, pl);
                 }
@@ -377,7 +382,7 @@ __global__ __launch_bounds__(64 * WAVES, kWideWaves / WAVES) void k_shrink_wide(
                                                               int k_slice_len, int n_slices,
                                                               float *__restrict__ v_f32,
                                                               uint16_t *__restrict__ v_hi,
-                                                              uint16_t *__restrict__ v_lo)
+                                                              uint16_t *__restrict__ v_lo, int scale_v)
 {
     constexpr int ROLES = kWideWaves / WAVES;
     // the sixteen partial tiles: behind the x regions, or (8 wavefronts, so that two work groups fit the
@@ -496,6 +501,7 @@ __global__ __launch_bounds__(64 * WAVES, kWideWaves / WAVES) void k_shrink_wide(
         if (x_ok && 4 * kq < pn) {
             const int64_t off = u.v_off + (int64_t)i * u.r8 + 4 * kq;
             if (v_hi) {
+                if (scale_v) t = u.scale * t;
                 uint2 h, l;
                 h.x = pack_bf16_rne(t[0], t[1]);
                 h.y = pack_bf16_rne(t[2], t[3]);
@@ -732,6 +738,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
     __syncthreads();
     if (wave != 0) return;
 
+    const float vs = sy.scale_v ? u.scale : 1.f;
     // lane (n, kq) holds, for token block tb and row block jb, v[token n][16*jb + 4*kq + e]
     if (n_ks == 1) {
 #pragma unroll
@@ -742,7 +749,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
             for (int jb = 0; jb < JB; ++jb) {
                 const int j = 16 * jb + 4 * kq;
                 if (j < r8)
-                    store_v4(acc[jb][tb] + red[0][jb * TB + tb][lane], row + j, v_hi, v_lo, v_f32, n_slices,
+                    store_v4(vs * (acc[jb][tb] + red[0][jb * TB + tb][lane]), row + j, v_hi, v_lo, v_f32, n_slices,
                              slice_stride);
             }
         }
@@ -786,7 +793,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
             f32x4 f0, f1;
             sum_slices(parts + u.v_off + 8 * task, n_ks, slice_stride, f0, f1);
             uint4 ph, pl;
-            split_bf16(f0, f1, ph, pl);
+            split_bf16(vs * f0, vs * f1, ph, pl);
             st_through_u16x8(v_hi + u.v_off + 8 * task, ph);
             st_through_u16x8(v_lo + u.v_off + 8 * task, pl);
         }
@@ -958,6 +965,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     if (g_clock_buf && threadIdx.x == 0 && blockIdx.x < g_clock_slots) g_clock_buf[(size_t)blockIdx.x * 8 + 1] = c_wait;
     LORA_CLOCK(2);
 #endif
+    const float vs = sy.scale_v ? u.scale : 1.f;
     // lane (n, kq) holds, for token block tb and its row block j, v[token 16 tb + n][16 jb + 4 kq + e]
     if (n_ks == 1) {
 #pragma unroll
@@ -967,7 +975,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
 #pragma unroll
             for (int j = 0; j < JBW; ++j) {
                 const int jr = 16 * (wave * JBW + j) + 4 * kq;
-                if (jr < r8) store_v4(acc[j][tb], row + jr, v_hi, v_lo, v_f32, n_slices, slice_stride);
+                if (jr < r8) store_v4(vs * acc[j][tb], row + jr, v_hi, v_lo, v_f32, n_slices, slice_stride);
             }
         }
         return;
@@ -1009,7 +1017,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
             f32x4 f0, f1;
             sum_slices(parts + u.v_off + 8 * task, n_ks, slice_stride, f0, f1);
             uint4 ph, pl;
-            split_bf16(f0, f1, ph, pl);
+            split_bf16(vs * f0, vs * f1, ph, pl);
             st_through_u16x8(v_hi + u.v_off + 8 * task, ph);
             st_through_u16x8(v_lo + u.v_off + 8 * task, pl);
         }
@@ -1982,9 +1990,10 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const float *__restrict__
 // ------------------------------------------------------------------------------------------------
 // The adapted layer as one GEMM whose epilogue adds the delta: y = bf16(x W + s_a (x A_a) B_a), y written
 // once and never read (the delta on its own reads y and writes it back: two thirds of its traffic on
-// token-heavy batches).  Rows are taken in the order "tokens grouped by adapter, groups padded to
-// multiples of 16", so that every 16-row MFMA block has one adapter; x is gathered and y scattered
-// through that order, so no copy of either is made.
+// token-heavy batches).  Rows are taken in the order "tokens grouped by adapter", without padding between
+// the groups; x is gathered and y scattered through that order, so no copy of either is made.  A 16-row
+// MFMA block may hold several adapters: its delta is added piece by piece (LinPiece), each piece's MFMAs
+// with the other rows' v at zero.
 //   * One work group (8 wavefronts) computes a 256 x 256 tile, wavefront w the rows 64 (w mod 4) .. + 63
 //     of it and the 128-column strip w / 4: 4 x 8 MFMA tiles of 16 x 16, 128 accumulator registers.  With
 //     the columns of sub-block b being 8 n + b, lane n ends up with 8 consecutive columns of 4 tokens per
@@ -2001,9 +2010,10 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const float *__restrict__
 //     W, one k step; pair j is computed from slots 2 j and 2 j + 1 while the copies of the next three
 //     slots are in flight, one barrier per pair.  Inside a 1 KB block of x, piece p of row r sits in
 //     slot 8 r + (p XOR r), so that the 8 lanes that read one piece of 8 rows meet 8 bank groups.
-//   * After the k loop every row block adds s (v_hi + v_lo) B_a for its adapter: ceil(r8 / 32) more k
-//     steps whose operands come straight from memory (v rows, and B^T in the pool's operand order,
-//     the very pieces the expand kernels read), accumulated apart and scaled once, as the expand does.
+//   * Before the k loop, while its first copies are on their way, every wavefront starts its accumulators with
+//     (s v_hi + s v_lo) B_a of its rows' adapters: ceil(r8 / 32) more k steps (v rows, and B^T in the pool's
+//     operand order, the very pieces the expand kernels read; v was scaled before its split), B^T taken once
+//     for all row blocks of one adapter.
 // ------------------------------------------------------------------------------------------------
 constexpr int kLinThreads = 512;
 constexpr int kLinRing = 5;
@@ -2012,23 +2022,77 @@ constexpr int kLinWBuf = 8 * 1024 * (kLinTileN / 128);  // bytes of W per slot: 
 constexpr int kLinLds = kLinRing * (kLinXBuf + kLinWBuf);  // 160 KB, all of a compute unit's LDS: one work group per compute unit
 static_assert(kLinTileM == 256 && kLinTileN == 256, "the wavefront roles below are written for 256 x 256");
 
-__global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
-    const int32_t *__restrict__ rows, const LinBlock *__restrict__ blocks, int m_tiles, int mt_per_xcd, int n_tiles,
-    const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp, const uint16_t *__restrict__ x, int64_t ldx,
-    int in, int out, const uint16_t *__restrict__ v_hi, const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y,
-    int64_t ldy)
+// v B_a of one piece for NB sub-blocks from b0 of the strip at column c0: rows outside the piece get zero.  NK
+// 32-wide steps of the rank from j0, all their operands requested before the first is used.
+template <int NB, int NK>
+static __device__ __forceinline__ void lin_delta_steps(const LinPiece &pc, int j0, const uint16_t *__restrict__ bt, int b0,
+                                                       bool row_ok, int64_t v_row, int kq,
+                                                       const uint16_t *__restrict__ v_hi,
+                                                       const uint16_t *__restrict__ v_lo, f32x4 (&dl)[NB])
 {
-    __shared__ __attribute__((aligned(16))) char lds[kLinLds];
-    // Work group b runs on XCD b mod 8.  Each XCD takes a run of row tiles, and the 32 work groups it runs
-    // at a time (one per compute unit) are 8 row tiles x 4 column tiles that walk k together: every
-    // chunk of x and of W that one of them brings into the XCD's L2 serves four or eight of them.
-    const int xcd = blockIdx.x & 7, jloc = blockIdx.x >> 3;
-    const int ngroups_n = (n_tiles + 3) >> 2;
-    const int grp = jloc >> 5, within = jloc & 31;
-    const int mt_loc = (grp / ngroups_n) * 8 + (within >> 2);
-    const int nt = (grp % ngroups_n) * 4 + (within & 3);
-    const int mt = xcd * mt_per_xcd + mt_loc;
-    if (mt_loc >= mt_per_xcd || mt >= m_tiles || nt >= n_tiles) return;
+    const uint4 zero = {0u, 0u, 0u, 0u};
+    const int r8 = pc.r8;
+    uint4 vh[NK], vl[NK], w[NK][NB];
+#pragma unroll
+    for (int st = 0; st < NK; ++st) {
+        const int j = j0 + 32 * st + 8 * kq, jc = j < r8 ? j : 0;  // lanes beyond the rank: any address, v at zero
+        vh[st] = ld16(v_hi + v_row + jc);
+        vl[st] = ld16(v_lo + v_row + jc);
+        // piece (sub-block b0 + b, rank piece jc / 8, column slot n) of the strip's B^T tile
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w[st][b] = ld16(bt + ((b0 + b) * (r8 >> 3) + (jc >> 3)) * 128);
+    }
+#pragma unroll
+    for (int st = 0; st < NK; ++st) {
+        const bool ok = row_ok && j0 + 32 * st + 8 * kq < r8;
+        const bf16x8 h = as_bf16x8(ok ? vh[st] : zero), l = as_bf16x8(ok ? vl[st] : zero);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            dl[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h, as_bf16x8(w[st][b]), dl[b], 0, 0, 0);
+            dl[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, as_bf16x8(w[st][b]), dl[b], 0, 0, 0);
+        }
+    }
+}
+
+template <int NB, int NK>
+static __device__ __forceinline__ void lin_delta(const LinPiece &pc, const uint16_t *__restrict__ arena, size_t c0, int b0,
+                                                 int n, int kq, const uint16_t *__restrict__ v_hi,
+                                                 const uint16_t *__restrict__ v_lo, f32x4 (&dl)[NB])
+{
+    const int r8 = pc.r8, row = n - (pc.place & 15);
+    const bool row_ok = row >= 0 && row < pc.ntok;
+    const uint16_t *bt = arena + pc.b_off + c0 * r8 + n * 8;
+    const int64_t v_row = pc.v_off + (int64_t)(row_ok ? row : 0) * r8;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) dl[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (r8 <= 32)
+        lin_delta_steps<NB, 1>(pc, 0, bt, b0, row_ok, v_row, kq, v_hi, v_lo, dl);
+    else if (r8 <= 64)
+        lin_delta_steps<NB, 2>(pc, 0, bt, b0, row_ok, v_row, kq, v_hi, v_lo, dl);
+    else
+        for (int j = 0; j < r8; j += 32 * NK) lin_delta_steps<NB, NK>(pc, j, bt, b0, row_ok, v_row, kq, v_hi, v_lo, dl);
+}
+
+// adds it to the piece's own rows: the zeros above times another adapter's weights are zero only if those are
+// finite, and what an adapter holds must not reach the tokens of its neighbours
+template <int NB>
+static __device__ __forceinline__ void lin_add(const LinPiece &pc, int kq, const f32x4 (&dl)[NB], f32x4 (&acc)[NB])
+{
+    const int row0 = pc.place & 15;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bool mine = 4 * kq + e >= row0 && 4 * kq + e < row0 + pc.ntok;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][e] = mine ? acc[b][e] + dl[b][e] : acc[b][e];
+    }
+}
+
+static __device__ __forceinline__ void linear_big_body(
+    int mt, int nt, const int32_t *__restrict__ rows, const int32_t *__restrict__ start,
+    const LinPiece *__restrict__ pieces, const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp,
+    const uint16_t *__restrict__ x, int64_t ldx, int in, int out, const uint16_t *__restrict__ v_hi,
+    const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y, int64_t ldy, char *lds)
+{
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2037,7 +2101,6 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
     const bool has_strip = strip * 128 < out;    // out is a multiple of 128: the last tile may hold one strip
     const int n = lane & 15, kq = lane >> 4;
     const int m0 = mt * kLinTileM;
-    const uint4 zero = {0u, 0u, 0u, 0u};
     auto xbuf = [&](int which) __attribute__((always_inline)) { return lds + which * (kLinXBuf + kLinWBuf); };
     auto wbuf = [&](int which) __attribute__((always_inline)) { return lds + which * (kLinXBuf + kLinWBuf) + kLinXBuf; };
 
@@ -2091,6 +2154,89 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
 #pragma unroll
     for (int h = 0; h < 3; ++h)
         if (h < nh) issue(h, h);
+    // ---- the delta, while the first copies are on their way: the accumulators start with it ----
+    const int c0 = strip * 128;
+    if (has_strip) {
+        const int32_t *st = start + (m0 >> 4) + 4 * rw;
+        unsigned todo = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) todo |= (st[i] < st[i + 1] ? 1u : 0u) << i;
+        // The first piece of every block: one pass over the rank for all blocks that share its adapter, B^T once
+        // for all of them.
+        while (todo) {
+            const LinPiece &p0 = pieces[st[__builtin_ctz(todo)]];
+            const int r8 = p0.r8;
+            const uint16_t *bt = arena + p0.b_off + (size_t)c0 * r8 + n * 8;
+            unsigned run = 0;
+            bool row_ok[4];
+            int64_t v_row[4];
+            int lo[4], hi[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const LinPiece &pc = pieces[(todo >> i) & 1u ? st[i] : st[__builtin_ctz(todo)]];
+                const bool in_run = ((todo >> i) & 1u) && pc.b_off == p0.b_off;
+                run |= (in_run ? 1u : 0u) << i;
+                lo[i] = pc.place & 15;
+                hi[i] = lo[i] + pc.ntok;
+                row_ok[i] = in_run && n >= lo[i] && n < hi[i];
+                v_row[i] = pc.v_off + (int64_t)(row_ok[i] ? n - lo[i] : 0) * r8;
+            }
+            todo &= ~run;
+            auto steps = [&](auto nk, int j0) __attribute__((always_inline)) {
+                constexpr int NK = decltype(nk)::value;
+                uint4 w[NK][8], vh[NK][4], vl[NK][4];
+#pragma unroll
+                for (int s = 0; s < NK; ++s) {
+                    const int j = j0 + 32 * s + 8 * kq, jc = j < r8 ? j : 0;  // lanes beyond the rank: v at zero
+#pragma unroll
+                    for (int b = 0; b < 8; ++b) w[s][b] = ld16(bt + (size_t)(b * (r8 >> 3) + (jc >> 3)) * 128);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        vh[s][i] = ld16(v_hi + v_row[i] + jc);
+                        vl[s][i] = ld16(v_lo + v_row[i] + jc);
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < NK; ++s)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if ((run >> i) & 1u) {
+                            const bool ok = row_ok[i] && j0 + 32 * s + 8 * kq < r8;
+                            const bf16x8 h = as_bf16x8(ok ? vh[s][i] : uint4{0u, 0u, 0u, 0u});
+                            const bf16x8 l = as_bf16x8(ok ? vl[s][i] : uint4{0u, 0u, 0u, 0u});
+#pragma unroll
+                            for (int b = 0; b < 8; ++b) {
+                                acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h, as_bf16x8(w[s][b]), acc[i][b], 0, 0, 0);
+                                acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l, as_bf16x8(w[s][b]), acc[i][b], 0, 0, 0);
+                            }
+                        }
+            };
+            for (int j = 0; j < r8; j += 32) steps(std::integral_constant<int, 1>{}, j);
+            // the zeros above times the adapter's weights are zero only if those are finite, and what an adapter
+            // holds must not reach the tokens of its neighbours
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (((run >> i) & 1u) && hi[i] - lo[i] < 16)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool mine = 4 * kq + e >= lo[i] && 4 * kq + e < hi[i];
+#pragma unroll
+                        for (int b = 0; b < 8; ++b) acc[i][b][e] = mine ? acc[i][b][e] : 0.f;
+                    }
+        }
+        // blocks where adapters meet: the pieces behind the first
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            for (int q = st[i] + 1; q < st[i + 1]; ++q) {
+                f32x4 dl[8];
+                lin_delta<8, 1>(pieces[q], arena, (size_t)c0, 0, n, kq, v_hi, v_lo, dl);
+                lin_add(pieces[q], kq, dl, acc[i]);
+            }
+    }
+    // Nothing the compiler knows of is in flight now: without this it would take loads of the delta (some are under
+    // conditions) to be outstanding still, and wait for them, and so for the copies, in every pass of the loop.
+    stores_done();
+
     // this wavefront's rows 64 rw .. 64 rw + 63 lie in row half rw / 2, blocks 8 (rw mod 2) .. + 7 of its 16
     const int x_half = rw >> 1;
     const int x_blk0 = 8 * (rw & 1);
@@ -2134,39 +2280,6 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
     }
     if (!has_strip) return;
 
-    // ---- the delta of each row block, then the store of y ----
-    const int c0 = strip * 128;
-    const LinBlock *bks = blocks + (m0 >> 4) + 4 * rw;
-    // the delta of one row block from its own loads of B^T (row blocks whose neighbours have other adapters)
-    auto delta_one = [&](int i) __attribute__((always_inline)) {
-        const LinBlock &bk = bks[i];
-        const int r8 = bk.r8;
-        if (r8 <= 0) return;
-        f32x4 dl[8];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) dl[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const uint16_t *bt = arena + bk.b_off + (size_t)c0 * r8 + n * 8;
-        for (int j = 0; j < r8; j += 32) {
-            const int jj = j + 8 * kq;
-            const bool j_ok = jj < r8;
-            const bool ok = j_ok && n < bk.ntok;
-            const int64_t off = bk.v_off + (int64_t)(ok ? n : 0) * r8 + (j_ok ? jj : 0);
-            uint4 vh = ld16(v_hi + off), vl = ld16(v_lo + off);
-            if (!ok) vh = vl = zero;
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                // piece (sub-block b, rank piece jj / 8, column slot n) of the strip's B^T tile
-                const uint4 wv = ld16(bt + (size_t)(b * (r8 >> 3) + (j_ok ? jj >> 3 : 0)) * 128);
-                dl[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vh), as_bf16x8(wv), dl[b], 0, 0, 0);
-                dl[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vl), as_bf16x8(wv), dl[b], 0, 0, 0);
-            }
-        }
-        const float scale = bk.scale;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[i][b] += scale * dl[b];
-    };
-#pragma unroll
-    for (int i = 0; i < 4; ++i) delta_one(i);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         // lane (n, kq) holds tokens 4 kq + e of the block, columns c0 + 8 n .. + 7
@@ -2183,6 +2296,230 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
             }
         }
     }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The same layer for batches of few tokens, where 256 x 256 tiles would leave most of the chip idle (256 tokens
+// x 4096 columns: 16 tiles) and the time is that of bringing W in once.  Tiles of 16 RB tokens x 16 CB columns
+// (CB sub-blocks of a 128-column strip), one work group each, whose 8 wavefronts split k: wavefront w takes
+// the 64-wide pieces w, w + 8, ... of k, so that what a work group has in flight lies side by side in memory.
+// No operand is shared between wavefronts, so there is no barrier in the loop and no LDS copy of W: a
+// wavefront's W operands come straight from memory in operand order (1 KB per load), its x as full cache lines
+// (128 bytes of 8 rows per load) that pass through a private LDS region to become operands; D pieces of both
+// are in flight per wavefront (registers).  The delta of the tile's adapters is dealt to the wavefronts piece
+// by piece and added to their partial sums; these meet in LDS and are added in wavefront order.
+// 256 tokens of 69 adapters at 4096 -> 4096: 109 us per layer with 256 x 256 tiles, 31 us (the shrink launch, 8 us,
+// included; 19 us for x W alone).  What bounds it is what a compute unit draws: 0.5 MB of W and 0.5 MB of x per
+// 64 x 64 tile at 60 - 70 GB/s.
+// ------------------------------------------------------------------------------------------------
+constexpr int kLinSmallWaves = kLinThreads / 64;
+
+template <int RB, int CB>
+constexpr int kLinSmallLds = kLinSmallWaves * 1024 * (2 * RB > RB * CB ? 2 * RB : RB * CB);  // x regions, then partial sums
+
+// Tile `blk` of those of the rows from place m_first on (a multiple of 256), m_tiles row tiles.
+template <int RB, int CB, int D>
+static __device__ __forceinline__ void linear_small_body(
+    int blk, int m_first, int m_tiles, const int32_t *__restrict__ rows, const int32_t *__restrict__ start,
+    const LinPiece *__restrict__ pieces, const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp,
+    const uint16_t *__restrict__ x, int64_t ldx, int in, int out, const uint16_t *__restrict__ v_hi,
+    const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y, int64_t ldy, char *lds)
+{
+    constexpr int NX = 2 * RB;               // x loads of a wavefront per piece of k: 8 rows each
+    constexpr int kSlab = 16 * RB * 128;     // bytes of a wavefront's x region: 16 RB rows of 64 k
+    constexpr int kTiles = RB * CB;
+    static_assert(8 % CB == 0, "a tile lies in one strip");
+    // Work group b runs on XCD b mod 8: a strip's tiles (all row tiles, all its column tiles) on one XCD, so
+    // that W and the adapters' B^T enter one L2 and the partial lines of y meet there.
+    constexpr int SUB = 8 / CB;
+    const int xcd = blk & 7, jloc = blk >> 3;
+    const int mt = jloc % m_tiles, sub = (jloc / m_tiles) % SUB;
+    const int strip = (jloc / m_tiles / SUB) * 8 + xcd;
+    if (strip * 128 >= out) return;
+    const int b0 = sub * CB;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kq = lane >> 4;
+    const int m0 = m_first + mt * 16 * RB;
+
+    f32x4 acc[RB][CB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int np = in >> 6;  // 64-wide pieces of k
+    const int mine = wave < np ? (np - 1 - wave) / kLinSmallWaves + 1 : 0;
+    if (mine > 0) {
+        // x: lane -> row lane / 8 of the load's 8, 16-byte chunk lane mod 8; in the region chunk c of row r sits in
+        // slot c XOR (r mod 8), so that neither the writes nor the operand reads meet in a bank
+        char *slab = lds + wave * kSlab;
+        const int lr = lane >> 3, lc = lane & 7;
+        const uint16_t *xrow[NX];
+#pragma unroll
+        for (int t = 0; t < NX; ++t) {
+            const int row = rows[m0 + 8 * t + lr];
+            xrow[t] = x + (int64_t)(row < 0 ? 0 : row) * ldx + 64 * wave + 8 * lc;
+        }
+        // (wavefront-uniform addresses plus a 32-bit lane offset: no address registers per load)
+        const uint16_t *wbase = wp + ((size_t)strip * (in / 32) + 2 * wave) * 4096 + b0 * 512;
+        const unsigned lane8 = lane * 8;
+        uint4 xq[D][NX], wq[D][2][CB];
+        // Loads without branches (around one the compiler would wait for everything in flight): past the last
+        // piece all lanes ask for one and the same line, and what comes is not used.
+        auto load_x = [&](int i, uint4(&xs)[NX]) __attribute__((always_inline)) {
+            const bool ok = i < mine;
+#pragma unroll
+            for (int t = 0; t < NX; ++t) xs[t] = ld16(ok ? xrow[t] + (size_t)i * (64 * kLinSmallWaves) : x);
+        };
+        auto load_w = [&](int i, uint4(&ws)[2][CB]) __attribute__((always_inline)) {
+            const bool ok = i < mine;
+            const uint16_t *at = ok ? wbase + (size_t)i * (2 * kLinSmallWaves) * 4096 : wbase;
+            const unsigned off = ok ? lane8 : 0u;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int b = 0; b < CB; ++b) ws[ks][b] = ld16(at + ks * 4096 + b * 512 + off);
+        };
+        auto wave_sync = [&]() __attribute__((always_inline)) {
+            // the region is private to this wavefront and LDS operations of a wavefront complete in order
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_wave_barrier();
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        };
+        auto stage = [&](const uint4(&xs)[NX]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < NX; ++t)
+                *reinterpret_cast<uint4 *>(slab + (8 * t + lr) * 128 + ((lc ^ lr) << 4)) = xs[t];
+        };
+        auto compute = [&](const uint4(&ws)[2][CB]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                bf16x8 xo[RB];
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+                    xo[i] = as_bf16x8(*reinterpret_cast<const uint4 *>(slab + (16 * i + n) * 128 +
+                                                                       (((4 * ks + kq) ^ (n & 7)) << 4)));
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+#pragma unroll
+                    for (int b = 0; b < CB; ++b)
+                        acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[i], as_bf16x8(ws[ks][b]), acc[i][b], 0, 0, 0);
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < D; ++q) {
+            // requested in the order of the loop below, which the compiler's count of what is in flight relies on
+            load_x(q, xq[q]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(q, wq[q]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for (int i0 = 0; i0 < mine; i0 += D) {
+#pragma unroll
+            for (int q = 0; q < D; ++q) {
+                stage(xq[q]);
+                load_x(i0 + q + D, xq[q]);
+                wave_sync();
+                if (i0 + q < mine) compute(wq[q]);
+                load_w(i0 + q + D, wq[q]);
+                wave_sync();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+
+    // ---- the delta: the tile's pieces in turn to the wavefronts ----
+    {
+        const int q_end = start[(m0 >> 4) + RB];
+        for (int q = start[m0 >> 4] + wave; q < q_end; q += kLinSmallWaves) {
+            f32x4 dl[CB];
+            lin_delta<CB, 4>(pieces[q], arena, (size_t)strip * 128, b0, n, kq, v_hi, v_lo, dl);
+            const int at = (pieces[q].place - m0) >> 4;
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+                if (i == at) lin_add(pieces[q], kq, dl, acc[i]);
+        }
+    }
+
+    // ---- the wavefronts' sums, in wavefront order, and the store of y ----
+    __syncthreads();  // everyone has left the x regions
+    f32x4(*red)[kTiles][64] = reinterpret_cast<f32x4(*)[kTiles][64]>(lds);
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int b = 0; b < CB; ++b) red[wave][i * CB + b][lane] = acc[i][b];
+    __syncthreads();
+    for (int o = tid; o < RB * 256; o += kLinThreads) {
+        // row 16 i + 4 kq + e of the tile, columns 8 n + b0 .. + CB - 1 of the strip
+        const int i = o >> 8, l = (o >> 2) & 63, e = o & 3;
+        const int row = rows[m0 + 16 * i + 4 * (l >> 4) + e];
+        if (row < 0) continue;
+        float f[CB];
+#pragma unroll
+        for (int b = 0; b < CB; ++b) f[b] = reinterpret_cast<const float *>(&red[0][i * CB + b][l])[e];
+#pragma unroll
+        for (int w = 1; w < kLinSmallWaves; ++w)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) f[b] += reinterpret_cast<const float *>(&red[w][i * CB + b][l])[e];
+        uint32_t *dst = reinterpret_cast<uint32_t *>(y + (int64_t)row * ldy + strip * 128 + 8 * (l & 15) + b0);
+#pragma unroll
+        for (int b = 0; b < CB; b += 2) dst[b >> 1] = pack_bf16_rne(f[b], f[b + 1]);
+    }
+}
+
+template <int RB, int CB, int D>
+__global__ __launch_bounds__(kLinThreads, 1) void k_linear_small(
+    const int32_t *__restrict__ rows, const int32_t *__restrict__ start, const LinPiece *__restrict__ pieces, int m_tiles,
+    const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp, const uint16_t *__restrict__ x, int64_t ldx,
+    int in, int out, const uint16_t *__restrict__ v_hi, const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y,
+    int64_t ldy)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kLinSmallLds<RB, CB>];
+    linear_small_body<RB, CB, D>(blockIdx.x, 0, m_tiles, rows, start, pieces, arena, wp, x, ldx, in, out, v_hi, v_lo, y, ldy,
+                                 lds);
+}
+
+// The first n_big work groups take 256 x 256 tiles of the first m_big row tiles, the others 64 x 64 tiles of the
+// rows behind them, which fill the compute units that the last round of large tiles leaves idle.
+__global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
+    const int32_t *__restrict__ rows, const int32_t *__restrict__ start, const LinPiece *__restrict__ pieces, int n_big,
+    int m_big, int n_tiles, int m_small, const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp,
+    const uint16_t *__restrict__ x, int64_t ldx, int in, int out, const uint16_t *__restrict__ v_hi,
+    const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y, int64_t ldy)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kLinLds];
+    static_assert(kLinSmallLds<4, 4> <= kLinLds, "a small tile fits the LDS of a large one");
+    if ((int)blockIdx.x >= n_big) {
+        linear_small_body<4, 4, 2>((int)blockIdx.x - n_big, m_big * kLinTileM, m_small, rows, start, pieces, arena, wp, x, ldx,
+                                   in, out, v_hi, v_lo, y, ldy, lds);
+        return;
+    }
+    // Work group b runs on XCD b mod 8.  Each XCD takes a run of row tiles, and the 32 work groups it runs
+    // at a time (one per compute unit) are 8 row tiles x 4 column tiles that walk k together: every
+    // chunk of x and of W that one of them brings into the XCD's L2 serves four or eight of them.
+    const int xcd = blockIdx.x & 7, jloc = blockIdx.x >> 3;
+    const int ngroups_n = (n_tiles + 3) >> 2;
+    const int grp = jloc >> 5, within = jloc & 31;
+    const int mt_loc = (grp / ngroups_n) * 8 + (within >> 2);
+    const int nt = (grp % ngroups_n) * 4 + (within & 3);
+    const int share = m_big >> 3, extra = m_big & 7;  // the first `extra` XCDs take one row tile more
+    if (mt_loc >= share + (xcd < extra ? 1 : 0) || nt >= n_tiles) return;
+    linear_big_body(xcd * share + min(xcd, extra) + mt_loc, nt, rows, start, pieces, arena, wp, x, ldx, in, out, v_hi, v_lo,
+                    y, ldy, lds);
+}
+
+template <int RB, int CB, int D>
+static void launch_linear_small(const int32_t *rows, const int32_t *start, const LinPiece *pieces, int n_places,
+                                const uint16_t *arena, const uint16_t *w_packed, const uint16_t *x, int64_t ldx, int in,
+                                int out, const uint16_t *v_hi, const uint16_t *v_lo, uint16_t *y, int64_t ldy,
+                                hipStream_t stream)
+{
+    const int m_tiles = (n_places + 16 * RB - 1) / (16 * RB);
+    const int grid = 8 * ((out / 128 + 7) / 8) * m_tiles * (8 / CB);
+    hipLaunchKernelGGL((k_linear_small<RB, CB, D>), dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, start,
+                       pieces, m_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
 }
 
 // W^T [out][in] row-major -> operand order (see launch_pack_weight).  One thread per destination element.
@@ -2295,13 +2632,13 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_adapter(const uint16_t *_
 // ------------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------------
-static Sync make_sync(const SyncArgs *a, int wait)
+static Sync make_sync(const SyncArgs *a, int wait, int scale_v = 0)
 {
     Sync sy;
     if (!a) {
-        sy = Sync{nullptr, nullptr, nullptr, nullptr, nullptr, 0u, 0u, 0};
+        sy = Sync{nullptr, nullptr, nullptr, nullptr, nullptr, 0u, 0u, 0, scale_v};
     } else {
-        sy = Sync{a->counters, a->ready, a->timeout_flag, a->v_hi, a->v_lo, a->epoch, a->spin_limit, wait};
+        sy = Sync{a->counters, a->ready, a->timeout_flag, a->v_hi, a->v_lo, a->epoch, a->spin_limit, wait, scale_v};
     }
     return sy;
 }
@@ -2311,7 +2648,7 @@ hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *x, int64_t ldx, int
 {
     if (c.n_units <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_shrink, dim3(c.n_units), dim3(kThreads), 0, stream, c.units, c.arena, x, ldx,
-                       c.in_features, k_slice_len, v_out, n_slices, slice_stride, make_sync(sync, 0));
+                       c.in_features, k_slice_len, v_out, n_slices, slice_stride, make_sync(sync, 0, c.scale_v));
     return hipGetLastError();
 }
 
@@ -2323,10 +2660,10 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
     if (n_slices < 1 || n_slices > kMaxSlices) return hipErrorInvalidValue;
     if (more_than_one_round)
         hipLaunchKernelGGL(k_shrink_wide<kWideHalfWaves>, dim3(c.n_units), dim3(64 * kWideHalfWaves), 0, stream,
-                           c.units, c.arena, x, ldx, c.in_features, k_slice_len, n_slices, v_f32, v_hi, v_lo);
+                           c.units, c.arena, x, ldx, c.in_features, k_slice_len, n_slices, v_f32, v_hi, v_lo, c.scale_v);
     else
         hipLaunchKernelGGL(k_shrink_wide<kWideWaves>, dim3(c.n_units), dim3(kWideThreads), 0, stream, c.units,
-                           c.arena, x, ldx, c.in_features, k_slice_len, n_slices, v_f32, v_hi, v_lo);
+                           c.arena, x, ldx, c.in_features, k_slice_len, n_slices, v_f32, v_hi, v_lo, c.scale_v);
     return hipGetLastError();
 }
 
@@ -2400,7 +2737,7 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
 {
     if (c.n_units <= 0) return hipSuccess;
     if (n_hi < 0 || n_hi > c.n_units) return hipErrorInvalidValue;
-    const Sync sy = make_sync(sync, 0);
+    const Sync sy = make_sync(sync, 0, c.scale_v);
     if (n_hi > 0)
         hipLaunchKernelGGL(k_shrink_prefill_any, dim3(c.n_units), dim3(kThreads), 0, stream, c.units, c.perm, c.arena,
                            x, ldx, c.in_features, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, sy);
@@ -2417,7 +2754,7 @@ hipError_t launch_shrink_mixed(const LaunchCtx &heavy, int n_hi, const LaunchCtx
     const int total = heavy.n_units + c.n_units;
     if (total <= 0) return hipSuccess;
     if (!sync || n_hi < 0 || n_hi > heavy.n_units) return hipErrorInvalidValue;
-    const Sync sy = make_sync(sync, 0);
+    const Sync sy = make_sync(sync, 0, c.scale_v);
     if (n_hi > 0)
         hipLaunchKernelGGL(k_shrink_mixed<true>, dim3(total), dim3(kThreads), 0, stream, heavy.units, heavy.n_units,
                            c.units, c.perm, c.arena, x, ldx, c.in_features, k_slice_len, parts, n_slices,
@@ -2441,20 +2778,74 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, const f
     return hipGetLastError();
 }
 
-hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int m_pad, const uint16_t *arena,
+constexpr int kComputeUnits = 256;
+
+// How many row tiles of the adapted layer go to 256 x 256 tiles (from the front of the row order), the rest to
+// 64 x 64 tiles: what ends first on kComputeUnits compute units, one work group each, large tiles first.  A large
+// tile takes as long as 5.5 small ones (96 us at 4096 input features against 17 - 18), twice that where it meets
+// the many adapters of small groups.  4096 -> 4096, us per layer, all small / all large / as chosen: 1024 tokens
+// of few adapters 90 / 118, 2048 tokens 204 / 125; 8 prompts beside 384 decode tokens, 4096 tokens in all 389 /
+// 189 / 181, 6144 tokens 558 / 284 / 234.
+static int choose_big_row_tiles(int n_places, int n_front, int n_tiles, int small_columns)
+{
+    const int all = (n_places + kLinTileM - 1) / kLinTileM, front = n_front / kLinTileM;
+    auto cost = [&](int m) {
+        const double big = 5.5;
+        const double n_big = (double)m * n_tiles, slow = (double)(m > front && n_front < n_places ? m - front : 0) * n_tiles;
+        const double small = n_places > m * kLinTileM ? (double)((n_places - m * kLinTileM + 63) / 64) * small_columns : 0.0;
+        const double work = (n_big + slow) * big + small;
+        const double rounds = std::ceil(n_big / kComputeUnits) * big;  // the large tiles alone
+        // small tiles fill what the last round of large ones leaves, then whole rounds of their own
+        return std::max(std::max(rounds + (slow > 0 ? big : 0.0), work / kComputeUnits),
+                        n_big > 0 ? 0.0 : std::ceil(small / kComputeUnits));
+    };
+    int best = 0;
+    const int per_round = (int)((int64_t)front * n_tiles / kComputeUnits * kComputeUnits / n_tiles);
+    for (int m : {per_round, front, std::min(front + 1, all), all})
+        if (cost(m) < cost(best)) best = m;
+    return best;
+}
+
+hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n_places, const uint16_t *arena,
                               const uint16_t *w_packed, const uint16_t *x, int64_t ldx, int in, int out,
                               const uint16_t *v_hi, const uint16_t *v_lo, uint16_t *y, int64_t ldy,
                               hipStream_t stream)
 {
-    if (m_pad <= 0) return hipSuccess;
-    if (m_pad % kLinTileM || in % 64 || out % 128 || out <= 0 || in < 64) return hipErrorInvalidValue;
-    const int m_tiles = m_pad / kLinTileM, n_tiles = (out + kLinTileN - 1) / kLinTileN;
-    const int mt_per_xcd = (m_tiles + 7) / 8;
+    if (n_places <= 0) return hipSuccess;
+    if (in % 64 || out % 128 || out <= 0 || in < 64) return hipErrorInvalidValue;
+    const int n_tiles = (out + kLinTileN - 1) / kLinTileN;
+    const int32_t *start = blocks->start;
+    const LinPiece *pieces = blocks->pieces;
+    const int m_big = choose_big_row_tiles(n_places, blocks->n_front, n_tiles, out / 64);
+    if (m_big == 0) {
+        // small tiles only: the largest that still make a work group per compute unit.  4096 -> 4096, us per layer
+        // of tokens without adapter, tiles of 64 x 64 / 32 x 64 / 32 x 32 / 16 x 32: 16 tokens 14.4 / 11.5 / 9.4 /
+        // 8.3, 64 tokens 17.4 / 13.1 / 10.8 / 14.2, 128 tokens 18.2 / 14.2, 256 tokens 19.0 / 24.1, 512 tokens
+        // 34.9 / 46.6 (256 x 256 tiles: 95 for each of them).
+        auto tiles = [&](int rb, int cb) { return (int64_t)((n_places + 16 * rb - 1) / (16 * rb)) * (out / (16 * cb)); };
+        auto fits = [&](int rb, int cb) { return (n_places + 15) / 16 >= rb && tiles(rb, cb) >= kComputeUnits; };
+        auto go = [&](auto rb, auto cb, auto d) {
+            launch_linear_small<decltype(rb)::value, decltype(cb)::value, decltype(d)::value>(
+                rows, start, pieces, n_places, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy, stream);
+        };
+        using std::integral_constant;
+        if (fits(4, 4))
+            go(integral_constant<int, 4>{}, integral_constant<int, 4>{}, integral_constant<int, 2>{});
+        else if (fits(2, 4))
+            go(integral_constant<int, 2>{}, integral_constant<int, 4>{}, integral_constant<int, 2>{});
+        else if (fits(2, 2))
+            go(integral_constant<int, 2>{}, integral_constant<int, 2>{}, integral_constant<int, 3>{});
+        else
+            go(integral_constant<int, 1>{}, integral_constant<int, 2>{}, integral_constant<int, 4>{});
+        return hipGetLastError();
+    }
+    const int m_small = n_places > m_big * kLinTileM ? (n_places - m_big * kLinTileM + 63) / 64 : 0;
     // per XCD: groups of 32 work groups = 8 row tiles x 4 column tiles (see the kernel)
-    const int64_t grid = (int64_t)8 * 32 * ((mt_per_xcd + 7) / 8) * ((n_tiles + 3) / 4);
+    const int64_t n_big = (int64_t)8 * 32 * (((m_big + 7) / 8 + 7) / 8) * ((n_tiles + 3) / 4);
+    const int64_t grid = n_big + (int64_t)8 * ((out / 128 + 7) / 8) * m_small * 2;
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_linear_lora, dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, blocks, m_tiles,
-                       mt_per_xcd, n_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
+    hipLaunchKernelGGL(k_linear_lora, dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, start, pieces, (int)n_big, m_big,
+                       n_tiles, m_small, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
     return hipGetLastError();
 }
 

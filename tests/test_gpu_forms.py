@@ -4,8 +4,10 @@ import pytest
 import torch
 
 from paper_2511_22880_amd import binding as L
+from paper_2511_22880_amd import workloads as wl
 
 import gpu_util as G
+from test_gpu_parity import _linear_case
 
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +61,63 @@ def test_packed_adapter_is_the_documented_layout(rank, shape, offset):
     end = info["b_offset"] + b.size
     assert (got[:info["a_offset"]] == 0xA5A5).all() and (got[end:] == 0xA5A5).all()
     L.lora_pool_destroy(pool)
+
+
+# ---- lora_linear: small tiles, large tiles, both in one launch --------------------------------------------------
+def _batch(in_features, out_features, groups, idle=0, seed=0):
+    """groups: (tokens, rank) of one adapter each; `idle` tokens without adapter; tokens in random order."""
+    ranks = np.array([r for _, r in groups] or [8], dtype=np.int32)
+    ta = np.concatenate([np.full(n, a, dtype=np.int32) for a, (n, _) in enumerate(groups)]
+                        + [np.full(idle, -1, dtype=np.int32)])
+    ta = ta[np.random.default_rng([seed, 77]).permutation(ta.shape[0])]
+    return wl.CoBatch(f"T{ta.shape[0]}_groups{len(groups)}_idle{idle}", in_features, out_features, ranks,
+                      (np.float32(1.7) / ranks).astype(np.float32), ta, seed=seed, config=9)
+
+
+@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 31, 33, 63, 65, 129, 257])
+@pytest.mark.parametrize("shape", [(64, 128), (576, 1024), (1088, 384)])
+def test_linear_small_tiles(tokens, shape):
+    """Every tile form of few tokens (fewer 64-wide pieces of k than wavefronts, remainders of rows and strips),
+    with many adapters per block of 16 rows and ranks on both sides of the 32-wide steps."""
+    ranks = (8, 1, 33, 64, 72, 130, 256, 16)
+    sizes, left = [], tokens - tokens // 5
+    while left > 0:
+        sizes.append(min(left, 1 + len(sizes) % 5))
+        left -= sizes[-1]
+    groups = [(n, ranks[i % len(ranks)]) for i, n in enumerate(sizes)]
+    _linear_case(_batch(*shape, groups, idle=tokens // 5, seed=tokens), 0.02, seed=tokens)
+
+
+@pytest.mark.parametrize("case", [
+    # large tiles alone, with a row tile and a strip that are not full and groups that meet inside a block
+    (4224, [(700, 128), (513, 8), (300, 40), (291, 200)], 0),
+    # large tiles, idle rows, and small tiles for the rest of the rows and the small groups
+    (4096, [(900, 16), (701, 128)] + [(n % 15 + 1, 8 * (n % 32) + 1) for n in range(40)], 100),
+    # nothing but small groups, far too many for small tiles alone
+    (2048, [(9, 8 + n % 60) for n in range(700)], 10),
+])
+def test_linear_large_and_small_tiles_together(case):
+    out_features, groups, idle = case
+    _linear_case(_batch(128, out_features, groups, idle=idle, seed=5), 0.02, seed=6)
+
+
+def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
+    """An adapter whose B holds infinities: its tokens are not finite, the neighbours in the same block of 16 rows are."""
+    for in_features, out_features, groups in ((128, 256, [(3, 16), (5, 40), (4, 8)]),
+                                              (64, 4096, [(1003, 16), (605, 40), (900, 8)])):
+        b = _batch(in_features, out_features, groups, seed=3)
+        dp = G.DevicePool(b)
+        A, B = b.adapter_bits(1)
+        B[:] = 0x7F80
+        L.lora_pool_load(dp.pool, 1, A, B)
+        x = G.bits_to_dev(b.x_bits())
+        wp = torch.zeros(in_features * out_features, dtype=torch.bfloat16, device="cuda")
+        y = torch.zeros(b.T, out_features, dtype=torch.bfloat16, device="cuda")
+        seg = L.lora_segments_build(dp.pool, b.token_adapter)
+        ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, seg), 256), dtype=torch.uint8, device="cuda")
+        L.lora_linear(dp.pool, seg, x, wp, y, ws)
+        torch.cuda.synchronize()
+        finite = torch.isfinite(y.float()).all(dim=1).cpu().numpy()
+        assert np.array_equal(finite, b.token_adapter != 1)
+        L.lora_segments_destroy(seg)
+        dp.close()
