@@ -113,8 +113,8 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
                               int k_slice_len, int n_slices, float *v_f32, uint16_t *v_hi, uint16_t *v_lo,
                               hipStream_t stream);
 
-// Without `sync`: v_in holds n_slices fp32 partial sums slice_stride floats apart (n_slices = 1: v
-// itself).  With `sync`: v comes from sync->v_hi / v_lo (written by a shrink launch of the same epoch).
+// Without `sync`: v_in is v itself, fp32 and complete (n_slices = 1).  With `sync`: v comes from sync->v_hi / v_lo
+// (written by a shrink launch of the same epoch), v_in and the slices are not read.
 // `big`: the list holds units of up to 64 tokens (token indices through perm).
 hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, int n_slices, int64_t slice_stride,
                          uint16_t *y, int64_t ldy, const SyncArgs *sync, hipStream_t stream);
@@ -122,10 +122,10 @@ hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, int n_
 // Shrink of token-heavy groups: one unit = (group, up to 32 tokens, all rank rows, the whole of k).
 // n_hi = how many of the units are above rank 64: with none, the launch takes the kernel that fits four
 // work groups on a compute unit, otherwise the one for any rank (two per compute unit).
-// Writes complete v: as bf16 hi + lo into v_hi / v_lo, or (v_f32 != NULL) as fp32 into v_f32 with the
-// other n_slices - 1 slices of the same rows set to zero.  Units cut by k (sync_n = slices of the unit's
-// tokens, ks = which) put their sums into slices of `parts` and complete v through `sync`'s counters
-// (apply), or into slices of v_f32 for the caller to add up (stand-alone shrink, sync = NULL).
+// Writes complete v: as bf16 hi + lo into v_hi / v_lo, or (v_f32 != NULL) as fp32 into v_f32.  Units cut by
+// k (sync_n = slices of the unit's tokens, ks = which) put their sums into slices of `parts` and complete v
+// through `sync`'s counters (apply), or into n_slices slices of v_f32 for the caller to add up, those beyond the
+// unit's own set to zero (stand-alone shrink, sync = NULL).
 hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x, int64_t ldx, uint16_t *v_hi,
                                  uint16_t *v_lo, float *v_f32, int n_slices, int64_t slice_stride, float *parts,
                                  const SyncArgs *sync, hipStream_t stream);
