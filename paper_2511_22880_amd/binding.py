@@ -89,6 +89,22 @@ def _opts(options):
 
 _lib = None
 
+# Argument types of the calls a serving loop makes for every projection or adapter: ctypes then converts plain
+# ints itself, without an object per argument made here (a decode step of one token waits for the host:
+# lora_apply of one token 9.8 -> 8.9 us a call, its launches included).
+_P, _I32, _I64, _SZ = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
+_ARGTYPES = {
+    "lora_pool_load": (_P, _I32, _P, _P, ctypes.c_int, _P),
+    "lora_pool_load_staged": (_P, _I32, _P, _P, _P, _SZ, _P),
+    "lora_segments_rebuild": (_P, _P, _I32, _P),
+    "lora_shrink": (_P, _P, _P, _I64, _P, _P, _SZ, _P),
+    "lora_expand": (_P, _P, _P, _P, _I64, _P),
+    "lora_apply": (_P, _P, _P, _I64, _P, _I64, _P, _SZ, _P),
+    "lora_apply_static": (_P, _P, _P, _I64, _P, _I64, _P),
+    "lora_apply_multi": (_P, _I32, _P, _P, _I64, _P, _I64, _P, _SZ, _P),
+    "lora_linear": (_P, _P, _P, _I64, _P, _P, _I64, _P, _SZ, _P),
+}
+
 
 def lib() -> ctypes.CDLL:
     global _lib
@@ -100,6 +116,8 @@ def lib() -> ctypes.CDLL:
         for name in EXPORTS:
             fn = getattr(L, name)
             fn.restype = ctypes.c_char_p if name in ("lora_status_string", "lora_last_error") else ctypes.c_int
+            if name in _ARGTYPES:
+                fn.argtypes = _ARGTYPES[name]
         _lib = L
     return _lib
 
@@ -124,12 +142,22 @@ def _ptr(obj) -> ctypes.c_void_p:
     raise TypeError(f"cannot take the address of {type(obj)}")
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _addr(obj):
+    """_ptr for the calls of _ARGTYPES: a plain int (or None, or a c_void_p)."""
+    if hasattr(obj, "data_ptr"):
+        return obj.data_ptr()
+    return obj if obj is None or isinstance(obj, int) else _ptr(obj)
+
+
+def _queue(stream):
+    """_stream for the calls of _ARGTYPES."""
     if stream is None:
-        return ctypes.c_void_p(None)
-    if hasattr(stream, "cuda_stream"):
-        stream = stream.cuda_stream
-    return ctypes.c_void_p(int(stream) or None)
+        return None
+    return int(stream.cuda_stream if hasattr(stream, "cuda_stream") else stream)
+
+
+def _stream(stream) -> ctypes.c_void_p:
+    return ctypes.c_void_p(_queue(stream) or None)
 
 
 def _i32(a) -> np.ndarray:
@@ -223,8 +251,7 @@ def lora_pool_load(pool: Pool, adapter: int, A, B, src_is_device: Optional[bool]
         if r >= 0 and (A.shape != (pool.in_features, r) or B.shape != (r, pool.out_features) or A.itemsize != 2
                        or B.itemsize != 2):
             raise ValueError(f"adapter {adapter}: A {A.shape} / B {B.shape} do not match rank {r}")
-    _check(lib().lora_pool_load(pool.handle, ctypes.c_int32(adapter), _ptr(A), _ptr(B),
-                                ctypes.c_int(1 if src_is_device else 0), _stream(stream)))
+    _check(lib().lora_pool_load(pool.handle, ctypes.c_int32(adapter), _addr(A), _addr(B), 1 if src_is_device else 0, _queue(stream)))
 
 
 def lora_pool_evict(pool: Pool, adapter: int) -> None:
@@ -280,8 +307,8 @@ def lora_pool_load_staging_bytes(pool: Pool, adapter: int) -> int:
 
 def lora_pool_load_staged(pool: Pool, adapter: int, A, B, dev_staging, stream=None) -> None:
     """A, B: host arrays (numpy uint16 or pinned torch tensors); dev_staging: device tensor of the caller's."""
-    _check(lib().lora_pool_load_staged(pool.handle, ctypes.c_int32(adapter), _ptr(A), _ptr(B), _ptr(dev_staging),
-                                       ctypes.c_size_t(_nbytes(dev_staging)), _stream(stream)))
+    _check(lib().lora_pool_load_staged(pool.handle, ctypes.c_int32(adapter), _addr(A), _addr(B), _addr(dev_staging), _nbytes(dev_staging),
+                                       _queue(stream)))
 
 
 def lora_segments_plan_ranges(pool: Pool, seg_start, seg_adapter) -> Segments:
@@ -317,7 +344,7 @@ def lora_segments_build_ranges(pool: Pool, seg_start, seg_adapter, stream=None) 
 
 def lora_segments_rebuild(seg: Segments, token_adapter, stream=None) -> None:
     ta = _i32(token_adapter)
-    _check(lib().lora_segments_rebuild(seg.handle, _ptr(ta), ctypes.c_int32(ta.shape[0]), _stream(stream)))
+    _check(lib().lora_segments_rebuild(seg.handle, _addr(ta), ta.shape[0], _queue(stream)))
 
 
 def lora_segments_info(seg: Segments) -> dict:
@@ -381,23 +408,26 @@ def _nbytes(ws) -> int:
     return 0 if ws is None else ws.numel() * ws.element_size()
 
 
+def _ws_bytes(workspace, ws_bytes):
+    return _nbytes(workspace) if ws_bytes is None else ctypes.c_size_t(ws_bytes)
+
+
 def lora_shrink(pool: Pool, seg: Segments, x, v, workspace=None, stream=None, ldx: Optional[int] = None,
                 ws_bytes: Optional[int] = None) -> None:
     """x: bf16 device tensor [T][in]; v: fp32 device tensor of info['v_floats'] elements."""
-    _check(lib().lora_shrink(pool.handle, seg.handle, _ptr(x), ctypes.c_int64(_ld(x, ldx)), _ptr(v), _ptr(workspace),
-                             ctypes.c_size_t(_nbytes(workspace) if ws_bytes is None else ws_bytes), _stream(stream)))
+    _check(lib().lora_shrink(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(v), _addr(workspace),
+                             _ws_bytes(workspace, ws_bytes), _queue(stream)))
 
 
 def lora_expand(pool: Pool, seg: Segments, v, y, stream=None, ldy: Optional[int] = None) -> None:
     """y: bf16 device tensor [T][out], updated in place."""
-    _check(lib().lora_expand(pool.handle, seg.handle, _ptr(v), _ptr(y), ctypes.c_int64(_ld(y, ldy)), _stream(stream)))
+    _check(lib().lora_expand(pool.handle, seg.handle, _addr(v), _addr(y), _ld(y, ldy), _queue(stream)))
 
 
 def lora_apply(pool: Pool, seg: Segments, x, y, workspace, stream=None, ldx: Optional[int] = None,
                ldy: Optional[int] = None, ws_bytes: Optional[int] = None) -> None:
-    _check(lib().lora_apply(pool.handle, seg.handle, _ptr(x), ctypes.c_int64(_ld(x, ldx)), _ptr(y),
-                            ctypes.c_int64(_ld(y, ldy)), _ptr(workspace),
-                            ctypes.c_size_t(_nbytes(workspace) if ws_bytes is None else ws_bytes), _stream(stream)))
+    _check(lib().lora_apply(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(y), _ld(y, ldy), _addr(workspace),
+                            _ws_bytes(workspace, ws_bytes), _queue(stream)))
 
 
 def lora_linear_pack_weight(wt, in_features: int, out_features: int, dev_packed, stream=None) -> None:
@@ -409,9 +439,8 @@ def lora_linear_pack_weight(wt, in_features: int, out_features: int, dev_packed,
 def lora_linear(pool: Pool, seg: Segments, x, w_packed, y, workspace, stream=None, ldx: Optional[int] = None,
                 ldy: Optional[int] = None, ws_bytes: Optional[int] = None) -> None:
     """y = bf16(x W + delta) for every token, y written once."""
-    _check(lib().lora_linear(pool.handle, seg.handle, _ptr(x), ctypes.c_int64(_ld(x, ldx)), _ptr(w_packed), _ptr(y),
-                             ctypes.c_int64(_ld(y, ldy)), _ptr(workspace),
-                             ctypes.c_size_t(_nbytes(workspace) if ws_bytes is None else ws_bytes), _stream(stream)))
+    _check(lib().lora_linear(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(w_packed), _addr(y), _ld(y, ldy),
+                             _addr(workspace), _ws_bytes(workspace, ws_bytes), _queue(stream)))
 
 
 LORA_STATIC_WORKSPACE_BYTES = 32 << 20
@@ -420,8 +449,7 @@ LORA_STATIC_WORKSPACE_BYTES = 32 << 20
 def lora_apply_static(pool: Pool, seg: Segments, x, y, stream=None, ldx: Optional[int] = None,
                       ldy: Optional[int] = None) -> None:
     """lora_apply on the library's own static workspace: allocates nothing."""
-    _check(lib().lora_apply_static(pool.handle, seg.handle, _ptr(x), ctypes.c_int64(_ld(x, ldx)), _ptr(y),
-                                   ctypes.c_int64(_ld(y, ldy)), _stream(stream)))
+    _check(lib().lora_apply_static(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(y), _ld(y, ldy), _queue(stream)))
 
 
 def _pool_array(pools):
@@ -449,10 +477,8 @@ def lora_segments_build_multi(pools, token_adapter, stream=None, options=None) -
 def lora_apply_multi(pools, seg: Segments, x, y, workspace, stream=None, ldx: Optional[int] = None,
                      ldy: Optional[int] = None, ws_bytes: Optional[int] = None) -> None:
     """y: bf16 device tensor [T][sum of the pools' out_features], updated in place."""
-    _check(lib().lora_apply_multi(_pool_array(pools), ctypes.c_int32(len(pools)), seg.handle, _ptr(x),
-                                  ctypes.c_int64(_ld(x, ldx)), _ptr(y), ctypes.c_int64(_ld(y, ldy)), _ptr(workspace),
-                                  ctypes.c_size_t(_nbytes(workspace) if ws_bytes is None else ws_bytes),
-                                  _stream(stream)))
+    _check(lib().lora_apply_multi(_pool_array(pools), len(pools), seg.handle, _addr(x), _ld(x, ldx), _addr(y), _ld(y, ldy),
+                                  _addr(workspace), _ws_bytes(workspace, ws_bytes), _queue(stream)))
 
 
 def lora_set_fused_apply(enabled: bool) -> None:
