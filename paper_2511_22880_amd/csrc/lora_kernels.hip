@@ -536,20 +536,96 @@ constexpr int kPfRow = kPfPassK + 8;          // LDS row length in bf16, padded 
 constexpr int kPfSlab = kPfTokens * kPfRow * 2;
 constexpr int kPrefillLds = 4 * kPfSlab;
 
-// lane (n, kq) holds v[token][j .. j+3] of a tile; `at` is the element's index in v
-static __device__ __forceinline__ void store_v4(f32x4 f, int64_t at, uint16_t *__restrict__ v_hi,
-                                                uint16_t *__restrict__ v_lo, float *__restrict__ v_f32)
+// A piece of memory that other XCDs' units write or read in this launch, in 16-byte accesses that go through to
+// memory (the cache bits of an agent-scope atomic, which stops at 8 bytes).  base is wavefront-uniform.
+struct Through {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Through(float *base, int floats)
+        : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, floats * 4, 0x00020000)) {}
+    static constexpr int kAgent = 16;  // sc1
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    __device__ __forceinline__ void st(int quad, f32x4 f) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f), r, 16 * quad, 0, kAgent);
+    }
+    __device__ __forceinline__ f32x4 ld(int quad) const
+    {
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, 16 * quad, 0, kAgent));
+    }
+};
+
+// four elements of v, at element index `at`, as bf16 hi + lo
+static __device__ __forceinline__ void store_v4(f32x4 f, int64_t at, uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo)
 {
-    if (v_f32) {
-        *reinterpret_cast<f32x4 *>(v_f32 + at) = f;
+    uint2 h, l;
+    h.x = pack_bf16_rne(f[0], f[1]);
+    h.y = pack_bf16_rne(f[2], f[3]);
+    l.x = pack_bf16_rne(f[0] - bf16_bits_to_f32(h.x & 0xFFFFu), f[1] - __uint_as_float(h.x & 0xFFFF0000u));
+    l.y = pack_bf16_rne(f[2] - bf16_bits_to_f32(h.y & 0xFFFFu), f[3] - __uint_as_float(h.y & 0xFFFF0000u));
+    *reinterpret_cast<uint2 *>(v_hi + at) = h;
+    *reinterpret_cast<uint2 *>(v_lo + at) = l;
+}
+
+// The end of a token-heavy shrink unit, by all threads of its work group: rows row0 .. row0 + rows - 1 of the unit's
+// v are one run of memory, which goes out in 16-byte pieces, neighbouring threads side by side; quad(i) = the sums
+// of its elements 4 i .. 4 i + 3.  (Straight from the MFMA registers a wavefront's stores were 8 bytes of each of 64
+// pieces of lines; written through to memory those were most of a cut unit's time: 2000 tokens of rank 128 at
+// 4096 features, 128 units, shrink launch 20.4 -> 15.2 us.)
+// Whole units write v.  Units cut along k leave their sums in slice u.ks of the fp32 partial sums: plainly for the
+// stand-alone shrink (v_f32: the caller adds the slices up, and slice 0's unit clears those this group does not
+// use), else through to memory for the unit that completes the tile (complete_tile).
+template <class Quad>
+static __device__ __forceinline__ void store_heavy_rows(const Unit &u, int n_ks, int row0, int rows, Quad quad,
+                                                        uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo,
+                                                        float *__restrict__ v_f32, int n_slices, int64_t slice_stride,
+                                                        float *__restrict__ parts, float vs)
+{
+    const int n = rows * (u.r8 >> 2);
+    const int64_t at = u.v_off + (int64_t)row0 * u.r8;
+    if (n_ks > 1 && !v_f32) {
+        const Through slice(parts + (int64_t)u.ks * slice_stride + at, 4 * n);
+        for (int i = threadIdx.x; i < n; i += kThreads) slice.st(i, quad(i));
+    } else if (v_f32) {
+        float *dst = v_f32 + (int64_t)u.ks * slice_stride + at;
+        for (int i = threadIdx.x; i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[i] = quad(i);
+        if (n_ks > 1 && u.ks == 0)
+            for (int sl = n_ks; sl < n_slices; ++sl)
+                for (int i = threadIdx.x; i < n; i += kThreads)
+                    reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
-        uint2 h, l;
-        h.x = pack_bf16_rne(f[0], f[1]);
-        h.y = pack_bf16_rne(f[2], f[3]);
-        l.x = pack_bf16_rne(f[0] - bf16_bits_to_f32(h.x & 0xFFFFu), f[1] - __uint_as_float(h.x & 0xFFFF0000u));
-        l.y = pack_bf16_rne(f[2] - bf16_bits_to_f32(h.y & 0xFFFFu), f[3] - __uint_as_float(h.y & 0xFFFF0000u));
-        *reinterpret_cast<uint2 *>(v_hi + at) = h;
-        *reinterpret_cast<uint2 *>(v_lo + at) = l;
+        for (int i = threadIdx.x; i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * i, v_hi, v_lo);
+    }
+}
+
+// A cut unit whose sums are on their way to memory: the one of the tile's n_ks that arrives last at the tile's counter
+// adds the slices in slice order and leaves v as bf16 hi + lo.  `word`: an LDS word that nothing else uses any more.
+static __device__ __forceinline__ void complete_tile(const Unit &u, int n_ks, int64_t slice_stride, float *__restrict__ parts,
+                                                     uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo, float vs,
+                                                     const Sync &sy, unsigned *word)
+{
+    stores_done();
+    __syncthreads();  // every wavefront's partial sums are out
+    if (threadIdx.x == 0) *word = atomicAdd(sy.counters + u.sync_idx, 1u);
+    __syncthreads();
+    if (*word + 1u != (unsigned)n_ks) return;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the loads of the slices stay behind the arrival
+    if (threadIdx.x == 0) atomicExch(sy.counters + u.sync_idx, 0u);  // back to zero for the next launch
+    const int n = u.ntok * (u.r8 >> 2);
+    const Through s0(parts + u.v_off, 4 * n), s1(parts + u.v_off + slice_stride, 4 * n);
+    if (n_ks <= 2) {
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n; i += kThreads) store_v4(vs * (s0.ld(i) + s1.ld(i)), u.v_off + 4 * i, v_hi, v_lo);
+    } else {
+        const Through s2(parts + u.v_off + 2 * slice_stride, 4 * n);
+        const Through s3(parts + u.v_off + (n_ks > 3 ? 3 : 2) * slice_stride, 4 * n);
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n; i += kThreads) {
+            f32x4 f = s0.ld(i) + s1.ld(i);
+            f += s2.ld(i);
+            const f32x4 f3 = s3.ld(i);
+            if (n_ks > 3) f += f3;
+            store_v4(vs * f, u.v_off + 4 * i, v_hi, v_lo);
+        }
     }
 }
 
@@ -565,7 +641,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
     constexpr int NT = JB * TB;
     constexpr int NL = 4 * TB;  // x loads of a wavefront per pass: 4 tokens each
     static_assert(16 * TB <= kPfTokens, "tokens of a unit");
-    static_assert(2 * NT * 64 * 16 <= kPrefillLds, "the partial tiles of two wavefronts fit the LDS");
+    static_assert(4 * NT * 64 * 16 + 4 <= kPrefillLds, "the wavefronts' partial tiles and a word fit the LDS");
     static_assert(WD == 1 || WD == 2 || WD == 4, "the weight ring must divide the 4 steps of a pass");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -710,90 +786,24 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         }
     }
 
-    // sum the four k-quarters: (wave 2 -> 0, wave 3 -> 1), then (wave 1 -> 0)
+    // the four k-quarters' sums meet in LDS, added as (0 + 2) + (1 + 3)
     __syncthreads();  // every wavefront has finished with its x region
-    if (wave >= 2) {
 #pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
+    for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-            for (int tb = 0; tb < TB; ++tb) red[wave - 2][jb * TB + tb][lane] = acc[jb][tb];
-    }
+        for (int tb = 0; tb < TB; ++tb) red[wave][jb * TB + tb][lane] = acc[jb][tb];
     __syncthreads();
-    if (wave < 2) {
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) acc[jb][tb] += red[wave][jb * TB + tb][lane];
-    }
-    __syncthreads();
-    if (wave == 1) {
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) red[0][jb * TB + tb][lane] = acc[jb][tb];
-    }
-    __syncthreads();
-    if (wave != 0) return;
-
     const float vs = sy.scale_v ? u.scale : 1.f;
-    // lane (n, kq) holds, for token block tb and row block jb, v[token n][16*jb + 4*kq + e]
-    if (n_ks == 1) {
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-            if (16 * tb + n >= ntok) continue;
-            const int64_t row = u.v_off + (int64_t)(16 * tb + n) * r8;
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb) {
-                const int j = 16 * jb + 4 * kq;
-                if (j < r8)
-                    store_v4(vs * (acc[jb][tb] + red[0][jb * TB + tb][lane]), row + j, v_hi, v_lo, v_f32);
-            }
-        }
-        return;
-    }
-    // A k-slice of the unit's tokens: the sums go to slice u.ks of the fp32 partial sums.  Stand-alone
-    // shrink (v_f32): the caller adds the slices up afterwards, so slice 0's unit clears the slices
-    // this group does not use.  Apply: stores that go through to memory, then the tile's counter; the
-    // unit that completes the tile adds the slices in slice order and leaves v as bf16 hi + lo.
-    float *dst = v_f32 ? v_f32 : parts;
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        if (16 * tb + n >= ntok) continue;
-        const int64_t row = u.v_off + (int64_t)(16 * tb + n) * r8;
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) {
-            const int j = 16 * jb + 4 * kq;
-            if (j >= r8) continue;
-            const f32x4 f = acc[jb][tb] + red[0][jb * TB + tb][lane];
-            if (v_f32) {
-                *reinterpret_cast<f32x4 *>(dst + (int64_t)u.ks * slice_stride + row + j) = f;
-                if (u.ks == 0)
-                    for (int sl = n_ks; sl < n_slices; ++sl)
-                        *reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride + row + j) =
-                            f32x4{0.f, 0.f, 0.f, 0.f};
-            } else {
-                st_through_f32x4(dst + (int64_t)u.ks * slice_stride + row + j, f);
-            }
-        }
-    }
-    if (v_f32) return;
-    stores_done();
-    unsigned old = 0;
-    if (lane == 0) old = atomicAdd(sy.counters + u.sync_idx, 1u);
-    old = __builtin_amdgcn_readfirstlane(old);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the loads of the slices stay behind the arrival
-    if (old + 1u == (unsigned)n_ks) {
-        if (lane == 0) atomicExch(sy.counters + u.sync_idx, 0u);  // back to zero for the next launch
-        const int tasks = ntok * (u.r8 >> 3);
-        for (int task = lane; task < tasks; task += 64) {
-            f32x4 f0, f1;
-            sum_slices(parts + u.v_off + 8 * task, n_ks, slice_stride, f0, f1);
-            uint4 ph, pl;
-            split_bf16(vs * f0, vs * f1, ph, pl);
-            st_through_u16x8(v_hi + u.v_off + 8 * task, ph);
-            st_through_u16x8(v_lo + u.v_off + 8 * task, pl);
-        }
-    }
+    const int quads = r8 >> 2;
+    // lane (n, kq) of tile (jb, tb) holds v[token 16 tb + n][16 jb + 4 kq + e]
+    auto quad = [&](int i) __attribute__((always_inline)) {
+        const int tok = i / quads, j4 = i - tok * quads;
+        const int t = (j4 >> 2) * TB + (tok >> 4), l = (j4 & 3) * 16 + (tok & 15);
+        return (red[0][t][l] + red[2][t][l]) + (red[1][t][l] + red[3][t][l]);
+    };
+    store_heavy_rows(u, n_ks, 0, ntok, quad, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, vs);
+    if (n_ks == 1 || v_f32) return;
+    complete_tile(u, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + 4 * NT * 64 * 16));
 }
 
 // Token-heavy units above rank 64: 16 * TB tokens, all rank rows, all of k or a slice of it.  Here the
@@ -962,62 +972,29 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     LORA_CLOCK(2);
 #endif
     const float vs = sy.scale_v ? u.scale : 1.f;
-    // lane (n, kq) holds, for token block tb and its row block j, v[token 16 tb + n][16 jb + 4 kq + e]
-    if (n_ks == 1) {
+    // lane (n, kq) holds, for token block tb and its row block j, v[token 16 tb + n][16 jb + 4 kq + e]: the rows
+    // meet in LDS as they lie in v, all of the unit's tokens at once where they fit, else half of them
+    constexpr int GO = 16 * TB * 64 * JBW * 4 + 16 <= kPrefillLds ? TB : TB / 2;
+    static_assert(16 * GO * 64 * JBW * 4 + 16 <= kPrefillLds, "the rows in LDS");
+    f32x4 *rows = reinterpret_cast<f32x4 *>(lds);
+    const int quads = r8 >> 2;
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-            if (16 * tb + n >= ntok) continue;
-            const int64_t row = u.v_off + (int64_t)(16 * tb + n) * r8;
+    for (int g = 0; g < TB; g += GO) {
+        __syncthreads();  // the x buffers, then the rows of the first half, have been read
+#pragma unroll
+        for (int tb = 0; tb < GO; ++tb)
 #pragma unroll
             for (int j = 0; j < JBW; ++j) {
-                const int jr = 16 * (wave * JBW + j) + 4 * kq;
-                if (jr < r8) store_v4(vs * acc[j][tb], row + jr, v_hi, v_lo, v_f32);
+                const int j4 = 4 * (wave * JBW + j) + kq;
+                if (j4 < quads) rows[(16 * tb + n) * quads + j4] = acc[j][g + tb];
             }
-        }
-        return;
+        __syncthreads();
+        if (16 * g < ntok)
+            store_heavy_rows(u, n_ks, 16 * g, min(16 * GO, ntok - 16 * g), [&](int i) { return rows[i]; }, v_hi, v_lo, v_f32,
+                             n_slices, slice_stride, parts, vs);
     }
-    // A k-slice of the unit's tokens, as in the body above: the sums go to slice u.ks of the fp32
-    // partial sums; the unit that completes the tile adds the slices in slice order.
-    float *dst = v_f32 ? v_f32 : parts;
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        if (16 * tb + n >= ntok) continue;
-        const int64_t row = u.v_off + (int64_t)(16 * tb + n) * r8;
-#pragma unroll
-        for (int j = 0; j < JBW; ++j) {
-            const int jr = 16 * (wave * JBW + j) + 4 * kq;
-            if (jr >= r8) continue;
-            if (v_f32) {
-                *reinterpret_cast<f32x4 *>(dst + (int64_t)u.ks * slice_stride + row + jr) = acc[j][tb];
-                if (u.ks == 0)
-                    for (int sl = n_ks; sl < n_slices; ++sl)
-                        *reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride + row + jr) =
-                            f32x4{0.f, 0.f, 0.f, 0.f};
-            } else {
-                st_through_f32x4(dst + (int64_t)u.ks * slice_stride + row + jr, acc[j][tb]);
-            }
-        }
-    }
-    if (v_f32) return;
-    stores_done();
-    __syncthreads();  // every wavefront's partial sums are out (and nobody reads the x buffers any more)
-    unsigned *arrived = reinterpret_cast<unsigned *>(lds);
-    if (threadIdx.x == 0) *arrived = atomicAdd(sy.counters + u.sync_idx, 1u);
-    __syncthreads();
-    const unsigned old = *arrived;
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the loads of the slices stay behind the arrival
-    if (old + 1u == (unsigned)n_ks) {
-        if (threadIdx.x == 0) atomicExch(sy.counters + u.sync_idx, 0u);  // back to zero for the next launch
-        const int tasks = ntok * (r8 >> 3);
-        for (int task = threadIdx.x; task < tasks; task += kThreads) {
-            f32x4 f0, f1;
-            sum_slices(parts + u.v_off + 8 * task, n_ks, slice_stride, f0, f1);
-            uint4 ph, pl;
-            split_bf16(vs * f0, vs * f1, ph, pl);
-            st_through_u16x8(v_hi + u.v_off + 8 * task, ph);
-            st_through_u16x8(v_lo + u.v_off + 8 * task, pl);
-        }
-    }
+    if (n_ks == 1 || v_f32) return;
+    complete_tile(u, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + kPrefillLds - 16));
 }
 
 // One wavefront copies 1 KB from memory into LDS without passing through registers: lane l's 16 bytes

@@ -63,6 +63,39 @@ def test_packed_adapter_is_the_documented_layout(rank, shape, offset):
     L.lora_pool_destroy(pool)
 
 
+# ---- token-heavy groups: units cut along k, column runs down to one strip, the two halves apart -----------------
+@pytest.mark.parametrize("shape", [(64, 128), (2112, 640), (3072, 1152), (4160, 4224)])
+@pytest.mark.parametrize("sizes", [
+    # (tokens, rank): every bucket of the shrink bodies, tiles of 64 and 32 with one row, one short of full and full
+    [(33, 8), (65, 24), (64, 40), (127, 64), (96, 72)],
+    [(64, 100), (129, 128), (63, 136), (65, 192), (32, 200), (33, 256)],
+    [(40, 16), (70, 160), (3, 64), (1, 256)],  # beside decode-sized groups
+])
+def test_token_heavy_units_cut_along_k(shape, sizes):
+    """lora_apply against the oracle, uncut (in_features 64) and in 2, 3 and 4 k-slices, and lora_shrink + lora_expand,
+    whose v is one rounding away from the one lora_apply hands over."""
+    b = _batch(*shape, sizes, idle=3, seed=len(sizes))
+    dp = G.DevicePool(b)
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_min_batch=64))
+    x_bits, y0 = b.x_bits(), np.zeros((b.T, b.out_features), dtype=np.uint16)
+    x, y = G.bits_to_dev(x_bits), G.bits_to_dev(y0)
+    ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    for _ in range(2):  # the counters are left as they were found
+        y.zero_()
+        L.lora_apply(dp.pool, seg, x, y, ws)
+        torch.cuda.synchronize()
+        G.check_all_rows(dp, x_bits, y0, G.dev_to_bits(y))
+    v = torch.full((L.lora_segments_info(seg)["v_floats"],), float("nan"), dtype=torch.float32, device="cuda")
+    vws = torch.full((max(L.lora_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    y.zero_()
+    L.lora_shrink(dp.pool, seg, x, v, vws)
+    L.lora_expand(dp.pool, seg, v, y)
+    torch.cuda.synchronize()
+    G.check_all_rows(dp, x_bits, y0, G.dev_to_bits(y))
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 # ---- lora_linear: small tiles, large tiles, both in one launch --------------------------------------------------
 def _batch(in_features, out_features, groups, idle=0, seed=0):
     """groups: (tokens, rank) of one adapter each; `idle` tokens without adapter; tokens in random order."""
