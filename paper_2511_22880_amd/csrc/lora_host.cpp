@@ -610,11 +610,13 @@ static_assert(kBigExpandMaxRank >= LORA_MAX_RANK_PADDED, "the 16-token expand un
 static const int kHeavyKCutMaxUnits = 320;
 static const int kHeavyKCutLongK = 8192;          // beyond this many input features:
 static const int kHeavyKCutMaxUnitsLongK = 750;
-// 64-token expand units take a group's columns in 8 runs instead of 4 while the launch stays within one
-// round of work groups (two per compute unit): expand launch, 4 / 8 runs, 50 tiles of 64 tokens 15.3 /
-// 14.0 us, 51 tiles 15.7 / 14.2, 64 tiles 17.2 / 15.9, 72 tiles 21.7 / 21.9; cfg3's routing at 1.5 k /
-// 2.7 k tokens 25.7 -> 19.5 / 26.6 -> 23.1 us at 4096 columns, 78.6 -> 60.8 / 80.5 -> 72.8 us at 14336;
-// at 4.9 k tokens and beyond 8 runs are level or lose.
+// 64-token expand units take a group's columns in 8, 16, .. runs instead of 4 (down to one strip of 128 columns
+// each), the most that keep the launch within one round of work groups (two per compute unit): it then
+// lasts as long as one unit, a strip after the other.  Expand launch in us by units allowed, 4 runs / 256 / 512 /
+// 1024 units; 4096 columns, rank 128: 16 tiles of 64 tokens 20.1 / 8.9 / 8.6 / 8.8, 32 tiles 21.0 / 13.0 / 10.6 /
+// 15.0, 63 tiles 22.5 / 22.5 / 18.4 / 20.7, 125 tiles 32.0 / 32.6 / 32.5 / 35.1; rank 16: 16 tiles 11.7 / 5.8 / 5.6 /
+// 5.9, 63 tiles 15.8 / 15.8 / 14.1 / 14.6; rank 256: 32 tiles 35.8 / 22.5 / 19.0 / 24.5; 1024 columns, rank 128, 16
+// tiles 11.7 / 6.3 / 6.2 / 6.4; 14336 columns, rank 256, 32 tiles 114 / 63 / 44 / 52.
 static const int kBigRunsWorkGroupsPerComputeUnit = 2;
 
 extern "C" lora_status_t lora_set_whole_k_limit(int32_t max_units)
@@ -1070,14 +1072,14 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
             if (heavy_units * c <= limit) heavy_k_slices = c;  // per projection: lora_apply_multi gives the bits of separate applies
     }
     sg->heavy_k_slices = heavy_k_slices;
-    // The 64-token expand units: a group's columns in 4 runs, or in 8 shorter ones while that keeps the
-    // launch at few such units (it then lasts as long as one of them; cfg3's routing at 1.5 k / 2.7 k
-    // tokens: expand launch 25.7 -> 19.5 / 26.6 -> 23.1 us at 4096 columns, 78.6 -> 60.8 / 80.5 -> 72.8
-    // us at 14336; at 4.9 k tokens and beyond 8 runs are level or lose).
+    // The 64-token expand units: a group's columns in 4 runs, or in more and shorter ones while that keeps the
+    // launch at few such units (it then lasts as long as one of them; see kBigRunsWorkGroupsPerComputeUnit)
     int64_t big_tiles = 0;
     for (const SegRec &r : sg->segs)
         if (r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch && r.r8 <= kBigExpandMaxRank) big_tiles += (r.ntok + 63) / 64;
-    const int big_runs = big_tiles * 8 * n_projections <= opt_big_runs_max_units(sg) ? 8 : 4;
+    int big_runs = 4;
+    for (int runs = 64; runs >= 8 && big_runs == 4; runs /= 2)
+        if (big_tiles * std::min(runs, out / 128) * n_projections <= opt_big_runs_max_units(sg)) big_runs = runs;
     for (int32_t si : order) {
         const SegRec &r = sg->segs[si];
         const bool token_heavy = r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch;
@@ -1138,12 +1140,12 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
                     }
         }
         // expand: small groups one column pass and <= 16 tokens per unit; token-heavy groups 64 tokens
-        // (16 per wavefront, v kept in registers) and a quarter (or an eighth) of the columns, at least 512
+        // (16 per wavefront, v kept in registers) and a quarter of the columns, at least 512, or fewer
         int cols = expand_cols_per_unit(r.r8, out);
         int etile = lora::kTokTile;
         if (token_heavy && r.r8 <= kBigExpandMaxRank) {
             etile = 64;
-            cols = std::min(out, std::max(512, (out / big_runs + 127) / 128 * 128));
+            cols = std::min(out, std::max(big_runs > 4 ? 128 : 512, (out / big_runs + 127) / 128 * 128));
         }
         auto emit = [&](int c0, int tok0) {
             Unit u;
@@ -1163,7 +1165,11 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
             (etile > lora::kTokTile ? sg->expand_big_units : sg->expand_units).push_back(u);
         };
         const int ncb = (out + cols - 1) / cols;
-        if (etile > lora::kTokTile && (ncb == 2 || ncb == 4 || ncb == 8)) {
+        if (etile > lora::kTokTile && ncb % 8 == 0) {
+            // (work group b runs on XCD b mod 8: a column run of any token tile on one XCD)
+            for (int t = 0; t < r.ntok; t += etile)
+                for (int cb = 0; cb < ncb; ++cb) emit(cb * cols, t);
+        } else if (etile > lora::kTokTile && (ncb == 2 || ncb == 4)) {
             // Work group b of a launch runs on XCD b mod 8, each XCD with an L2 of its own.  With the
             // units of a group in rows of 8 (each column run with 8 / ncb consecutive token tiles) a
             // column run's rows of B^T are fetched by 8 / ncb XCDs instead of all eight (cfg2 4096->4096:
