@@ -419,7 +419,8 @@ lora_status_t lora_apply_multi(const lora_pool_t *const *pools, int32_t n_pools,
  * their sums).  Default 1024 (four rounds of one work group per compute unit); 0 = always k-slices. */
 lora_status_t lora_set_whole_k_limit(int32_t max_units);
 
-/* lora_apply is two launches by default (shrink units, then expand units).  With k-slices the shrink
+/* lora_apply is two launches (shrink units, then expand units) unless one of the single-launch forms is
+ * taken (here and lora_set_decode_single_launch).  With k-slices the shrink
  * unit that completes a token tile (found through per-tile counters in the segment object's device
  * table) adds the k-slices up and leaves the tile's v for the expand units.
  * lora_set_fused_apply(1) selects, for batches planned with k-slices and without token-heavy groups,
@@ -433,7 +434,10 @@ lora_status_t lora_set_whole_k_limit(int32_t max_units);
  * and the table address of the plan it was captured with: after lora_segments_rebuild on the
  * object, capture again.  The single-launch form takes an epoch from
  * host state of the segment object at launch: it must not be captured, and not be used on an object
- * that a captured graph replays.  The setting is process-wide. */
+ * that a captured graph replays.  The setting is process-wide.  Until this is called, batches of few
+ * units (at most 32 shrink units and 96 in all) take the single launch by themselves, with the same
+ * bits, unless lora_set_decode_single_launch(0) holds or the stream is being captured (where the two
+ * launches are issued; a graph that holds those may be replayed between such applies). */
 lora_status_t lora_set_fused_apply(int enabled);
 
 /* A mixed batch holds token-heavy groups and decode-sized groups, whose units are of different kinds.

@@ -757,7 +757,15 @@ static int opt_big_runs_max_units(const lora_segments *sg)
 static const int kXcds = 8;         // XCDs of the chip, each with an L2 of its own; work group b of a launch runs on XCD b mod 8
 static std::atomic<int> g_decode_single_launch{1};
 static std::atomic<int> g_side_stream{1};
-static std::atomic<int> g_fused_apply{0};
+static std::atomic<int> g_fused_apply{-1};  // 1: always where it can be, 0: never, -1: batches of few units
+// Batches of at most this many units on the k-slice plan run as one launch: it lasts 6 to 10 us, two launches about as
+// long as the host takes to issue them.  us per lora_apply called from Python, two launches / one, by (shrink units,
+// expand units): 4096 -> 4096 (4, 8) 10.5 / 7.2, (20, 24) 10.1 / 8.8, (28, 32) 10.1 / 9.3, (32, 32) 10.3 / 9.2,
+// (64, 32) 11.0 / 10.9, (96, 104) 10.1 / 12.5; 1024 -> 8192 (7, 64) 10.2 / 7.9, (24, 208) 10.5 / 10.0, (31, 304) 10.8 /
+// 10.8; 3008 -> 1920 (32, 15) 12.5 / 11.6, (46, 51) 10.9 / 11.8; 14336 -> 4096 (4, 8) 12.0 / 10.4, (28, 32) 12.8 /
+// 12.6, (64, 32) 15.0 / 15.7.  Beyond them the units that wait and poll slow those they wait for.
+static const int kSingleLaunchShrinkUnits = 32;
+static const int kSingleLaunchUnits = 96;
 static const unsigned kSpinLimit = 1u << 18;  // polls of a waiting expand unit before it gives up
 static std::atomic<unsigned> g_spin_limit{kSpinLimit};
 
@@ -766,7 +774,7 @@ static const lora_plan_options_t kDefaultOptions = LORA_PLAN_OPTIONS_DEFAULT;
 static int opt_whole_k_limit(const lora_segments *sg) { return sg->opts.whole_k_limit >= 0 ? sg->opts.whole_k_limit : g_whole_k_limit.load(); }
 static bool opt_merged(const lora_segments *sg) { return (sg->opts.merged_launches >= 0 ? sg->opts.merged_launches : g_merged_mixed.load()) != 0; }
 static bool opt_side_stream(const lora_segments *sg) { return (sg->opts.side_stream >= 0 ? sg->opts.side_stream : g_side_stream.load()) != 0; }
-static bool opt_fused_apply(const lora_segments *sg) { return (sg->opts.fused_apply >= 0 ? sg->opts.fused_apply : g_fused_apply.load()) != 0; }
+static int opt_fused_apply(const lora_segments *sg) { return sg->opts.fused_apply >= 0 ? sg->opts.fused_apply : g_fused_apply.load(); }
 static bool opt_decode_single(const lora_segments *sg) { return (sg->opts.decode_single_launch >= 0 ? sg->opts.decode_single_launch : g_decode_single_launch.load()) != 0; }
 static int opt_whole_k_max_in(const lora_segments *sg) { return sg->opts.whole_k_max_in >= 0 ? sg->opts.whole_k_max_in : kWholeKMaxIn; }
 static int opt_heavy_min_tokens(const lora_segments *sg) { return sg->opts.heavy_min_tokens >= 0 ? sg->opts.heavy_min_tokens : kPrefillMinTokens; }
@@ -2115,6 +2123,14 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     // Nor on a device where the probe launch did not find work group b on the XCD of b mod 8.
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     const DeviceProfile *prof = nullptr;
+    const int fused = opt_fused_apply(sg);
+    bool single = fused != 0 && !sg->has_big_units && !sg->wide &&
+                  (fused > 0 || (opt_decode_single(sg) && cs.n_units <= kSingleLaunchShrinkUnits &&
+                                 cs.n_units + ce.n_units <= kSingleLaunchUnits));
+    if (single && fused < 0) {  // under capture the two launches, as for the one-launch decode form above
+        HIP_TRY(hipStreamIsCapturing(s, &capturing));
+        single = capturing == hipStreamCaptureStatusNone;
+    }
     if (opt_decode_single(sg) && sg->decode_fused) {
         HIP_TRY(hipStreamIsCapturing(s, &capturing));
         int dev = -1;
@@ -2128,7 +2144,7 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
                                           sg->fused_grid, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices,
                                           (uint16_t *)y, ldy, prof->xcc_map.load(std::memory_order_relaxed), &sa, s));
         if (ev[1]) HIP_TRY(hipEventRecord(ev[1], s));
-    } else if (opt_fused_apply(sg) && !sg->has_big_units && !sg->wide) {
+    } else if (single) {
         ++msg->launches;
         HIP_TRY(lora::launch_apply_fused(cs, ce, (const uint16_t *)x, ldx, sg->k_slice_len, parts, nsl, stride,
                                          (uint16_t *)y, ldy, &sa, s));

@@ -1198,6 +1198,8 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 bk.yv[s] = zero;
                 if (c0 + s * kStrip < ncols) bk.yv[s] = ld16_stream(bk.e_y + c0 + s * kStrip);
             }
+            // (single launch) the weights and y are on their way while v is waited for
+            if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 const bool ok = (n < bk.ntok) && j_ok[it];
@@ -1222,7 +1224,6 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
             }
         };
 
-        if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx);  // weights are in flight
         // all of the unit's y and v go out at once (up to 4 blocks of 16 tokens), so that the HBM
         // latency of y is paid once per column pass, not once per block
         constexpr int NB = BIG ? 4 : 1;

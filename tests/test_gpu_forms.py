@@ -96,6 +96,51 @@ def test_token_heavy_units_cut_along_k(shape, sizes):
     dp.close()
 
 
+# ---- batches of few units: one launch by themselves, two under capture ------------------------------------------
+@pytest.mark.parametrize("case", [
+    (64, 128, [(1, 1)]),
+    (4096, 4096, [(1, 16)]),
+    (1088, 384, [(5, 256), (16, 256)]),             # 32 shrink units
+    (1088, 384, [(5, 256), (16, 256), (1, 8)]),     # 33: two launches
+    (4160, 1152, [(17, 40), (1, 8), (2, 16)]),      # k-slices, two token tiles
+    (512, 8192, [(3, 100)]),                        # 64 expand units
+])
+def test_batches_of_few_units(case):
+    in_features, out_features, groups = case
+    b = _batch(in_features, out_features, groups, idle=2, seed=8)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    x = G.bits_to_dev(x_bits)
+    segs = [L.lora_segments_build(dp.pool, b.token_adapter, options=o)
+            for o in (None, L.plan_options(fused_apply=0), L.plan_options(decode_single_launch=0))]
+    ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, segs[0]), 256), dtype=torch.uint8, device="cuda")
+    ys = []
+    for seg in segs:
+        y = G.bits_to_dev(y0)
+        L.lora_apply(dp.pool, seg, x, y, ws)
+        torch.cuda.synchronize()
+        L.lora_segments_check(seg)
+        ys.append(G.dev_to_bits(y))
+    G.check_all_rows(dp, x_bits, y0, ys[0])
+    assert np.array_equal(ys[0], ys[1]) and np.array_equal(ys[0], ys[2])
+    y = G.bits_to_dev(y0)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        L.lora_apply(dp.pool, segs[0], x, y, ws, stream=torch.cuda.current_stream())
+    eager = G.bits_to_dev(y0)
+    for _ in range(3):
+        y.copy_(G.bits_to_dev(y0))
+        graph.replay()
+        eager.copy_(G.bits_to_dev(y0))
+        L.lora_apply(dp.pool, segs[0], x, eager, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(G.dev_to_bits(y), ys[0]) and np.array_equal(G.dev_to_bits(eager), ys[0])
+    del graph
+    for seg in segs:
+        L.lora_segments_destroy(seg)
+    dp.close()
+
+
 # ---- lora_linear: small tiles, large tiles, both in one launch --------------------------------------------------
 def _batch(in_features, out_features, groups, idle=0, seed=0):
     """groups: (tokens, rank) of one adapter each; `idle` tokens without adapter; tokens in random order."""
