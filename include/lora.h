@@ -209,7 +209,7 @@ typedef struct {
     int32_t heavy_min_tokens;      /* a group of at least this many tokens is token-heavy (32) ...        */
     int32_t heavy_min_batch;       /* ... in a batch of at least this many active tokens (1024)           */
     int32_t heavy_k_cut_max_units; /* token-heavy shrink units are cut along k while the cut units stay    *
-                                    * within this count (320; 750 beyond in_features 8192)                 */
+                                    * within this count (built in: 1, 2 or 4 slices by estimated time)     */
     int32_t big_runs_max_units;    /* 64-token expand units take their columns in 8 runs or more, not 4, while *
                                     * the launch stays within this many of them (two per compute unit: 512) */
 } lora_plan_options_t;

@@ -4,6 +4,7 @@
 #include "lora_internal.h"
 
 #include <algorithm>
+#include <functional>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -596,20 +597,51 @@ static int heavy_tile(int r8) { return r8 <= 64 || r8 > 192 ? 32 : 64; }
 // rank, must fit the kernel's 64 KiB of LDS): every rank the pool holds
 static const int kBigExpandMaxRank = 256;
 static_assert(kBigExpandMaxRank >= LORA_MAX_RANK_PADDED, "the 16-token expand units of token-heavy groups are gone");
-// A token-heavy shrink unit is one walk through k (a wavefront takes a quarter of k in passes of 128, one
-// trip to memory each), and a launch of few such units lasts as long as one unit's walk (cfg3's routing
-// scaled to 1.5 k .. 9.5 k tokens: 32-37 us at 4096 input features, 99-116 us at 14336, whatever the
-// number of tokens).  In a batch planned in k-slices such units are cut into 4 or 2 slices along k while
-// the cut units stay within these counts.  Measured, shrink launch in us uncut / 2 / 4 slices; 4096: 41
-// units 32 / 28 / 23, 79 units 33 / 28 / 25, 148 units 33 / 30 / 33, 161 units 19.5 / 21.4, 291 units
-// 37 / 40 / 45, 321 units 28.2 / 28.2; 8192: 250 units 38.7 / 38.9; 14336: 41 units 99 / 67 / 52, 79
-// units 102 / 67 / 59, 148 units 102 / 75 / 77, 291 units 116 / 102 / 109, 301 units 85.6 / 75.7, 450
-// units 94 / 101.5, 600 units 126.6 / 126.3, cfg2's 718 units 155 / 155 / 162.  So two slices pay up
-// to about 320 cut units at 4096 .. 8192 input features and up to 600 .. 900 at 14336, where a unit's
-// walk is 3.5 times as long.
-static const int kHeavyKCutMaxUnits = 320;
-static const int kHeavyKCutLongK = 8192;          // beyond this many input features:
-static const int kHeavyKCutMaxUnitsLongK = 750;
+static int g_compute_units = 256;  // of the chip: a whole-k launch within this many units is one round
+
+// K-slices of a launch's token-heavy shrink units: 1, 2 or 4, by what a launch is estimated to last.  A unit is one walk
+// through k, and a compute unit passes about 50 GB/s, so a launch of few units lasts as long as its heaviest one
+// (rows of x and A^T times in_features), or as the two that share a compute unit; the low ranks' bodies take at
+// least a trip to memory per pass of 128 of k and wavefront; a cut costs 4 - 5 us for the sums' way through memory.
+// Beyond the counts below the cut units run in rounds and the estimate no longer holds.  lora_apply in us (128 columns,
+// so nearly all of it the shrink), 1 / 2 / 4 slices.  8 prompts of 1150 tokens, ranks 8..128 (164 units): 2048 features
+// 24.2 / 21.0 / 21.2, 4096 36.6 / 29.3 / 31.5, 8192 61.7 / 45.5 / 46.3, 14336 99 / 70 / 66; 4 prompts beside 200 decode
+// tokens (78 units): 4096 38.3 / 29.3 / 24.9, 14336 104 / 67 / 51; 4 prompts of 1500 at rank 128 (77 units): 4096 36.6 /
+// 27.9 / 31.1; 8 prompts of 1500 (258 units) at rank 64: 4096 30.5 / 31.9 / 33.0, 8192 53.2 / 49.7 / 47.8, at rank 16:
+// 4096 20.5 / 20.5 / 20.4, 8192 40.3 / 32.5 / 31.6; 16 prompts of 1000 (359 units): 2048 25.6 / 28.1 / 27.8, 4096 39.1 /
+// 37.8 / 41.1, 8192 65.9 / 55.6 / 59.2.
+static const int kHeavyCutMaxUnits = 512;       // two work groups per compute unit; beside decode-sized groups, whose
+static const int kHeavyCutMaxUnitsMixed = 448;  // units want places too, an eighth less; from 8192 input features on,
+static const int kHeavyCutMaxUnitsLongK = 750;  // where a slice is long, some of a second round
+static const double kHeavyRowsPerUs = 25000.0;  // rows of one input feature, 2 bytes each, that a compute unit passes per us
+static int choose_heavy_k_slices(std::vector<int> &rows, bool low_ranks, bool mixed, int in, int max_slices)
+{
+    const int n = (int)rows.size(), cus = g_compute_units;
+    if (n == 0) return 1;
+    std::sort(rows.begin(), rows.end(), std::greater<int>());
+    int best = 1;
+    double best_us = 0;
+    for (int c : {1, 2, 4}) {
+        // (the long-k limit not for four slices beside decode-sized groups: 8 prompts and 384 decode tokens, 169 units,
+        // 14336 features, 2 / 4 slices 79.4 / 83.1 us)
+        const int most = in < 8192 ? (mixed ? kHeavyCutMaxUnitsMixed : kHeavyCutMaxUnits)
+                                   : (mixed && c == 4 ? kHeavyCutMaxUnits : kHeavyCutMaxUnitsLongK);
+        if (c > max_slices || (c > 1 && n * c > most)) break;
+        double load = rows[0];  // of the busiest compute unit, in rows of the whole of k
+        if (n * c > cus) load = std::max(load, (rows[0] + rows[cus / c]) / (low_ranks ? 1.4 : 1.0));
+        double total = 0;
+        if (n * c > 2 * cus) {
+            for (int r : rows) total += r;
+            load = std::max(load, 1.3 * c * total / cus);
+        }
+        const double us = std::max(load / c * in / kHeavyRowsPerUs, in / (512.0 * c) * (low_ranks ? 1.9 : 0.9)) + (c == 1 ? 0 : c == 2 ? 4 : 5);
+        if (c == 1 || us < best_us - 1.0) {
+            best = c;
+            best_us = us;
+        }
+    }
+    return best;
+}
 // 64-token expand units take a group's columns in 8, 16, .. runs instead of 4 (down to one strip of 128 columns
 // each), the most that keep the launch within one round of work groups (two per compute unit): it then
 // lasts as long as one unit, a strip after the other.  Expand launch in us by units allowed, 4 runs / 256 / 512 /
@@ -749,7 +781,6 @@ static void order_heavy_units_by_xcd(std::vector<Unit> &units)
 // groups of at least this many tokens go to the front of the adapted layer's row order (lora_linear)
 static const int kLinFillingGroup = 16;
 
-static int g_compute_units = 256;  // of the chip: a whole-k launch within this many units is one round
 static int opt_big_runs_max_units(const lora_segments *sg)
 {
     return sg->opts.big_runs_max_units >= 0 ? sg->opts.big_runs_max_units : kBigRunsWorkGroupsPerComputeUnit * g_compute_units;
@@ -780,11 +811,6 @@ static int opt_whole_k_max_in(const lora_segments *sg) { return sg->opts.whole_k
 static int opt_heavy_min_tokens(const lora_segments *sg) { return sg->opts.heavy_min_tokens >= 0 ? sg->opts.heavy_min_tokens : kPrefillMinTokens; }
 static int opt_heavy_min_batch(const lora_segments *sg) { return sg->opts.heavy_min_batch >= 0 ? sg->opts.heavy_min_batch : kPrefillMinBatch; }
 static int opt_big_runs_max_units(const lora_segments *sg);
-static int opt_heavy_k_cut_max_units(const lora_segments *sg, int in_features)
-{
-    if (sg->opts.heavy_k_cut_max_units >= 0) return sg->opts.heavy_k_cut_max_units;
-    return in_features > kHeavyKCutLongK ? kHeavyKCutMaxUnitsLongK : kHeavyKCutMaxUnits;
-}
 static unsigned opt_spin_limit(const lora_segments *sg) { return sg->opts.fused_wait_limit ? sg->opts.fused_wait_limit : g_spin_limit.load(); }
 
 // Offsets of the lists inside the device table.
@@ -1067,17 +1093,27 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     sg->has_big_units = false;
     sg->heavy_small_expand = false;
     sg->n_prefill_hi = 0;
-    // A launch of few token-heavy shrink units lasts as long as one unit's walk through k (a wavefront
-    // takes a quarter of k in passes of 128, one trip to memory each); such units are cut into k-slices.
-    int64_t heavy_units = 0;
-    for (const SegRec &r : sg->segs)
-        if (r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch)
-            heavy_units += (r.ntok + heavy_tile(r.r8) - 1) / heavy_tile(r.r8);
+    // (per projection, whatever the number of projections: lora_apply_multi gives the bits of separate applies)
     int heavy_k_slices = 1;
-    if (sg->n_k_slices >= 2 && heavy_units > 0) {
-        const int64_t limit = opt_heavy_k_cut_max_units(sg, pool->in_features);
-        for (int c = std::min(4, sg->n_k_slices); c >= 2 && heavy_k_slices == 1; c /= 2)
-            if (heavy_units * c <= limit) heavy_k_slices = c;  // per projection: lora_apply_multi gives the bits of separate applies
+    if (sg->n_k_slices >= 2) {
+        std::vector<int> rows;
+        int top = 0;
+        int64_t n_units = 0;
+        for (const SegRec &r : sg->segs) {
+            if (!(r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch)) continue;
+            const int tile = heavy_tile(r.r8);
+            n_units += (r.ntok + tile - 1) / tile;
+            top = std::max(top, r.r8);
+            if (2 * n_units <= kHeavyCutMaxUnitsLongK)
+                for (int t = 0; t < r.ntok; t += tile) rows.push_back(std::min(tile, r.ntok - t) + r.r8);
+        }
+        const int max_slices = std::min(4, sg->n_k_slices);
+        if (sg->opts.heavy_k_cut_max_units < 0) {
+            if (2 * n_units <= kHeavyCutMaxUnitsLongK) heavy_k_slices = choose_heavy_k_slices(rows, top <= 64, whole_k_units > 0, pool->in_features, max_slices);
+        } else {
+            for (int c = max_slices; c >= 2 && n_units > 0 && heavy_k_slices == 1; c /= 2)
+                if (n_units * c <= sg->opts.heavy_k_cut_max_units) heavy_k_slices = c;
+        }
     }
     sg->heavy_k_slices = heavy_k_slices;
     // The 64-token expand units: a group's columns in 4 runs, or in more and shorter ones while that keeps the
