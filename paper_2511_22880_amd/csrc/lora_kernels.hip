@@ -2293,14 +2293,17 @@ static __device__ __forceinline__ void linear_small_body(
     constexpr int kSlab = 16 * RB * 128;     // bytes of a wavefront's x region: 16 RB rows of 64 k
     constexpr int kTiles = RB * CB;
     static_assert(8 % CB == 0, "a tile lies in one strip");
-    // Work group b runs on XCD b mod 8: a strip's tiles (all row tiles, all its column tiles) on one XCD, so
-    // that W and the adapters' B^T enter one L2 and the partial lines of y meet there.
+    // Work group b runs on XCD b mod 8: every XCD an eighth of the tiles, a run of them in the order column tile,
+    // row tile, so that W and the adapters' B^T of a column tile enter one or two L2s and the partial lines of a
+    // strip's y meet there.  (Whole strips dealt to the XCDs left some of them with nothing or twice the others'
+    // share: 1428 tokens at 7168 -> 640, 5 strips, 52.5 -> 48.6 us per
+    // layer; 2796 tokens at 1664 -> 640 63.0 -> 47.0; 81 tokens at 1536 -> 2688 19.5 -> 16.6; multiples of 8 level.)
     constexpr int SUB = 8 / CB;
-    const int xcd = blk & 7, jloc = blk >> 3;
-    const int mt = jloc % m_tiles, sub = (jloc / m_tiles) % SUB;
-    const int strip = (jloc / m_tiles / SUB) * 8 + xcd;
-    if (strip * 128 >= out) return;
-    const int b0 = sub * CB;
+    const int total = m_tiles * (out / (16 * CB)), per_xcd = (total + 7) >> 3;
+    const int idx = (blk & 7) * per_xcd + (blk >> 3);
+    if ((blk >> 3) >= per_xcd || idx >= total) return;
+    const int ct = idx / m_tiles, mt = idx - ct * m_tiles;
+    const int strip = ct / SUB, b0 = ct % SUB * CB;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2481,7 +2484,7 @@ static void launch_linear_small(const int32_t *rows, const int32_t *start, const
                                 hipStream_t stream)
 {
     const int m_tiles = (n_places + 16 * RB - 1) / (16 * RB);
-    const int grid = 8 * ((out / 128 + 7) / 8) * m_tiles * (8 / CB);
+    const int grid = 8 * ((m_tiles * (out / (16 * CB)) + 7) / 8);  // an eighth of the tiles per XCD
     hipLaunchKernelGGL((k_linear_small<RB, CB, D>), dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, start,
                        pieces, m_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
 }
@@ -2803,7 +2806,7 @@ hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n
     const int m_small = n_places > m_big * kLinTileM ? (n_places - m_big * kLinTileM + 63) / 64 : 0;
     // per XCD: groups of 32 work groups = 8 row tiles x 4 column tiles (see the kernel)
     const int64_t n_big = (int64_t)8 * 32 * (((m_big + 7) / 8 + 7) / 8) * ((n_tiles + 3) / 4);
-    const int64_t grid = n_big + (int64_t)8 * ((out / 128 + 7) / 8) * m_small * 2;
+    const int64_t grid = n_big + (int64_t)8 * (((int64_t)m_small * (out / 64) + 7) / 8);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_linear_lora, dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, start, pieces, (int)n_big, m_big,
                        n_tiles, m_small, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
