@@ -478,8 +478,10 @@ lora_status_t lora_set_merged_launches(int enabled);
  * one stream, as ever.  Two such launches that run at the same time on one GPU (different objects on
  * different streams) can hold each other's compute units while they wait: their waits are bounded and
  * reported, but callers that overlap applies should select two launches.
- * lora_set_decode_single_launch(0): always two launches.  Read when a batch is planned and again when it
- * is applied.  Process-wide; default 1. */
+ * lora_set_decode_single_launch(0): always two launches; (1): the one launch wherever the batch fits it.  Until
+ * this is called (and with -1 in the plan settings until then) a batch is planned for the one launch where
+ * that is the faster form: at least 192 shrink units and in_features + out_features of at least 8192.
+ * Read when a batch is planned and again when it is applied.  Process-wide. */
 lora_status_t lora_set_decode_single_launch(int enabled);
 lora_status_t lora_set_side_stream(int enabled);
 

@@ -786,7 +786,7 @@ static int opt_big_runs_max_units(const lora_segments *sg)
     return sg->opts.big_runs_max_units >= 0 ? sg->opts.big_runs_max_units : kBigRunsWorkGroupsPerComputeUnit * g_compute_units;
 }
 static const int kXcds = 8;         // XCDs of the chip, each with an L2 of its own; work group b of a launch runs on XCD b mod 8
-static std::atomic<int> g_decode_single_launch{1};
+static std::atomic<int> g_decode_single_launch{-1};  // 1: wherever it can be, 0: never, -1: where it is the faster form
 static std::atomic<int> g_side_stream{1};
 static std::atomic<int> g_fused_apply{-1};  // 1: always where it can be, 0: never, -1: batches of few units
 // Batches of at most this many units on the k-slice plan run as one launch: it lasts 6 to 10 us, two launches about as
@@ -806,7 +806,19 @@ static int opt_whole_k_limit(const lora_segments *sg) { return sg->opts.whole_k_
 static bool opt_merged(const lora_segments *sg) { return (sg->opts.merged_launches >= 0 ? sg->opts.merged_launches : g_merged_mixed.load()) != 0; }
 static bool opt_side_stream(const lora_segments *sg) { return (sg->opts.side_stream >= 0 ? sg->opts.side_stream : g_side_stream.load()) != 0; }
 static int opt_fused_apply(const lora_segments *sg) { return sg->opts.fused_apply >= 0 ? sg->opts.fused_apply : g_fused_apply.load(); }
-static bool opt_decode_single(const lora_segments *sg) { return (sg->opts.decode_single_launch >= 0 ? sg->opts.decode_single_launch : g_decode_single_launch.load()) != 0; }
+static int opt_decode_single(const lora_segments *sg) { return sg->opts.decode_single_launch >= 0 ? sg->opts.decode_single_launch : g_decode_single_launch.load(); }
+// A whole-k decode batch in one launch (k_decode_fused) or in two?  The one launch saves a boundary but runs its expand
+// units four to a compute unit behind the compute unit's own shrink unit; it wins where the shrink units nearly fill
+// the chip and there is much to read.  us per lora_apply, one / two launches, by shrink units as the one launch counts
+// them: 4096 -> 4096 199 14.4 / 15.9, 202 15.1 / 15.2, 160 (rank 128) 16.3 / 14.8, 161 (ranks 1..256) 16.6 / 14.9, 128 (rank
+// 256) 18.3 / 14.3, 97 12.0 / 11.5, 64 13.0 / 12.5; 14336 -> 4096 199 25.5 / 27.8, 161 27.7 / 25.0, 128 25.9 / 23.6, 97 18.6 /
+// 19.2; 8192 -> 2048 199 18.2 / 18.0, 202 16.7 / 17.3, 161 19.1 / 17.6; 3008 -> 1920 199 13.2 / 13.0, 161 15.1 / 13.3, 128
+// 16.8 / 13.2; 4096 -> 1024 199 12.9 / 12.5, 160 13.7 / 12.1; 2048 -> 8192 161 19.7 / 16.3, 97 14.5 / 12.0; 1024 -> 2048 202
+// 10.3 / 10.0, 128 15.3 / 11.2.
+static bool decode_single_pays(int opt, int64_t whole_k_units, int in, int out)
+{
+    return opt > 0 || (opt < 0 && 4 * whole_k_units >= 3 * (int64_t)g_compute_units && in + out >= 8192);
+}
 static int opt_whole_k_max_in(const lora_segments *sg) { return sg->opts.whole_k_max_in >= 0 ? sg->opts.whole_k_max_in : kWholeKMaxIn; }
 static int opt_heavy_min_tokens(const lora_segments *sg) { return sg->opts.heavy_min_tokens >= 0 ? sg->opts.heavy_min_tokens : kPrefillMinTokens; }
 static int opt_heavy_min_batch(const lora_segments *sg) { return sg->opts.heavy_min_batch >= 0 ? sg->opts.heavy_min_batch : kPrefillMinBatch; }
@@ -841,13 +853,13 @@ static void layout_table(lora_segments *sg)
 // with the most tokens are cut into two units of 8 (they pass the most bytes, x beside A^T, through
 // their compute unit and would end the launch).  Inside an XCD the heaviest shrink units share a work
 // group with the lightest expand units.
-static void finish_decode_fused(lora_segments *sg, int in_features)
+static void finish_decode_fused(lora_segments *sg, bool want, int in_features)
 {
     sg->fused_shrink.clear();
     sg->fused_expand.clear();
     sg->fused_grid = 0;
     const int cap_s = g_compute_units / kXcds, cap_e = 4 * cap_s;
-    sg->decode_fused = opt_decode_single(sg) && sg->wide && sg->prefill_units.empty() && sg->expand_big_units.empty() &&
+    sg->decode_fused = want && sg->wide && sg->prefill_units.empty() && sg->expand_big_units.empty() &&
                        !sg->shrink_units.empty() && !sg->expand_units.empty() && sg->n_sync > 0 &&
                        sg->shrink_units.size() <= (size_t)g_compute_units &&
                        sg->expand_units.size() <= (size_t)(4 * g_compute_units) && g_compute_units % kXcds == 0;
@@ -1001,8 +1013,8 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     // us): split_min_tokens is the smallest token count whose units can all be cut within that budget.
     int split_min_tokens = 0;
     // (a batch that may run as one launch gets its row halves per XCD, in finish_decode_fused)
-    const bool want_fused = opt_decode_single(sg) && sg->wide && !heavy_groups && n_projections == 1 &&
-                            whole_k_units <= g_compute_units;
+    const bool want_fused = decode_single_pays(opt_decode_single(sg), whole_k_units, pool->in_features, pool->out_features) &&
+                            sg->wide && !heavy_groups && n_projections == 1 && whole_k_units <= g_compute_units;
     if (sg->wide && !want_fused) {
         int64_t per_tokens[lora::kTokTile + 1] = {0};  // full 16-row units by their token count
         for (int a = 0; a < N; ++a) {
@@ -1232,10 +1244,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     order_units_by_xcd(sg->shrink_units);
     order_heavy_units_by_xcd(sg->prefill_units);
 
-    if (n_projections == 1)
-        finish_decode_fused(sg, pool->in_features);
-    else
-        sg->decode_fused = false;
+    finish_decode_fused(sg, want_fused, pool->in_features);
     // row order of the adapted layer: groups that fill blocks of 16 rows, the tokens without adapter, then the
     // small groups (the kernel's large tiles take rows from the front, and a block of many adapters costs
     // them most), the whole padded to a multiple of the kernel's row tile

@@ -199,3 +199,27 @@ def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
         assert np.array_equal(finite, b.token_adapter != 1)
         L.lora_segments_destroy(seg)
         dp.close()
+
+
+# ---- whole-k decode batches: one launch from 192 shrink units and 8192 features in and out together, else two -------
+@pytest.mark.parametrize("units", [64, 191, 192, 256])
+@pytest.mark.parametrize("shape", [(4096, 4096), (4096, 3968), (1024, 7168)])
+def test_decode_batches_on_either_side_of_the_one_launch_rule(units, shape):
+    """Groups of one rank block each: the built-in choice, one launch and two launches give the same bits."""
+    b = _batch(*shape, [(1 + i % 2, 16) for i in range(units)], seed=units)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    x, ys = G.bits_to_dev(x_bits), []
+    for o in (None, L.plan_options(decode_single_launch=1), L.plan_options(decode_single_launch=0)):
+        seg = L.lora_segments_build(dp.pool, b.token_adapter, options=o)
+        ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, seg), 256), dtype=torch.uint8, device="cuda")
+        y = G.bits_to_dev(y0)
+        L.lora_apply(dp.pool, seg, x, y, ws)
+        torch.cuda.synchronize()
+        L.lora_segments_check(seg)
+        ys.append(G.dev_to_bits(y))
+        L.lora_segments_destroy(seg)
+    assert np.array_equal(ys[0], ys[1]) and np.array_equal(ys[0], ys[2])
+    rows = np.arange(0, b.T, 7)
+    G.check_parity(ys[0], G.oracle_apply(dp, x_bits, y0, rows=rows), y0, b.token_adapter, rows=rows)
+    dp.close()
