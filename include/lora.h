@@ -435,7 +435,7 @@ lora_status_t lora_set_whole_k_limit(int32_t max_units);
  * object, capture again.  The single-launch form takes an epoch from
  * host state of the segment object at launch: it must not be captured, and not be used on an object
  * that a captured graph replays.  The setting is process-wide.  Until this is called, batches of few
- * units (at most 32 shrink units and 96 in all) take the single launch by themselves, with the same
+ * units (at most 64 active tokens, 32 shrink units and 96 units in all) take the single launch by themselves, with the same
  * bits, unless lora_set_decode_single_launch(0) holds or the stream is being captured (where the two
  * launches are issued; a graph that holds those may be replayed between such applies). */
 lora_status_t lora_set_fused_apply(int enabled);

@@ -794,9 +794,12 @@ static std::atomic<int> g_fused_apply{-1};  // 1: always where it can be, 0: nev
 // expand units): 4096 -> 4096 (4, 8) 10.5 / 7.2, (20, 24) 10.1 / 8.8, (28, 32) 10.1 / 9.3, (32, 32) 10.3 / 9.2,
 // (64, 32) 11.0 / 10.9, (96, 104) 10.1 / 12.5; 1024 -> 8192 (7, 64) 10.2 / 7.9, (24, 208) 10.5 / 10.0, (31, 304) 10.8 /
 // 10.8; 3008 -> 1920 (32, 15) 12.5 / 11.6, (46, 51) 10.9 / 11.8; 14336 -> 4096 (4, 8) 12.0 / 10.4, (28, 32) 12.8 /
-// 12.6, (64, 32) 15.0 / 15.7.  Beyond them the units that wait and poll slow those they wait for.
+// 12.6, (64, 32) 15.0 / 15.7.  Beyond them the units that wait and poll slow those they wait for; so they do with
+// many full token tiles: 126 tokens of 2 adapters, 4096 -> 4096 (32, 64) 9.6 / 11.2, 8192 -> 2048 (32, 32) 11.1 / 12.2
+// (40 tokens, (24, 32), 10.5 / 9.7).
 static const int kSingleLaunchShrinkUnits = 32;
 static const int kSingleLaunchUnits = 96;
+static const int kSingleLaunchTokens = 64;
 static const unsigned kSpinLimit = 1u << 18;  // polls of a waiting expand unit before it gives up
 static std::atomic<unsigned> g_spin_limit{kSpinLimit};
 
@@ -2170,8 +2173,8 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     const DeviceProfile *prof = nullptr;
     const int fused = opt_fused_apply(sg);
     bool single = fused != 0 && !sg->has_big_units && !sg->wide &&
-                  (fused > 0 || (opt_decode_single(sg) && cs.n_units <= kSingleLaunchShrinkUnits &&
-                                 cs.n_units + ce.n_units <= kSingleLaunchUnits));
+                  (fused > 0 || (opt_decode_single(sg) != 0 && sg->n_active <= kSingleLaunchTokens &&
+                                 cs.n_units <= kSingleLaunchShrinkUnits && cs.n_units + ce.n_units <= kSingleLaunchUnits));
     if (single && fused < 0) {  // under capture the two launches, as for the one-launch decode form above
         HIP_TRY(hipStreamIsCapturing(s, &capturing));
         single = capturing == hipStreamCaptureStatusNone;

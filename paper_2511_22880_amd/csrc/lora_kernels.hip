@@ -813,7 +813,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
 // one barrier per pass).  With k split over the wavefronts as above, a unit of 32 tokens loads all of
 // A^T for 32 tokens' worth of x: at rank 128 four times the bytes of x, which made the compute units'
 // vector caches, not memory, the bound (uniform rank 128 on cfg2's routing: 78 us against 35 us at
-// rank 8; 62 us with this body).  No sums cross wavefronts: each stores the rows of v it owns.  (Up to
+// rank 8; 62 us with this body).  No sums cross wavefronts: each puts the rows of v it owns into LDS, from where they leave.  (Up to
 // rank 64 the k-split body of 32 tokens stayed as fast or faster: 50 us at uniform rank 64 either way.
 // Ranks 129..192 take three row blocks per wavefront and 64 tokens, ranks 193..256 four and 32 tokens, the
 // accumulators of 64 not fitting the registers: against units of 16 tokens with k split, the shrink
