@@ -566,6 +566,16 @@ static __device__ __forceinline__ void store_v4(f32x4 f, int64_t at, uint16_t *_
     *reinterpret_cast<uint2 *>(v_lo + at) = l;
 }
 
+// threadIdx.x for the stores behind a unit's k loop, where the compiler cannot see it: it computes what depends on the
+// thread index before the loop otherwise, and carries it through on spilled registers (k_shrink_prefill 9 spilled, one
+// this way; rank 64, 16 prompts of 1000 tokens, uncut, 4096 features, shrink launch 34.5 -> 30.4 us).
+static __device__ __forceinline__ int late_thread()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // The end of a token-heavy shrink unit, by all threads of its work group: rows row0 .. row0 + rows - 1 of the unit's
 // v are one run of memory, which goes out in 16-byte pieces, neighbouring threads side by side; quad(i) = the sums
 // of its elements 4 i .. 4 i + 3.  (Straight from the MFMA registers a wavefront's stores were 8 bytes of each of 64
@@ -584,16 +594,16 @@ static __device__ __forceinline__ void store_heavy_rows(const Unit &u, int n_ks,
     const int64_t at = u.v_off + (int64_t)row0 * u.r8;
     if (n_ks > 1 && !v_f32) {
         const Through slice(parts + (int64_t)u.ks * slice_stride + at, 4 * n);
-        for (int i = threadIdx.x; i < n; i += kThreads) slice.st(i, quad(i));
+        for (int i = late_thread(); i < n; i += kThreads) slice.st(i, quad(i));
     } else if (v_f32) {
         float *dst = v_f32 + (int64_t)u.ks * slice_stride + at;
-        for (int i = threadIdx.x; i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[i] = quad(i);
+        for (int i = late_thread(); i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[i] = quad(i);
         if (n_ks > 1 && u.ks == 0)
             for (int sl = n_ks; sl < n_slices; ++sl)
-                for (int i = threadIdx.x; i < n; i += kThreads)
+                for (int i = late_thread(); i < n; i += kThreads)
                     reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
-        for (int i = threadIdx.x; i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * i, v_hi, v_lo);
+        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * i, v_hi, v_lo);
     }
 }
 
@@ -614,12 +624,12 @@ static __device__ __forceinline__ void complete_tile(const Unit &u, int n_ks, in
     const Through s0(parts + u.v_off, 4 * n), s1(parts + u.v_off + slice_stride, 4 * n);
     if (n_ks <= 2) {
 #pragma unroll 4
-        for (int i = threadIdx.x; i < n; i += kThreads) store_v4(vs * (s0.ld(i) + s1.ld(i)), u.v_off + 4 * i, v_hi, v_lo);
+        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * (s0.ld(i) + s1.ld(i)), u.v_off + 4 * i, v_hi, v_lo);
     } else {
         const Through s2(parts + u.v_off + 2 * slice_stride, 4 * n);
         const Through s3(parts + u.v_off + (n_ks > 3 ? 3 : 2) * slice_stride, 4 * n);
 #pragma unroll 4
-        for (int i = threadIdx.x; i < n; i += kThreads) {
+        for (int i = late_thread(); i < n; i += kThreads) {
             f32x4 f = s0.ld(i) + s1.ld(i);
             f += s2.ld(i);
             const f32x4 f3 = s3.ld(i);
