@@ -434,10 +434,12 @@ lora_status_t lora_set_whole_k_limit(int32_t max_units);
  * and the table address of the plan it was captured with: after lora_segments_rebuild on the
  * object, capture again.  The single-launch form takes an epoch from
  * host state of the segment object at launch: it must not be captured, and not be used on an object
- * that a captured graph replays.  The setting is process-wide.  Until this is called, batches of few
+ * that a captured graph replays.  lora_set_fused_apply(0): always two launches (unless the whole-k form of
+ * lora_set_decode_single_launch applies).  lora_set_fused_apply(-1), the state before the first call: batches of few
  * units (at most 64 active tokens, 32 shrink units and 96 units in all) take the single launch by themselves, with the same
  * bits, unless lora_set_decode_single_launch(0) holds or the stream is being captured (where the two
- * launches are issued; a graph that holds those may be replayed between such applies). */
+ * launches are issued; a graph that holds those may be replayed between such applies).  What is said below about
+ * launches of one-launch forms that run at the same time on one GPU holds for these too.  Process-wide. */
 lora_status_t lora_set_fused_apply(int enabled);
 
 /* A mixed batch holds token-heavy groups and decode-sized groups, whose units are of different kinds.
@@ -478,8 +480,8 @@ lora_status_t lora_set_merged_launches(int enabled);
  * one stream, as ever.  Two such launches that run at the same time on one GPU (different objects on
  * different streams) can hold each other's compute units while they wait: their waits are bounded and
  * reported, but callers that overlap applies should select two launches.
- * lora_set_decode_single_launch(0): always two launches; (1): the one launch wherever the batch fits it.  Until
- * this is called (and with -1 in the plan settings until then) a batch is planned for the one launch where
+ * lora_set_decode_single_launch(0): always two launches; (1): the one launch wherever the batch fits it;
+ * (-1), the state before the first call: a batch is planned for the one launch where
  * that is the faster form: at least 192 shrink units and in_features + out_features of at least 8192.
  * Read when a batch is planned and again when it is applied.  Process-wide. */
 lora_status_t lora_set_decode_single_launch(int enabled);

@@ -481,12 +481,18 @@ def lora_apply_multi(pools, seg: Segments, x, y, workspace, stream=None, ldx: Op
                                   _addr(workspace), _ws_bytes(workspace, ws_bytes), _queue(stream)))
 
 
-def lora_set_fused_apply(enabled: bool) -> None:
-    _check(lib().lora_set_fused_apply(ctypes.c_int(1 if enabled else 0)))
+def _switch(enabled) -> ctypes.c_int:
+    return ctypes.c_int(-1 if enabled == -1 else 1 if enabled else 0)
 
 
-def lora_set_decode_single_launch(enabled: bool) -> None:
-    _check(lib().lora_set_decode_single_launch(ctypes.c_int(1 if enabled else 0)))
+def lora_set_fused_apply(enabled) -> None:
+    """True, False, or -1: the library's own choice, as before the first call."""
+    _check(lib().lora_set_fused_apply(_switch(enabled)))
+
+
+def lora_set_decode_single_launch(enabled) -> None:
+    """True, False, or -1: the library's own choice, as before the first call."""
+    _check(lib().lora_set_decode_single_launch(_switch(enabled)))
 
 
 def lora_set_side_stream(enabled: bool) -> None:

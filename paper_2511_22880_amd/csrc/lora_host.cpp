@@ -2056,14 +2056,14 @@ static const int kSideStreamMinUnits = 32;  // decode shrink units below which a
 
 extern "C" lora_status_t lora_set_fused_apply(int enabled)
 try {
-    g_fused_apply = enabled ? 1 : 0;
+    g_fused_apply = enabled == -1 ? -1 : enabled ? 1 : 0;
     return LORA_OK;
 }
 API_CATCH
 
 extern "C" lora_status_t lora_set_decode_single_launch(int enabled)
 try {
-    g_decode_single_launch = enabled ? 1 : 0;
+    g_decode_single_launch = enabled == -1 ? -1 : enabled ? 1 : 0;
     return LORA_OK;
 }
 API_CATCH

@@ -27,3 +27,13 @@ def lora():
 @pytest.fixture(scope="session")
 def quick_parity(request):
     return bool(request.config.getoption("--quick-parity"))
+
+
+@pytest.fixture(autouse=True)
+def built_in_choice_of_launches():
+    """Whatever a test switched: the next one meets the library's own choice between its launch forms."""
+    yield
+    from paper_2511_22880_amd import binding
+    if binding._lib is not None:
+        binding.lora_set_fused_apply(-1)
+        binding.lora_set_decode_single_launch(-1)

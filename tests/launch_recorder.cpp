@@ -1,0 +1,82 @@
+// The library's host source on top of a runtime that lives in host memory and launchers that write down what they are
+// asked to launch: which kernels a call issues, with how many units, can then be tested without a GPU.  Built and
+// loaded by test_launch_routes.py; "device" pointers are host addresses, and no kernel runs.
+#include "lora_internal.h"
+#include <cstdlib>
+#include <cstring>
+#include <string>
+
+static std::string g_log;
+static int g_capturing;
+
+static hipError_t note(const std::string &s)
+{
+    g_log += s + "\n";
+    return hipSuccess;
+}
+static std::string num(long long v) { return " " + std::to_string(v); }
+
+extern "C" {
+const char *recorder_take()
+{
+    static std::string out;
+    out.swap(g_log);
+    g_log.clear();
+    return out.c_str();
+}
+void recorder_capture(int on) { g_capturing = on; }
+
+hipError_t hipMalloc(void **p, size_t n) { return (*p = aligned_alloc(4096, (n + 4095) / 4096 * 4096)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void *p) { return hipFree(p); }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memmove(d, s, n); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
+{
+    *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)
+{
+    memset(p, 0, sizeof *p);
+    strcpy(p->gcnArchName, "gfx950");
+    p->multiProcessorCount = 256;
+    return hipSuccess;
+}
+const char *hipGetErrorString(hipError_t) { return "error"; }
+}
+
+namespace lora {
+hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink" + num(c.n_units)) : hipSuccess; }
+hipError_t launch_shrink_wide(const LaunchCtx &c, bool, const uint16_t *, int64_t, int, int, float *, uint16_t *, uint16_t *, hipStream_t) { return c.n_units ? note("shrink_wide" + num(c.n_units)) : hipSuccess; }
+hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note((big ? "expand_big" : "expand") + num(c.n_units)) : hipSuccess; }
+hipError_t launch_shrink_prefill(const LaunchCtx &c, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int n_slices, int64_t, float *, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink_prefill" + num(c.n_units) + num(n_slices)) : hipSuccess; }
+hipError_t launch_shrink_mixed(const LaunchCtx &h, int, const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return note("shrink_mixed" + num(h.n_units) + num(c.n_units)); }
+hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, const float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("expand_mixed" + num(b.n_units) + num(c.n_units)); }
+hipError_t launch_apply_fused(const LaunchCtx &s, const LaunchCtx &e, const uint16_t *, int64_t, int, float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("apply_fused" + num(s.n_units) + num(e.n_units)); }
+hipError_t launch_decode_fused(const LaunchCtx &, const LaunchCtx &, int grid, const uint16_t *, int64_t, int, int, uint16_t *, int64_t, unsigned, const SyncArgs *, hipStream_t) { return note("decode_fused" + num(grid)); }
+hipError_t launch_reduce_slices(const float *, int n, int64_t, float *, int64_t, hipStream_t) { return note("reduce_slices" + num(n)); }
+hipError_t launch_pack_adapter(const uint16_t *, const uint16_t *, int, int, int, int, uint16_t *, uint16_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_linear_lora(const int32_t *, const LinBlock *, int n_places, const uint16_t *, const uint16_t *, const uint16_t *, int64_t, int, int, const uint16_t *, const uint16_t *, uint16_t *, int64_t, hipStream_t) { return note("linear" + num(n_places)); }
+hipError_t launch_pack_weight(const uint16_t *, int, int, uint16_t *, hipStream_t) { return hipSuccess; }
+hipError_t probe_xcc(unsigned *x, int n, hipStream_t)
+{
+    for (int b = 0; b < n; ++b) x[b] = (unsigned)b % 8;
+    return hipSuccess;
+}
+hipError_t static_scratch(void **p)
+{
+    static char *mem = (char *)aligned_alloc(4096, kStaticScratchBytes);
+    *p = mem;
+    return hipSuccess;
+}
+}

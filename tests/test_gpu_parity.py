@@ -52,6 +52,7 @@ def test_decode_batches_up_to_the_widest_whole_k_plan():
         assert (L.lora_segments_info(seg)["n_k_slices"] == 1) == (in_f <= 18432)
         L.lora_segments_destroy(seg)
         dp.close()
+        L.lora_set_decode_single_launch(True)
         _full_parity(b)
         L.lora_set_decode_single_launch(False)
         try:
@@ -104,6 +105,7 @@ def test_two_launch_apply_matches_fused_apply():
         for b in (wl.small_mixed(seed=4), wl.cfg1_decode(in_features=2048, out_features=512)):
             dp = G.DevicePool(b)
             x_bits, y0_bits = b.x_bits(), b.y0_bits("small")
+            L.lora_set_fused_apply(False)
             y_two = G.apply_on_gpu(dp, x_bits, y0_bits)
             try:
                 L.lora_set_fused_apply(True)
@@ -130,6 +132,7 @@ def test_one_launch_decode_apply_matches_two_launches_bitwise():
         dp = G.DevicePool(b)
         x_bits, y0_bits = b.x_bits(), b.y0_bits("small")
         x = G.bits_to_dev(x_bits)
+        L.lora_set_decode_single_launch(True)
         seg = L.lora_segments_build(dp.pool, b.token_adapter)
         assert L.lora_segments_info(seg)["n_k_slices"] == 1, "the case is meant to be on the whole-k plan"
         ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, seg), 256), dtype=torch.uint8, device="cuda")

@@ -601,7 +601,7 @@ def test_one_launch_decode_plan_keeps_every_tile_on_one_xcd():
         pool = L.lora_pool_create(b.in_features, b.out_features, b.ranks, b.scales, FAKE_ARENA, n)
         for a in range(b.n_adapters):
             L.lora_pool_mark_resident(pool, a)
-        seg = L.lora_segments_plan(pool, b.token_adapter)
+        seg = L.lora_segments_plan(pool, b.token_adapter, options=L.plan_options(decode_single_launch=1))
         info = L.lora_segments_info(seg)
         if not info["single_launch"]:
             L.lora_segments_destroy(seg)

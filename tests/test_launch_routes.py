@@ -1,0 +1,114 @@
+"""Which launches a call takes, by rules on sizes, settings and capture: the library's host source against launchers
+that record (launch_recorder.cpp).  No GPU."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2511_22880_amd import binding as L
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2511_22880_amd", "csrc")
+HIP_INCLUDE = "/opt/rocm/include"
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(HIP_INCLUDE),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    """The binding on top of the recording library, for this module's tests."""
+    so = str(tmp_path_factory.mktemp("recorder") / "liblora_recorder.so")
+    cmd = ["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I" + HIP_INCLUDE,
+           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-o", so, os.path.join(ROOT, "tests", "launch_recorder.cpp"),
+           os.path.join(CSRC, "lora_host.cpp"), os.path.join(CSRC, "lora_place.cpp")]
+    build = subprocess.run(cmd, capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-2000:]
+    path, loaded = L.LIB_PATH, L._lib
+    L.LIB_PATH, L._lib = so, None
+    lib = L.lib()
+    lib.recorder_take.restype = ctypes.c_char_p
+    yield lib
+    L.LIB_PATH, L._lib = path, loaded
+
+
+class Batch:
+    """A pool (or several side by side) with every adapter resident, in host memory."""
+
+    def __init__(self, in_features, outs, groups, idle=0):
+        self.ranks = np.array([r for _, r in groups], dtype=np.int32)
+        self.scales = np.ones(len(groups), dtype=np.float32)
+        outs = [outs] if isinstance(outs, int) else outs
+        self.ta = np.concatenate([np.full(n, a, dtype=np.int32) for a, (n, _) in enumerate(groups)]
+                                 + [np.full(idle, -1, dtype=np.int32)])
+        base, at = 1 << 40, 0  # never touched: no kernel runs
+        self.pools = []
+        for o in outs:
+            nbytes = L.lora_pool_bytes(in_features, o, self.ranks, self.scales)
+            pool = L.lora_pool_create(in_features, o, self.ranks, self.scales, base + at, arena_bytes=nbytes)
+            at += (nbytes + 4095) // 4096 * 4096
+            for a in range(len(groups)):
+                L.lora_pool_mark_resident(pool, a)
+            self.pools.append(pool)
+        self.in_features, self.out = in_features, sum(outs)
+
+    def build(self, options=None):
+        if len(self.pools) > 1:
+            return L.lora_segments_build_multi(self.pools, self.ta, options=options)
+        return L.lora_segments_build(self.pools[0], self.ta, options=options)
+
+    def launches(self, lib, seg, call="apply"):
+        """[(kernel, numbers ...), ...] of one call."""
+        lib.recorder_take()
+        x, y, v, ws, n = 1 << 44, 1 << 45, 1 << 46, 1 << 47, 1 << 40
+        if call == "apply" and len(self.pools) > 1:
+            L.lora_apply_multi(self.pools, seg, x, y, ws, ldx=self.in_features, ldy=self.out, ws_bytes=n)
+        elif call == "apply":
+            L.lora_apply(self.pools[0], seg, x, y, ws, ldx=self.in_features, ldy=self.out, ws_bytes=n)
+        elif call == "static":
+            L.lora_apply_static(self.pools[0], seg, x, y, ldx=self.in_features, ldy=self.out)
+        elif call == "shrink":
+            L.lora_shrink(self.pools[0], seg, x, v, ws, ldx=self.in_features, ws_bytes=n)
+        else:
+            L.lora_linear(self.pools[0], seg, x, 1 << 43, y, ws, ldx=self.in_features, ldy=self.out, ws_bytes=n)
+        return [tuple(int(w) if w.lstrip("-").isdigit() else w for w in line.split())
+                for line in lib.recorder_take().decode().splitlines()]
+
+    def close(self):
+        for p in self.pools:
+            L.lora_pool_destroy(p)
+
+
+def _names(launches):
+    return [n[0] for n in launches]
+
+
+# ---- the process-wide switches and the built-in choice ----------------------------------------------------------
+def test_the_built_in_choice_of_launches_can_be_restored(recorder):
+    """Off, on, and back to the choice the library makes before either is called: the same launches as at the start."""
+    few, whole = Batch(4096, 4096, [(1, 16)]), Batch(3008, 1920, [(1, 16)] * 128)
+    try:
+        def forms():
+            out = []
+            for b in (few, whole):
+                seg = b.build()
+                out.append(_names(b.launches(recorder, seg)))
+                L.lora_segments_destroy(seg)
+            return out
+
+        built_in = forms()
+        assert built_in == [["apply_fused"], ["shrink_wide", "expand"]]
+        L.lora_set_fused_apply(False)
+        assert forms()[0] == ["shrink", "expand"]
+        L.lora_set_fused_apply(-1)
+        L.lora_set_decode_single_launch(False)
+        assert forms() == [["shrink", "expand"], ["shrink_wide", "expand"]]
+        L.lora_set_decode_single_launch(True)
+        assert forms()[1] == ["decode_fused"]
+        L.lora_set_decode_single_launch(-1)
+        assert forms() == built_in
+    finally:
+        few.close()
+        whole.close()
