@@ -465,8 +465,8 @@ lora_status_t lora_set_fused_apply(int enabled);
 lora_status_t lora_set_merged_launches(int enabled);
 
 /* A decode-sized batch on the whole-k plan (no token-heavy groups, one pool) whose units fit one round of
- * the chip (at most 256 shrink units, 1024 expand units) is planned for, and run as, ONE launch of at
- * most one work group per compute unit: work group b does one shrink unit and then four expand
+ * the chip (at most 256 shrink units, 1024 expand units) can be planned for, and run as, ONE launch of at
+ * most one work group per compute unit (when it is: see below): work group b does one shrink unit and then four expand
  * units, and the expand units' loads of B^T follow the shrink units' loads of A^T without the tail,
  * the pause and the ramp of a launch boundary.  v goes from the shrink units to the expand units of a
  * (group, token tile) through the L2 of one XCD: the planner puts all of a tile's units at places of
@@ -482,7 +482,8 @@ lora_status_t lora_set_merged_launches(int enabled);
  * reported, but callers that overlap applies should select two launches.
  * lora_set_decode_single_launch(0): always two launches; (1): the one launch wherever the batch fits it;
  * (-1), the state before the first call: a batch is planned for the one launch where
- * that is the faster form: at least 192 shrink units and in_features + out_features of at least 8192.
+ * that is the faster form: ranks of at most 128, and six times the shrink units and the expand units together
+ * at least 2048.
  * Read when a batch is planned and again when it is applied.  Process-wide. */
 lora_status_t lora_set_decode_single_launch(int enabled);
 lora_status_t lora_set_side_stream(int enabled);

@@ -811,16 +811,18 @@ static bool opt_side_stream(const lora_segments *sg) { return (sg->opts.side_str
 static int opt_fused_apply(const lora_segments *sg) { return sg->opts.fused_apply >= 0 ? sg->opts.fused_apply : g_fused_apply.load(); }
 static int opt_decode_single(const lora_segments *sg) { return sg->opts.decode_single_launch >= 0 ? sg->opts.decode_single_launch : g_decode_single_launch.load(); }
 // A whole-k decode batch in one launch (k_decode_fused) or in two?  The one launch saves a boundary but runs its expand
-// units four to a compute unit behind the compute unit's own shrink unit; it wins where the shrink units nearly fill
-// the chip and there is much to read.  us per lora_apply, one / two launches, by shrink units as the one launch counts
-// them: 4096 -> 4096 199 14.4 / 15.9, 202 15.1 / 15.2, 160 (rank 128) 16.3 / 14.8, 161 (ranks 1..256) 16.6 / 14.9, 128 (rank
-// 256) 18.3 / 14.3, 97 12.0 / 11.5, 64 13.0 / 12.5; 14336 -> 4096 199 25.5 / 27.8, 161 27.7 / 25.0, 128 25.9 / 23.6, 97 18.6 /
-// 19.2; 8192 -> 2048 199 18.2 / 18.0, 202 16.7 / 17.3, 161 19.1 / 17.6; 3008 -> 1920 199 13.2 / 13.0, 161 15.1 / 13.3, 128
-// 16.8 / 13.2; 4096 -> 1024 199 12.9 / 12.5, 160 13.7 / 12.1; 2048 -> 8192 161 19.7 / 16.3, 97 14.5 / 12.0; 1024 -> 2048 202
-// 10.3 / 10.0, 128 15.3 / 11.2.
-static bool decode_single_pays(int opt, int64_t whole_k_units, int in, int out)
+// units four to a compute unit behind the compute unit's own shrink unit: the more of both kinds there are, the better it
+// stands, and above rank 128, where an expand unit asks for B^T step by step, it loses.  540 random batches of up to 512
+// tokens at 512 .. 16384 features, us per lora_apply, (shrink units as the one launch counts them, expand units) one / two:
+// up to rank 128: 12480 -> 1792 (254, 529) 24.0 / 25.3, 2752 -> 2560 (253, 715) 13.2 / 13.7, 3328 -> 3840 (191, 838) 13.9 /
+// 14.5, 1024 -> 3456 (233, 946) 11.8 / 12.6, 2304 -> 4224 (208, 998) 15.1 / 14.6, 1728 -> 896 (205, 217) 11.2 / 10.0, 2496 ->
+// 4096 (112, 448) 14.3 / 12.4, 7552 -> 1024 (104, 104) 19.4 / 15.1; ranks up to 256: 12928 -> 2176 (208, 221) 32.3 / 24.6,
+// 8704 -> 640 (222, 93) 28.0 / 20.6, 1408 -> 8064 (206, 980) 21.5 / 17.8, 7808 -> 14208 (64, 694) 32.2 / 18.0.  The line below
+// is 0.2 % from the better form of each batch in the mean and 7 % at most (1216 -> 4736 (91, 910) 10.9 / 11.6); always one launch
+// 11 % and 79 %.  A line at 192 shrink units and 8192 features in and out together, 0.5 % and 36 %.
+static bool decode_single_pays(int opt, int64_t whole_k_units, int64_t expand_units, int top_rank)
 {
-    return opt > 0 || (opt < 0 && 4 * whole_k_units >= 3 * (int64_t)g_compute_units && in + out >= 8192);
+    return opt > 0 || (opt < 0 && top_rank <= 128 && 6 * whole_k_units + expand_units >= 8 * (int64_t)g_compute_units);
 }
 static int opt_whole_k_max_in(const lora_segments *sg) { return sg->opts.whole_k_max_in >= 0 ? sg->opts.whole_k_max_in : kWholeKMaxIn; }
 static int opt_heavy_min_tokens(const lora_segments *sg) { return sg->opts.heavy_min_tokens >= 0 ? sg->opts.heavy_min_tokens : kPrefillMinTokens; }
@@ -1016,8 +1018,17 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     // us): split_min_tokens is the smallest token count whose units can all be cut within that budget.
     int split_min_tokens = 0;
     // (a batch that may run as one launch gets its row halves per XCD, in finish_decode_fused)
-    const bool want_fused = decode_single_pays(opt_decode_single(sg), whole_k_units, pool->in_features, pool->out_features) &&
-                            sg->wide && !heavy_groups && n_projections == 1 && whole_k_units <= g_compute_units;
+    int64_t small_expand_units = 0;
+    int top_rank = 0;
+    for (int a = 0; a < N; ++a) {
+        if (!count[a] || (count[a] >= heavy_min_tokens && n_active >= heavy_min_batch)) continue;
+        const int cols = expand_cols_per_unit(pool->r8[a], pool->out_features);
+        small_expand_units += (int64_t)((pool->out_features + cols - 1) / cols) * ((count[a] + lora::kTokTile - 1) / lora::kTokTile);
+        top_rank = std::max(top_rank, pool->r8[a]);
+    }
+    const bool want_fused = decode_single_pays(opt_decode_single(sg), whole_k_units, small_expand_units, top_rank) && sg->wide &&
+                            !heavy_groups && n_projections == 1 && whole_k_units <= g_compute_units &&
+                            small_expand_units <= 4 * (int64_t)g_compute_units;
     if (sg->wide && !want_fused) {
         int64_t per_tokens[lora::kTokTile + 1] = {0};  // full 16-row units by their token count
         for (int a = 0; a < N; ++a) {

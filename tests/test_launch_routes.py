@@ -112,3 +112,31 @@ def test_the_built_in_choice_of_launches_can_be_restored(recorder):
     finally:
         few.close()
         whole.close()
+
+
+@pytest.mark.parametrize("in_features, out_features, groups, one", [
+    # six times the shrink units and the expand units (of 512 columns here) at 2048: 11 per group
+    (4096, 2560, [(1, 16)] * 186, False),
+    (4096, 2560, [(1, 16)] * 187, True),
+    # more expand units than one round holds
+    (4096, 4096, [(1, 16)] * 200, False),
+    # little to read in all, but units enough: the one launch was the faster form at 1024 -> 3456 and at 2752 -> 2560
+    (1024, 3456, [(1, 64)] * 58, True),
+    (2752, 2560, [(1, 64)] * 64, True),
+    # nearly 256 shrink units, few expand units
+    (14336, 384, [(1, 16)] * 256, False),
+    (14336, 512, [(1, 16)] * 256, False),
+    # ranks above 128
+    (8192, 8192, [(1, 16)] * 190 + [(1, 256)], False),
+    (12928, 2176, [(16, 255)] * 13, False),
+])
+def test_whole_k_decode_batches_in_one_launch(recorder, in_features, out_features, groups, one):
+    b = Batch(in_features, out_features, groups)
+    seg = b.build()
+    assert L.lora_segments_info(seg)["single_launch"] == one
+    assert _names(b.launches(recorder, seg)) == (["decode_fused"] if one else ["shrink_wide", "expand"])
+    recorder.recorder_capture(1)  # two launches under capture
+    assert _names(b.launches(recorder, seg)) == ["shrink_wide", "expand"]
+    recorder.recorder_capture(0)
+    L.lora_segments_destroy(seg)
+    b.close()
