@@ -436,7 +436,7 @@ lora_status_t lora_set_whole_k_limit(int32_t max_units);
  * host state of the segment object at launch: it must not be captured, and not be used on an object
  * that a captured graph replays.  lora_set_fused_apply(0): always two launches (unless the whole-k form of
  * lora_set_decode_single_launch applies).  lora_set_fused_apply(-1), the state before the first call: batches of few
- * units (at most 64 active tokens, 32 shrink units and 96 units in all) take the single launch by themselves, with the same
+ * units (at most 64 active tokens, ranks of at most 128, 16 shrink units and 96 units in all) take the single launch by themselves, with the same
  * bits, unless lora_set_decode_single_launch(0) holds or the stream is being captured (where the two
  * launches are issued; a graph that holds those may be replayed between such applies).  What is said below about
  * launches of one-launch forms that run at the same time on one GPU holds for these too.  Process-wide. */

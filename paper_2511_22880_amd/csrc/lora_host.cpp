@@ -110,6 +110,7 @@ struct lora_segments {
     size_t staging_capacity;
     size_t off_perm, off_shrink, off_prefill, off_expand, off_expand_big, off_fused_shrink, off_fused_expand, off_sync,
         table_bytes;
+    int top_rank;           // the largest padded rank the batch uses
     bool has_big_units;     // some unit holds more than 16 tokens (token-heavy groups)
     bool heavy_small_expand;  // a token-heavy group above kBigExpandMaxRank (none, as the pool's ranks stand): shrunk by token-heavy units, expanded by 16-token units
     bool wide;              // decode shrink units span all of k (work groups of 16 wavefronts, no partial sums)
@@ -789,15 +790,17 @@ static const int kXcds = 8;         // XCDs of the chip, each with an L2 of its 
 static std::atomic<int> g_decode_single_launch{-1};  // 1: wherever it can be, 0: never, -1: where it is the faster form
 static std::atomic<int> g_side_stream{1};
 static std::atomic<int> g_fused_apply{-1};  // 1: always where it can be, 0: never, -1: batches of few units
-// Batches of at most this many units on the k-slice plan run as one launch: it lasts 6 to 10 us, two launches about as
-// long as the host takes to issue them.  us per lora_apply called from Python, two launches / one, by (shrink units,
-// expand units): 4096 -> 4096 (4, 8) 10.5 / 7.2, (20, 24) 10.1 / 8.8, (28, 32) 10.1 / 9.3, (32, 32) 10.3 / 9.2,
-// (64, 32) 11.0 / 10.9, (96, 104) 10.1 / 12.5; 1024 -> 8192 (7, 64) 10.2 / 7.9, (24, 208) 10.5 / 10.0, (31, 304) 10.8 /
-// 10.8; 3008 -> 1920 (32, 15) 12.5 / 11.6, (46, 51) 10.9 / 11.8; 14336 -> 4096 (4, 8) 12.0 / 10.4, (28, 32) 12.8 /
-// 12.6, (64, 32) 15.0 / 15.7.  Beyond them the units that wait and poll slow those they wait for; so they do with
-// many full token tiles: 126 tokens of 2 adapters, 4096 -> 4096 (32, 64) 9.6 / 11.2, 8192 -> 2048 (32, 32) 11.1 / 12.2
-// (40 tokens, (24, 32), 10.5 / 9.7).
-static const int kSingleLaunchShrinkUnits = 32;
+// Batches of at most this many units and this rank on the k-slice plan run as one launch: it lasts 6 to 10 us, two
+// launches about as long as the host takes to issue them, but the units that wait and poll slow those they wait for.  260
+// random batches within the other two limits at 512 .. 16384 features, called from Python one after the other, one launch
+// against two by shrink units: up to 8 10 % faster in the mean, none slower; 9 .. 15 5 % faster; 17 .. 24 level, from 6 % faster
+// to 9 % slower; 25 .. 32 3 % slower in the mean, 12 % at most (2816 -> 7552, one token of rank 256, (32, 59) 13.2 / 11.7 us);
+// within all four limits 8.5 % faster in the mean, 5 % slower at most but for one of 11 %.  By rank: up to 64 9 % faster,
+// 128 level, above 2 % slower.  More units or tokens: 4096 -> 4096 (96, 104) 12.5 /
+// 10.1, 3008 -> 1920 (46, 51) 11.8 / 10.9; 126 tokens of 2 adapters, 4096 -> 4096 (32, 64) 11.2 / 9.6, 8192 -> 2048 (32, 32)
+// 12.2 / 11.1.
+static const int kSingleLaunchShrinkUnits = 16;
+static const int kSingleLaunchRank = 128;
 static const int kSingleLaunchUnits = 96;
 static const int kSingleLaunchTokens = 64;
 static const unsigned kSpinLimit = 1u << 18;  // polls of a waiting expand unit before it gives up
@@ -1080,6 +1083,8 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         wbytes += 2LL * r.r8 * ((int64_t)pool->in_features + pool->out_features);
     }
     sg->seg_start.push_back(pos);
+    sg->top_rank = 0;
+    for (const SegRec &r : sg->segs) sg->top_rank = std::max(sg->top_rank, r.r8);
     sg->v_floats = voff;
     sg->weight_bytes = wbytes;
 
@@ -2184,7 +2189,7 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     const DeviceProfile *prof = nullptr;
     const int fused = opt_fused_apply(sg);
     bool single = fused != 0 && !sg->has_big_units && !sg->wide &&
-                  (fused > 0 || (opt_decode_single(sg) != 0 && sg->n_active <= kSingleLaunchTokens &&
+                  (fused > 0 || (opt_decode_single(sg) != 0 && sg->n_active <= kSingleLaunchTokens && sg->top_rank <= kSingleLaunchRank &&
                                  cs.n_units <= kSingleLaunchShrinkUnits && cs.n_units + ce.n_units <= kSingleLaunchUnits));
     if (single && fused < 0) {  // under capture the two launches, as for the one-launch decode form above
         HIP_TRY(hipStreamIsCapturing(s, &capturing));

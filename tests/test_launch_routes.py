@@ -140,3 +140,34 @@ def test_whole_k_decode_batches_in_one_launch(recorder, in_features, out_feature
     recorder.recorder_capture(0)
     L.lora_segments_destroy(seg)
     b.close()
+
+
+@pytest.mark.parametrize("in_features, outs, groups, single", [
+    (4096, 4096, [(1, 16)], True),
+    (1024, 1024, [(1, 128), (1, 128)], True),                      # 16 shrink units
+    (1024, 1024, [(1, 128), (1, 128), (1, 8)], False),             # 17
+    (2816, 7552, [(1, 256)], False),                               # rank above 128: 13.2 us in one launch, 11.7 in two
+    (1024, 1024, [(1, 136)], False),
+    (1024, 512 * 84, [(3, 64), (1, 8)], False),                    # many expand units
+    (512, 512, [(16, 8)] * 4, True),                               # 64 tokens
+    (512, 512, [(16, 8)] * 4 + [(1, 8)], False),                   # 65
+    (4096, [4096, 1024, 1024], [(1, 16)], True),                   # q|k|v of one token: 12 shrink units
+    (4096, [4096, 1024, 1024], [(1, 16), (1, 16)], False),         # 24
+])
+def test_batches_of_few_units_in_one_launch(recorder, in_features, outs, groups, single):
+    """... by themselves, in lora_apply, lora_apply_multi and lora_apply_static; not under capture, nor where either switch
+    is off."""
+    b = Batch(in_features, outs, groups, idle=3)
+    two = ["shrink", "expand"]
+    for options, expect in ((None, single), (L.plan_options(fused_apply=0), False),
+                            (L.plan_options(decode_single_launch=0), False), (L.plan_options(fused_apply=1), True)):
+        seg = b.build(options)
+        assert _names(b.launches(recorder, seg)) == (["apply_fused"] if expect else two)
+        if options is None:
+            recorder.recorder_capture(1)
+            assert _names(b.launches(recorder, seg)) == two
+            recorder.recorder_capture(0)
+            if len(b.pools) == 1:
+                assert _names(b.launches(recorder, seg, "static")) == (["apply_fused"] if expect else two)
+        L.lora_segments_destroy(seg)
+    b.close()
