@@ -209,7 +209,7 @@ typedef struct {
     int32_t heavy_min_tokens;      /* a group of at least this many tokens is token-heavy (32) ...        */
     int32_t heavy_min_batch;       /* ... in a batch of at least this many active tokens (1024)           */
     int32_t heavy_k_cut_max_units; /* token-heavy shrink units are cut along k while the cut units stay    *
-                                    * within this count (built in: 1, 2 or 4 slices by estimated time)     */
+                                    * within this count (built in: 1 to 4 slices by estimated time)        */
     int32_t big_runs_max_units;    /* 64-token expand units take their columns in 8 runs or more, not 4, while *
                                     * the launch stays within this many of them (two per compute unit: 512) */
 } lora_plan_options_t;
@@ -284,15 +284,15 @@ lora_status_t lora_segments_export(const lora_segments_t *seg, int32_t *perm, in
  * come as two units of 8 rank rows each, as many token counts as fit 256 units); token-heavy groups
  * into shrink units of up to 32 tokens (64 for ranks 65..192) x all rank
  * rows x all of k (listed after the others, k-slice 0; in a batch planned in k-slices with few such
- * units, two or four k-slices each) and into expand units of up to 64 tokens.
+ * units, two to four k-slices each) and into expand units of up to 64 tokens.
  * The order is the launch order: the decode shrink units of one group take places of one residue
  * mod 8 where the counts allow it (the launch's work groups go to the chip's 8 XCDs in turn, and the
  * group's rows of x then stay in one XCD's L2); the token-heavy shrink units of one adapter likewise
  * (its A^T then enters one L2), the eight lists filled to equal bytes and the shorter ones padded at
  * their end with places that hold no work: segment -1, token count 0; the 64-token expand units (listed after the others)
- * of one group (its columns in 4 runs, 8 in a launch of few such units) come in rows of 8, each
- * column run with 8 / (column runs) consecutive token tiles, so that a column run's part of B^T is
- * fetched by that many XCDs instead of all 8.  Either output may be NULL. */
+ * of one group (its columns in 4 runs, 8 to 64 in a launch of few such units) come in rows of 8, each
+ * column run of 4 with 2 consecutive token tiles and those of a multiple of 8 on one XCD each, so that a column
+ * run's part of B^T is fetched by that many XCDs instead of all 8.  Either output may be NULL. */
 lora_status_t lora_segments_export_units(const lora_segments_t *seg, int32_t *shrink_units,
                                          int32_t *expand_units);
 
@@ -458,9 +458,9 @@ lora_status_t lora_set_fused_apply(int enabled);
  * `stream` at the start of the apply and one that `stream` waits for at its end: the pairs run side
  * by side and everything later on `stream` is ordered behind both.  lora_set_side_stream(0) keeps all
  * four launches on `stream`.  y is bitwise the same in all three forms, except where the merged
- * form's plan also cuts the token-heavy shrink units along k (launches of few such units: at most
- * 160 of them, 375 beyond 8192 input features; the sums of v are then grouped differently, within
- * the same tolerance).
+ * form's plan also cuts the token-heavy shrink units along k (where fewer than a few hundred of them would leave
+ * the launch longer: see lora_plan_options_t.heavy_k_cut_max_units; the sums of v are then grouped
+ * differently, within the same tolerance).
  * Process-wide. */
 lora_status_t lora_set_merged_launches(int enabled);
 

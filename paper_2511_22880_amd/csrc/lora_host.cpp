@@ -600,43 +600,45 @@ static const int kBigExpandMaxRank = 256;
 static_assert(kBigExpandMaxRank >= LORA_MAX_RANK_PADDED, "the 16-token expand units of token-heavy groups are gone");
 static int g_compute_units = 256;  // of the chip: a whole-k launch within this many units is one round
 
-// K-slices of a launch's token-heavy shrink units: 1, 2 or 4, by what a launch is estimated to last.  A unit is one walk
-// through k, and a compute unit passes about 50 GB/s, so a launch of few units lasts as long as its heaviest one
-// (rows of x and A^T times in_features), or as the two that share a compute unit; the low ranks' bodies take at
-// least a trip to memory per pass of 128 of k and wavefront; a cut costs 4 - 5 us for the sums' way through memory.
-// Beyond the counts below the cut units run in rounds and the estimate no longer holds.  lora_apply in us (128 columns,
-// so nearly all of it the shrink), 1 / 2 / 4 slices.  8 prompts of 1150 tokens, ranks 8..128 (164 units): 2048 features
-// 24.2 / 21.0 / 21.2, 4096 36.6 / 29.3 / 31.5, 8192 61.7 / 45.5 / 46.3, 14336 99 / 70 / 66; 4 prompts beside 200 decode
-// tokens (78 units): 4096 38.3 / 29.3 / 24.9, 14336 104 / 67 / 51; 4 prompts of 1500 at rank 128 (77 units): 4096 36.6 /
-// 27.9 / 31.1; 8 prompts of 1500 (258 units) at rank 64: 4096 30.5 / 31.9 / 33.0, 8192 53.2 / 49.7 / 47.8, at rank 16:
-// 4096 20.5 / 20.5 / 20.4, 8192 40.3 / 32.5 / 31.6; 16 prompts of 1000 (359 units): 2048 25.6 / 28.1 / 27.8, 4096 39.1 /
-// 37.8 / 41.1, 8192 65.9 / 55.6 / 59.2.
-static const int kHeavyCutMaxUnits = 512;       // two work groups per compute unit; beside decode-sized groups, whose
-static const int kHeavyCutMaxUnitsMixed = 448;  // units want places too, an eighth less; from 8192 input features on,
-static const int kHeavyCutMaxUnitsLongK = 750;  // where a slice is long, some of a second round
-static const double kHeavyRowsPerUs = 25000.0;  // rows of one input feature, 2 bytes each, that a compute unit passes per us
-static int choose_heavy_k_slices(std::vector<int> &rows, bool low_ranks, bool mixed, int in, int max_slices)
+// K-slices of a launch's token-heavy shrink units: as many as keep it shortest by an estimate.  A compute unit passes
+// about 68 GB/s (rows of x and A^T, 2 bytes each), so a launch lasts as long as its heaviest unit, as the two that share a
+// compute unit, or as everything it holds spread evenly, decode-sized units (24 rows each) included; the low ranks'
+// body takes at least a trip to memory per 512 of k; a cut costs 3 us and the sums' way through memory, each slice's v
+// written and read once (of three slices the addition reads four).  Shrink launch in us, 1 / 2 / 4 slices, 128 columns:
+// 13952 features, ranks 8..128, 136 units 92 / 65 / 44; 5120, 294 units 44 / 31 / 37; 7104, 232 units and 333 decode-sized
+// 58 / 44 / 50; 2176, ranks up to 256, 205 units 23 / 29; 14848, rank 8, 97 units 25 / 19 / 22; 1 / 2 / 3 slices: 3648, 264
+// units 29 / 28 / 23; 3968, ranks 8 and 256, 160 units 39 / 25 / 31.  Missed: 6656, rank 8, 247 units 17.1 / 19.5 / 23.9
+// (takes 2); 10112, 372 units 63 / 57 / 57 (takes 1).  Over 269 random batches of 2048 .. 16384 features and up to 600
+// such units the choice is 2.6 % from the best of 1 to 4 slices in the mean and 31 % at most; with 50 GB/s, no account of
+// v and limits of 448 to 750 cut units it was 5.2 % and 48 %.  Beyond kHeavyCutMaxUnits cut units the estimate no longer
+// holds.
+static const int kHeavyCutMaxUnits = 900;
+static const double kHeavyRowsPerUs = 34000.0;  // rows of one input feature that a compute unit passes per us
+struct HeavyShrink {
+    std::vector<int> rows;   // of x and A^T, per unit
+    int64_t v_floats = 0;    // of all units
+    int top_rank = 0;
+    int64_t small_units = 0; // decode-sized units beside them, as whole-k ones
+};
+static int choose_heavy_k_slices(HeavyShrink &h, int in, int max_slices)
 {
-    const int n = (int)rows.size(), cus = g_compute_units;
-    if (n == 0) return 1;
-    std::sort(rows.begin(), rows.end(), std::greater<int>());
+    const int n = (int)h.rows.size(), cus = g_compute_units;
+    std::sort(h.rows.begin(), h.rows.end(), std::greater<int>());
+    double total = 24.0 * h.small_units;
+    for (int r : h.rows) total += r;
     int best = 1;
     double best_us = 0;
-    for (int c : {1, 2, 4}) {
-        // (the long-k limit not for four slices beside decode-sized groups: 8 prompts and 384 decode tokens, 169 units,
-        // 14336 features, 2 / 4 slices 79.4 / 83.1 us)
-        const int most = in < 8192 ? (mixed ? kHeavyCutMaxUnitsMixed : kHeavyCutMaxUnits)
-                                   : (mixed && c == 4 ? kHeavyCutMaxUnits : kHeavyCutMaxUnitsLongK);
-        if (c > max_slices || (c > 1 && n * c > most)) break;
-        double load = rows[0];  // of the busiest compute unit, in rows of the whole of k
-        if (n * c > cus) load = std::max(load, (rows[0] + rows[cus / c]) / (low_ranks ? 1.4 : 1.0));
-        double total = 0;
-        if (n * c > 2 * cus) {
-            for (int r : rows) total += r;
-            load = std::max(load, 1.3 * c * total / cus);
-        }
-        const double us = std::max(load / c * in / kHeavyRowsPerUs, in / (512.0 * c) * (low_ranks ? 1.9 : 0.9)) + (c == 1 ? 0 : c == 2 ? 4 : 5);
-        if (c == 1 || us < best_us - 1.0) {
+    for (int c : {1, 2, 3, 4}) {
+        if (c > max_slices || (c == 3 && max_slices == 4)) continue;
+        // (four slices with the decode-sized units counted in: 14336 features, 169 + 305 units, 2 / 4 slices 79 / 83 us;
+        // 4416, 152 + 317 39 / 45; 13312, 128 + 262 62 / 52)
+        if ((c > 1 && n * c > kHeavyCutMaxUnits) || (c == 4 && n * c + h.small_units > kHeavyCutMaxUnits + 64)) break;
+        double load = std::max((double)h.rows[0], c * total / cus);  // of the busiest compute unit, in rows of a slice of k
+        if (n * c > cus) load = std::max(load, (h.rows[0] + h.rows[std::min(n - 1, cus / c)]) / 1.15);
+        double us = load * in / (c * kHeavyRowsPerUs);
+        if (h.top_rank <= 64) us = std::max(us, 1.2 * in / (512.0 * c));
+        if (c > 1) us += 3.0 + 0.6 * (c == 3 ? 4 : c) * 8e-6 * h.v_floats;
+        if (c == 1 || us < best_us) {
             best = c;
             best_us = us;
         }
@@ -1127,20 +1129,21 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     // (per projection, whatever the number of projections: lora_apply_multi gives the bits of separate applies)
     int heavy_k_slices = 1;
     if (sg->n_k_slices >= 2) {
-        std::vector<int> rows;
-        int top = 0;
+        HeavyShrink h;
+        h.small_units = whole_k_units;
         int64_t n_units = 0;
         for (const SegRec &r : sg->segs) {
             if (!(r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch)) continue;
             const int tile = heavy_tile(r.r8);
             n_units += (r.ntok + tile - 1) / tile;
-            top = std::max(top, r.r8);
-            if (2 * n_units <= kHeavyCutMaxUnitsLongK)
-                for (int t = 0; t < r.ntok; t += tile) rows.push_back(std::min(tile, r.ntok - t) + r.r8);
+            h.top_rank = std::max(h.top_rank, r.r8);
+            h.v_floats += (int64_t)r.ntok * r.r8;
+            if (2 * n_units <= kHeavyCutMaxUnits)
+                for (int t = 0; t < r.ntok; t += tile) h.rows.push_back(std::min(tile, r.ntok - t) + r.r8);
         }
         const int max_slices = std::min(4, sg->n_k_slices);
         if (sg->opts.heavy_k_cut_max_units < 0) {
-            if (2 * n_units <= kHeavyCutMaxUnitsLongK) heavy_k_slices = choose_heavy_k_slices(rows, top <= 64, whole_k_units > 0, pool->in_features, max_slices);
+            if (n_units > 0 && 2 * n_units <= kHeavyCutMaxUnits) heavy_k_slices = choose_heavy_k_slices(h, pool->in_features, max_slices);
         } else {
             for (int c = max_slices; c >= 2 && n_units > 0 && heavy_k_slices == 1; c /= 2)
                 if (n_units * c <= sg->opts.heavy_k_cut_max_units) heavy_k_slices = c;

@@ -171,3 +171,44 @@ def test_batches_of_few_units_in_one_launch(recorder, in_features, outs, groups,
                 assert _names(b.launches(recorder, seg, "static")) == (["apply_fused"] if expect else two)
         L.lora_segments_destroy(seg)
     b.close()
+
+
+# ---- token-heavy groups: how many k-slices their shrink units are cut into ---------------------------------------
+def _heavy_slices(b):
+    """Into how many slices the tiles of the groups of 32 tokens and more are cut, and how many such tiles there are."""
+    seg = b.build()
+    u = L.lora_segments_export_units(seg)["shrink"]
+    sizes = np.diff(L.lora_segments_export(seg)["seg_start"])
+    L.lora_segments_destroy(seg)
+    tiles = {}
+    for s, tok0, _nt, _p0, _pn, ks in u[u[:, 0] >= 0]:
+        if sizes[s] >= 32:
+            tiles.setdefault((int(s), int(tok0)), []).append(int(ks))
+    slices = len(next(iter(tiles.values()))) // len(b.pools)
+    assert all(sorted(k) == sorted(list(range(slices)) * len(b.pools)) for k in tiles.values())
+    return slices, len(tiles)
+
+
+@pytest.mark.parametrize("in_features, groups, slices", [
+    # (measured: shrink launch in us, 1 / 2 / 4 slices)
+    (64, [(2000, 128)], 1),                                        # nothing to cut
+    (4096, [(2000, 128)], 4),                                      # 32 units
+    (2176, [(656, 256)] * 10, 1),                                  # 210 units of rank 256: 23.3 / 28.9
+    (5120, [(2352, 16), (2352, 32), (2352, 64), (2352, 8)], 2),    # 296 units: 44.0 / 30.8 / 36.6
+    (13952, [(1200, 16), (1200, 32), (1200, 64), (1200, 128)], 4), # 134 units: 92.3 / 64.5 / 44.2
+    (13952, [(1200, 16), (1200, 32), (1200, 64), (1200, 128)] + [(1, 16)] * 44, 4),
+    # 169 + 305 units, the down projection beside 384 decode tokens: 79.4 / 83.1 in 2 / 4 slices
+    (14336, [(1400, 8), (1400, 16), (1200, 32), (1200, 64), (320, 128)] + [(1, 16)] * 305, 2),
+    # three slices at most: 30 units 27.0 / 20.0 / 16.8 in 1 / 2 / 3, 160 units 39.2 / 25.3 / 30.8, 196 units 30.6 / 23.4 / 25.6
+    (3968, [(1920, 128)], 3),
+    (3968, [(1249, 256), (1249, 8), (1249, 8), (1249, 256)], 2),
+    (4096, [(2000, 128)] * 20, 1),                                 # 640 units
+])
+def test_token_heavy_shrink_units_are_cut_where_that_is_shorter(recorder, in_features, groups, slices):
+    b = Batch(in_features, 512, groups)
+    assert _heavy_slices(b)[0] == slices, _heavy_slices(b)
+    b.close()
+    # the units' cut does not depend on how many projections share the launch: their sums are the same bits
+    b = Batch(in_features, [512, 128, 128], groups)
+    assert _heavy_slices(b)[0] == slices
+    b.close()
