@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <functional>
 #include <atomic>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -97,10 +98,11 @@ struct lora_segments {
     std::vector<Unit> fused_shrink, fused_expand;
     // the adapted layer's row order (lora_linear): batch row of every place (-1: none), behind them where
     // every block of 16 places has its first piece, and the pieces of one adapter each; all T tokens are in
-    // it, the ones without adapter last
+    // it (see order_linear_rows)
     std::vector<int32_t> lin_rows;
     std::vector<LinPiece> lin_pieces;
-    int lin_front;  // places of the small groups start here
+    int lin_places;     // places in use, those between padded groups included
+    int lin_big_tiles;  // row tiles of 256 places, from the front, that take the kernel's large tiles
     size_t off_lin_rows, off_lin_pieces;
     // device table: [perm | shrink units | prefill shrink units | expand units | arrival counters,
     // ready counters, time-out flag]
@@ -781,9 +783,6 @@ static void order_heavy_units_by_xcd(std::vector<Unit> &units)
     units.swap(out);
 }
 
-// groups of at least this many tokens go to the front of the adapted layer's row order (lora_linear)
-static const int kLinFillingGroup = 16;
-
 static int opt_big_runs_max_units(const lora_segments *sg)
 {
     return sg->opts.big_runs_max_units >= 0 ? sg->opts.big_runs_max_units : kBigRunsWorkGroupsPerComputeUnit * g_compute_units;
@@ -978,6 +977,140 @@ static void finish_decode_fused(lora_segments *sg, bool want, int in_features)
             sg->fused_expand[((j / 4) * kXcds + q) * 4 + j % 4] = u;
         }
     }
+}
+
+// ---- the adapted layer's rows ----
+// What k_linear_lora is estimated to last, in us, with the first m row tiles (of 256 places) as large tiles of 256 columns and
+// the rows behind them as small ones of 64 x 64.  A large tile takes 5 us, 0.02 per input feature and 0.5 per 32-wide step of
+// the longest delta that one of its wavefronts starts with (`chain`); a small one 3 us, 0.0013 per input feature, 0.6
+// per MB of x and W that the 32 work groups of an XCD walk through together, and 1.2 per 128 of rank that the busiest of
+// its wavefronts adds.  A work group takes a compute unit; an XCD takes every eighth row tile, and of its four groups of
+// eight compute units one takes every fourth column tile, so 9 row tiles of 256 columns (XCD 0: two) last as long as 16.
+static double linear_us(int in, int out, int places, int m, int chain, double small_pieces)
+{
+    const int xcd_tiles = (m + 7) / 8 * (((out + lora::kLinTileN - 1) / lora::kLinTileN + 3) / 4);  // per 8 compute units
+    const int strips = places > m * lora::kLinTileM ? (places - m * lora::kLinTileM + 63) / 64 : 0;
+    const double small = std::ceil(strips * (out / 64) / 8.0);  // per XCD
+    const int side = std::min(std::max(strips, 1), 32);
+    const double big_us = 5.0 + 0.02 * in + 0.5 * chain;
+    const double small_us = 3.0 + 0.0013 * in + 0.6 * (side + 32.0 / side) * 64 * 2e-6 * in + 1.2 * small_pieces;
+    if (m == 0) return (small > 64 ? small / 32 : std::ceil(small / 32)) * small_us;
+    const double rounds = (xcd_tiles + 7) / 8 * big_us;
+    if (small == 0) return rounds;
+    return std::max(rounds, (4 * xcd_tiles * big_us + small * small_us) / 32 + 0.5 * small_us) + 0.05 * small_us;
+}
+
+// groups of at least this many tokens go to the front
+static const int kLinFillingGroup = 16;
+
+struct LinearOrder {
+    std::vector<int32_t> rows;
+    std::vector<LinPiece> pieces;
+    int places, big_tiles;
+    double us;
+};
+
+// Groups that fill blocks of 16 places, the tokens without adapter, then the small groups (large tiles take rows from the
+// front, and a block of many adapters costs them most); `pad`: every group starts a block of its own.
+static void try_linear_order(const lora_segments *sg, const int32_t *ta, int32_t T, int in, int out, bool pad, LinearOrder *o)
+{
+    o->rows.clear();
+    o->pieces.clear();
+    auto add_groups = [&](bool filling) {
+        for (const SegRec &r : sg->segs) {
+            if ((r.ntok >= kLinFillingGroup) != filling) continue;
+            if (pad) o->rows.resize((o->rows.size() + 15) / 16 * 16, -1);
+            int32_t at = (int32_t)o->rows.size();
+            const int32_t first = at, end = at + r.ntok;
+            o->rows.insert(o->rows.end(), sg->perm.begin() + r.tok_start, sg->perm.begin() + r.tok_start + r.ntok);
+            while (at < end) {
+                LinPiece q;
+                memset(&q, 0, sizeof q);
+                q.place = at;
+                q.ntok = std::min(end, at / 16 * 16 + 16) - at;
+                q.b_off = r.b_off;
+                q.v_off = r.v_off + (int64_t)(at - first) * r.r8;
+                q.r8 = r.r8;
+                o->pieces.push_back(q);
+                at += q.ntok;
+            }
+        }
+    };
+    add_groups(true);
+    for (int32_t t = 0; t < T; ++t)
+        if (ta[t] < 0) o->rows.push_back(t);
+    add_groups(false);
+    o->places = (int)o->rows.size();
+
+    // per strip of 64 places: the longest chain of a large tile's wavefront, the busiest wavefront of a small tile
+    const int strips = (o->places + 63) / 64, tiles = (o->places + lora::kLinTileM - 1) / lora::kLinTileM;
+    std::vector<int> chain(strips, 0);
+    std::vector<double> small(strips + 1, 0.0);  // of this strip and all behind it
+    size_t q = 0;
+    for (int st = 0; st < strips; ++st) {
+        int load[8] = {0}, n = 0, n_first = 0;
+        uint64_t first[4];  // adapters of the blocks' first pieces: B^T of one adapter is taken once for all of them
+        for (int32_t block = -1; q < o->pieces.size() && o->pieces[q].place < 64 * (st + 1); ++q, ++n) {
+            const LinPiece &pc = o->pieces[q];
+            bool again = false;
+            if (pc.place / 16 != block) {
+                block = pc.place / 16;
+                for (int i = 0; i < n_first; ++i) again |= first[i] == pc.b_off;
+                if (!again) first[n_first++] = pc.b_off;
+            }
+            if (!again) chain[st] += (pc.r8 + 31) / 32;
+            load[n % 8] += (pc.r8 + 127) / 128;
+        }
+        small[st] = *std::max_element(load, load + 8);
+    }
+    for (int st = strips - 1; st >= 0; --st) small[st] += small[st + 1];
+    int longest = 0;
+    for (int m = 0; m <= tiles; ++m) {
+        for (int st = 4 * m - 4; st >= 0 && st < std::min(4 * m, strips); ++st) longest = std::max(longest, chain[st]);
+        const double us = linear_us(in, out, o->places, m, longest, 4 * m < strips ? small[4 * m] / (strips - 4 * m) : 0.0);
+        if (m == 0 || us < o->us) {
+            o->us = us;
+            o->big_tiles = m;
+        }
+    }
+}
+
+// Blocks of 16 places without padding between the groups are the least work; but where large tiles leave compute units
+// idle or the blocks hold many adapters, whose deltas a wavefront starts one after the other, every group may better have
+// blocks of its own.  us per layer, all 64 x 64 / all 256 x 256 without padding / all 256 x 256 with it: 1088 -> 8192, 707
+// tokens, 56 groups below 16 of them, 72 / 112 / 53; 832 -> 8192, 1370 tokens, 17 such groups 99 / 63 / 51; 1280 -> 8192, 1648 tokens, 22 154 / 70 / 66;
+// 3584 -> 8192, 1510 tokens, 17 234 / 139 / 123; 768 -> 512, 10185 tokens 68 / 62 / 46; 5888 -> 8192, 644 tokens of 2
+// adapters 149 / 183 / -; 4096 -> 4096, 1024 tokens of few adapters 90 / 118 / -.  Large tiles for the rows that fill the
+// compute units and small ones behind them: 2176 -> 3072, 4512 tokens 207 / 138 / 136, 16 of 18 row tiles large 87.  Over 330
+// random batches with prompts 1.1 % from the best of the choices in the mean, 17 % at most.  (With a large tile at 5.5 small
+// ones whatever the size, no padding and compute units counted over the whole chip: 2.5 %, up to 60 %.)
+static void order_linear_rows(lora_segments *sg, const int32_t *ta, int32_t T, int in, int out)
+{
+    sg->lin_rows.clear();
+    sg->lin_pieces.clear();
+    sg->lin_places = sg->lin_big_tiles = 0;
+    if (T <= 0) return;
+    LinearOrder best;
+    best.rows.swap(sg->lin_rows);
+    best.pieces.swap(sg->lin_pieces);
+    try_linear_order(sg, ta, T, in, out, false, &best);
+    bool aligned = true;
+    for (const LinPiece &q : best.pieces) aligned &= q.place % 16 == 0;
+    if (!aligned && 1.01 * linear_us(in, out, lora::kLinTileM, 1, 0, 0.0) < best.us) {
+        LinearOrder padded;
+        try_linear_order(sg, ta, T, in, out, true, &padded);
+        if (padded.big_tiles > 0 && 1.01 * padded.us < best.us) std::swap(best, padded);
+    }
+    best.rows.swap(sg->lin_rows);
+    best.pieces.swap(sg->lin_pieces);
+    sg->lin_places = best.places;
+    sg->lin_big_tiles = best.big_tiles;
+    const size_t places = ((size_t)sg->lin_places + lora::kLinTileM - 1) / lora::kLinTileM * lora::kLinTileM;
+    sg->lin_rows.resize(places + places / 16 + 1, -1);
+    int32_t *start = sg->lin_rows.data() + places;
+    std::fill(start, start + places / 16 + 1, 0);
+    for (const LinPiece &q : sg->lin_pieces) ++start[q.place / 16 + 1];
+    for (size_t b = 1; b <= places / 16; ++b) start[b] += start[b - 1];
 }
 
 static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const int32_t *ta, int32_t T,
@@ -1267,44 +1400,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     order_heavy_units_by_xcd(sg->prefill_units);
 
     finish_decode_fused(sg, want_fused, pool->in_features);
-    // row order of the adapted layer: groups that fill blocks of 16 rows, the tokens without adapter, then the
-    // small groups (the kernel's large tiles take rows from the front, and a block of many adapters costs
-    // them most), the whole padded to a multiple of the kernel's row tile
-    sg->lin_rows.clear();
-    sg->lin_pieces.clear();
-    if (n_projections == 1 && T > 0) {
-        const size_t places = ((size_t)T + lora::kLinTileM - 1) / lora::kLinTileM * lora::kLinTileM;
-        sg->lin_rows.reserve(places + places / 16 + 1);
-        std::vector<int32_t> per_block(places / 16 + 1, 0);
-        auto add_groups = [&](bool filling) {
-            for (const SegRec &r : sg->segs) {
-                if ((r.ntok >= kLinFillingGroup) != filling) continue;
-                int32_t at = (int32_t)sg->lin_rows.size();
-                const int32_t first = at, end = at + r.ntok;
-                sg->lin_rows.insert(sg->lin_rows.end(), sg->perm.begin() + r.tok_start, sg->perm.begin() + r.tok_start + r.ntok);
-                while (at < end) {
-                    LinPiece q;
-                    memset(&q, 0, sizeof q);
-                    q.place = at;
-                    q.ntok = std::min(end, at / 16 * 16 + 16) - at;
-                    q.b_off = r.b_off;
-                    q.v_off = r.v_off + (int64_t)(at - first) * r.r8;
-                    q.r8 = r.r8;
-                    sg->lin_pieces.push_back(q);
-                    ++per_block[at / 16 + 1];
-                    at += q.ntok;
-                }
-            }
-        };
-        add_groups(true);
-        for (int32_t t = 0; t < T; ++t)
-            if (ta[t] < 0) sg->lin_rows.push_back(t);
-        sg->lin_front = (int)sg->lin_rows.size();
-        add_groups(false);
-        sg->lin_rows.resize(places, -1);
-        for (size_t b = 1; b < per_block.size(); ++b) per_block[b] += per_block[b - 1];
-        sg->lin_rows.insert(sg->lin_rows.end(), per_block.begin(), per_block.end());
-    }
+    order_linear_rows(sg, ta, n_projections == 1 ? T : 0, pool->in_features, out);
     layout_table(sg);
     return LORA_OK;
 }
@@ -1536,8 +1632,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
     sg->fused_shrink.clear();
     sg->fused_expand.clear();
     sg->fused_grid = 0;
-    sg->lin_rows.clear();
-    sg->lin_pieces.clear();
+    order_linear_rows(sg, ta, 0, 0, 0);
     layout_table(sg);
     return LORA_OK;
 }
@@ -2333,9 +2428,9 @@ try {
         }
     }
     const int32_t *rows = (const int32_t *)(sg->dev + sg->off_lin_rows);
-    const size_t places = ((size_t)sg->T + lora::kLinTileM - 1) / lora::kLinTileM * lora::kLinTileM;
-    const lora::LinBlock blocks = {rows + places, (const LinPiece *)(sg->dev + sg->off_lin_pieces), sg->lin_front};
-    HIP_TRY(lora::launch_linear_lora(rows, &blocks, sg->T, pool->arena,
+    const size_t places = ((size_t)sg->lin_places + lora::kLinTileM - 1) / lora::kLinTileM * lora::kLinTileM;
+    const lora::LinBlock blocks = {rows + places, (const LinPiece *)(sg->dev + sg->off_lin_pieces), sg->lin_big_tiles};
+    HIP_TRY(lora::launch_linear_lora(rows, &blocks, sg->lin_places, pool->arena,
                                      (const uint16_t *)w_packed, (const uint16_t *)x, ldx, in, out, sa.v_hi, sa.v_lo,
                                      (uint16_t *)y, ldy, s));
     return LORA_OK;

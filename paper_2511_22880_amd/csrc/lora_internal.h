@@ -47,9 +47,9 @@ static_assert(sizeof(Unit) == 128, "Unit is 128 bytes");
 
 // One run of at most 16 places of the adapted layer's row order (lora_linear: groups that fill blocks of 16 rows,
 // then the tokens without adapter, then the small groups) that share an adapter and lie in one block of 16
-// places.  A block of a large group holds one piece, a block of small groups one per adapter met there: the base
-// product does no work for padding, and the delta of a piece is added with the rows of the other pieces of
-// its block at zero.
+// places.  A block of a large group holds one piece, a block of small groups one per adapter met there, or (where the plan
+// gives every group blocks of its own) one beside empty places: the delta of a piece is added with the rows of the other
+// pieces of its block at zero.
 struct LinPiece {
     uint64_t b_off;  // element offset of the group's B^T in the arena
     int64_t v_off;   // element offset of the v row of the piece's first token
@@ -60,11 +60,11 @@ struct LinPiece {
 };
 static_assert(sizeof(LinPiece) == 32, "LinPiece is 32 bytes");
 // The blocks of 16 places as a launch needs them: pieces[start[i]] .. pieces[start[i + 1] - 1] (device memory) are
-// the adapters of places 16 i .. 16 i + 15; the places from n_front on are those of the small groups.
+// the adapters of places 16 i .. 16 i + 15; the first big_tiles * kLinTileM places take large tiles.
 struct LinBlock {
     const int32_t *start;
     const LinPiece *pieces;
-    int n_front;
+    int big_tiles;
 };
 constexpr int kLinTileM = 256;  // rows of a work group's output tile (the row order is padded to a multiple)
 constexpr int kLinTileN = 256;  // columns of it: two 128-column strips of B^T (the last tile of a row may hold one)
@@ -167,7 +167,7 @@ hipError_t probe_xcc(unsigned *host_out, int n_work_groups, hipStream_t stream);
 
 // The adapted layer in one pass over y: y[row] = bf16(x[row] W + s_a v[row] B_a), W in operand order
 // (launch_pack_weight), s_a v as bf16 hi + lo from a shrink launch with scale_v.  n_places places in use;
-// rows[m] = batch row of place m, -1 from n_places to the next multiple of kLinTileM.
+// rows[m] = batch row of place m, -1 for none and from n_places to the next multiple of kLinTileM.
 hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n_places, const uint16_t *arena,
                               const uint16_t *w_packed, const uint16_t *x, int64_t ldx, int in, int out,
                               const uint16_t *v_hi, const uint16_t *v_lo, uint16_t *y, int64_t ldy,

@@ -19,7 +19,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <cmath>
 #include <type_traits>
 
 namespace lora {
@@ -2754,32 +2753,6 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, const f
 
 constexpr int kComputeUnits = 256;
 
-// How many row tiles of the adapted layer go to 256 x 256 tiles (from the front of the row order), the rest to
-// 64 x 64 tiles: what ends first on kComputeUnits compute units, one work group each, large tiles first.  A large
-// tile takes as long as 5.5 small ones (96 us at 4096 input features against 17 - 18), twice that where it meets
-// the many adapters of small groups.  4096 -> 4096, us per layer, all small / all large / as chosen: 1024 tokens
-// of few adapters 90 / 118, 2048 tokens 204 / 125; 8 prompts beside 384 decode tokens, 4096 tokens in all 389 /
-// 189 / 181, 6144 tokens 558 / 284 / 234.
-static int choose_big_row_tiles(int n_places, int n_front, int n_tiles, int small_columns)
-{
-    const int all = (n_places + kLinTileM - 1) / kLinTileM, front = n_front / kLinTileM;
-    auto cost = [&](int m) {
-        const double big = 5.5;
-        const double n_big = (double)m * n_tiles, slow = (double)(m > front && n_front < n_places ? m - front : 0) * n_tiles;
-        const double small = n_places > m * kLinTileM ? (double)((n_places - m * kLinTileM + 63) / 64) * small_columns : 0.0;
-        const double work = (n_big + slow) * big + small;
-        const double rounds = std::ceil(n_big / kComputeUnits) * big;  // the large tiles alone
-        // small tiles fill what the last round of large ones leaves, then whole rounds of their own
-        return std::max(std::max(rounds + (slow > 0 ? big : 0.0), work / kComputeUnits),
-                        n_big > 0 ? 0.0 : std::ceil(small / kComputeUnits));
-    };
-    int best = 0;
-    const int per_round = (int)((int64_t)front * n_tiles / kComputeUnits * kComputeUnits / n_tiles);
-    for (int m : {per_round, front, std::min(front + 1, all), all})
-        if (cost(m) < cost(best)) best = m;
-    return best;
-}
-
 hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n_places, const uint16_t *arena,
                               const uint16_t *w_packed, const uint16_t *x, int64_t ldx, int in, int out,
                               const uint16_t *v_hi, const uint16_t *v_lo, uint16_t *y, int64_t ldy,
@@ -2790,7 +2763,8 @@ hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n
     const int n_tiles = (out + kLinTileN - 1) / kLinTileN;
     const int32_t *start = blocks->start;
     const LinPiece *pieces = blocks->pieces;
-    const int m_big = choose_big_row_tiles(n_places, blocks->n_front, n_tiles, out / 64);
+    const int m_big = std::min(blocks->big_tiles, (n_places + kLinTileM - 1) / kLinTileM);
+    if (m_big < 0) return hipErrorInvalidValue;
     if (m_big == 0) {
         // small tiles only: the largest that still make a work group per compute unit.  4096 -> 4096, us per layer
         // of tokens without adapter, tiles of 64 x 64 / 32 x 64 / 32 x 32 / 16 x 32: 16 tokens 14.4 / 11.5 / 9.4 /

@@ -66,7 +66,7 @@ hipError_t launch_apply_fused(const LaunchCtx &s, const LaunchCtx &e, const uint
 hipError_t launch_decode_fused(const LaunchCtx &, const LaunchCtx &, int grid, const uint16_t *, int64_t, int, int, uint16_t *, int64_t, unsigned, const SyncArgs *, hipStream_t) { return note("decode_fused" + num(grid)); }
 hipError_t launch_reduce_slices(const float *, int n, int64_t, float *, int64_t, hipStream_t) { return note("reduce_slices" + num(n)); }
 hipError_t launch_pack_adapter(const uint16_t *, const uint16_t *, int, int, int, int, uint16_t *, uint16_t *, hipStream_t) { return hipSuccess; }
-hipError_t launch_linear_lora(const int32_t *, const LinBlock *, int n_places, const uint16_t *, const uint16_t *, const uint16_t *, int64_t, int, int, const uint16_t *, const uint16_t *, uint16_t *, int64_t, hipStream_t) { return note("linear" + num(n_places)); }
+hipError_t launch_linear_lora(const int32_t *, const LinBlock *b, int n_places, const uint16_t *, const uint16_t *, const uint16_t *, int64_t, int, int, const uint16_t *, const uint16_t *, uint16_t *, int64_t, hipStream_t) { return note("linear" + num(n_places) + num(b->big_tiles)); }
 hipError_t launch_pack_weight(const uint16_t *, int, int, uint16_t *, hipStream_t) { return hipSuccess; }
 hipError_t probe_xcc(unsigned *x, int n, hipStream_t)
 {

@@ -8,6 +8,7 @@ from paper_2511_22880_amd import workloads as wl
 
 import gpu_util as G
 from test_gpu_parity import _linear_case
+from test_launch_routes import LINEAR_ORDERS
 
 pytestmark = pytest.mark.gpu
 
@@ -177,6 +178,14 @@ def test_linear_small_tiles(tokens, shape):
 def test_linear_large_and_small_tiles_together(case):
     out_features, groups, idle = case
     _linear_case(_batch(128, out_features, groups, idle=idle, seed=5), 0.02, seed=6)
+
+
+@pytest.mark.parametrize("case", [c for c in LINEAR_ORDERS if c[3] or c[0] < 4096])
+def test_linear_row_orders(case):
+    """Groups side by side or in blocks of 16 rows of their own, large tiles, small tiles and both: the orders the planner
+    chooses among (which one each shape takes is tested in test_launch_routes.py), on every 5th row."""
+    b = _batch(*case[:3], idle=case[3], seed=12)
+    _linear_case(b, 0.02, seed=13, rows=np.arange(0, b.T, 5, dtype=np.int32))
 
 
 def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():

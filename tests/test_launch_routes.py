@@ -212,3 +212,35 @@ def test_token_heavy_shrink_units_are_cut_where_that_is_shorter(recorder, in_fea
     b = Batch(in_features, [512, 128, 128], groups)
     assert _heavy_slices(b)[0] == slices
     b.close()
+
+
+# ---- the adapted layer's row order and tiles ---------------------------------------------------------------------
+# (in, out, groups, idle tokens, every group in blocks of its own, row tiles of 256 places as large tiles, of how many);
+# test_gpu_forms.py runs them
+LINEAR_ORDERS = [
+    # large tiles for all rows, padded: small groups that would meet in a block; 1088 -> 8192 was 50 us so, 73 in small tiles
+    (1088, 8192, [(170, 64), (150, 8), (96, 16)] + [(3, 8 * (n % 16) + 8) for n in range(56)], 120, True, 6, 6),
+    (128, 8192, [(300, 128), (200, 16)] + [(n % 15 + 1, 8 * (n % 16) + 8) for n in range(40)], 60, True, 5, 5),
+    # large tiles that fill the compute units, small ones behind them: padded, and not
+    (128, 4096, [(900, 16), (701, 128)] + [(n % 15 + 1, 8 * (n % 32) + 1) for n in range(40)], 100, True, 8, 10),
+    (576, 3072, [(1128, 8)] * 4, 0, True, 16, 18),
+    (2176, 3072, [(1128, 8)] * 4, 0, False, 16, 18),
+    # large tiles for all rows, not padded
+    (128, 2048, [(9, 8 + n % 60) for n in range(700)], 10, False, 25, 25),
+    # small tiles
+    (4096, 4096, [(2, 64)] * 128, 0, False, 0, 1),
+    (64, 128, [], 5, False, 0, 1),
+]
+
+
+@pytest.mark.parametrize("case", LINEAR_ORDERS)
+def test_row_order_and_tiles_of_the_adapted_layer(recorder, case):
+    in_features, out_features, groups, idle, padded, big, tiles = case
+    b = Batch(in_features, out_features, groups or [(0, 8)], idle)
+    seg = b.build()
+    name, places, got = b.launches(recorder, seg, "linear")[-1]
+    assert name == "linear" and got == big and (places + 255) // 256 == tiles
+    assert places <= sum((n + 15) // 16 * 16 for n, _ in groups) + idle + 16 if padded else places == len(b.ta)
+    assert (places > len(b.ta)) == padded
+    L.lora_segments_destroy(seg)
+    b.close()
