@@ -65,24 +65,31 @@ def test_packed_adapter_is_the_documented_layout(rank, shape, offset):
 
 
 # ---- token-heavy groups: units cut along k, column runs down to one strip, the two halves apart -----------------
-@pytest.mark.parametrize("shape", [(64, 128), (2112, 640), (3072, 1152), (4160, 4224)])
+@pytest.mark.parametrize("shape, most", [((64, 128), 1), ((2112, 640), 2), ((3072, 1152), 3), ((4160, 4224), 4)])
 @pytest.mark.parametrize("sizes", [
     # (tokens, rank): every bucket of the shrink bodies, tiles of 64 and 32 with one row, one short of full and full
     [(33, 8), (65, 24), (64, 40), (127, 64), (96, 72)],
     [(64, 100), (129, 128), (63, 136), (65, 192), (32, 200), (33, 256)],
     [(40, 16), (70, 160), (3, 64), (1, 256)],  # beside decode-sized groups
 ])
-def test_token_heavy_units_cut_along_k(shape, sizes):
-    """lora_apply against the oracle, uncut (in_features 64) and in 2, 3 and 4 k-slices, and lora_shrink + lora_expand,
-    whose v is one rounding away from the one lora_apply hands over."""
+@pytest.mark.parametrize("cut", ["whole", "most", "built in"])
+def test_token_heavy_units_cut_along_k(shape, most, sizes, cut):
+    """lora_apply against the oracle, uncut and in as many k-slices as the in_features allow (1 to 4), and lora_shrink +
+    lora_expand, whose v is one rounding away from the one lora_apply hands over."""
     b = _batch(*shape, sizes, idle=3, seed=len(sizes))
     dp = G.DevicePool(b)
-    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_min_batch=64))
+    limit = {"whole": 0, "most": 1 << 20, "built in": -1}[cut]
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_min_batch=64, heavy_k_cut_max_units=limit))
+    u = L.lora_segments_export_units(seg)["shrink"]
+    heavy = u[(u[:, 0] >= 0) & (np.diff(L.lora_segments_export(seg)["seg_start"])[u[:, 0]] >= 32)]
+    slices = int(heavy[:, 5].max()) + 1
+    assert slices == {"whole": 1, "most": most, "built in": slices}[cut]
     x_bits, y0 = b.x_bits(), np.zeros((b.T, b.out_features), dtype=np.uint16)
     x, y = G.bits_to_dev(x_bits), G.bits_to_dev(y0)
-    ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, seg), 256), dtype=torch.uint8, device="cuda")
     for _ in range(2):  # the counters are left as they were found
         y.zero_()
+        ws.fill_(0xFF)
         L.lora_apply(dp.pool, seg, x, y, ws)
         torch.cuda.synchronize()
         G.check_all_rows(dp, x_bits, y0, G.dev_to_bits(y))
@@ -99,47 +106,82 @@ def test_token_heavy_units_cut_along_k(shape, sizes):
 
 # ---- batches of few units: one launch by themselves, two under capture ------------------------------------------
 @pytest.mark.parametrize("case", [
+    # (which of them take the one launch is tested in test_launch_routes.py)
     (64, 128, [(1, 1)]),
     (4096, 4096, [(1, 16)]),
-    (1088, 384, [(5, 256), (16, 256)]),             # 32 shrink units
-    (1088, 384, [(5, 256), (16, 256), (1, 8)]),     # 33: two launches
-    (4160, 1152, [(17, 40), (1, 8), (2, 16)]),      # k-slices, two token tiles
+    (1088, 384, [(5, 128), (16, 128)]),             # 16 shrink units
+    (1088, 384, [(5, 128), (16, 128), (1, 8)]),     # 17: two launches
+    (4160, 1152, [(17, 16), (2, 16)]),              # k-slices, two token tiles
     (512, 8192, [(3, 100)]),                        # 64 expand units
+    (2048, [640, 128, 256], [(2, 16), (1, 40)]),    # three projections
 ])
 def test_batches_of_few_units(case):
-    in_features, out_features, groups = case
-    b = _batch(in_features, out_features, groups, idle=2, seed=8)
-    dp = G.DevicePool(b)
-    x_bits, y0 = b.x_bits(), b.y0_bits("small")
-    x = G.bits_to_dev(x_bits)
-    segs = [L.lora_segments_build(dp.pool, b.token_adapter, options=o)
+    """Two inputs in turn, the workspace full of NaNs before every apply and replay: an expand unit that did not wait for
+    its v would show."""
+    in_features, outs, groups = case
+    outs = [outs] if isinstance(outs, int) else outs
+    b = _batch(in_features, outs[0], groups, idle=2, seed=8)
+    others = [_batch(in_features, o, groups, idle=2, seed=8) for o in outs[1:]]
+    dps = [G.DevicePool(q) for q in [b] + others]
+    pools = [dp.pool for dp in dps]
+    build = L.lora_segments_build_multi if len(pools) > 1 else L.lora_segments_build
+    x_bits = [b.x_bits(), np.ascontiguousarray(b.x_bits()[::-1])]
+    x = [G.bits_to_dev(q) for q in x_bits]
+    y0 = np.concatenate([q.y0_bits("small") for q in [b] + others], axis=1)
+    segs = [build(pools if len(pools) > 1 else pools[0], b.token_adapter, options=o)
             for o in (None, L.plan_options(fused_apply=0), L.plan_options(decode_single_launch=0))]
-    ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, segs[0]), 256), dtype=torch.uint8, device="cuda")
-    ys = []
-    for seg in segs:
-        y = G.bits_to_dev(y0)
-        L.lora_apply(dp.pool, seg, x, y, ws)
-        torch.cuda.synchronize()
-        L.lora_segments_check(seg)
-        ys.append(G.dev_to_bits(y))
-    G.check_all_rows(dp, x_bits, y0, ys[0])
-    assert np.array_equal(ys[0], ys[1]) and np.array_equal(ys[0], ys[2])
-    y = G.bits_to_dev(y0)
+    ws = torch.empty(max(L.lora_apply_workspace_bytes(pools[0], segs[0]), 256), dtype=torch.uint8, device="cuda")
+
+    def apply(seg, i, y, **kw):
+        if len(pools) > 1:
+            L.lora_apply_multi(pools, seg, x[i], y, ws, **kw)
+        else:
+            L.lora_apply(pools[0], seg, x[i], y, ws, **kw)
+
+    expect = [None, None]
+    for seg in segs + segs:  # (each object twice: the counters are left as the next launch needs them)
+        for i in (0, 1):
+            y = G.bits_to_dev(y0)
+            ws.fill_(0xFF)
+            apply(seg, i, y)
+            torch.cuda.synchronize()
+            L.lora_segments_check(seg)
+            got = G.dev_to_bits(y)
+            if expect[i] is None:
+                expect[i] = got
+                at = 0
+                for dp, q in zip(dps, [b] + others):
+                    part = slice(at, at + q.out_features)
+                    G.check_all_rows(dp, x_bits[i], np.ascontiguousarray(y0[:, part]), np.ascontiguousarray(got[:, part]))
+                    at += q.out_features
+            assert np.array_equal(got, expect[i])
+    if len(pools) == 1:  # the library's own workspace, which holds the other input's v
+        for i in (0, 1, 0):
+            y = G.bits_to_dev(y0)
+            L.lora_apply_static(pools[0], segs[0], x[i], y)
+            torch.cuda.synchronize()
+            L.lora_segments_check(segs[0])
+            assert np.array_equal(G.dev_to_bits(y), expect[i])
+    y, eager = G.bits_to_dev(y0), G.bits_to_dev(y0)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        L.lora_apply(dp.pool, segs[0], x, y, ws, stream=torch.cuda.current_stream())
-    eager = G.bits_to_dev(y0)
-    for _ in range(3):
+        apply(segs[0], 0, y, stream=torch.cuda.current_stream())
+    for rep in range(4):
         y.copy_(G.bits_to_dev(y0))
+        ws.fill_(0xFF)
         graph.replay()
         eager.copy_(G.bits_to_dev(y0))
-        L.lora_apply(dp.pool, segs[0], x, eager, ws)
         torch.cuda.synchronize()
-        assert np.array_equal(G.dev_to_bits(y), ys[0]) and np.array_equal(G.dev_to_bits(eager), ys[0])
+        ws.fill_(0xFF)
+        apply(segs[0], rep % 2, eager)
+        torch.cuda.synchronize()
+        L.lora_segments_check(segs[0])
+        assert np.array_equal(G.dev_to_bits(y), expect[0]) and np.array_equal(G.dev_to_bits(eager), expect[rep % 2])
     del graph
     for seg in segs:
         L.lora_segments_destroy(seg)
-    dp.close()
+    for dp in dps:
+        dp.close()
 
 
 # ---- lora_linear: small tiles, large tiles, both in one launch --------------------------------------------------
@@ -210,10 +252,14 @@ def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
         dp.close()
 
 
-# ---- whole-k decode batches: one launch from 192 shrink units and 8192 features in and out together, else two -------
-@pytest.mark.parametrize("units", [64, 191, 192, 256])
-@pytest.mark.parametrize("shape", [(4096, 4096), (4096, 3968), (1024, 7168)])
-def test_decode_batches_on_either_side_of_the_one_launch_rule(units, shape):
+# ---- whole-k decode batches: one launch or two, by the units of both kinds --------------------------------------------
+@pytest.mark.parametrize("units, shape, one", [
+    (64, (4096, 4096), False),
+    # 6 units and the expand units (one per 512 columns and token tile) together at 2048
+    (186, (4096, 2560), False), (187, (4096, 2560), True), (256, (1024, 1024), True), (255, (2112, 1152), True),
+    (256, (1024, 7168), False),  # more expand units than one round holds
+])
+def test_decode_batches_on_either_side_of_the_one_launch_rule(units, shape, one):
     """Groups of one rank block each: the built-in choice, one launch and two launches give the same bits."""
     b = _batch(*shape, [(1 + i % 2, 16) for i in range(units)], seed=units)
     dp = G.DevicePool(b)
@@ -221,7 +267,9 @@ def test_decode_batches_on_either_side_of_the_one_launch_rule(units, shape):
     x, ys = G.bits_to_dev(x_bits), []
     for o in (None, L.plan_options(decode_single_launch=1), L.plan_options(decode_single_launch=0)):
         seg = L.lora_segments_build(dp.pool, b.token_adapter, options=o)
-        ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, seg), 256), dtype=torch.uint8, device="cuda")
+        if o is None:
+            assert bool(L.lora_segments_info(seg)["single_launch"]) == one
+        ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
         y = G.bits_to_dev(y0)
         L.lora_apply(dp.pool, seg, x, y, ws)
         torch.cuda.synchronize()
