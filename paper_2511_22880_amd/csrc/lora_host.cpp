@@ -2245,6 +2245,16 @@ try {
 }
 API_CATCH
 
+// Whether work on `s` may be captured.  The legacy stream cannot be asked while a blocking stream captures (the answer is an
+// error, which must not reach the caller's next call): the launches that a capture would take are right there too.
+static bool may_be_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // The launches of one apply: `arena` is the base the units' weight offsets count from, `out` the
 // width of y that the units' columns lie in.
 // may_create: the apply may make the segment object's side stream and events at its first use.
@@ -2283,24 +2293,20 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     // The one-launch decode form takes its epoch from the host at launch, which a replayed graph would
     // repeat: under stream capture the batch takes the two launches, which give the same bits.
     // Nor on a device where the probe launch did not find work group b on the XCD of b mod 8.
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     const DeviceProfile *prof = nullptr;
     const int fused = opt_fused_apply(sg);
-    bool single = fused != 0 && !sg->has_big_units && !sg->wide &&
-                  (fused > 0 || (opt_decode_single(sg) != 0 && sg->n_active <= kSingleLaunchTokens && sg->top_rank <= kSingleLaunchRank &&
-                                 cs.n_units <= kSingleLaunchShrinkUnits && cs.n_units + ce.n_units <= kSingleLaunchUnits));
-    if (single && fused < 0) {  // under capture the two launches, as for the one-launch decode form above
-        HIP_TRY(hipStreamIsCapturing(s, &capturing));
-        single = capturing == hipStreamCaptureStatusNone;
-    }
-    if (opt_decode_single(sg) && sg->decode_fused) {
-        HIP_TRY(hipStreamIsCapturing(s, &capturing));
+    // (the few-units form takes two launches under capture too, unless it was asked for)
+    const bool single = fused != 0 && !sg->has_big_units && !sg->wide &&
+                        (fused > 0 || (opt_decode_single(sg) != 0 && sg->n_active <= kSingleLaunchTokens && sg->top_rank <= kSingleLaunchRank &&
+                                       cs.n_units <= kSingleLaunchShrinkUnits && cs.n_units + ce.n_units <= kSingleLaunchUnits &&
+                                       !may_be_captured(s)));
+    if (opt_decode_single(sg) && sg->decode_fused && !may_be_captured(s)) {
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));
         if (dev >= 0 && dev < lora::kMaxDevices && g_profile[dev].state.load(std::memory_order_acquire) == 1)
             prof = &g_profile[dev];
     }
-    if (prof && capturing == hipStreamCaptureStatusNone) {
+    if (prof) {
         ++msg->launches;
         HIP_TRY(lora::launch_decode_fused(ctx_for(arena, in, out, sg, kFusedShrink), ctx_for(arena, in, out, sg, kFusedExpand),
                                           sg->fused_grid, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices,

@@ -24,6 +24,7 @@ const char *recorder_take()
     g_log.clear();
     return out.c_str();
 }
+// 1: the stream captures; 2: it is the legacy stream and a blocking stream captures
 void recorder_capture(int on) { g_capturing = on; }
 
 hipError_t hipMalloc(void **p, size_t n) { return (*p = aligned_alloc(4096, (n + 4095) / 4096 * 4096)) ? hipSuccess : hipErrorOutOfMemory; }
@@ -41,8 +42,8 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
 {
-    *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
-    return hipSuccess;
+    *s = g_capturing == 1 ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return g_capturing == 2 ? hipErrorStreamCaptureImplicit : hipSuccess;
 }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)
@@ -52,6 +53,7 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)
     p->multiProcessorCount = 256;
     return hipSuccess;
 }
+hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
 }
 

@@ -34,6 +34,12 @@ def recorder(tmp_path_factory):
     L.LIB_PATH, L._lib = path, loaded
 
 
+@pytest.fixture(autouse=True)
+def no_capture(recorder):
+    yield
+    recorder.recorder_capture(0)
+
+
 class Batch:
     """A pool (or several side by side) with every adapter resident, in host memory."""
 
@@ -135,8 +141,9 @@ def test_whole_k_decode_batches_in_one_launch(recorder, in_features, out_feature
     seg = b.build()
     assert L.lora_segments_info(seg)["single_launch"] == one
     assert _names(b.launches(recorder, seg)) == (["decode_fused"] if one else ["shrink_wide", "expand"])
-    recorder.recorder_capture(1)  # two launches under capture
-    assert _names(b.launches(recorder, seg)) == ["shrink_wide", "expand"]
+    for state in (1, 2):  # two launches under capture, and on the legacy stream while a blocking stream captures
+        recorder.recorder_capture(state)
+        assert _names(b.launches(recorder, seg)) == ["shrink_wide", "expand"]
     recorder.recorder_capture(0)
     L.lora_segments_destroy(seg)
     b.close()
@@ -164,8 +171,9 @@ def test_batches_of_few_units_in_one_launch(recorder, in_features, outs, groups,
         seg = b.build(options)
         assert _names(b.launches(recorder, seg)) == (["apply_fused"] if expect else two)
         if options is None:
-            recorder.recorder_capture(1)
-            assert _names(b.launches(recorder, seg)) == two
+            for state in (1, 2):  # 2: the legacy stream while a blocking stream captures
+                recorder.recorder_capture(state)
+                assert _names(b.launches(recorder, seg)) == two
             recorder.recorder_capture(0)
             if len(b.pools) == 1:
                 assert _names(b.launches(recorder, seg, "static")) == (["apply_fused"] if expect else two)
