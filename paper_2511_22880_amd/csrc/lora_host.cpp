@@ -600,7 +600,7 @@ static int heavy_tile(int r8) { return r8 <= 64 || r8 > 192 ? 32 : 64; }
 // rank, must fit the kernel's 64 KiB of LDS): every rank the pool holds
 static const int kBigExpandMaxRank = 256;
 static_assert(kBigExpandMaxRank >= LORA_MAX_RANK_PADDED, "the 16-token expand units of token-heavy groups are gone");
-static int g_compute_units = 256;  // of the chip: a whole-k launch within this many units is one round
+using lora::kComputeUnits;  // a whole-k launch within this many units is one round
 
 // K-slices of a launch's token-heavy shrink units: as many as keep it shortest by an estimate.  A compute unit passes
 // about 68 GB/s (rows of x and A^T, 2 bytes each), so a launch lasts as long as its heaviest unit, as the two that share a
@@ -624,7 +624,7 @@ struct HeavyShrink {
 };
 static int choose_heavy_k_slices(HeavyShrink &h, int in, int max_slices)
 {
-    const int n = (int)h.rows.size(), cus = g_compute_units;
+    const int n = (int)h.rows.size(), cus = kComputeUnits;
     std::sort(h.rows.begin(), h.rows.end(), std::greater<int>());
     double total = 24.0 * h.small_units;
     for (int r : h.rows) total += r;
@@ -785,7 +785,7 @@ static void order_heavy_units_by_xcd(std::vector<Unit> &units)
 
 static int opt_big_runs_max_units(const lora_segments *sg)
 {
-    return sg->opts.big_runs_max_units >= 0 ? sg->opts.big_runs_max_units : kBigRunsWorkGroupsPerComputeUnit * g_compute_units;
+    return sg->opts.big_runs_max_units >= 0 ? sg->opts.big_runs_max_units : kBigRunsWorkGroupsPerComputeUnit * kComputeUnits;
 }
 static const int kXcds = 8;         // XCDs of the chip, each with an L2 of its own; work group b of a launch runs on XCD b mod 8
 static std::atomic<int> g_decode_single_launch{-1};  // 1: wherever it can be, 0: never, -1: where it is the faster form
@@ -826,7 +826,7 @@ static int opt_decode_single(const lora_segments *sg) { return sg->opts.decode_s
 // 11 % and 79 %.  A line at 192 shrink units and 8192 features in and out together, 0.5 % and 36 %.
 static bool decode_single_pays(int opt, int64_t whole_k_units, int64_t expand_units, int top_rank)
 {
-    return opt > 0 || (opt < 0 && top_rank <= 128 && 6 * whole_k_units + expand_units >= 8 * (int64_t)g_compute_units);
+    return opt > 0 || (opt < 0 && top_rank <= 128 && 6 * whole_k_units + expand_units >= 8 * (int64_t)kComputeUnits);
 }
 static int opt_whole_k_max_in(const lora_segments *sg) { return sg->opts.whole_k_max_in >= 0 ? sg->opts.whole_k_max_in : kWholeKMaxIn; }
 static int opt_heavy_min_tokens(const lora_segments *sg) { return sg->opts.heavy_min_tokens >= 0 ? sg->opts.heavy_min_tokens : kPrefillMinTokens; }
@@ -867,11 +867,11 @@ static void finish_decode_fused(lora_segments *sg, bool want, int in_features)
     sg->fused_shrink.clear();
     sg->fused_expand.clear();
     sg->fused_grid = 0;
-    const int cap_s = g_compute_units / kXcds, cap_e = 4 * cap_s;
+    const int cap_s = kComputeUnits / kXcds, cap_e = 4 * cap_s;
     sg->decode_fused = want && sg->wide && sg->prefill_units.empty() && sg->expand_big_units.empty() &&
                        !sg->shrink_units.empty() && !sg->expand_units.empty() && sg->n_sync > 0 &&
-                       sg->shrink_units.size() <= (size_t)g_compute_units &&
-                       sg->expand_units.size() <= (size_t)(4 * g_compute_units) && g_compute_units % kXcds == 0;
+                       sg->shrink_units.size() <= (size_t)kComputeUnits &&
+                       sg->expand_units.size() <= (size_t)(4 * kComputeUnits) && kComputeUnits % kXcds == 0;
     if (!sg->decode_fused) return;
     struct Tile {
         std::vector<int> s, e;
@@ -1165,8 +1165,8 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         top_rank = std::max(top_rank, pool->r8[a]);
     }
     const bool want_fused = decode_single_pays(opt_decode_single(sg), whole_k_units, small_expand_units, top_rank) && sg->wide &&
-                            !heavy_groups && n_projections == 1 && whole_k_units <= g_compute_units &&
-                            small_expand_units <= 4 * (int64_t)g_compute_units;
+                            !heavy_groups && n_projections == 1 && whole_k_units <= kComputeUnits &&
+                            small_expand_units <= 4 * (int64_t)kComputeUnits;
     if (sg->wide && !want_fused) {
         int64_t per_tokens[lora::kTokTile + 1] = {0};  // full 16-row units by their token count
         for (int a = 0; a < N; ++a) {
@@ -1175,7 +1175,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
                 per_tokens[std::min(lora::kTokTile, count[a] - tok0)] += pool->r8[a] / lora::kRowTile;
         }
         int64_t extra = 0;
-        for (int m = lora::kTokTile; m >= kSplitRowsFloor && whole_k_units + extra + per_tokens[m] <= g_compute_units; --m) {
+        for (int m = lora::kTokTile; m >= kSplitRowsFloor && whole_k_units + extra + per_tokens[m] <= kComputeUnits; --m) {
             extra += per_tokens[m];
             if (per_tokens[m]) split_min_tokens = m;
         }
@@ -1677,7 +1677,7 @@ try {
 API_CATCH
 
 // What the library found out about a device at the first upload there: whether it is the chip the
-// planner's constants describe (gfx950, at least g_compute_units compute units) and, from one probe
+// planner's constants describe (gfx950, at least kComputeUnits compute units) and, from one probe
 // launch, whether the work groups of one residue mod 8 share an XCD (xcc_map: 4 bits per XCD number, the
 // residue found there).  The one-launch decode form needs both; everything else runs without them.
 struct DeviceProfile {
@@ -1702,16 +1702,16 @@ static lora_status_t device_profile(hipStream_t s, DeviceProfile **out)
     if (strncmp(prop.gcnArchName, "gfx950", 6) != 0)
         return fail(LORA_ERR_DEVICE, "device %d is %s: this library's kernels and planner are for gfx950", dev,
                     prop.gcnArchName);
-    bool ok = prop.multiProcessorCount >= g_compute_units;
+    bool ok = prop.multiProcessorCount >= kComputeUnits;
     unsigned map = 0;
     if (ok) {
-        std::vector<unsigned> xcc((size_t)g_compute_units);
-        HIP_TRY(lora::probe_xcc(xcc.data(), g_compute_units, s));
+        std::vector<unsigned> xcc((size_t)kComputeUnits);
+        HIP_TRY(lora::probe_xcc(xcc.data(), kComputeUnits, s));
         // work groups of one residue mod 8 on one XCD, eight different XCDs numbered 0..7; the map gives
         // each XCD number the residue it had in this launch (launches may start at another XCD)
         bool seen[16] = {false};
         for (int r = 0; r < kXcds && ok; ++r) {
-            for (int b = r; b < g_compute_units; b += kXcds) ok = ok && xcc[b] == xcc[r];
+            for (int b = r; b < kComputeUnits; b += kXcds) ok = ok && xcc[b] == xcc[r];
             ok = ok && xcc[r] < (unsigned)kXcds && !seen[xcc[r] & 15];
             seen[xcc[r] & 15] = true;
             if (ok) map |= (unsigned)r << (4 * xcc[r]);
@@ -2120,7 +2120,7 @@ try {
     hipStream_t s = (hipStream_t)stream;
     const lora::LaunchCtx c = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, kPrefill);
     if (sg->wide) {
-        HIP_TRY(lora::launch_shrink_wide(c, c.n_units > g_compute_units, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, v, nullptr,
+        HIP_TRY(lora::launch_shrink_wide(c, c.n_units > kComputeUnits, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, v, nullptr,
                                          nullptr, s));
         HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
                                             nullptr, s));
@@ -2157,9 +2157,9 @@ try {
     if (sg->n_active == 0) return LORA_OK;
     if ((st = check_matrix(y, ldy, pool->out_features, "y")) != LORA_OK) return st;
     if (!v || ((uintptr_t)v) % 16) return fail(LORA_ERR_INVALID_ARG, "v is NULL or not 16-byte aligned");
-    HIP_TRY(lora::launch_expand(ctx_for(pool, sg, kExpand), false, v, 1, 0, (uint16_t *)y, ldy, nullptr,
+    HIP_TRY(lora::launch_expand(ctx_for(pool, sg, kExpand), false, v, (uint16_t *)y, ldy, nullptr,
                                 (hipStream_t)stream));
-    HIP_TRY(lora::launch_expand(ctx_for(pool, sg, kExpandBig), true, v, 1, 0, (uint16_t *)y, ldy, nullptr,
+    HIP_TRY(lora::launch_expand(ctx_for(pool, sg, kExpandBig), true, v, (uint16_t *)y, ldy, nullptr,
                                 (hipStream_t)stream));
     return LORA_OK;
 }
@@ -2325,7 +2325,7 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
             HIP_TRY(lora::launch_shrink_mixed(cp, sg->n_prefill_hi, cs, (const uint16_t *)x, ldx, sg->k_slice_len, parts,
                                               nsl, stride, &sa, s));
             if (ev[1]) HIP_TRY(hipEventRecord(ev[1], s));
-            HIP_TRY(lora::launch_expand_mixed(cb, ce, parts, nsl, stride, (uint16_t *)y, ldy, &sa, s));
+            HIP_TRY(lora::launch_expand_mixed(cb, ce, (uint16_t *)y, ldy, &sa, s));
             if (ev[2]) HIP_TRY(hipEventRecord(ev[2], s));
             return LORA_OK;
         }
@@ -2349,13 +2349,13 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
         HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, sa.v_hi, sa.v_lo, nullptr,
                                             nsl, stride, parts, &sa, s));
         if (sg->wide)
-            HIP_TRY(lora::launch_shrink_wide(cs, cs.n_units > g_compute_units, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, nullptr,
+            HIP_TRY(lora::launch_shrink_wide(cs, cs.n_units > kComputeUnits, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, nullptr,
                                              sa.v_hi, sa.v_lo, sd));
         else
             HIP_TRY(lora::launch_shrink(cs, (const uint16_t *)x, ldx, sg->k_slice_len, parts, nsl, stride, &sa, sd));
         if (ev[1]) HIP_TRY(hipEventRecord(ev[1], s));
-        HIP_TRY(lora::launch_expand(ce, false, parts, nsl, stride, (uint16_t *)y, ldy, &sa, sd));
-        HIP_TRY(lora::launch_expand(cb, true, parts, nsl, stride, (uint16_t *)y, ldy, &sa, s));
+        HIP_TRY(lora::launch_expand(ce, false, nullptr, (uint16_t *)y, ldy, &sa, sd));
+        HIP_TRY(lora::launch_expand(cb, true, nullptr, (uint16_t *)y, ldy, &sa, s));
         if (split) {
             HIP_TRY(hipEventRecord(msg->join, sd));
             HIP_TRY(hipStreamWaitEvent(s, msg->join, 0));
@@ -2427,7 +2427,7 @@ try {
             HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, sa.v_hi, sa.v_lo, nullptr, nsl,
                                                 stride, parts, &sa, s));
             if (sg->wide)
-                HIP_TRY(lora::launch_shrink_wide(cs, cs.n_units > g_compute_units, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, nullptr,
+                HIP_TRY(lora::launch_shrink_wide(cs, cs.n_units > kComputeUnits, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, nullptr,
                                                  sa.v_hi, sa.v_lo, s));
             else
                 HIP_TRY(lora::launch_shrink(cs, (const uint16_t *)x, ldx, sg->k_slice_len, parts, nsl, stride, &sa, s));

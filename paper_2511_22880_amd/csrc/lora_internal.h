@@ -66,6 +66,7 @@ struct LinBlock {
     const LinPiece *pieces;
     int big_tiles;
 };
+constexpr int kComputeUnits = 256;  // of the chip
 constexpr int kLinTileM = 256;  // rows of a work group's output tile (the row order is padded to a multiple)
 constexpr int kLinTileN = 256;  // columns of it: two 128-column strips of B^T (the last tile of a row may hold one)
 
@@ -113,11 +114,11 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
                               int k_slice_len, int n_slices, float *v_f32, uint16_t *v_hi, uint16_t *v_lo,
                               hipStream_t stream);
 
-// Without `sync`: v_in is v itself, fp32 and complete (n_slices = 1).  With `sync`: v comes from sync->v_hi / v_lo
-// (written by a shrink launch of the same epoch), v_in and the slices are not read.
+// Without `sync`: v_in is v itself, fp32 and complete.  With `sync`: v comes from sync->v_hi / v_lo (written by a
+// shrink launch of the same epoch), v_in is not read.
 // `big`: the list holds units of up to 64 tokens (token indices through perm).
-hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, int n_slices, int64_t slice_stride,
-                         uint16_t *y, int64_t ldy, const SyncArgs *sync, hipStream_t stream);
+hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16_t *y, int64_t ldy, const SyncArgs *sync,
+                         hipStream_t stream);
 
 // Shrink of token-heavy groups: one unit = (group, up to 32 tokens, all rank rows, the whole of k).
 // n_hi = how many of the units are above rank 64: with none, the launch takes the kernel that fits four
@@ -137,8 +138,7 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
 hipError_t launch_shrink_mixed(const LaunchCtx &heavy, int n_hi, const LaunchCtx &c, const uint16_t *x, int64_t ldx,
                                int k_slice_len, float *parts, int n_slices, int64_t slice_stride,
                                const SyncArgs *sync, hipStream_t stream);
-hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, const float *parts, int n_slices,
-                               int64_t slice_stride, uint16_t *y, int64_t ldy, const SyncArgs *sync,
+hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_t *y, int64_t ldy, const SyncArgs *sync,
                                hipStream_t stream);
 
 // Both halves in one launch (shrink units first); the expand units poll `ready` of their token tile,

@@ -1207,7 +1207,7 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 bk.yv[s] = zero;
                 if (c0 + s * kStrip < ncols) bk.yv[s] = ld16_stream(bk.e_y + c0 + s * kStrip);
             }
-            // (single launch) the weights and y are on their way while v is waited for
+            // (single launch) y, and up to rank 128 the weights, are on their way while v is waited for
             if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
@@ -2643,12 +2643,11 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
     return hipGetLastError();
 }
 
-hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, int n_slices, int64_t slice_stride,
-                         uint16_t *y, int64_t ldy, const SyncArgs *sync, hipStream_t stream)
+hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16_t *y, int64_t ldy, const SyncArgs *sync,
+                         hipStream_t stream)
 {
     if (c.n_units <= 0) return hipSuccess;
-    if (!sync && n_slices != 1) return hipErrorInvalidValue;
-    (void)slice_stride;
+    if (!sync && !v_in) return hipErrorInvalidValue;
     const Sync sy = make_sync(sync, 0);
     const dim3 g(c.n_units), b(kThreads);
     if (big && sync)
@@ -2740,7 +2739,7 @@ hipError_t launch_shrink_mixed(const LaunchCtx &heavy, int n_hi, const LaunchCtx
     return hipGetLastError();
 }
 
-hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, const float *, int, int64_t, uint16_t *y, int64_t ldy, const SyncArgs *sync,
+hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_t *y, int64_t ldy, const SyncArgs *sync,
                                hipStream_t stream)
 {
     const int total = big.n_units + c.n_units;
@@ -2750,8 +2749,6 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, const f
                        c.perm, c.arena, y, ldy, make_sync(sync, 0));
     return hipGetLastError();
 }
-
-constexpr int kComputeUnits = 256;
 
 hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n_places, const uint16_t *arena,
                               const uint16_t *w_packed, const uint16_t *x, int64_t ldx, int in, int out,

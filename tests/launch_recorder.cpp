@@ -60,10 +60,10 @@ const char *hipGetErrorString(hipError_t) { return "error"; }
 namespace lora {
 hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink" + num(c.n_units)) : hipSuccess; }
 hipError_t launch_shrink_wide(const LaunchCtx &c, bool, const uint16_t *, int64_t, int, int, float *, uint16_t *, uint16_t *, hipStream_t) { return c.n_units ? note("shrink_wide" + num(c.n_units)) : hipSuccess; }
-hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note((big ? "expand_big" : "expand") + num(c.n_units)) : hipSuccess; }
+hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note((big ? "expand_big" : "expand") + num(c.n_units)) : hipSuccess; }
 hipError_t launch_shrink_prefill(const LaunchCtx &c, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int n_slices, int64_t, float *, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink_prefill" + num(c.n_units) + num(n_slices)) : hipSuccess; }
 hipError_t launch_shrink_mixed(const LaunchCtx &h, int, const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return note("shrink_mixed" + num(h.n_units) + num(c.n_units)); }
-hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, const float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("expand_mixed" + num(b.n_units) + num(c.n_units)); }
+hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("expand_mixed" + num(b.n_units) + num(c.n_units)); }
 hipError_t launch_apply_fused(const LaunchCtx &s, const LaunchCtx &e, const uint16_t *, int64_t, int, float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("apply_fused" + num(s.n_units) + num(e.n_units)); }
 hipError_t launch_decode_fused(const LaunchCtx &, const LaunchCtx &, int grid, const uint16_t *, int64_t, int, int, uint16_t *, int64_t, unsigned, const SyncArgs *, hipStream_t) { return note("decode_fused" + num(grid)); }
 hipError_t launch_reduce_slices(const float *, int n, int64_t, float *, int64_t, hipStream_t) { return note("reduce_slices" + num(n)); }

@@ -16,10 +16,10 @@
 namespace lora {
 hipError_t launch_shrink(const LaunchCtx &, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
 hipError_t launch_shrink_wide(const LaunchCtx &, bool, const uint16_t *, int64_t, int, int, float *, uint16_t *, uint16_t *, hipStream_t) { return hipSuccess; }
-hipError_t launch_expand(const LaunchCtx &, bool, const float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
+hipError_t launch_expand(const LaunchCtx &, bool, const float *, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
 hipError_t launch_shrink_prefill(const LaunchCtx &, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int, int64_t, float *, const SyncArgs *, hipStream_t) { return hipSuccess; }
 hipError_t launch_shrink_mixed(const LaunchCtx &, int, const LaunchCtx &, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
-hipError_t launch_expand_mixed(const LaunchCtx &, const LaunchCtx &, const float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
+hipError_t launch_expand_mixed(const LaunchCtx &, const LaunchCtx &, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
 hipError_t launch_apply_fused(const LaunchCtx &, const LaunchCtx &, const uint16_t *, int64_t, int, float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return hipSuccess; }
 hipError_t launch_reduce_slices(const float *, int, int64_t, float *, int64_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_pack_adapter(const uint16_t *, const uint16_t *, int, int, int, int, uint16_t *, uint16_t *, hipStream_t) { return hipSuccess; }
