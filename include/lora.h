@@ -243,7 +243,8 @@ lora_status_t lora_segments_upload(lora_segments_t *seg, void *stream);
 /* The same with memory of the caller's: the table goes into dev_table (device memory, 256-byte aligned)
  * through host_staging (host memory, pinned if the copy is to be asynchronous, 16-byte aligned), each
  * at least lora_segments_table_bytes(seg) long (known after planning).  The object uses both from now
- * on, for lora_segments_rebuild too (LORA_ERR_OOM, with the sizes, if a later batch needs more), and
+ * on, for lora_segments_rebuild too (a later batch that they have no room for is planned without the
+ * forms that take more table for speed alone; LORA_ERR_OOM, with the sizes, if that needs more too), and
  * never frees them; the caller keeps them alive as long as the object and leaves them alone while
  * launches that use the object may run.  No allocation is made. */
 lora_status_t lora_segments_table_bytes(const lora_segments_t *seg, size_t *bytes);

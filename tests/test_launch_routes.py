@@ -7,6 +7,7 @@ import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2511_22880_amd import binding as L
 
@@ -251,4 +252,38 @@ def test_row_order_and_tiles_of_the_adapted_layer(recorder, case):
     assert places <= sum((n + 15) // 16 * 16 for n, _ in groups) + idle + 16 if padded else places == len(b.ta)
     assert (places > len(b.ta)) == padded
     L.lora_segments_destroy(seg)
+    b.close()
+
+
+@pytest.mark.parametrize("in_features, outs, groups, call, faster, plainer", [
+    (1088, 8192, LINEAR_ORDERS[0][2], "linear", 
+     [("shrink_wide", 296), ("linear", 1315, 6)], [("shrink_wide", 296), ("linear", 584, 0)]),
+    (1024, 3456, [(1, 64)] * 58, "apply", 
+     [("decode_fused", 256)], [("shrink_wide", 232), ("expand", 812)]),
+    (4096, 8192, [(2000, 128)], "apply", 
+     [("shrink_prefill", 128, 4), ("expand_big", 512)], [("shrink_prefill", 32, 4), ("expand_big", 128)]),
+    (1024, 4096, [(600, 64)] * 2, "apply", 
+     [("shrink_prefill", 40, 1), ("expand_big", 320)], [("shrink_prefill", 40, 1), ("expand_big", 80)]),
+    (4096, [4096, 1024], [(600, 64)] * 3, "apply", 
+     [("shrink_prefill", 464, 4), ("expand_big", 480)], [("shrink_prefill", 128, 4), ("expand_big", 180)]),
+])
+def test_a_caller_s_table_without_room_for_the_faster_form(recorder, in_features, outs, groups, call, faster, plainer):
+    """lora_segments_rebuild into memory that holds the batch's units, but not padded rows, the one launch's lists, k-slices or
+    short column runs: accepted, in the plainer form; refused where that has no room either."""
+    b = Batch(in_features, outs, groups)
+    plan = (lambda ta: L.lora_segments_plan_multi(b.pools, ta)) if len(b.pools) > 1 else lambda ta: L.lora_segments_plan(b.pools[0], ta)
+    seg = plan(b.ta)
+    need = L.lora_segments_table_bytes(seg)
+    L.lora_segments_destroy(seg)
+    for size, expect in ((need, faster), (need - 256, plainer), (need // 4, None)):
+        first = plan(b.ta[:1])
+        dev, staging = (m[-m.data_ptr() % 256:][:size] for m in (torch.zeros(size + 256, dtype=torch.uint8) for _ in range(2)))
+        L.lora_segments_upload_to(first, dev, staging)
+        if expect is None:
+            with pytest.raises(L.LoraError, match="OOM"):
+                L.lora_segments_rebuild(first, b.ta)
+        else:
+            L.lora_segments_rebuild(first, b.ta)
+            assert b.launches(recorder, first, call) == expect
+        L.lora_segments_destroy(first)
     b.close()
