@@ -1896,7 +1896,7 @@ try {
     };
     lora_status_t st = plan(false);
     // memory of the caller's that has no room for k-slices, short column runs, the one launch's lists or padded rows, but for the
-    // batch without them (tables of the two plans over 600 random batches: up to 1.9 to 1)
+    // batch without them (tables of the two plans over 600 random batches: up to 1.8 to 1)
     if (st == LORA_OK && sg->caller_memory && sg->table_bytes > std::min(sg->dev_capacity, sg->staging_capacity)) st = plan(true);
     if (st != LORA_OK) {
         sg->uploaded = false;

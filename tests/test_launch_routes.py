@@ -271,7 +271,9 @@ def test_a_caller_s_table_without_room_for_the_faster_form(recorder, in_features
     """lora_segments_rebuild into memory that holds the batch's units, but not padded rows, the one launch's lists, k-slices or
     short column runs: accepted, in the plainer form; refused where that has no room either."""
     b = Batch(in_features, outs, groups)
-    plan = (lambda ta: L.lora_segments_plan_multi(b.pools, ta)) if len(b.pools) > 1 else lambda ta: L.lora_segments_plan(b.pools[0], ta)
+    def plan(ta):
+        return L.lora_segments_plan_multi(b.pools, ta) if len(b.pools) > 1 else L.lora_segments_plan(b.pools[0], ta)
+
     seg = plan(b.ta)
     need = L.lora_segments_table_bytes(seg)
     L.lora_segments_destroy(seg)
