@@ -1553,6 +1553,21 @@ try {
 }
 API_CATCH
 
+// Token-heavy shrink units of P projections, their lists one after the other: in rows of 8 in turn, so that the P units of
+// one tile of tokens run on one XCD at about the same time and share its rows of x through that L2.  With one list behind the
+// other every projection brought x in anew: 12,552 tokens of 16 prompts at 4096 features, whole layers (q|k|v, o, gate|up,
+// down) 733 -> 709 us each; 4,416 tokens of 6 prompts 356 -> 348; beside 384 decode tokens 597 -> 590.
+static void interleave_heavy_units(std::vector<Unit> &units, size_t P)
+{
+    const size_t per = units.size() / P;
+    if (P < 2 || per * P != units.size() || per % kXcds) return;  // lists too short to be ordered by XCD
+    std::vector<Unit> out;
+    out.reserve(units.size());
+    for (size_t row = 0; row < per; row += kXcds)
+        for (size_t q = 0; q < P; ++q) out.insert(out.end(), units.begin() + q * per + row, units.begin() + q * per + row + kXcds);
+    units.swap(out);
+}
+
 // Plans every projection on its own, then strings the unit lists together.
 static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const lora_pool *> &pools,
                                      const int32_t *ta, int32_t T, bool lean = false)
@@ -1625,6 +1640,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         weight_bytes += tmp->weight_bytes;
     }
     if (st != LORA_OK) return st;
+    interleave_heavy_units(sg->prefill_units, pools.size());
     sg->out_total = col;
     sg->v_floats = v_one * (int64_t)pools.size();
     sg->n_sync = sync_one * (int)pools.size();

@@ -555,6 +555,33 @@ def test_token_heavy_shrink_units_of_an_adapter_share_an_xcd_at_equal_cost():
     L.lora_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("n_prompts,projections", [(1, 2), (5, 2), (12, 3)])
+def test_token_heavy_units_of_several_projections_come_in_rows_of_eight_in_turn(n_prompts, projections):
+    """Several projections in one object: the token-heavy shrink units of one tile of tokens, one per projection, take
+    neighbouring rows of 8 of the launch at one residue mod 8 (one XCD), each projection's units in the order of its own plan."""
+    ranks = np.array([8, 16, 32, 64, 128, 200] * 2, dtype=np.int32)
+    scales = (2.0 / ranks).astype(np.float32)
+    outs = (512, 128, 256)[:projections]
+    pools, addr = [], FAKE_ARENA
+    for o in outs:
+        n = L.lora_pool_bytes(2048, o, ranks, scales)
+        pools.append(L.lora_pool_create(2048, o, ranks, scales, addr, n))
+        addr += (n + 4095) // 4096 * 4096
+        for a in range(len(ranks)):
+            L.lora_pool_mark_resident(pools[-1], a)
+    ta = np.concatenate([np.full(1100 if n_prompts == 1 else 190 + 37 * a, a, dtype=np.int32) for a in range(n_prompts)])
+    multi, single = L.lora_segments_plan_multi(pools, ta), L.lora_segments_plan(pools[0], ta)
+    mu, su = (L.lora_segments_export_units(s)["shrink"] for s in (multi, single))
+    assert len(mu) == projections * len(su) and len(su) % 8 == 0 and len(su) >= 16
+    rows = mu.reshape(len(su) // 8, projections, 8, 6)
+    for q in range(projections):
+        assert np.array_equal(rows[:, q].reshape(-1, 6), su)
+    for s in (multi, single):
+        L.lora_segments_destroy(s)
+    for p in pools:
+        L.lora_pool_destroy(p)
+
+
 def test_token_heavy_units_above_rank_128():
     """Token-heavy groups above rank 128 are cut like the others: shrink units of 64 tokens up to rank 192
     and of 32 above, all rank rows each; expand units of up to 64 tokens (none of 16)."""
