@@ -132,6 +132,16 @@ static __device__ __forceinline__ void stores_done()
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// at most N of this wavefront's vector memory operations are still under way
+template <int N>
+static __device__ __forceinline__ void wait_vm()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 static __device__ __forceinline__ void st_through_u16x8(uint16_t *p, uint4 v)
 {
     uint64_t *q = reinterpret_cast<uint64_t *>(p);
@@ -1023,6 +1033,29 @@ static __device__ __forceinline__ void dma16_to_lds(const uint4 *gptr, const uin
                  "s_mov_b32 m0, %0"
                  : "=&s"(saved_m0)
                  : "v"(gptr), "s"(lds_addr)
+                 : "memory");
+}
+
+// Two and four such copies, to consecutive KB from LDS address `to`, for a loop in which every instruction beside its matrix
+// instructions counts.  An instruction's offset is added to the address in memory and to the one in LDS, so M0 is set once:
+// copy q's source is given less q KB.
+static __device__ __forceinline__ void dma16x2_to_lds(const void *g0, const void *g1, uint32_t to)
+{
+    uint32_t saved_m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\t"
+                 "global_load_lds_dwordx4 %2, off offset:1024\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved_m0)
+                 : "v"(g0), "v"(g1), "s"(to)
+                 : "memory");
+}
+static __device__ __forceinline__ void dma16x4_to_lds(const void *g0, const void *g1, const void *g2, const void *g3, uint32_t to)
+{
+    uint32_t saved_m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\t"
+                 "global_load_lds_dwordx4 %2, off offset:1024\n\tglobal_load_lds_dwordx4 %3, off offset:2048\n\t"
+                 "global_load_lds_dwordx4 %4, off offset:3072\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved_m0)
+                 : "v"(g0), "v"(g1), "v"(g2), "v"(g3), "s"(to)
                  : "memory");
 }
 
@@ -1973,26 +2006,34 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const float *__restrict__
 //     row block, and y leaves in 16-byte pieces.  (A compute unit takes about 50 GB/s from the L2s
 //     whatever it runs; a 256 x 128 tile draws 48 KB per 64 of k and sat exactly at that rate, 720 us for
 //     cfg2's 22.5 k x 4096 x 4096; two strips per tile share the 32 KB of x.)
-//   * Everything is copied by loads that write LDS directly, through a ring of five 32 KB slots (all of a
-//     compute unit's LDS), so no request passes through registers the compiler tracks and the waits are
-//     exact: every wavefront issues four copies per slot and waits until at most four are in flight.
-//     W comes packed in operand order (1 KB per wavefront operand, see launch_pack_weight), so a 32-wide
-//     k step of a strip is 8 KB of consecutive bytes.  x is gathered in operand order by the copy itself,
-//     in full cache lines: a copy takes 128 bytes (64 of k) of 8 rows (64 bytes of 16 rows took twice as
-//     long to arrive), so a slot holds, of x, one half of the tile's rows for a pair of k steps and, of
-//     W, one k step; pair j is computed from slots 2 j and 2 j + 1 while the copies of the next three
-//     slots are in flight, one barrier per pair.  Inside a 1 KB block of x, piece p of row r sits in
-//     slot 8 r + (p XOR r), so that the 8 lanes that read one piece of 8 rows meet 8 bank groups.
+//   * Everything is copied by loads that write LDS directly, through two rings that take all of a compute unit's LDS: x in
+//     three slots of 64 of k, W in four of 32.  No request passes through registers the compiler tracks, so the waits are
+//     exact.  W comes packed in operand order (1 KB per wavefront operand, see launch_pack_weight), so a 32-wide k step of a
+//     strip is 8 KB of consecutive bytes.  x is gathered in operand order by the copy itself, in full cache lines: a copy
+//     takes 128 bytes (64 of k) of 8 rows (64 bytes of 16 rows took twice as long to arrive).  Inside a 1 KB block of x, piece p
+//     of row r sits in slot 8 r + (p XOR r), so that the 8 lanes that read one piece of 8 rows meet 8 bank groups.
+//   * Per k step a compute unit's LDS hands out 96 KB and its matrix units work 1024 cycles: either alone takes about as long
+//     as the other, so they have to run beside each other.  The two wavefronts of a SIMD (one of each strip) therefore take
+//     turns: a k step is a phase that reads the step's 12 operands from LDS and requests copies, and a phase of its 32 MFMAs,
+//     with a barrier behind every phase and the second strip's wavefronts one phase behind, so that in every phase one
+//     wavefront of each SIMD multiplies while the other reads.  With all eight reading and then multiplying behind one barrier per
+//     pair of k steps the matrix units were busy half of the time, now two thirds; us for x W alone (19,675 tokens,
+//     before / now / the library's product): 4096 -> 4096 561 / 470 / 603, 1024 -> 4096 158 / 140 / 161, 8192 -> 8192 2227 /
+//     1860 / 1902; the adapted layer at 4096 -> 4096 623 / 543.  The reading phase is the longer one: every instruction in
+//     it counts (four copies behind one setting of M0 instead of four 2 %), and it holds four copies, not six and two (1.5 %),
+//     in front of the reads (1.5 %).  Phases of 16 MFMAs 4 - 6 % slower; copies requested between the MFMAs 4 %; raised wave
+//     priority for the MFMAs nothing.  Lines touched 4 to 16 pairs ahead, so that copies hit the L2: 1 to 5 % slower, the
+//     copies do not wait for memory.
 //   * Before the k loop, while its first copies are on their way, every wavefront starts its accumulators with
 //     (s v_hi + s v_lo) B_a of its rows' adapters: ceil(r8 / 32) more k steps (v rows, and B^T in the pool's
 //     operand order, the very pieces the expand kernels read; v was scaled before its split), B^T taken once
 //     for all row blocks of one adapter.
 // ------------------------------------------------------------------------------------------------
 constexpr int kLinThreads = 512;
-constexpr int kLinRing = 5;
-constexpr int kLinXBuf = (kLinTileM / 16) * 1024;       // bytes of x per slot: 128 rows x 128 bytes = 16 KB
+constexpr int kLinXRing = 3, kLinWRing = 4;
+constexpr int kLinXBuf = kLinTileM * 128;               // bytes of x per slot: 64 of k
 constexpr int kLinWBuf = 8 * 1024 * (kLinTileN / 128);  // bytes of W per slot: one k step of 2 strips, 8 KB each
-constexpr int kLinLds = kLinRing * (kLinXBuf + kLinWBuf);  // 160 KB, all of a compute unit's LDS: one work group per compute unit
+constexpr int kLinLds = kLinXRing * kLinXBuf + kLinWRing * kLinWBuf;  // 160 KB, all of a compute unit's LDS: one work group per compute unit
 static_assert(kLinTileM == 256 && kLinTileN == 256, "the wavefront roles below are written for 256 x 256");
 
 // v B_a of one piece for NB sub-blocks from b0 of the strip at column c0: rows outside the piece get zero.  NK
@@ -2074,44 +2115,40 @@ static __device__ __forceinline__ void linear_big_body(
     const bool has_strip = strip * 128 < out;    // out is a multiple of 128: the last tile may hold one strip
     const int n = lane & 15, kq = lane >> 4;
     const int m0 = mt * kLinTileM;
-    auto xbuf = [&](int which) __attribute__((always_inline)) { return lds + which * (kLinXBuf + kLinWBuf); };
-    auto wbuf = [&](int which) __attribute__((always_inline)) { return lds + which * (kLinXBuf + kLinWBuf) + kLinXBuf; };
-
     // Copies of x.  A copy takes 8 rows x 128 bytes (64 of k): full cache lines; with 64 bytes of 16 rows per
     // copy the same bytes took twice as long to arrive (0.57 against 0.33 us per 32 of k and compute unit
-    // in a kernel that only copies).  One ring slot ("half stage" h) therefore holds, of x, the 128 rows
-    // of row half h mod 2 for the 64 of k of pair h / 2, as 16 blocks of 1 KB; this wavefront fills blocks
-    // 2 wave and 2 wave + 1, its lane l the slot l of a block with piece (l mod 8) XOR (l / 8) of row l / 8,
-    // so that the 8 lanes that read one piece of 8 rows meet 8 different bank groups.
-    const uint16_t *xsrc[2][2];
+    // in a kernel that only copies).  A slot holds the tile's 256 rows as 32 blocks of 1 KB; this wavefront fills blocks
+    // 4 wave .. + 3, its lane l the slot l of a block with piece (l mod 8) XOR (l / 8) of row l / 8, so that the 8 lanes
+    // that read one piece of 8 rows meet 8 different bank groups.
+    char *const xring = lds, *const wring = lds + kLinXRing * kLinXBuf;
+    const uint16_t *xsrc[4];
     {
         const int r = lane >> 3, piece = (lane & 7) ^ r;
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int row = rows[m0 + 128 * hf + 8 * (2 * wave + j) + r];
-                xsrc[hf][j] = x + (int64_t)(row < 0 ? 0 : row) * ldx + 8 * piece;
-            }
+        for (int j = 0; j < 4; ++j) {
+            const int row = rows[m0 + 8 * (4 * wave + j) + r];
+            xsrc[j] = x + (int64_t)(row < 0 ? 0 : row) * ldx + 8 * piece - 512 * j;  // as dma16x4_to_lds takes it
+        }
     }
     // copies of W: k step h of a strip is 8 KB at wp + (strip * (in / 32) + h) * 4096 elements; the four
     // wavefronts of a strip copy two of its eight 1 KB pieces each.  (The wavefronts of a strip the matrix
     // does not have copy strip 0's pieces into their unused half: every wavefront then has the same
     // number of copies in flight, which the waits below count.)
-    const uint4 *wsrc = reinterpret_cast<const uint4 *>(wp + (size_t)(has_strip ? strip : 0) * (in / 32) * 4096);
+    const uint4 *wsrc = reinterpret_cast<const uint4 *>(wp + (size_t)(has_strip ? strip : 0) * (in / 32) * 4096) + 2 * rw * 64 + lane;
     const int w_half = (wave >> 2) * (kLinWBuf / 2);
-    auto issue = [&](int h, int which) __attribute__((always_inline)) {
-        const int hf = h & 1;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds);
+    const uint32_t x_end = lds0 + kLinXRing * kLinXBuf, w_end = lds0 + kLinLds;
+    uint32_t x_to = lds0 + 4 * wave * 1024, w_to = x_end + w_half + 2 * rw * 1024;  // where the next pair, the next k step goes
+    auto issue_x = [&]() __attribute__((always_inline)) {
+        dma16x4_to_lds(xsrc[0], xsrc[1], xsrc[2], xsrc[3], x_to);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            dma16_to_lds(reinterpret_cast<const uint4 *>((hf ? xsrc[1][j] : xsrc[0][j]) + (h >> 1) * 64),
-                         reinterpret_cast<const uint4 *>(xbuf(which) + (2 * wave + j) * 1024));
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int piece = 2 * rw + q;
-            dma16_to_lds(wsrc + (size_t)h * 512 + piece * 64 + lane,
-                         reinterpret_cast<const uint4 *>(wbuf(which) + w_half + piece * 1024));
-        }
+        for (int q = 0; q < 4; ++q) xsrc[q] += 64;
+        x_to = x_to + kLinXBuf >= x_end ? x_to - (kLinXRing - 1) * kLinXBuf : x_to + kLinXBuf;
+    };
+    auto issue_w = [&]() __attribute__((always_inline)) {
+        dma16x2_to_lds(wsrc, wsrc, w_to);  // the second KB lies behind the first in both places
+        wsrc += 512;
+        w_to = w_to + kLinWBuf >= w_end ? w_to - (kLinWRing - 1) * kLinWBuf : w_to + kLinWBuf;
     };
 
     f32x4 acc[4][8];
@@ -2120,13 +2157,12 @@ static __device__ __forceinline__ void linear_big_body(
 #pragma unroll
         for (int b = 0; b < 8; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Pair j (64 of k) is computed from half stages 2 j and 2 j + 1; while it is, the copies of 2 j + 2 ..
-    // 2 j + 4 are in flight (a ring of five slots, all of the LDS).  One barrier per pair.
-    const int nh = in / 32;   // half stages; in is a multiple of 64, so nh is even
-    static_assert(kLinRing == 5, "the schedule below is written for five slots");
-#pragma unroll
-    for (int h = 0; h < 3; ++h)
-        if (h < nh) issue(h, h);
+    const int np = in / 64;  // pairs of k steps
+    issue_x();
+    issue_w();
+    if (np > 1) issue_x();
+    issue_w();
+    if (np > 1) issue_w();
     // ---- the delta, while the first copies are on their way: the accumulators start with it ----
     const int c0 = strip * 128;
     if (has_strip) {
@@ -2210,47 +2246,70 @@ static __device__ __forceinline__ void linear_big_body(
     // conditions) to be outstanding still, and wait for them, and so for the copies, in every pass of the loop.
     stores_done();
 
-    // this wavefront's rows 64 rw .. 64 rw + 63 lie in row half rw / 2, blocks 8 (rw mod 2) .. + 7 of its 16
-    const int x_half = rw >> 1;
-    const int x_blk0 = 8 * (rw & 1);
-    for (int j = 0; 2 * j < nh; ++j) {
-        // half stages 2 j and 2 j + 1 have landed when at most the copies of 2 j + 2 are in flight (4 per half
-        // stage and wavefront)
+    // the end of a phase: every wavefront has come this far
+    auto phase_end = [&]() __attribute__((always_inline)) {
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (2 * j + 2 < nh)
-            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    };
+    // .. of a phase that read from LDS: what it read is in registers, and the slots may be written
+    auto operands_here = [&]() __attribute__((always_inline)) {
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        phase_end();
+    };
+    phase_end();
+    if (wave >= 4) phase_end();  // the second strip's wavefronts run one phase behind the first's
+    int xget = 0, wget = 0;      // ring places of the pair and the k step being computed, in bytes
+    const int xlane = (8 * rw + (n >> 3)) * 1024 + (n & 7) * 128;
+    bf16x8 xo[4], wo[8];
+    auto read = [&](int ks) __attribute__((always_inline)) {
+        // row 16 i + n of this wavefront's rows: block 8 rw + 2 i + n / 8, row n mod 8 of it, piece 4 ks + kq
+        const int p = ((4 * ks + kq) ^ (n & 7)) * 16;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xo[i] = as_bf16x8(*reinterpret_cast<const uint4 *>(xring + xget + xlane + p + 2048 * i));
+#pragma unroll
+        for (int b = 0; b < 8; ++b) wo[b] = as_bf16x8(*reinterpret_cast<const uint4 *>(wring + wget + w_half + (b * 64 + lane) * 16));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto compute = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[i], wo[b], acc[i][b], 0, 0, 0);
+        phase_end();
+    };
+    for (int j = 0; j < np; ++j) {
+        if (j + 2 < np) issue_x();
+        read(0);
+        // W of step 2 j + 1 has landed: behind it were requested W of step 2 j + 2 and x of pair j + 2
+        if (j + 2 < np)
+            wait_vm<6>();
+        else if (j + 1 < np)
+            wait_vm<2>();
         else
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        // everyone's copies have landed, and everyone has left the slots of pair j - 1, which the copies of
-        // half stages 2 j + 3 and 2 j + 4 now fill
-        __syncthreads();
-        if (2 * j + 3 < nh) issue(2 * j + 3, (2 * j + 3) % kLinRing);
-        if (2 * j + 4 < nh) issue(2 * j + 4, (2 * j + 4) % kLinRing);
-        if (has_strip) {
-            const char *xcur = xbuf((2 * j + x_half) % kLinRing);
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const char *wcur = wbuf((2 * j + ks) % kLinRing) + w_half;
-                bf16x8 xo[4], wo[8];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    // row 16 i + n of this wavefront's rows: block x_blk0 + 2 i + n / 8, row n mod 8 of it, piece 4 ks + kq
-                    const int r = n & 7, p = 4 * ks + kq;
-                    xo[i] = as_bf16x8(*reinterpret_cast<const uint4 *>(
-                        xcur + (x_blk0 + 2 * i + (n >> 3)) * 1024 + (r * 8 + (p ^ r)) * 16));
-                }
-#pragma unroll
-                for (int b = 0; b < 8; ++b)
-                    wo[b] = as_bf16x8(*reinterpret_cast<const uint4 *>(wcur + (b * 64 + lane) * 16));
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int b = 0; b < 8; ++b)
-                        acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[i], wo[b], acc[i][b], 0, 0, 0);
-            }
-        }
+            wait_vm<0>();
+        operands_here();
+        compute();
+        wget = wget == (kLinWRing - 1) * kLinWBuf ? 0 : wget + kLinWBuf;
+        if (j + 1 < np) issue_w();
+        if (j + 2 < np) issue_w();
+        read(1);
+        // x of pair j + 1 and W of step 2 j + 2 have landed: behind them x of pair j + 2, W of steps 2 j + 3 and 2 j + 4
+        if (j + 2 < np)
+            wait_vm<8>();
+        else if (j + 1 < np)
+            wait_vm<2>();
+        operands_here();
+        compute();
+        wget = wget == (kLinWRing - 1) * kLinWBuf ? 0 : wget + kLinWBuf;
+        xget = xget == (kLinXRing - 1) * kLinXBuf ? 0 : xget + kLinXBuf;
     }
+    if (wave < 4) phase_end();
     if (!has_strip) return;
 
 #pragma unroll

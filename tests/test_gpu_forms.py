@@ -222,6 +222,15 @@ def test_linear_large_and_small_tiles_together(case):
     _linear_case(_batch(128, out_features, groups, idle=idle, seed=5), 0.02, seed=6)
 
 
+@pytest.mark.parametrize("in_features", [64, 128, 192, 256, 320, 512])
+def test_linear_large_tiles_from_one_pair_of_k_steps_on(in_features):
+    """Large tiles (one strip in the last column tile, rows left over) of 1 to 8 pairs of k steps: fewer than the copies'
+    rings hold, as many, and beyond the first turn of both."""
+    groups = [(700, 128), (513, 8), (300, 40), (291, 200)]
+    b = _batch(in_features, 4224, groups, seed=in_features)
+    _linear_case(b, 0.02, seed=7, rows=np.arange(0, b.T, 3, dtype=np.int32))
+
+
 @pytest.mark.parametrize("case", [c for c in LINEAR_ORDERS if c[3] or c[0] < 4096])
 def test_linear_row_orders(case):
     """Groups side by side or in blocks of 16 rows of their own, large tiles, small tiles and both: the orders the planner
