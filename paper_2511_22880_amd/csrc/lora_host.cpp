@@ -981,8 +981,8 @@ static void finish_decode_fused(lora_segments *sg, bool want, int in_features)
 
 // ---- the adapted layer's rows ----
 // What k_linear_lora is estimated to last, in us, with the first m row tiles (of 256 places) as large tiles of 256 columns and
-// the rows behind them as small ones of 64 x 64.  A large tile takes 5 us, 0.02 per input feature and 0.5 per 32-wide step of
-// the longest delta that one of its wavefronts starts with (`chain`); a small one 3 us, 0.0013 per input feature, 0.6
+// the rows behind them as small ones of 64 x 64.  A large tile takes 5 us, 0.016 per input feature and 0.5 per 32-wide step of
+// the longest delta that one of its wavefronts starts with (`chain`); a small one 3.3 us, 0.0014 per input feature, 0.8
 // per MB of x and W that the 32 work groups of an XCD walk through together, and 1.2 per 128 of rank that the busiest of
 // its wavefronts adds.  A work group takes a compute unit; an XCD takes every eighth row tile, and of its four groups of
 // eight compute units one takes every fourth column tile, so 9 row tiles of 256 columns (XCD 0: two) last as long as 16.
@@ -992,8 +992,8 @@ static double linear_us(int in, int out, int places, int m, int chain, double sm
     const int strips = places > m * lora::kLinTileM ? (places - m * lora::kLinTileM + 63) / 64 : 0;
     const double small = std::ceil(strips * (out / 64) / 8.0);  // per XCD
     const int side = std::min(std::max(strips, 1), 32);
-    const double big_us = 5.0 + 0.02 * in + 0.5 * chain;
-    const double small_us = 3.0 + 0.0013 * in + 0.6 * (side + 32.0 / side) * 64 * 2e-6 * in + 1.2 * small_pieces;
+    const double big_us = 5.0 + 0.016 * in + 0.5 * chain;
+    const double small_us = 3.3 + 0.0014 * in + 0.8 * (side + 32.0 / side) * 64 * 2e-6 * in + 1.2 * small_pieces;
     if (m == 0) return (small > 64 ? small / 32 : std::ceil(small / 32)) * small_us;
     const double rounds = (xcd_tiles + 7) / 8 * big_us;
     if (small == 0) return rounds;
@@ -1081,9 +1081,10 @@ static void try_linear_order(const lora_segments *sg, const int32_t *ta, int32_t
 // tokens, 56 groups below 16 of them, 72 / 112 / 53; 832 -> 8192, 1370 tokens, 17 such groups 99 / 63 / 51; 1280 -> 8192, 1648 tokens, 22 154 / 70 / 66;
 // 3584 -> 8192, 1510 tokens, 17 234 / 139 / 123; 768 -> 512, 10185 tokens 68 / 62 / 46; 5888 -> 8192, 644 tokens of 2
 // adapters 149 / 183 / -; 4096 -> 4096, 1024 tokens of few adapters 90 / 118 / -.  Large tiles for the rows that fill the
-// compute units and small ones behind them: 2176 -> 3072, 4512 tokens 207 / 138 / 136, 16 of 18 row tiles large 87.  Over 330
-// random batches with prompts 1.1 % from the best of the choices in the mean, 17 % at most.  (With a large tile at 5.5 small
-// ones whatever the size, no padding and compute units counted over the whole chip: 2.5 %, up to 60 %.)
+// compute units and small ones behind them: 2176 -> 3072, 4512 tokens 207 / 138 / 136, 16 of 18 row tiles large 87.  (All of
+// these with large tiles a seventh slower than they are.)  Over 110 random batches of 300 tokens and more 1.2 % from the best of the
+// choices in the mean, 11 % at most; with the figures that fitted the slower large tiles, 3.2 % and 48 % (8192 -> 3328, 1600
+// tokens 239 / 163).
 static void order_linear_rows(lora_segments *sg, const int32_t *ta, int32_t T, int in, int out, bool may_pad = true)
 {
     sg->lin_rows.clear();
