@@ -981,23 +981,26 @@ static void finish_decode_fused(lora_segments *sg, bool want, int in_features)
 
 // ---- the adapted layer's rows ----
 // What k_linear_lora is estimated to last, in us, with the first m row tiles (of 256 places) as large tiles of 256 columns and
-// the rows behind them as small ones of 64 x 64.  A large tile takes 5 us, 0.016 per input feature and 0.5 per 32-wide step of
-// the longest delta that one of its wavefronts starts with (`chain`); a small one 3.3 us, 0.0014 per input feature, 0.8
-// per MB of x and W that the 32 work groups of an XCD walk through together, and 1.2 per 128 of rank that the busiest of
-// its wavefronts adds.  A work group takes a compute unit; an XCD takes every eighth row tile, and of its four groups of
-// eight compute units one takes every fourth column tile, so 9 row tiles of 256 columns (XCD 0: two) last as long as 16.
-static double linear_us(int in, int out, int places, int m, int chain, double small_pieces)
+// the rows behind them as small ones of 64 x 64.  A large tile takes 5.8 us, 0.0145 per input feature and, for the delta that
+// its wavefronts start with, 0.6 per 32-wide step of the longest one (`chain`: the trip to memory) and 0.37 per step whose
+// 64 rows are all of them one adapter's (`cover`: v of every row, 64 KB per work group and step); a small one 4.15 us,
+// 0.0009 per input feature, 0.9 per MB of x and W that the 32 work groups of an XCD walk through together, and 0.78 per 128 of
+// rank that the busiest of its wavefronts adds.  A work group takes a compute unit; an XCD takes every eighth row tile, and of
+// its four groups of eight compute units one takes every fourth column tile, so 9 row tiles of 256 columns (XCD 0: two)
+// last as long as 16.  The figures are fitted together, so that the choice between the two is right; neither is a model of its
+// tile alone.
+static double linear_us(int in, int out, int places, int m, int chain, double cover, double small_pieces)
 {
     const int xcd_tiles = (m + 7) / 8 * (((out + lora::kLinTileN - 1) / lora::kLinTileN + 3) / 4);  // per 8 compute units
     const int strips = places > m * lora::kLinTileM ? (places - m * lora::kLinTileM + 63) / 64 : 0;
     const double small = std::ceil(strips * (out / 64) / 8.0);  // per XCD
     const int side = std::min(std::max(strips, 1), 32);
-    const double big_us = 5.0 + 0.016 * in + 0.5 * chain;
-    const double small_us = 3.3 + 0.0014 * in + 0.8 * (side + 32.0 / side) * 64 * 2e-6 * in + 1.2 * small_pieces;
+    const double big_us = 5.8 + 0.0145 * in + 0.6 * chain + 0.37 * cover;
+    const double small_us = 4.15 + 0.0009 * in + 0.9 * (side + 32.0 / side) * 64 * 2e-6 * in + 0.78 * small_pieces;
     if (m == 0) return (small > 64 ? small / 32 : std::ceil(small / 32)) * small_us;
     const double rounds = (xcd_tiles + 7) / 8 * big_us;
     if (small == 0) return rounds;
-    return std::max(rounds, (4 * xcd_tiles * big_us + small * small_us) / 32 + 0.5 * small_us) + 0.05 * small_us;
+    return std::max(rounds, (4 * xcd_tiles * big_us + small * small_us) / 32 + 0.5 * small_us) + 0.02 * small_us;
 }
 
 // groups of at least this many tokens go to the front
@@ -1045,6 +1048,7 @@ static void try_linear_order(const lora_segments *sg, const int32_t *ta, int32_t
     // per strip of 64 places: the longest chain of a large tile's wavefront, the busiest wavefront of a small tile
     const int strips = (o->places + 63) / 64, tiles = (o->places + lora::kLinTileM - 1) / lora::kLinTileM;
     std::vector<int> chain(strips, 0);
+    std::vector<double> cover(strips, 0.0);
     std::vector<double> small(strips + 1, 0.0);  // of this strip and all behind it
     size_t q = 0;
     for (int st = 0; st < strips; ++st) {
@@ -1059,15 +1063,20 @@ static void try_linear_order(const lora_segments *sg, const int32_t *ta, int32_t
                 if (!again) first[n_first++] = pc.b_off;
             }
             if (!again) chain[st] += (pc.r8 + 31) / 32;
+            cover[st] += (pc.r8 + 31) / 32 * pc.ntok / 64.0;
             load[n % 8] += (pc.r8 + 127) / 128;
         }
         small[st] = *std::max_element(load, load + 8);
     }
     for (int st = strips - 1; st >= 0; --st) small[st] += small[st + 1];
     int longest = 0;
+    double widest = 0;
     for (int m = 0; m <= tiles; ++m) {
-        for (int st = 4 * m - 4; st >= 0 && st < std::min(4 * m, strips); ++st) longest = std::max(longest, chain[st]);
-        const double us = linear_us(in, out, o->places, m, longest, 4 * m < strips ? small[4 * m] / (strips - 4 * m) : 0.0);
+        for (int st = 4 * m - 4; st >= 0 && st < std::min(4 * m, strips); ++st) {
+            longest = std::max(longest, chain[st]);
+            widest = std::max(widest, cover[st]);
+        }
+        const double us = linear_us(in, out, o->places, m, longest, widest, 4 * m < strips ? small[4 * m] / (strips - 4 * m) : 0.0);
         if (m == 0 || us < o->us) {
             o->us = us;
             o->big_tiles = m;
@@ -1077,14 +1086,16 @@ static void try_linear_order(const lora_segments *sg, const int32_t *ta, int32_t
 
 // Blocks of 16 places without padding between the groups are the least work; but where large tiles leave compute units
 // idle or the blocks hold many adapters, whose deltas a wavefront starts one after the other, every group may better have
-// blocks of its own.  us per layer, all 64 x 64 / all 256 x 256 without padding / all 256 x 256 with it: 1088 -> 8192, 707
-// tokens, 56 groups below 16 of them, 72 / 112 / 53; 832 -> 8192, 1370 tokens, 17 such groups 99 / 63 / 51; 1280 -> 8192, 1648 tokens, 22 154 / 70 / 66;
-// 3584 -> 8192, 1510 tokens, 17 234 / 139 / 123; 768 -> 512, 10185 tokens 68 / 62 / 46; 5888 -> 8192, 644 tokens of 2
-// adapters 149 / 183 / -; 4096 -> 4096, 1024 tokens of few adapters 90 / 118 / -.  Large tiles for the rows that fill the
-// compute units and small ones behind them: 2176 -> 3072, 4512 tokens 207 / 138 / 136, 16 of 18 row tiles large 87.  (All of
-// these with large tiles a seventh slower than they are.)  Over 110 random batches of 300 tokens and more 1.2 % from the best of the
-// choices in the mean, 11 % at most; with the figures that fitted the slower large tiles, 3.2 % and 48 % (8192 -> 3328, 1600
-// tokens 239 / 163).
+// blocks of its own.  us per layer, all 64 x 64 / all 256 x 256 without padding / all 256 x 256 with it: 1088 -> 8192, 704
+// tokens, 56 groups below 16 of them, 59 / 90 / 50; 832 -> 8192, 1347 tokens, 17 such groups 100 / 64 / 50; 1280 -> 8192, 1627
+// tokens, 22 145 / 68 / 60; 3584 -> 8192, 1487 tokens, 17 235 / 120 / 112; 768 -> 512, 10185 tokens of 4 adapters 61 / 39 / 39;
+// 8192 -> 3328, 1600 tokens of 4 218 / 159 / 159; 5888 -> 8192, 644 tokens of 2 135 / 150 / 148; 4096 -> 4096, 1024 tokens of 3
+// 79 / 83 / 82; short k and high ranks: 128 -> 512, 4560 rows, ranks 256, 40 and 128, 27 in small tiles, 33 in large ones; 192
+// -> 384, 4397 tokens of rank 256 29 and 34; 128 -> 1280, 841 tokens of ranks 128 and 8 14 and 20.  Large tiles for the rows that
+// fill the compute units and small ones behind them: 2176 -> 3072, 4512 tokens 202 / 100 / 99, 16 of 18 row tiles large 69.  Over
+// 3,900 random batches (64 .. 12,000 features, up to 20,000 tokens, ranks up to 256; 12 choices each) 0.6 % from the best in the mean,
+// 3.5 % for 95 in 100 of them and 23 % at most; without `cover` and with 5, 0.016, 0.5 / 3.3, 0.0014, 0.8, 1.2 it was 0.7 % and
+// 48 %, and 1 batch in 100 was more than 3 % slower than by the figures before those (5, 0.02, 0.5 / 3, 0.0013, 0.6, 1.2: 1.8 % and 69 %).
 static void order_linear_rows(lora_segments *sg, const int32_t *ta, int32_t T, int in, int out, bool may_pad = true)
 {
     sg->lin_rows.clear();
@@ -1097,7 +1108,7 @@ static void order_linear_rows(lora_segments *sg, const int32_t *ta, int32_t T, i
     try_linear_order(sg, ta, T, in, out, false, &best);
     bool aligned = true;
     for (const LinPiece &q : best.pieces) aligned &= q.place % 16 == 0;
-    if (may_pad && !aligned && 1.01 * linear_us(in, out, lora::kLinTileM, 1, 0, 0.0) < best.us) {
+    if (may_pad && !aligned && 1.01 * linear_us(in, out, lora::kLinTileM, 1, 0, 0.0, 0.0) < best.us) {
         LinearOrder padded;
         try_linear_order(sg, ta, T, in, out, true, &padded);
         if (padded.big_tiles > 0 && 1.01 * padded.us < best.us) std::swap(best, padded);

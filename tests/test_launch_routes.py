@@ -234,10 +234,16 @@ LINEAR_ORDERS = [
     (128, 4096, [(900, 16), (701, 128)] + [(n % 15 + 1, 8 * (n % 32) + 1) for n in range(40)], 100, True, 8, 10),
     (576, 3072, [(1128, 8)] * 4, 0, True, 16, 18),
     (2176, 3072, [(1128, 8)] * 4, 0, False, 16, 18),
+    # few row tiles, but a long k: 8192 -> 3328 was 218 us in small tiles, 159 in large ones
+    (8192, 3328, [(400, 8), (400, 16), (400, 64), (400, 128)], 0, False, 4, 7),
     # large tiles for all rows, not padded
     (128, 2048, [(9, 8 + n % 60) for n in range(700)], 10, False, 25, 25),
     # small tiles
     (4096, 4096, [(2, 64)] * 128, 0, False, 0, 1),
+    # short k and high ranks: v of whole wavefronts of rows is what a large tile starts with (27 us, in large tiles 33; 14, 20; 29, 34)
+    (128, 512, [(1843, 256), (725, 40), (1232, 128)], 760, False, 0, 18),
+    (128, 1280, [(500, 128), (341, 8)], 0, False, 0, 4),
+    (192, 384, [(4000, 256), (397, 256)], 0, False, 0, 18),
     (64, 128, [], 5, False, 0, 1),
 ]
 
