@@ -41,10 +41,11 @@ def build(verbose: bool = False, clocks: bool = False) -> str:
 
 
 def is_stale() -> bool:
+    """Whether a source, a header or the compile command (this file) is newer than the library, or there is none."""
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
+    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS + [os.path.abspath(__file__)])
 
 
 if __name__ == "__main__":

@@ -1,4 +1,6 @@
-"""Registers of the built kernels, from the metadata the compiler leaves in the library's code object."""
+"""Registers of the built kernels, from the metadata the compiler leaves in the library's code object; when it is out of date."""
+import os
+
 import msgpack
 import pytest
 
@@ -31,3 +33,13 @@ def test_spilled_registers(kernel, most):
     hits = [k for name, k in _kernels().items() if "4lora" in name and kernel in name]
     assert len(hits) == 1
     assert hits[0][".vgpr_spill_count"] <= most, hits[0][".vgpr_spill_count"]
+
+
+@pytest.mark.parametrize("newer", ["a source", "a header", "the compile command"])
+def test_a_library_older_than_what_it_is_built_from_is_stale(monkeypatch, newer):
+    path = {"a source": build.SOURCES[0], "a header": build.HEADERS[0], "the compile command": build.__file__}[newer]
+    times = {build.LIB: 2.0}
+    monkeypatch.setattr(os.path, "getmtime", lambda p: times.get(p, 1.0))
+    assert not build.is_stale()
+    times[os.path.abspath(path)] = 3.0
+    assert build.is_stale()
