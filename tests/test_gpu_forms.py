@@ -8,7 +8,7 @@ from paper_2511_22880_amd import workloads as wl
 
 import gpu_util as G
 from test_gpu_parity import _linear_case
-from test_launch_routes import LINEAR_ORDERS
+from test_launch_routes import LARGE_TILES, LARGE_TILES_MEETING, LARGE_TILES_PADDED, LINEAR_ORDERS
 
 pytestmark = pytest.mark.gpu
 
@@ -210,8 +210,8 @@ def test_linear_small_tiles(tokens, shape):
 
 
 @pytest.mark.parametrize("case", [
-    # large tiles alone, with a row tile and a strip that are not full and groups that meet inside a block
-    (4224, [(700, 128), (513, 8), (300, 40), (291, 200)], 0),
+    # large tiles alone, with a row tile and a strip that are not full
+    (LARGE_TILES[1][1], LARGE_TILES[1][2], 0),
     # large tiles, idle rows, and small tiles for the rest of the rows and the small groups
     (4096, [(900, 16), (701, 128)] + [(n % 15 + 1, 8 * (n % 32) + 1) for n in range(40)], 100),
     # nothing but small groups, far too many for small tiles alone
@@ -222,12 +222,12 @@ def test_linear_large_and_small_tiles_together(case):
     _linear_case(_batch(128, out_features, groups, idle=idle, seed=5), 0.02, seed=6)
 
 
-@pytest.mark.parametrize("in_features", [64, 128, 192, 256, 320, 512])
-def test_linear_large_tiles_from_one_pair_of_k_steps_on(in_features):
-    """Large tiles (one strip in the last column tile, rows left over) of 1 to 8 pairs of k steps: fewer than the copies'
-    rings hold, as many, and beyond the first turn of both."""
-    groups = [(700, 128), (513, 8), (300, 40), (291, 200)]
-    b = _batch(in_features, 4224, groups, seed=in_features)
+@pytest.mark.parametrize("in_features, out_features, groups", LARGE_TILES, ids=[c[0] for c in LARGE_TILES])
+def test_linear_large_tiles_from_one_pair_of_k_steps_on(in_features, out_features, groups):
+    """Large tiles (one strip in the last column tile, rows left over; that no row is in a small one is tested in
+    test_launch_routes.py) of 1 to 8 pairs of k steps: fewer than the copies' rings hold, as many, and beyond the first turn of
+    both."""
+    b = _batch(in_features, out_features, groups, seed=in_features)
     _linear_case(b, 0.02, seed=7, rows=np.arange(0, b.T, 3, dtype=np.int32))
 
 
@@ -240,9 +240,10 @@ def test_linear_row_orders(case):
 
 
 def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
-    """An adapter whose B holds infinities: its tokens are not finite, the neighbours in the same block of 16 rows are."""
+    """An adapter whose B holds infinities: its tokens are not finite, the neighbours in the same block of 16 rows are (small
+    tiles; large ones with every group in blocks of its own; large ones whose blocks hold two or three groups)."""
     for in_features, out_features, groups in ((128, 256, [(3, 16), (5, 40), (4, 8)]),
-                                              (64, 4096, [(1003, 16), (605, 40), (900, 8)])):
+                                              LARGE_TILES_PADDED, LARGE_TILES_MEETING):
         b = _batch(in_features, out_features, groups, seed=3)
         dp = G.DevicePool(b)
         A, B = b.adapter_bits(1)

@@ -261,6 +261,25 @@ def test_row_order_and_tiles_of_the_adapted_layer(recorder, case):
     b.close()
 
 
+# (in, out, groups) of which every row is in a large tile: what test_gpu_forms.py checks the large tiles' copies, waits and
+# deltas with.  The last column tile of the first ones holds one strip; the last batch is the one whose groups meet in blocks of 16.
+LARGE_TILES = [(n, 4224, [(700, 128), (513, 8), (300, 40), (291, 200)]) for n in (64, 128, 192, 256, 320, 512)]
+LARGE_TILES_PADDED = (64, 4096, [(1003, 16), (605, 40), (900, 8)])
+LARGE_TILES_MEETING = (64, 2048, [(9, 8 + n % 60) for n in range(700)])
+
+
+@pytest.mark.parametrize("case", LARGE_TILES + [LARGE_TILES_PADDED, LARGE_TILES_MEETING])
+def test_batches_that_are_large_tiles_only(recorder, case):
+    in_features, out_features, groups = case
+    b = Batch(in_features, out_features, groups)
+    seg = b.build()
+    name, places, big = b.launches(recorder, seg, "linear")[-1]
+    assert name == "linear" and big == (places + 255) // 256
+    assert (places == len(b.ta)) == (case is LARGE_TILES_MEETING)
+    L.lora_segments_destroy(seg)
+    b.close()
+
+
 @pytest.mark.parametrize("in_features, outs, groups, call, faster, plainer", [
     (1088, 8192, LINEAR_ORDERS[0][2], "linear", 
      [("shrink_wide", 296), ("linear", 1315, 6)], [("shrink_wide", 296), ("linear", 584, 0)]),
