@@ -24,9 +24,12 @@ def build(verbose: bool = False, clocks: bool = False) -> str:
     cmd = [hipcc, "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
            # packed-FP32 instructions stay off in device code (the host pass does not know the flag)
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           # the first eight kernel arguments (the unit list among them) arrive in registers with the wavefront instead of by
-           # a load of its own, the first of a short launch's trips to memory: one launch pair of 57 decode tokens 12.40 ->
-           # 12.07 us, a decode layer stack 1075 -> 1065, lora_linear of 256 tokens 31.4 -> 31.0, the 32-layer decode step level
+           # Kernel arguments that arrive in registers with the wavefront instead of by a load, the first of a short launch's
+           # trips to memory: the first eight, or as many of them as fit 14 scalar registers and stand in front of a struct.
+           # That is six to eight (unit list, arena and x among them; k_linear_lora: up to the arena); the others are loaded as
+           # before.  Without and with it, us: one launch pair of 57 decode tokens 12.41 -> 12.04, one apply of 512 tokens 57.5 ->
+           # 57.1, a decode layer stack 1073 -> 1063, lora_linear of 256 tokens 31.3 -> 30.9 (two runs of one side differ by 0.2 %
+           # at most), the 32-layer decode step level.
            "-mllvm", "-amdgpu-kernarg-preload-count=8",
            "-Wall", "-Wextra", "-I" + os.path.join(ROOT, "include"), "-o", lib] + SOURCES
     if clocks:

@@ -27,12 +27,52 @@ def _kernels():
     ("k_shrink_mixedILb1E", 12),
     ("k_apply_fusedE", 0),
     ("k_decode_fusedE", 0),
+    # 254 of 256 registers; its waits count memory operations, and a spill's are among them
+    ("k_linear_loraE", 0),
 ])
 def test_spilled_registers(kernel, most):
     """A register spilled in a unit's k loop is a trip to memory in every pass of it."""
     hits = [k for name, k in _kernels().items() if "4lora" in name and kernel in name]
     assert len(hits) == 1
     assert hits[0][".vgpr_spill_count"] <= most, hits[0][".vgpr_spill_count"]
+
+
+def _preloaded():
+    """{kernel symbol: scalar registers of arguments that are there when a wavefront starts} from the kernel descriptors."""
+    data, found, at = open(build.LIB, "rb").read(), {}, 0
+    num = lambda at, size: int.from_bytes(data[at:at + size], "little")
+    while (at := data.find(b"\x7fELF", at)) >= 0:
+        if num(at + 18, 2) == 224:  # EM_AMDGPU
+            sections = [at + num(at + 40, 8) + k * num(at + 58, 2) for k in range(num(at + 60, 2))]
+            for sec in sections:
+                if num(sec + 4, 4) != 11:  # SHT_DYNSYM
+                    continue
+                names = at + num(sections[num(sec + 40, 4)] + 24, 8)
+                for sym in range(at + num(sec + 24, 8), at + num(sec + 24, 8) + num(sec + 32, 8), 24):
+                    name = data[names + num(sym, 4):data.index(b"\0", names + num(sym, 4))].decode()
+                    if name.endswith(".kd"):
+                        home = sections[num(sym + 6, 2)]
+                        kd = at + num(home + 24, 8) + num(sym + 8, 8) - num(home + 16, 8)
+                        found[name[:-3]] = num(kd + 58, 2) & 127
+        at += 4
+    return found
+
+
+@pytest.mark.parametrize("kernel, dwords", [
+    # pointers and 64-bit strides take two; an argument that no longer fits the 14 ends the list, as does a struct
+    ("k_decode_fusedE", 14),
+    ("k_shrinkE", 13),
+    ("k_shrink_wideILi8E", 14),
+    ("k_expandILb0ELb0E", 12),
+    ("k_apply_fusedE", 14),
+    ("k_shrink_prefillE", 14),
+    ("k_linear_smallILi4ELi4ELi2E", 14),
+    ("k_linear_loraE", 12),
+])
+def test_arguments_that_arrive_in_registers(kernel, dwords):
+    """The unit list, the arena and x (k_linear_lora: the rows, the pieces and the arena) need no load of their own."""
+    hits = [n for name, n in _preloaded().items() if "4lora" in name and kernel in name]
+    assert hits == [dwords]
 
 
 @pytest.mark.parametrize("newer", ["a source", "a header", "the compile command"])
