@@ -289,9 +289,10 @@ lora_status_t lora_segments_export(const lora_segments_t *seg, int32_t *perm, in
  * The order is the launch order: the decode shrink units of one group take places of one residue
  * mod 8 where the counts allow it (the launch's work groups go to the chip's 8 XCDs in turn, and the
  * group's rows of x then stay in one XCD's L2); the token-heavy shrink units of one adapter likewise
- * (its A^T then enters one L2), the eight lists filled to equal bytes and the shorter ones padded at
- * their end with places that hold no work: segment -1, token count 0 (several projections: these lists
- * in rows of 8 in turn, every other list whole, one projection after the other); the 64-token expand units (listed after the others)
+ * where a projection has 16 or more of them (its A^T then enters one L2), the eight lists filled to equal
+ * bytes and the shorter ones padded at their end with places that hold no work: segment -1, token count 0
+ * (several projections: these padded lists in rows of 8 in turn; shorter and all other lists whole, one
+ * projection after the other); the 64-token expand units (listed after the others)
  * of one group (its columns in 4 runs, 8 to 64 in a launch of few such units) come in rows of 8, each
  * column run of 4 with 2 consecutive token tiles and those of a multiple of 8 on one XCD each, so that a column
  * run's part of B^T is fetched by that many XCDs instead of all 8.  Either output may be NULL. */

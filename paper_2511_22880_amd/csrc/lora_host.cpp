@@ -1567,8 +1567,8 @@ API_CATCH
 
 // Token-heavy shrink units of P projections, their lists one after the other: in rows of 8 in turn, so that the P units of
 // one tile of tokens run on one XCD at about the same time and share its rows of x through that L2.  With one list behind the
-// other every projection brought x in anew: 12,552 tokens of 16 prompts at 4096 features, whole layers (q|k|v, o, gate|up,
-// down) 733 -> 709 us each; 4,416 tokens of 6 prompts 356 -> 348; beside 384 decode tokens 597 -> 590.
+// other every projection brought x in anew; whole layers (q|k|v, o, gate|up, down; 4096 features, 14336 in the MLP), us each:
+// 13,966 tokens of 16 prompts 799 -> 774, 4,829 of 6 346 -> 337, 8 prompts beside 384 decode tokens (6,624 in all) 586 -> 576.
 static void interleave_heavy_units(std::vector<Unit> &units, size_t P)
 {
     const size_t per = units.size() / P;

@@ -2017,7 +2017,7 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const float *__restrict__
 //     turns: a k step is a phase that reads the step's 12 operands from LDS and requests copies, and a phase of its 32 MFMAs,
 //     with a barrier behind every phase and the second strip's wavefronts one phase behind, so that in every phase one
 //     wavefront of each SIMD multiplies while the other reads.  With all eight reading and then multiplying behind one barrier per
-//     pair of k steps the matrix units were busy half of the time, now two thirds; us for x W alone (19,675 tokens,
+//     pair of k steps the matrix units were busy half of the time, now 73 %; us for x W alone (19,675 tokens,
 //     before / now / the library's product): 4096 -> 4096 561 / 470 / 603, 1024 -> 4096 158 / 140 / 161, 8192 -> 8192 2227 /
 //     1860 / 1902; the adapted layer at 4096 -> 4096 623 / 543.  The reading phase is the longer one: every instruction in
 //     it counts (four copies behind one setting of M0 instead of four 2 %), and it holds four copies, not six and two (1.5 %),
@@ -2112,7 +2112,11 @@ static __device__ __forceinline__ void linear_big_body(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rw = wave & 3;                     // rows 64 rw .. 64 rw + 63 of the tile
     const int strip = 2 * nt + (wave >> 2);      // this wavefront's 128-column strip
-    const bool has_strip = strip * 128 < out;    // out is a multiple of 128: the last tile may hold one strip
+    // out is a multiple of 128: the last tile may hold one strip.  The four wavefronts without one take part in everything
+    // up to the epilogue, so that copies and barriers count alike, and multiply strip 0's W for nothing; with all eight behind one
+    // barrier per pair of k steps they left that out, and the tile was slower still: 19,664 tokens at 4096 -> 384 169 -> 148 us,
+    // 8,000 at 4096 -> 640 123 -> 101, at 256 -> 384 27.6 -> 25.9.
+    const bool has_strip = strip * 128 < out;
     const int n = lane & 15, kq = lane >> 4;
     const int m0 = mt * kLinTileM;
     // Copies of x.  A copy takes 8 rows x 128 bytes (64 of k): full cache lines; with 64 bytes of 16 rows per
@@ -2340,8 +2344,8 @@ static __device__ __forceinline__ void linear_big_body(
 // (128 bytes of 8 rows per load) that pass through a private LDS region to become operands; D pieces of both
 // are in flight per wavefront (registers).  The delta of the tile's adapters is dealt to the wavefronts piece
 // by piece and added to their partial sums; these meet in LDS and are added in wavefront order.
-// 256 tokens of 69 adapters at 4096 -> 4096: 109 us per layer with 256 x 256 tiles, 31 us (the shrink launch, 8 us,
-// included; 19 us for x W alone).  What bounds it is what a compute unit draws: 0.5 MB of W and 0.5 MB of x per
+// 256 tokens of 62 adapters at 4096 -> 4096: 84 us per layer with 256 x 256 tiles and every group in blocks of its own (138
+// without), 31 us here (the shrink launch, 8 us, included; 19 us for x W alone).  What bounds it is what a compute unit draws: 0.5 MB of W and 0.5 MB of x per
 // 64 x 64 tile at 60 - 70 GB/s.
 // ------------------------------------------------------------------------------------------------
 constexpr int kLinSmallWaves = kLinThreads / 64;
@@ -2823,9 +2827,9 @@ hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n
     if (m_big < 0) return hipErrorInvalidValue;
     if (m_big == 0) {
         // small tiles only: the largest that still make a work group per compute unit.  4096 -> 4096, us per layer
-        // of tokens without adapter, tiles of 64 x 64 / 32 x 64 / 32 x 32 / 16 x 32: 16 tokens 14.4 / 11.5 / 9.4 /
-        // 8.3, 64 tokens 17.4 / 13.1 / 10.8 / 14.2, 128 tokens 18.2 / 14.2, 256 tokens 19.0 / 24.1, 512 tokens
-        // 34.9 / 46.6 (256 x 256 tiles: 95 for each of them).
+        // of tokens without adapter (eight weights in rotation), tiles of 64 x 64 / 32 x 64 / 32 x 32 / 16 x 32: 16 tokens 14.8 /
+        // 12.0 / 9.4 / 8.5, 64 tokens 17.7 / 13.1 / 10.8 / 13.0, 128 tokens 18.7 / 14.2 / 18.2 / 23.8, 256 tokens 19.4 / 23.1, 512
+        // tokens 36.2 / 48.0 (256 x 256 tiles: 65 to 69 for each of them).
         auto tiles = [&](int rb, int cb) { return (int64_t)((n_places + 16 * rb - 1) / (16 * rb)) * (out / (16 * cb)); };
         auto fits = [&](int rb, int cb) { return (n_places + 15) / 16 >= rb && tiles(rb, cb) >= kComputeUnits; };
         auto go = [&](auto rb, auto cb, auto d) {
