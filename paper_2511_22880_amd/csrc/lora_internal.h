@@ -142,7 +142,7 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_
                                hipStream_t stream);
 
 // Both halves in one launch (shrink units first); the expand units poll `ready` of their token tile,
-// at most spin_limit times each.
+// at most spin_limit times each, and add the k-slices of `parts` up.
 hipError_t launch_apply_fused(const LaunchCtx &shrink, const LaunchCtx &expand, const uint16_t *x, int64_t ldx,
                               int k_slice_len, float *parts, int n_slices, int64_t slice_stride, uint16_t *y,
                               int64_t ldy, const SyncArgs *sync, hipStream_t stream);

@@ -74,20 +74,24 @@ static __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __
 // are not coherent with each other, and a device-scope fence (write back / invalidate a whole L2)
 // costs far more than the data is worth.  So the partial sums of v never live in a cache: they are
 // stored and loaded with device-scope relaxed atomics (64 bits at a time), which go through to
-// memory.  A shrink work group waits until its stores have completed, then bumps the arrival counter
-// of its (group, token tile); the one whose bump completes the tile's count for this launch adds the
-// slices up, sets the arrival counter back to zero (a launch leaves the table as it found it, so a
-// launch replayed from a captured graph finds what the first one found) and bumps the tile's ready
-// counter.  Only the single-launch form reads the ready counters: an expand work group polls its
-// tile's until it has reached epoch, the number of such launches the table has seen (they only
-// grow, so nothing is cleared between launches).  The wait is bounded: at the limit
+// memory.  A shrink work group waits until its stores have completed, then bumps a counter of its
+// (group, token tile).  In launches of their own (k_shrink, k_shrink_mixed) that is the arrival counter: the
+// work group whose bump completes the tile's count adds the slices up and sets the counter back to
+// zero (a launch leaves the table as it found it, so a launch replayed from a captured graph finds
+// what the first one found).  In the single-launch form it is the ready counter, and the expand work groups
+// add the slices up themselves, each for its own tokens, behind a wait for all of the tile's bumps: one
+// trip of v through memory instead of three (partial sums out and in, the complete v out and in, with a
+// counter behind either), and the additions are few.  Calls one after the other, us: one token of rank 16, 4096 -> 4096,
+// 6.7 -> 5.8; three tokens of ranks 8 to 32, 8192 -> 8192, 9.7 -> 8.4; 60 tokens of four adapters of rank 16, 4096 -> 4096, 9.2 -> 8.1.
+// The ready counters only grow (the target is epoch, the number of such launches the table has seen, times
+// the tile's units), so nothing is cleared between launches.  The wait is bounded: at the limit
 // the work group records it in *timeout_flag and goes on, so every wavefront reaches its end.
 // Shrink units come first in the grid and never wait, and work groups are dispatched in grid order,
 // so a waiting expand unit never keeps a shrink unit from running.
 // ------------------------------------------------------------------------------------------------
 struct Sync {
     unsigned *counters;       // arrivals, one per (group, token tile); NULL = no hand-over through counters
-    unsigned *ready;          // one per tile: bumped once per single-launch apply when the tile's v is complete
+    unsigned *ready;          // one per tile: bumped by every shrink unit of a single-launch apply
     unsigned *timeout_flag;
     uint16_t *v_hi;           // complete v as two bf16 terms, same indexing as the fp32 partial sums
     uint16_t *v_lo;
@@ -95,6 +99,10 @@ struct Sync {
     unsigned spin_limit;
     int wait;                 // expand units poll `ready` (single launch) or not (expand launched after shrink)
     int scale_v;              // shrink: v_hi / v_lo receive s_a v, not v
+    // single launch: the k-slices' partial sums of v, which the expand units add up
+    const float *parts;
+    int n_slices;
+    int64_t slice_stride;
 };
 
 static __device__ __forceinline__ void st_through_f32x4(float *p, f32x4 v)
@@ -157,12 +165,13 @@ static __device__ __forceinline__ uint4 ld_through_u16x8(const uint16_t *p)
     return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
 }
 
-static __device__ __forceinline__ void wait_for(const Sync &sy, int idx)
+// until the tile's n shrink units of this launch have stored their part of v
+static __device__ __forceinline__ void wait_for(const Sync &sy, int idx, int n)
 {
     if (threadIdx.x == 0) {
-        const unsigned target = sy.epoch;
+        const unsigned target = sy.epoch * (unsigned)n;
         unsigned spins = 0;
-        while (__hip_atomic_load(sy.ready + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        while ((int)(__hip_atomic_load(sy.ready + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
             if (++spins > sy.spin_limit) {
                 atomicOr(sy.timeout_flag, 1u);
                 break;
@@ -309,9 +318,13 @@ static __device__ __forceinline__ void shrink_body(const Unit &u, const uint16_t
             st_through_f32x4(dst, t);
         }
         if (sy.counters) {
-            // count this unit in; the unit that completes its token tile adds the k-slices up and
-            // leaves the tile's v as bf16 hi + lo for the expand units
+            // count this unit in; in a launch of its own, the unit that completes its token tile adds the k-slices up
+            // and leaves the tile's v as bf16 hi + lo for the expand units
             stores_done();
+            if (sy.wait) {
+                if (lane == 0) atomicAdd(sy.ready + u.sync_idx, 1u);
+                return;
+            }
             unsigned old = 0;
             if (lane == 0) old = atomicAdd(sy.counters + u.sync_idx, 1u);
             old = __builtin_amdgcn_readfirstlane(old);
@@ -332,8 +345,6 @@ static __device__ __forceinline__ void shrink_body(const Unit &u, const uint16_t
                     st_through_u16x8(sy.v_hi + tile_off + 8 * task, ph);
                     st_through_u16x8(sy.v_lo + tile_off + 8 * task, pl);
                 }
-                stores_done();
-                if (sy.wait && lane == 0) atomicAdd(sy.ready + u.sync_idx, 1u);  // polled by the single-launch form only
             }
         }
     }
@@ -1241,7 +1252,7 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 if (c0 + s * kStrip < ncols) bk.yv[s] = ld16_stream(bk.e_y + c0 + s * kStrip);
             }
             // (single launch) y, and up to rank 128 the weights, are on their way while v is waited for
-            if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx);
+            if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx, u.sync_n);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 const bool ok = (n < bk.ntok) && j_ok[it];
@@ -1249,8 +1260,9 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 uint4 ph, pl;
                 if (!VF32) {
                     if (!BIG && sy.wait) {  // written earlier in this very launch: read through to memory
-                        ph = ld_through_u16x8(sy.v_hi + off);
-                        pl = ld_through_u16x8(sy.v_lo + off);
+                        f32x4 f0, f1;
+                        sum_slices(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
+                        split_bf16(f0, f1, ph, pl);
                     } else {
                         ph = ld16(sy.v_hi + off);
                         pl = ld16(sy.v_lo + off);
@@ -2675,9 +2687,9 @@ static Sync make_sync(const SyncArgs *a, int wait, int scale_v = 0)
 {
     Sync sy;
     if (!a) {
-        sy = Sync{nullptr, nullptr, nullptr, nullptr, nullptr, 0u, 0u, 0, scale_v};
+        sy = Sync{nullptr, nullptr, nullptr, nullptr, nullptr, 0u, 0u, 0, scale_v, nullptr, 0, 0};
     } else {
-        sy = Sync{a->counters, a->ready, a->timeout_flag, a->v_hi, a->v_lo, a->epoch, a->spin_limit, wait, scale_v};
+        sy = Sync{a->counters, a->ready, a->timeout_flag, a->v_hi, a->v_lo, a->epoch, a->spin_limit, wait, scale_v, nullptr, 0, 0};
     }
     return sy;
 }
@@ -2730,9 +2742,12 @@ hipError_t launch_apply_fused(const LaunchCtx &cs, const LaunchCtx &ce, const ui
 {
     const int total = cs.n_units + ce.n_units;
     if (total <= 0) return hipSuccess;
+    Sync sy = make_sync(sync, 1);
+    sy.parts = parts;
+    sy.n_slices = n_slices;
+    sy.slice_stride = slice_stride;
     hipLaunchKernelGGL(k_apply_fused, dim3(total), dim3(kThreads), 0, stream, cs.units, cs.n_units, ce.units,
-                       ce.perm, cs.arena, x, ldx, cs.in_features, k_slice_len, parts, n_slices, slice_stride, y, ldy,
-                       make_sync(sync, 1));
+                       ce.perm, cs.arena, x, ldx, cs.in_features, k_slice_len, parts, n_slices, slice_stride, y, ldy, sy);
     return hipGetLastError();
 }
 
