@@ -2316,6 +2316,11 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     sa.v_lo = (uint16_t *)((char *)workspace + apply_parts_bytes(sg) + apply_packed_bytes(sg));
     sa.epoch = msg->launches + 1;  // read by the single-launch form only, which also advances it
     sa.spin_limit = opt_spin_limit(sg);
+    if (!sg->wide) {  // decode-sized groups' v in k-slices: added up by their expand units (see the kernels)
+        sa.parts = parts;
+        sa.n_slices = nsl;
+        sa.slice_stride = stride;
+    }
     const lora::LaunchCtx cs = ctx_for(arena, in, out, sg, kShrink), cp = ctx_for(arena, in, out, sg, kPrefill),
                           ce = ctx_for(arena, in, out, sg, kExpand), cb = ctx_for(arena, in, out, sg, kExpandBig);
     if (ev[0]) HIP_TRY(hipEventRecord(ev[0], s));

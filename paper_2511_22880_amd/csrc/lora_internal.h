@@ -97,11 +97,16 @@ struct SyncArgs {
     uint16_t *v_lo;
     unsigned epoch;
     unsigned spin_limit;
+    // the k-slices' partial sums of v, which expand units of up to 16 tokens then add up themselves; NULL: the shrink launch
+    // completes v_hi and v_lo
+    const float *parts = nullptr;
+    int n_slices = 0;
+    int64_t slice_stride = 0;
 };
 
 // v_out[ks * slice_stride + ...] receives k-slice ks's partial sums (slice_stride = 0 when there is
-// a single slice).  With `sync`, the unit that completes a token tile also writes the tile's summed v
-// as bf16 hi + lo.
+// a single slice).  With `sync` and no sync->parts, the unit that completes a token tile also writes the tile's
+// summed v as bf16 hi + lo.
 hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *x, int64_t ldx, int k_slice_len, float *v_out,
                          int n_slices, int64_t slice_stride, const SyncArgs *sync, hipStream_t stream);
 
@@ -114,8 +119,8 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
                               int k_slice_len, int n_slices, float *v_f32, uint16_t *v_hi, uint16_t *v_lo,
                               hipStream_t stream);
 
-// Without `sync`: v_in is v itself, fp32 and complete.  With `sync`: v comes from sync->v_hi / v_lo (written by a
-// shrink launch of the same epoch), v_in is not read.
+// Without `sync`: v_in is v itself, fp32 and complete.  With `sync`: v comes from sync->v_hi / v_lo, or (units of up to
+// 16 tokens, sync->parts) from the k-slices there, written by a shrink launch of the same epoch, v_in is not read.
 // `big`: the list holds units of up to 64 tokens (token indices through perm).
 hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16_t *y, int64_t ldy, const SyncArgs *sync,
                          hipStream_t stream);
@@ -132,9 +137,9 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
                                  const SyncArgs *sync, hipStream_t stream);
 
 // A mixed batch's shrink in one launch: the token-heavy units of `heavy` (n_hi of them above rank 64),
-// then the k-slice units of `c`, which leave partial sums in `parts` and complete v through `sync` as
-// launch_shrink does.  Likewise the expand: the 64-token units of `big`, then the units of `c`; both
-// read v from sync->v_hi / v_lo.
+// then the k-slice units of `c`, which leave partial sums in `parts` and complete v through `sync` where
+// launch_shrink does.  Likewise the expand: the 64-token units of `big`, which read v from sync->v_hi / v_lo, then the
+// units of `c`, which add sync->parts up.
 hipError_t launch_shrink_mixed(const LaunchCtx &heavy, int n_hi, const LaunchCtx &c, const uint16_t *x, int64_t ldx,
                                int k_slice_len, float *parts, int n_slices, int64_t slice_stride,
                                const SyncArgs *sync, hipStream_t stream);

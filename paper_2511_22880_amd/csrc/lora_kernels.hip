@@ -74,15 +74,22 @@ static __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __
 // are not coherent with each other, and a device-scope fence (write back / invalidate a whole L2)
 // costs far more than the data is worth.  So the partial sums of v never live in a cache: they are
 // stored and loaded with device-scope relaxed atomics (64 bits at a time), which go through to
-// memory.  A shrink work group waits until its stores have completed, then bumps a counter of its
-// (group, token tile).  In launches of their own (k_shrink, k_shrink_mixed) that is the arrival counter: the
-// work group whose bump completes the tile's count adds the slices up and sets the counter back to
-// zero (a launch leaves the table as it found it, so a launch replayed from a captured graph finds
-// what the first one found).  In the single-launch form it is the ready counter, and the expand work groups
-// add the slices up themselves, each for its own tokens, behind a wait for all of the tile's bumps: one
-// trip of v through memory instead of three (partial sums out and in, the complete v out and in, with a
-// counter behind either), and the additions are few.  Calls one after the other, us: one token of rank 16, 4096 -> 4096,
-// 6.7 -> 5.8; three tokens of ranks 8 to 32, 8192 -> 8192, 9.7 -> 8.4; 60 tokens of four adapters of rank 16, 4096 -> 4096, 9.2 -> 8.1.
+// memory.  In the single-launch form a shrink work group waits until its stores have completed, then
+// bumps the ready counter of its (group, token tile), and the expand work groups add the k-slices up
+// themselves, each for its own tokens, behind a wait for all of the tile's bumps.  (With the shrink unit that
+// arrived last adding them up, v took three trips through memory, a counter behind each.  Calls one after the other, us: one
+// token of rank 16, 4096 -> 4096, 6.7 -> 5.8; three tokens of ranks 8 to 32, 8192 -> 8192, 9.7 -> 8.4; 60 tokens of four adapters
+// of rank 16, 4096 -> 4096, 9.2 -> 8.1.)
+// In launches of their own the expand units of up to 16 tokens (k_expand_parts, k_expand_mixed) add the slices up as well, and the
+// shrink units of k-slices leave plain stores and end: to wait for its stores, its counter and, in the last unit of a tile, for the
+// other slices held a work group's place for longer than its products took.  Calls one after the other, us, completed in the
+// shrink launch / added up in the expand launch: 16 tokens of 10 adapters, 4096 -> 4096, 10.2 / 7.5; 100 tokens of one of rank
+// 64 12.1 / 9.1; 16 tokens of rank 256, 16384 -> 16384, 23.0 / 17.4; 500 tokens of 100 adapters of rank 256, 4096 -> 4096 (6400
+// and 3200 units), 104.9 / 82.0; of 500 adapters of ranks 8 to 128 74.8 / 73.4.
+// Only lora_linear has the k-slices completed by the shrink launch (as bf16 hi + lo, which every column tile of it reads): a unit
+// bumps the arrival counter of its tile, the one whose bump completes the tile's count adds the slices up and sets the counter back
+// to zero (a launch leaves the table as it found it, so a launch replayed from a captured graph finds what the first one found).
+// Token-heavy units that are cut along k do the same (complete_tile).
 // The ready counters only grow (the target is epoch, the number of such launches the table has seen, times
 // the tile's units), so nothing is cleared between launches.  The wait is bounded: at the limit
 // the work group records it in *timeout_flag and goes on, so every wavefront reaches its end.
@@ -99,7 +106,7 @@ struct Sync {
     unsigned spin_limit;
     int wait;                 // expand units poll `ready` (single launch) or not (expand launched after shrink)
     int scale_v;              // shrink: v_hi / v_lo receive s_a v, not v
-    // single launch: the k-slices' partial sums of v, which the expand units add up
+    // the k-slices' partial sums of v, which the expand units add up (NULL: v_hi and v_lo are complete)
     const float *parts;
     int n_slices;
     int64_t slice_stride;
@@ -206,7 +213,9 @@ static __device__ __forceinline__ void split_bf16(f32x4 f0, f32x4 f1, uint4 &ph,
 
 constexpr int kMaxSlices = 4;  // upper bound of the shrink's k-slices
 
-// sum of the k-slices' partial sums of 8 consecutive v elements, in slice order
+// sum of the k-slices' partial sums of 8 consecutive v elements, in slice order.  EARLIER: of an earlier launch, else read
+// through to memory.
+template <bool EARLIER = false>
 static __device__ __forceinline__ void sum_slices(const float *__restrict__ src, int n_slices, int64_t slice_stride,
                                                   f32x4 &f0, f32x4 &f1)
 {
@@ -214,8 +223,8 @@ static __device__ __forceinline__ void sum_slices(const float *__restrict__ src,
 #pragma unroll
     for (int sl = 0; sl < kMaxSlices; ++sl) {
         const int64_t off = (int64_t)(sl < n_slices ? sl : 0) * slice_stride;
-        p0[sl] = ld_through_f32x4(src + off);
-        p1[sl] = ld_through_f32x4(src + off + 4);
+        p0[sl] = EARLIER ? *reinterpret_cast<const f32x4 *>(src + off) : ld_through_f32x4(src + off);
+        p1[sl] = EARLIER ? *reinterpret_cast<const f32x4 *>(src + off + 4) : ld_through_f32x4(src + off + 4);
     }
     f0 = p0[0];
     f1 = p1[0];
@@ -309,17 +318,21 @@ static __device__ __forceinline__ void shrink_body(const Unit &u, const uint16_t
     red[wave][lane] = acc;
     __syncthreads();
     if (wave == 0) {
+        const bool meets = sy.counters && (sy.wait || !sy.parts);  // other units of this launch wait for this one
         f32x4 t = red[0][lane];
         t += red[1][lane];
         t += red[2][lane];
         t += red[3][lane];
         if (x_ok && 4 * kq < pn) {
             float *dst = v_out + (int64_t)ks * slice_stride + u.v_off + (int64_t)i * u.r8 + 4 * kq;
-            st_through_f32x4(dst, t);
+            if (meets)
+                st_through_f32x4(dst, t);
+            else
+                *reinterpret_cast<f32x4 *>(dst) = t;
         }
-        if (sy.counters) {
-            // count this unit in; in a launch of its own, the unit that completes its token tile adds the k-slices up
-            // and leaves the tile's v as bf16 hi + lo for the expand units
+        if (meets) {
+            // count this unit in; where no expand unit adds the slices up, the unit that completes its token tile does and
+            // leaves the tile's v as bf16 hi + lo
             stores_done();
             if (sy.wait) {
                 if (lane == 0) atomicAdd(sy.ready + u.sync_idx, 1u);
@@ -1173,7 +1186,8 @@ static __device__ __forceinline__ void load_v_operand(const float *__restrict__ 
 
 // KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).  A unit may hold several blocks
 // of 16 tokens; the weights of a column pass stay in registers while the token blocks go by.
-template <int KSTEPS, bool BIG, bool VF32>
+// PARTS: v is the sum of the k-slices' partial sums (sy.parts) of the launch before.
+template <int KSTEPS, bool BIG, bool VF32, bool PARTS>
 static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t *__restrict__ perm,
                                                    const uint16_t *__restrict__ arena,
                                                    const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
@@ -1259,9 +1273,9 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 const int64_t off = u.v_off + (int64_t)(ok ? t0 + n : 0) * r8 + jc[it];
                 uint4 ph, pl;
                 if (!VF32) {
-                    if (!BIG && sy.wait) {  // written earlier in this very launch: read through to memory
+                    if (!BIG && (PARTS || sy.wait)) {
                         f32x4 f0, f1;
-                        sum_slices(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
+                        sum_slices<PARTS>(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
                         split_bf16(f0, f1, ph, pl);
                     } else {
                         ph = ld16(sy.v_hi + off);
@@ -1520,7 +1534,7 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
 #undef LORA_DMA_WAIT
 }
 
-template <bool BIG, bool VF32>
+template <bool BIG, bool VF32, bool PARTS = false>
 static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int32_t *__restrict__ perm,
                                                        const uint16_t *__restrict__ arena,
                                                        const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
@@ -1537,13 +1551,13 @@ static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int3
             expand_big_body<8, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
     } else {
         if (r8 <= 32)
-            expand_body<1, false, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<1, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 64)
-            expand_body<2, false, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<2, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 128)
-            expand_body<4, false, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<4, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
         else
-            expand_body<8, false, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<8, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
     }
 }
 
@@ -1934,6 +1948,16 @@ __global__ __launch_bounds__(kThreads, BIG ? 2 : 4) void k_expand(const Unit *__
     LORA_CLOCK_E(4);
 }
 
+// Units of up to 16 tokens whose v the launch before left as k-slices' partial sums.
+__global__ __launch_bounds__(kThreads, 4) void k_expand_parts(const Unit *__restrict__ units, const uint16_t *__restrict__ arena,
+                                                              uint16_t *__restrict__ y, int64_t ldy, Sync sy)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kExpandLds];
+    LORA_CLOCK_E(0);
+    expand_dispatch<false, false, true>(units[blockIdx.x], nullptr, arena, nullptr, y, ldy, lds, sy);
+    LORA_CLOCK_E(4);
+}
+
 // Both halves in one launch: blocks [0, n_shrink) are shrink units, the rest expand units that wait
 // for their tokens' v through the counters.
 __global__ __launch_bounds__(kThreads, 4) void k_apply_fused(const Unit *__restrict__ shrink_units, int n_shrink,
@@ -1991,7 +2015,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__rest
     if (b < n_big)
         expand_dispatch<true, false>(big_units[b], perm, arena, nullptr, y, ldy, lds, sy);
     else
-        expand_dispatch<false, false>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
+        expand_dispatch<false, false, true>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 
@@ -2689,7 +2713,8 @@ static Sync make_sync(const SyncArgs *a, int wait, int scale_v = 0)
     if (!a) {
         sy = Sync{nullptr, nullptr, nullptr, nullptr, nullptr, 0u, 0u, 0, scale_v, nullptr, 0, 0};
     } else {
-        sy = Sync{a->counters, a->ready, a->timeout_flag, a->v_hi, a->v_lo, a->epoch, a->spin_limit, wait, scale_v, nullptr, 0, 0};
+        sy = Sync{a->counters, a->ready, a->timeout_flag, a->v_hi, a->v_lo, a->epoch, a->spin_limit, wait, scale_v,
+                  a->parts, a->n_slices, a->slice_stride};
     }
     return sy;
 }
@@ -2725,7 +2750,9 @@ hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16
     if (!sync && !v_in) return hipErrorInvalidValue;
     const Sync sy = make_sync(sync, 0);
     const dim3 g(c.n_units), b(kThreads);
-    if (big && sync)
+    if (!big && sync && sync->parts)
+        hipLaunchKernelGGL(k_expand_parts, g, b, 0, stream, c.units, c.arena, y, ldy, sy);
+    else if (big && sync)
         hipLaunchKernelGGL((k_expand<true, false>), g, b, 0, stream, c.units, c.perm, c.arena, v_in, y, ldy, sy);
     else if (big)
         hipLaunchKernelGGL((k_expand<true, true>), g, b, 0, stream, c.units, c.perm, c.arena, v_in, y, ldy, sy);
@@ -2742,12 +2769,10 @@ hipError_t launch_apply_fused(const LaunchCtx &cs, const LaunchCtx &ce, const ui
 {
     const int total = cs.n_units + ce.n_units;
     if (total <= 0) return hipSuccess;
-    Sync sy = make_sync(sync, 1);
-    sy.parts = parts;
-    sy.n_slices = n_slices;
-    sy.slice_stride = slice_stride;
+    if (!sync || !sync->parts) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_apply_fused, dim3(total), dim3(kThreads), 0, stream, cs.units, cs.n_units, ce.units,
-                       ce.perm, cs.arena, x, ldx, cs.in_features, k_slice_len, parts, n_slices, slice_stride, y, ldy, sy);
+                       ce.perm, cs.arena, x, ldx, cs.in_features, k_slice_len, parts, n_slices, slice_stride, y, ldy,
+                       make_sync(sync, 1));
     return hipGetLastError();
 }
 
@@ -2822,7 +2847,7 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_
 {
     const int total = big.n_units + c.n_units;
     if (total <= 0) return hipSuccess;
-    if (!sync) return hipErrorInvalidValue;
+    if (!sync || !sync->parts) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_expand_mixed, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
                        c.perm, c.arena, y, ldy, make_sync(sync, 0));
     return hipGetLastError();

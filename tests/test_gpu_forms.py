@@ -262,6 +262,35 @@ def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
         dp.close()
 
 
+# ---- k-slice units: what the shrink launch leaves, the expand launch adds up -------------------------------------------
+@pytest.mark.parametrize("shape, groups", [
+    ((64, 128), [(1, 1), (17, 8)]),                                     # one slice
+    ((2048, 640), [(16, 24), (17, 33), (1, 256)]),                      # two
+    ((3968, 384), [(5, 129), (33, 64), (16, 8)]),                       # three, the last of them short
+    ((4096, 1152), [(1, 16)] * 24),                                     # four
+    ((4096, 256), [(40, 72), (1000, 16), (3, 136), (15, 255), (31, 8)]),  # beside token-heavy groups
+])
+def test_k_slices_added_up_by_the_expand_units(shape, groups):
+    """Every form of the batch gives the bits of every other, and the oracle's rows: two launches, one, four, replayed."""
+    b = _batch(*shape, groups, idle=3)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    x, ys = G.bits_to_dev(x_bits), []
+    for o in ({"fused_apply": 0}, {"fused_apply": 1}, {"merged_launches": 0, "fused_apply": 0}):
+        seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(whole_k_limit=0, heavy_k_cut_max_units=0, **o))
+        ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+        for _ in range(2):
+            y = G.bits_to_dev(y0)
+            L.lora_apply(dp.pool, seg, x, y, ws)
+            torch.cuda.synchronize()
+            ys.append(G.dev_to_bits(y))
+        L.lora_segments_check(seg)
+        L.lora_segments_destroy(seg)
+    assert all(np.array_equal(ys[0], other) for other in ys[1:])
+    G.check_all_rows(dp, x_bits, y0, ys[0])
+    dp.close()
+
+
 # ---- whole-k decode batches: one launch or two, by the units of both kinds --------------------------------------------
 @pytest.mark.parametrize("units, shape, one", [
     (64, (4096, 4096), False),
