@@ -2373,8 +2373,8 @@ static __device__ __forceinline__ void linear_big_body(
 // ------------------------------------------------------------------------------------------------
 // The same layer for batches of few tokens, where 256 x 256 tiles would leave most of the chip idle (256 tokens
 // x 4096 columns: 16 tiles) and the time is that of bringing W in once.  Tiles of 16 RB tokens x 16 CB columns
-// (CB sub-blocks of a 128-column strip), one work group each, whose 8 wavefronts split k: wavefront w takes
-// the 64-wide pieces w, w + 8, ... of k, so that what a work group has in flight lies side by side in memory.
+// (CB sub-blocks of a 128-column strip), one work group each, whose 8 (or 4) wavefronts split k: wavefront w takes
+// the 64-wide pieces w, w + 8 (w + 4), ... of k, so that what a work group has in flight lies side by side in memory.
 // No operand is shared between wavefronts, so there is no barrier in the loop and no LDS copy of W: a
 // wavefront's W operands come straight from memory in operand order (1 KB per load), its x as full cache lines
 // (128 bytes of 8 rows per load) that pass through a private LDS region to become operands; D pieces of both
@@ -2385,12 +2385,18 @@ static __device__ __forceinline__ void linear_big_body(
 // 64 x 64 tile at 60 - 70 GB/s.
 // ------------------------------------------------------------------------------------------------
 constexpr int kLinSmallWaves = kLinThreads / 64;
+// Where there are more tiles than compute units, a tile takes a work group of half as many wavefronts and two work groups share a
+// compute unit: what a tile waits for (its rows, the first operands, v and B^T, the sums) then passes beside another's products, and
+// there are no rounds.  k_linear_small -> k_linear_rounds, us per layer: 576 -> 8192, 208 tokens (512 tiles) 24.9 -> 19.2; 832 -> 4864, 544
+// tokens (688) 32.3 -> 27.9; 1728 -> 5120, 630 tokens (800) 49.0 -> 43.3; 8192 -> 2432, 1068 tokens (648) 109 -> 101; 32 x 64 tiles, 7168 -> 640,
+// 1428 tokens (456) 57.4 -> 55.2; 16 x 32, 1536 -> 2688, 81 tokens (504) 15.7 -> 14.6, 8192 -> 4224, 28 tokens (264) 34.9 -> 33.8.
+constexpr int kLinRoundsWaves = kLinSmallWaves / 2;
 
-template <int RB, int CB>
-constexpr int kLinSmallLds = kLinSmallWaves * 1024 * (2 * RB > RB * CB ? 2 * RB : RB * CB);  // x regions, then partial sums
+template <int RB, int CB, int WAVES>
+constexpr int kLinSmallLds = WAVES * 1024 * (2 * RB > RB * CB ? 2 * RB : RB * CB);  // x regions, then partial sums
 
 // Tile `blk` of those of the rows from place m_first on (a multiple of 256), m_tiles row tiles.
-template <int RB, int CB, int D>
+template <int RB, int CB, int D, int WAVES>
 static __device__ __forceinline__ void linear_small_body(
     int blk, int m_first, int m_tiles, const int32_t *__restrict__ rows, const int32_t *__restrict__ start,
     const LinPiece *__restrict__ pieces, const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp,
@@ -2425,7 +2431,7 @@ static __device__ __forceinline__ void linear_small_body(
         for (int b = 0; b < CB; ++b) acc[i][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int np = in >> 6;  // 64-wide pieces of k
-    const int mine = wave < np ? (np - 1 - wave) / kLinSmallWaves + 1 : 0;
+    const int mine = wave < np ? (np - 1 - wave) / WAVES + 1 : 0;
     if (mine > 0) {
         // x: lane -> row lane / 8 of the load's 8, 16-byte chunk lane mod 8; in the region chunk c of row r sits in
         // slot c XOR (r mod 8), so that neither the writes nor the operand reads meet in a bank
@@ -2446,11 +2452,11 @@ static __device__ __forceinline__ void linear_small_body(
         auto load_x = [&](int i, uint4(&xs)[NX]) __attribute__((always_inline)) {
             const bool ok = i < mine;
 #pragma unroll
-            for (int t = 0; t < NX; ++t) xs[t] = ld16(ok ? xrow[t] + (size_t)i * (64 * kLinSmallWaves) : x);
+            for (int t = 0; t < NX; ++t) xs[t] = ld16(ok ? xrow[t] + (size_t)i * (64 * WAVES) : x);
         };
         auto load_w = [&](int i, uint4(&ws)[2][CB]) __attribute__((always_inline)) {
             const bool ok = i < mine;
-            const uint16_t *at = ok ? wbase + (size_t)i * (2 * kLinSmallWaves) * 4096 : wbase;
+            const uint16_t *at = ok ? wbase + (size_t)i * (2 * WAVES) * 4096 : wbase;
             const unsigned off = ok ? lane8 : 0u;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
@@ -2508,7 +2514,7 @@ static __device__ __forceinline__ void linear_small_body(
     // ---- the delta: the tile's pieces in turn to the wavefronts ----
     {
         const int q_end = start[(m0 >> 4) + RB];
-        for (int q = start[m0 >> 4] + wave; q < q_end; q += kLinSmallWaves) {
+        for (int q = start[m0 >> 4] + wave; q < q_end; q += WAVES) {
             f32x4 dl[CB];
             lin_delta<CB, 4>(pieces[q], arena, (size_t)strip * 128, b0, n, kq, v_hi, v_lo, dl);
             const int at = (pieces[q].place - m0) >> 4;
@@ -2526,7 +2532,7 @@ static __device__ __forceinline__ void linear_small_body(
 #pragma unroll
         for (int b = 0; b < CB; ++b) red[wave][i * CB + b][lane] = acc[i][b];
     __syncthreads();
-    for (int o = tid; o < RB * 256; o += kLinThreads) {
+    for (int o = tid; o < RB * 256; o += 64 * WAVES) {
         // row 16 i + 4 kq + e of the tile, columns 8 n + b0 .. + CB - 1 of the strip
         const int i = o >> 8, l = (o >> 2) & 63, e = o & 3;
         const int row = rows[m0 + 16 * i + 4 * (l >> 4) + e];
@@ -2535,7 +2541,7 @@ static __device__ __forceinline__ void linear_small_body(
 #pragma unroll
         for (int b = 0; b < CB; ++b) f[b] = reinterpret_cast<const float *>(&red[0][i * CB + b][l])[e];
 #pragma unroll
-        for (int w = 1; w < kLinSmallWaves; ++w)
+        for (int w = 1; w < WAVES; ++w)
 #pragma unroll
             for (int b = 0; b < CB; ++b) f[b] += reinterpret_cast<const float *>(&red[w][i * CB + b][l])[e];
         uint32_t *dst = reinterpret_cast<uint32_t *>(y + (int64_t)row * ldy + strip * 128 + 8 * (l & 15) + b0);
@@ -2551,9 +2557,21 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_small(
     int in, int out, const uint16_t *__restrict__ v_hi, const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y,
     int64_t ldy)
 {
-    __shared__ __attribute__((aligned(16))) char lds[kLinSmallLds<RB, CB>];
-    linear_small_body<RB, CB, D>(blockIdx.x, 0, m_tiles, rows, start, pieces, arena, wp, x, ldx, in, out, v_hi, v_lo, y, ldy,
-                                 lds);
+    __shared__ __attribute__((aligned(16))) char lds[kLinSmallLds<RB, CB, kLinSmallWaves>];
+    linear_small_body<RB, CB, D, kLinSmallWaves>(blockIdx.x, 0, m_tiles, rows, start, pieces, arena, wp, x, ldx, in, out, v_hi,
+                                                 v_lo, y, ldy, lds);
+}
+
+template <int RB, int CB, int D>
+__global__ __launch_bounds__(64 * kLinRoundsWaves, 2) void k_linear_rounds(
+    const int32_t *__restrict__ rows, const int32_t *__restrict__ start, const LinPiece *__restrict__ pieces, int m_tiles,
+    const uint16_t *__restrict__ arena, const uint16_t *__restrict__ wp, const uint16_t *__restrict__ x, int64_t ldx,
+    int in, int out, const uint16_t *__restrict__ v_hi, const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y,
+    int64_t ldy)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kLinSmallLds<RB, CB, kLinRoundsWaves>];
+    linear_small_body<RB, CB, D, kLinRoundsWaves>(blockIdx.x, 0, m_tiles, rows, start, pieces, arena, wp, x, ldx, in, out, v_hi,
+                                                  v_lo, y, ldy, lds);
 }
 
 // The first n_big work groups take 256 x 256 tiles of the first m_big row tiles, the others 64 x 64 tiles of the
@@ -2565,10 +2583,10 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
     const uint16_t *__restrict__ v_lo, uint16_t *__restrict__ y, int64_t ldy)
 {
     __shared__ __attribute__((aligned(16))) char lds[kLinLds];
-    static_assert(kLinSmallLds<4, 4> <= kLinLds, "a small tile fits the LDS of a large one");
+    static_assert(kLinSmallLds<4, 4, kLinSmallWaves> <= kLinLds, "a small tile fits the LDS of a large one");
     if ((int)blockIdx.x >= n_big) {
-        linear_small_body<4, 4, 2>((int)blockIdx.x - n_big, m_big * kLinTileM, m_small, rows, start, pieces, arena, wp, x, ldx,
-                                   in, out, v_hi, v_lo, y, ldy, lds);
+        linear_small_body<4, 4, 2, kLinSmallWaves>((int)blockIdx.x - n_big, m_big * kLinTileM, m_small, rows, start, pieces, arena,
+                                                   wp, x, ldx, in, out, v_hi, v_lo, y, ldy, lds);
         return;
     }
     // Work group b runs on XCD b mod 8.  Each XCD takes a run of row tiles, and the 32 work groups it runs
@@ -2593,8 +2611,12 @@ static void launch_linear_small(const int32_t *rows, const int32_t *start, const
 {
     const int m_tiles = (n_places + 16 * RB - 1) / (16 * RB);
     const int grid = 8 * ((m_tiles * (out / (16 * CB)) + 7) / 8);  // an eighth of the tiles per XCD
-    hipLaunchKernelGGL((k_linear_small<RB, CB, D>), dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, start,
-                       pieces, m_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
+    if (grid > kComputeUnits)
+        hipLaunchKernelGGL((k_linear_rounds<RB, CB, D>), dim3((unsigned)grid), dim3(64 * kLinRoundsWaves), 0, stream, rows, start,
+                           pieces, m_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
+    else
+        hipLaunchKernelGGL((k_linear_small<RB, CB, D>), dim3((unsigned)grid), dim3(kLinThreads), 0, stream, rows, start,
+                           pieces, m_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
 }
 
 // W^T [out][in] row-major -> operand order (see launch_pack_weight).  One thread per destination element.

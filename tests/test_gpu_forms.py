@@ -222,6 +222,17 @@ def test_linear_large_and_small_tiles_together(case):
     _linear_case(_batch(128, out_features, groups, idle=idle, seed=5), 0.02, seed=6)
 
 
+@pytest.mark.parametrize("in_features", [64, 320, 1024])  # 64-wide pieces of k: fewer than a work group's four wavefronts, 5, 16
+@pytest.mark.parametrize("out_features, groups", [
+    (8192, [(70, 24), (1, 256), (40, 8), (19, 130)]),   # 384 tiles of 64 x 64
+    (8064, [(33, 64), (29, 9), (3, 200)]),              # 378 of 32 x 64
+    (4224, [(9, 16), (23, 72)]),                        # 264 of 32 x 32
+    (8320, [(7, 40), (6, 255)]),                        # 260 of 16 x 32
+])
+def test_linear_small_tiles_beyond_one_per_compute_unit(in_features, out_features, groups):
+    _linear_case(_batch(in_features, out_features, groups, idle=1, seed=out_features), 0.02, seed=9)
+
+
 @pytest.mark.parametrize("in_features, out_features, groups", LARGE_TILES, ids=[c[0] for c in LARGE_TILES])
 def test_linear_large_tiles_from_one_pair_of_k_steps_on(in_features, out_features, groups):
     """Large tiles (one strip in the last column tile, rows left over; that no row is in a small one is tested in
