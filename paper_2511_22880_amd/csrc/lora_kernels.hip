@@ -1438,6 +1438,13 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
     const uint4 *gtile = reinterpret_cast<const uint4 *>(arena + u.w_off);  // strip s starts tile_pieces * s further
     uint4 *ltile = reinterpret_cast<uint4 *>(lds);
     const int nstrips = ncols / kStrip;
+    // The order of the strips: from the first one, or (runs and rows of whole multiples of 4 KB) every tile of tokens from another
+    // one.  All units of a launch walk their runs at about the same pace; where the runs' starts and the rows differ by multiples of
+    // 4 KB they otherwise ask a part of the memory's channels for y at any one time.  Expand launch of 19,675 tokens of ranks 8 to
+    // 128, us from the first strip / each from another: 8192 columns 166 / 138; rank 8 167 / 133, rank 128 184 /
+    // 167; 16384 columns, 10,082 tokens 179 / 161; 4096 columns (runs of 2 KB) 75.1 / 75.5, 14336 (runs of 7 KB) 138.5 / 141.7.
+    const int turn = (ncols * 2) % 4096 == 0 && (ldy * 2) % 4096 == 0 ? (u.tok0 >> 6) * 5 % nstrips : 0;
+    auto strip_at = [&](int i) __attribute__((always_inline)) { return i + turn < nstrips ? i + turn : i + turn - nstrips; };
 
     // Copy of strip S_'s tile from the pool into LDS buffer BUF_ with loads that write LDS directly
     // (no registers in between, so the copy runs while the MFMAs of the current strip do): every
@@ -1499,33 +1506,33 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
         }
     };
 
-    LORA_DMA_TILE(0, 0)
-    fetch_y(0, ya);
+    LORA_DMA_TILE(0, strip_at(0))
+    fetch_y(strip_at(0), ya);
     LORA_DMA_WAIT()
     __syncthreads();
     for (int s = 0; s < nstrips; s += 2) {
         // even strips from buffer 0, odd strips from buffer 1 (a single buffer above rank 128)
         if (s + 1 < nstrips) {
-            if (DB) { LORA_DMA_TILE(1, s + 1) }
-            fetch_y(s + 1, yb);
+            if (DB) { LORA_DMA_TILE(1, strip_at(s + 1)) }
+            fetch_y(strip_at(s + 1), yb);
         }
-        compute(s, 0, ya);
+        compute(strip_at(s), 0, ya);
         if (s + 1 >= nstrips) break;
         if (!DB) {
             __syncthreads();  // single buffer: everyone has finished reading strip s
-            LORA_DMA_TILE(0, s + 1)
+            LORA_DMA_TILE(0, strip_at(s + 1))
         }
         LORA_DMA_WAIT()
         __syncthreads();
         if (s + 2 < nstrips) {
-            if (DB) { LORA_DMA_TILE(0, s + 2) }
-            fetch_y(s + 2, ya);
+            if (DB) { LORA_DMA_TILE(0, strip_at(s + 2)) }
+            fetch_y(strip_at(s + 2), ya);
         }
-        compute(s + 1, DB ? 1 : 0, yb);
+        compute(strip_at(s + 1), DB ? 1 : 0, yb);
         if (s + 2 >= nstrips) break;
         if (!DB) {
             __syncthreads();
-            LORA_DMA_TILE(0, s + 2)
+            LORA_DMA_TILE(0, strip_at(s + 2))
         }
         LORA_DMA_WAIT()
         __syncthreads();

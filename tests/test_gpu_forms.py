@@ -104,6 +104,26 @@ def test_token_heavy_units_cut_along_k(shape, most, sizes, cut):
     dp.close()
 
 
+@pytest.mark.parametrize("out_features, pad", [(8192, 0), (16384, 0), (8192, 64), (8320, 0), (8192, 2048)])
+def test_strips_of_token_heavy_expand_units_in_any_order(out_features, pad):
+    """Runs of 4 KB and its multiples are walked from another strip by every tile of tokens, others (8320 columns, padded rows)
+    from the first: 16, 17 and 32 strips a run, ranks with one buffer and with two, the last tile of a group short."""
+    b = _batch(64, out_features, [(700, 16), (257, 136), (190, 72)], idle=2, seed=4)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(big_runs_max_units=0))
+    ws = torch.empty(max(L.lora_apply_workspace_bytes(dp.pool, seg), 256), dtype=torch.uint8, device="cuda")
+    y = torch.full((b.T, out_features + pad), 7.0, dtype=torch.bfloat16, device="cuda")
+    y[:, :out_features] = G.bits_to_dev(y0)
+    L.lora_apply(dp.pool, seg, G.bits_to_dev(x_bits), y[:, :out_features], ws)
+    torch.cuda.synchronize()
+    assert bool((y[:, out_features:] == 7.0).all())
+    rows = np.arange(0, b.T, 3)
+    G.check_parity(G.dev_to_bits(y[:, :out_features].contiguous()), G.oracle_apply(dp, x_bits, y0, rows=rows), y0, b.token_adapter, rows=rows)
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 # ---- batches of few units: one launch by themselves, two under capture ------------------------------------------
 @pytest.mark.parametrize("case", [
     # (which of them take the one launch is tested in test_launch_routes.py)
