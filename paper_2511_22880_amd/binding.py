@@ -243,15 +243,23 @@ def lora_pool_compact(pool: Pool, scratch=None, stream=None, scratch_bytes: Opti
 
 def lora_pool_load(pool: Pool, adapter: int, A, B, src_is_device: Optional[bool] = None, stream=None) -> None:
     """A [in][rank], B [rank][out] bf16: numpy uint16 arrays (host) or torch device tensors."""
+    host = isinstance(A, np.ndarray)
     if src_is_device is None:
-        src_is_device = not isinstance(A, np.ndarray)
-    if isinstance(A, np.ndarray):
+        src_is_device = not host
+    if host:
         A, B = np.ascontiguousarray(A), np.ascontiguousarray(B)
         r = int(pool.ranks[adapter]) if 0 <= adapter < pool.n_adapters else -1
         if r >= 0 and (A.shape != (pool.in_features, r) or B.shape != (r, pool.out_features) or A.itemsize != 2
                        or B.itemsize != 2):
             raise ValueError(f"adapter {adapter}: A {A.shape} / B {B.shape} do not match rank {r}")
-    _check(lib().lora_pool_load(pool.handle, ctypes.c_int32(adapter), _addr(A), _addr(B), 1 if src_is_device else 0, _queue(stream)))
+    try:
+        a, b = A.data_ptr(), B.data_ptr()
+    except AttributeError:
+        a, b = _addr(A), _addr(B)
+    status = (_lib or lib()).lora_pool_load(pool.handle, adapter, a, b, 1 if src_is_device else 0,
+                                            None if stream is None else _queue(stream))
+    if status:
+        _check(status)
 
 
 def lora_pool_evict(pool: Pool, adapter: int) -> None:
@@ -412,22 +420,46 @@ def _ws_bytes(workspace, ws_bytes):
     return _nbytes(workspace) if ws_bytes is None else ctypes.c_size_t(ws_bytes)
 
 
+# The calls of a serving loop take their common arguments, tensors that state their own strides and sizes, without the helpers above;
+# anything else (an address, an array, None) has no such attributes and goes through them.
 def lora_shrink(pool: Pool, seg: Segments, x, v, workspace=None, stream=None, ldx: Optional[int] = None,
                 ws_bytes: Optional[int] = None) -> None:
     """x: bf16 device tensor [T][in]; v: fp32 device tensor of info['v_floats'] elements."""
-    _check(lib().lora_shrink(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(v), _addr(workspace),
-                             _ws_bytes(workspace, ws_bytes), _queue(stream)))
+    try:
+        px, pv, pw = x.data_ptr(), v.data_ptr(), workspace.data_ptr()
+        lx = x.stride(0) if ldx is None else int(ldx)
+        nw = workspace.nbytes if ws_bytes is None else ctypes.c_size_t(ws_bytes)
+    except AttributeError:
+        px, pv, pw, lx, nw = _addr(x), _addr(v), _addr(workspace), _ld(x, ldx), _ws_bytes(workspace, ws_bytes)
+    status = (_lib or lib()).lora_shrink(pool.handle, seg.handle, px, lx, pv, pw, nw, None if stream is None else _queue(stream))
+    if status:
+        _check(status)
 
 
 def lora_expand(pool: Pool, seg: Segments, v, y, stream=None, ldy: Optional[int] = None) -> None:
     """y: bf16 device tensor [T][out], updated in place."""
-    _check(lib().lora_expand(pool.handle, seg.handle, _addr(v), _addr(y), _ld(y, ldy), _queue(stream)))
+    try:
+        pv, py = v.data_ptr(), y.data_ptr()
+        ly = y.stride(0) if ldy is None else int(ldy)
+    except AttributeError:
+        pv, py, ly = _addr(v), _addr(y), _ld(y, ldy)
+    status = (_lib or lib()).lora_expand(pool.handle, seg.handle, pv, py, ly, None if stream is None else _queue(stream))
+    if status:
+        _check(status)
 
 
 def lora_apply(pool: Pool, seg: Segments, x, y, workspace, stream=None, ldx: Optional[int] = None,
                ldy: Optional[int] = None, ws_bytes: Optional[int] = None) -> None:
-    _check(lib().lora_apply(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(y), _ld(y, ldy), _addr(workspace),
-                            _ws_bytes(workspace, ws_bytes), _queue(stream)))
+    try:
+        px, py, pw = x.data_ptr(), y.data_ptr(), workspace.data_ptr()
+        lx = x.stride(0) if ldx is None else int(ldx)
+        ly = y.stride(0) if ldy is None else int(ldy)
+        nw = workspace.nbytes if ws_bytes is None else ctypes.c_size_t(ws_bytes)
+    except AttributeError:
+        px, py, pw, lx, ly, nw = _addr(x), _addr(y), _addr(workspace), _ld(x, ldx), _ld(y, ldy), _ws_bytes(workspace, ws_bytes)
+    status = (_lib or lib()).lora_apply(pool.handle, seg.handle, px, lx, py, ly, pw, nw, None if stream is None else _queue(stream))
+    if status:
+        _check(status)
 
 
 def lora_linear_pack_weight(wt, in_features: int, out_features: int, dev_packed, stream=None) -> None:
@@ -439,8 +471,18 @@ def lora_linear_pack_weight(wt, in_features: int, out_features: int, dev_packed,
 def lora_linear(pool: Pool, seg: Segments, x, w_packed, y, workspace, stream=None, ldx: Optional[int] = None,
                 ldy: Optional[int] = None, ws_bytes: Optional[int] = None) -> None:
     """y = bf16(x W + delta) for every token, y written once."""
-    _check(lib().lora_linear(pool.handle, seg.handle, _addr(x), _ld(x, ldx), _addr(w_packed), _addr(y), _ld(y, ldy),
-                             _addr(workspace), _ws_bytes(workspace, ws_bytes), _queue(stream)))
+    try:
+        px, pp, py, pw = x.data_ptr(), w_packed.data_ptr(), y.data_ptr(), workspace.data_ptr()
+        lx = x.stride(0) if ldx is None else int(ldx)
+        ly = y.stride(0) if ldy is None else int(ldy)
+        nw = workspace.nbytes if ws_bytes is None else ctypes.c_size_t(ws_bytes)
+    except AttributeError:
+        px, pp, py, pw = _addr(x), _addr(w_packed), _addr(y), _addr(workspace)
+        lx, ly, nw = _ld(x, ldx), _ld(y, ldy), _ws_bytes(workspace, ws_bytes)
+    status = (_lib or lib()).lora_linear(pool.handle, seg.handle, px, lx, pp, py, ly, pw, nw,
+                                         None if stream is None else _queue(stream))
+    if status:
+        _check(status)
 
 
 LORA_STATIC_WORKSPACE_BYTES = 32 << 20
@@ -477,8 +519,17 @@ def lora_segments_build_multi(pools, token_adapter, stream=None, options=None) -
 def lora_apply_multi(pools, seg: Segments, x, y, workspace, stream=None, ldx: Optional[int] = None,
                      ldy: Optional[int] = None, ws_bytes: Optional[int] = None) -> None:
     """y: bf16 device tensor [T][sum of the pools' out_features], updated in place."""
-    _check(lib().lora_apply_multi(_pool_array(pools), len(pools), seg.handle, _addr(x), _ld(x, ldx), _addr(y), _ld(y, ldy),
-                                  _addr(workspace), _ws_bytes(workspace, ws_bytes), _queue(stream)))
+    try:
+        px, py, pw = x.data_ptr(), y.data_ptr(), workspace.data_ptr()
+        lx = x.stride(0) if ldx is None else int(ldx)
+        ly = y.stride(0) if ldy is None else int(ldy)
+        nw = workspace.nbytes if ws_bytes is None else ctypes.c_size_t(ws_bytes)
+    except AttributeError:
+        px, py, pw, lx, ly, nw = _addr(x), _addr(y), _addr(workspace), _ld(x, ldx), _ld(y, ldy), _ws_bytes(workspace, ws_bytes)
+    status = (_lib or lib()).lora_apply_multi(_pool_array(pools), len(pools), seg.handle, px, lx, py, ly, pw, nw,
+                                              None if stream is None else _queue(stream))
+    if status:
+        _check(status)
 
 
 def _switch(enabled) -> ctypes.c_int:
