@@ -1236,15 +1236,14 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
         // this lane's piece of sub-block 0, rank piece 0 of the wavefront's strip; sub-block b is
         // 16*r8 elements further, rank piece kp 128 elements further
         const uint16_t *brow = arena + u.w_off + (int64_t)(strip_ok ? cs : 0) * r8 + n * 8;
-        // weights: row (column of y) cs + 8*n + b, 16 bytes at jc.  One k step per wavefront: they stay
-        // in registers for all token blocks; two (rank > 128): each block re-reads them (L1 / L2 hits).
+        // weights: row (column of y) cs + 8*n + b, 16 bytes at jc, of the wavefront's first k step.  (Ranks above 128, two k
+        // steps: with both requested behind the wait for v a launch of 10 units lasted 6.6 us, now 5.7; 6076 units of 576 -> 11136,
+        // ranks 1 to 256, 52.5 -> 49.6.)
         uint4 w[8];
-        if (ITEMS == 1) {
 #pragma unroll
-            for (int b = 0; b < 8; ++b) w[b] = ld16_stream(brow + b * 16 * r8 + jc[0] * 16);
-            // nothing that needs the row index (a wait for its load) moves up in front of these requests
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int b = 0; b < 8; ++b) w[b] = ld16_stream(brow + b * 16 * r8 + jc[0] * 16);
+        // nothing that needs the row index (a wait for its load) moves up in front of these requests
+        __builtin_amdgcn_sched_barrier(0);
 
         // one block of 16 tokens: this thread's share of y and this wavefront's v operand
         struct Blk {
@@ -1313,15 +1312,13 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
             for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
-                if (ITEMS > 1) {
-#pragma unroll
-                    for (int b = 0; b < 8; ++b) w[b] = ld16_stream(brow + b * 16 * r8 + jc[it] * 16);
-                }
 #pragma unroll
                 for (int b = 0; b < 8; ++b) {
                     const bf16x8 ww = as_bf16x8(j_ok[it] ? w[b] : zero);
                     acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(cur.vh[it]), ww, acc[b], 0, 0, 0);
                     acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(cur.vl[it]), ww, acc[b], 0, 0, 0);
+                    // ranks above 128: the second k step's operand takes the register as soon as it is free
+                    if (it + 1 < ITEMS) w[b] = ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
                 }
             }
             if (strip_ok) {
