@@ -609,71 +609,100 @@ static __device__ __forceinline__ int late_thread()
     return t;
 }
 
+// The rank rows of a token-heavy shrink unit that a work group takes: all of them, or (launches of at most kHeavyHalvesMaxUnits
+// units) one of two halves.  A compute unit passes about 50 GB/s of x and A^T together, so a launch of few units lasts as long as
+// one of them however many compute units stand idle; halves read x twice (the second time from the L2: both run on one XCD) and every
+// row of A^T once, and nothing is added up between them.  Shrink launch in us,
+// whole / halves: one prompt of 2000 tokens, 4096 features, rank 128 (128 units, cut along k) 15.4 / 13.1, rank 192 18.3 / 16.4, 1024 tokens
+// at 14336 features 29.5 / 23.2; uncut, 1984 features, 2000 tokens (32 units) 17.2 / 14.1, 7900 tokens of rank 192 (124) 21.8 / 18.7.  From
+// more than half a unit per compute unit on: 188 units of rank 256 at 4096 features 16.9 / 18.0, 252 of rank 64 10.5 / 11.2.
+struct RankRows {
+    int first, n;  // rank rows first .. first + n - 1 (first a multiple of 16, n of 8)
+    int part, of;  // which of how many work groups
+};
+constexpr int kHeavyHalvesMaxUnits = kComputeUnits / 2;
+
+// where element quad i of those rows lies in the unit's v, in quads from its first row; i counts n / 4 quads per token
+static __device__ __forceinline__ int quad_place(const Unit &u, const RankRows &rr, int i)
+{
+    if (rr.of == 1) return i;
+    const int quads = rr.n >> 2, tok = i / quads;
+    return tok * (u.r8 >> 2) + (rr.first >> 2) + (i - tok * quads);
+}
+
 // The end of a token-heavy shrink unit, by all threads of its work group: rows row0 .. row0 + rows - 1 of the unit's
-// v are one run of memory, which goes out in 16-byte pieces, neighbouring threads side by side; quad(i) = the sums
-// of its elements 4 i .. 4 i + 3.  (Straight from the MFMA registers a wavefront's stores were 8 bytes of each of 64
+// v are one run of memory (or, of half the rank rows, a run per token), which goes out in 16-byte pieces, neighbouring threads side by
+// side; quad(i) = the sums of its elements 4 i .. 4 i + 3.  (Straight from the MFMA registers a wavefront's stores were 8 bytes of each of 64
 // pieces of lines; written through to memory those were most of a cut unit's time: 2000 tokens of rank 128 at
 // 4096 features, 128 units, shrink launch 20.4 -> 15.2 us.)
 // Whole units write v.  Units cut along k leave their sums in slice u.ks of the fp32 partial sums: plainly for the
 // stand-alone shrink (v_f32: the caller adds the slices up, and slice 0's unit clears those this group does not
 // use), else through to memory for the unit that completes the tile (complete_tile).
 template <class Quad>
-static __device__ __forceinline__ void store_heavy_rows(const Unit &u, int n_ks, int row0, int rows, Quad quad,
+static __device__ __forceinline__ void store_heavy_rows(const Unit &u, const RankRows &rr, int n_ks, int row0, int rows, Quad quad,
                                                         uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo,
                                                         float *__restrict__ v_f32, int n_slices, int64_t slice_stride,
                                                         float *__restrict__ parts, float vs)
 {
-    const int n = rows * (u.r8 >> 2);
+    const int n = rows * (rr.n >> 2);
     const int64_t at = u.v_off + (int64_t)row0 * u.r8;
     if (n_ks > 1 && !v_f32) {
-        const Through slice(parts + (int64_t)u.ks * slice_stride + at, 4 * n);
-        for (int i = late_thread(); i < n; i += kThreads) slice.st(i, quad(i));
+        const Through slice(parts + (int64_t)u.ks * slice_stride + at, rows * u.r8);
+        for (int i = late_thread(); i < n; i += kThreads) slice.st(quad_place(u, rr, i), quad(i));
     } else if (v_f32) {
         float *dst = v_f32 + (int64_t)u.ks * slice_stride + at;
-        for (int i = late_thread(); i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[i] = quad(i);
+        for (int i = late_thread(); i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[quad_place(u, rr, i)] = quad(i);
         if (n_ks > 1 && u.ks == 0)
             for (int sl = n_ks; sl < n_slices; ++sl)
                 for (int i = late_thread(); i < n; i += kThreads)
-                    reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride)[quad_place(u, rr, i)] = f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
-        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * i, v_hi, v_lo);
+        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * quad_place(u, rr, i), v_hi, v_lo);
     }
 }
 
 // A cut unit whose sums are on their way to memory: the one of the tile's n_ks that arrives last at the tile's counter
-// adds the slices in slice order and leaves v as bf16 hi + lo.  `word`: an LDS word that nothing else uses any more.
-static __device__ __forceinline__ void complete_tile(const Unit &u, int n_ks, int64_t slice_stride, float *__restrict__ parts,
-                                                     uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo, float vs,
-                                                     const Sync &sy, unsigned *word)
+// adds the slices in slice order and leaves v as bf16 hi + lo.  Halves of the rank rows have a counter each where the tile has two
+// (it has one per 16 tokens), else the last of all completes all rows.  `word`: an LDS word that nothing else uses any more.
+static __device__ __forceinline__ void complete_tile(const Unit &u, const RankRows &rr, int n_ks, int64_t slice_stride,
+                                                     float *__restrict__ parts, uint16_t *__restrict__ v_hi,
+                                                     uint16_t *__restrict__ v_lo, float vs, const Sync &sy, unsigned *word)
 {
     stores_done();
     __syncthreads();  // every wavefront's partial sums are out
-    if (threadIdx.x == 0) *word = atomicAdd(sy.counters + u.sync_idx, 1u);
+    const bool own = rr.of == 1 || u.ntok > kTokTile;
+    unsigned *const counter = sy.counters + u.sync_idx + (own ? rr.part : 0);
+    if (threadIdx.x == 0) *word = atomicAdd(counter, 1u);
     __syncthreads();
-    if (*word + 1u != (unsigned)n_ks) return;
+    if (*word + 1u != (unsigned)(own ? n_ks : n_ks * rr.of)) return;
     __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the loads of the slices stay behind the arrival
-    if (threadIdx.x == 0) atomicExch(sy.counters + u.sync_idx, 0u);  // back to zero for the next launch
-    const int n = u.ntok * (u.r8 >> 2);
-    const Through s0(parts + u.v_off, 4 * n), s1(parts + u.v_off + slice_stride, 4 * n);
+    if (threadIdx.x == 0) atomicExch(counter, 0u);  // back to zero for the next launch
+    const RankRows all = own ? rr : RankRows{0, u.r8, 0, 1};
+    const int n = u.ntok * (all.n >> 2), len = u.ntok * u.r8;
+    const Through s0(parts + u.v_off, len), s1(parts + u.v_off + slice_stride, len);
     if (n_ks <= 2) {
 #pragma unroll 4
-        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * (s0.ld(i) + s1.ld(i)), u.v_off + 4 * i, v_hi, v_lo);
+        for (int i = late_thread(); i < n; i += kThreads) {
+            const int q = quad_place(u, all, i);
+            store_v4(vs * (s0.ld(q) + s1.ld(q)), u.v_off + 4 * q, v_hi, v_lo);
+        }
     } else {
-        const Through s2(parts + u.v_off + 2 * slice_stride, 4 * n);
-        const Through s3(parts + u.v_off + (n_ks > 3 ? 3 : 2) * slice_stride, 4 * n);
+        const Through s2(parts + u.v_off + 2 * slice_stride, len);
+        const Through s3(parts + u.v_off + (n_ks > 3 ? 3 : 2) * slice_stride, len);
 #pragma unroll 4
         for (int i = late_thread(); i < n; i += kThreads) {
-            f32x4 f = s0.ld(i) + s1.ld(i);
-            f += s2.ld(i);
-            const f32x4 f3 = s3.ld(i);
+            const int q = quad_place(u, all, i);
+            f32x4 f = s0.ld(q) + s1.ld(q);
+            f += s2.ld(q);
+            const f32x4 f3 = s3.ld(q);
             if (n_ks > 3) f += f3;
-            store_v4(vs * f, u.v_off + 4 * i, v_hi, v_lo);
+            store_v4(vs * f, u.v_off + 4 * q, v_hi, v_lo);
         }
     }
 }
 
 template <int JB, int TB, int WD, int XD = 1>
-static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, const int32_t *__restrict__ perm,
+static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, const RankRows &rr, const int32_t *__restrict__ perm,
                                                              const uint16_t *__restrict__ arena,
                                                              const uint16_t *__restrict__ x, int64_t ldx, int in,
                                                              uint16_t *__restrict__ v_hi,
@@ -692,7 +721,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
     f32x4(*red)[NT][64] = reinterpret_cast<f32x4(*)[NT][64]>(lds);  // re-uses the x regions after the k loop
     const int n = lane & 15;
     const int kq = lane >> 4;
-    const int r8 = u.r8;
+    const int r8 = rr.n;  // of this work group
     const int ntok = u.ntok;
 
     // staging: load t of a pass takes tokens 4t .. 4t+3, this lane token 4t + kq, 16-byte chunk n
@@ -705,7 +734,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
     // The caller picks JB from the rank; telling the compiler so removes the branches around the row
     // blocks that always exist (with a branch per block the same loop ran 2.4 times slower).
     __builtin_assume(r8 <= 16 * JB && (JB == 1 ? r8 >= 8 : r8 > 8 * JB));
-    const uint16_t *wbase = arena + u.w_off;
+    const uint16_t *wbase = arena + u.w_off + (int64_t)rr.first * in;
     int woff[JB];  // element offset of this lane's 16-byte piece in k step 0 of row block jb
     int wh[JB];    // rows in block jb (16, or 8 for the last block of a padded rank that is 8 mod 16)
     // The loop below has no branch: a block beyond the padded rank (ranks 33..48 of the bucket up to 64) is
@@ -844,9 +873,9 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         const int t = (j4 >> 2) * TB + (tok >> 4), l = (j4 & 3) * 16 + (tok & 15);
         return (red[0][t][l] + red[2][t][l]) + (red[1][t][l] + red[3][t][l]);
     };
-    store_heavy_rows(u, n_ks, 0, ntok, quad, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, vs);
+    store_heavy_rows(u, rr, n_ks, 0, ntok, quad, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, vs);
     if (n_ks == 1 || v_f32) return;
-    complete_tile(u, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + 4 * NT * 64 * 16));
+    complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + 4 * NT * 64 * 16));
 }
 
 // Token-heavy units above rank 64: 16 * TB tokens, all rank rows, all of k or a slice of it.  Here the
@@ -862,7 +891,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
 // accumulators of 64 not fitting the registers: against units of 16 tokens with k split, the shrink
 // launch at uniform rank 160 / 192 / 256 went from 105 / 121 / 156 us to 78 / 86 / 112.)
 template <int JBW, int TB, int PD, int WP>
-static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, const int32_t *__restrict__ perm,
+static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, const RankRows &rr, const int32_t *__restrict__ perm,
                                                                const uint16_t *__restrict__ arena,
                                                                const uint16_t *__restrict__ x, int64_t ldx, int in,
                                                                uint16_t *__restrict__ v_hi,
@@ -879,7 +908,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     uint16_t(*buf)[kPfRow] = reinterpret_cast<uint16_t(*)[kPfRow]>(lds);  // [2 * TOK] rows
     const int n = lane & 15;
     const int kq = lane >> 4;
-    const int r8 = u.r8;
+    const int r8 = rr.n;  // of this work group
     const int ntok = u.ntok;
 
     // staging: thread (xr, xc) copies 16-byte chunk xc of tokens xr, xr + 16, ...
@@ -890,7 +919,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
 
     // A wavefront whose row blocks lie beyond the padded rank (ranks that are not multiples of 64) works on
     // the last block that exists instead: its sums are never stored, and the loop needs no branch for it.
-    const uint16_t *wbase = arena + u.w_off;
+    const uint16_t *wbase = arena + u.w_off + (int64_t)rr.first * in;
     const int nblk = (r8 + 15) >> 4;
     int woff[JBW], wh[JBW];
 #pragma unroll
@@ -1033,11 +1062,11 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
             }
         __syncthreads();
         if (16 * g < ntok)
-            store_heavy_rows(u, n_ks, 16 * g, min(16 * GO, ntok - 16 * g), [&](int i) { return rows[i]; }, v_hi, v_lo, v_f32,
+            store_heavy_rows(u, rr, n_ks, 16 * g, min(16 * GO, ntok - 16 * g), [&](int i) { return rows[i]; }, v_hi, v_lo, v_f32,
                              n_slices, slice_stride, parts, vs);
     }
     if (n_ks == 1 || v_f32) return;
-    complete_tile(u, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + kPrefillLds - 16));
+    complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + kPrefillLds - 16));
 }
 
 // One wavefront copies 1 KB from memory into LDS without passing through registers: lane l's 16 bytes
@@ -1096,23 +1125,24 @@ static __device__ __forceinline__ void prefill_dispatch(const Unit &u, const int
                                                         float *__restrict__ parts, const Sync &sy)
 {
     const int r8 = u.r8;
+    const RankRows rr = {0, r8, 0, 1};
     // (three in flight for ranks up to 32: cfg2 4096 -> 4096 shrink 48.3 against 43.9 us)
     constexpr int XD = ANY ? 2 : 1;  // passes of x in flight per wavefront: two where two work groups share a compute unit
     if (r8 <= 16)
-        shrink_prefill_ksplit<1, 2, 4, XD>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+        shrink_prefill_ksplit<1, 2, 4, XD>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
     else if (r8 <= 32)
-        shrink_prefill_ksplit<2, 2, 4, XD>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+        shrink_prefill_ksplit<2, 2, 4, XD>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
     else if (!ANY)  // the launcher takes this form only for batches whose token-heavy units are all up to rank 64
-        shrink_prefill_ksplit<4, 2, 1>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+        shrink_prefill_ksplit<4, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
     else if (r8 <= 64)
-        shrink_prefill_ksplit<4, 2, 4, XD>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+        shrink_prefill_ksplit<4, 2, 4, XD>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
     else if constexpr (ANY) {
         if (r8 <= 128)
-            shrink_prefill_rowsplit<2, 4, 2, 1>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+            shrink_prefill_rowsplit<2, 4, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
         else if (r8 <= 192)
-            shrink_prefill_rowsplit<3, 4, 2, 1>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+            shrink_prefill_rowsplit<3, 4, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
         else  // 32 tokens: the 16 accumulator tiles of 64 tokens x 64 rank rows per wavefront do not fit the registers
-            shrink_prefill_rowsplit<4, 2, 2, 1>(u, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+            shrink_prefill_rowsplit<4, 2, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
     }
 }
 
@@ -1130,6 +1160,38 @@ __global__ __launch_bounds__(kThreads, 4) void k_shrink_prefill(const Unit *__re
     LORA_CLOCK(0);
     prefill_dispatch<false>(units[blockIdx.x], perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride,
                             lds, parts, sy);
+    LORA_CLOCK(4);
+}
+
+// A launch of few token-heavy units of any rank, two work groups a unit (RankRows).  They run on one XCD (b mod 8), a row of 8 behind
+// the other.  Units up to rank 32 are the first one's alone.
+__global__ __launch_bounds__(kThreads, 2) void k_shrink_halves(const Unit *__restrict__ units,
+                                                               const int32_t *__restrict__ perm,
+                                                               const uint16_t *__restrict__ arena,
+                                                               const uint16_t *__restrict__ x, int64_t ldx, int in,
+                                                               uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo,
+                                                               float *__restrict__ v_f32, int n_slices, int64_t slice_stride,
+                                                               float *__restrict__ parts, int n_units, Sync sy)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kPrefillLds];
+    const int at = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7), part = (blockIdx.x >> 3) & 1;
+    if (at >= n_units || units[at].ntok <= 0) return;  // behind the list, or a place that only pads an XCD's share of it
+    const Unit &u = units[at];
+    const int r8 = u.r8, half = r8 <= 32 ? r8 : (r8 / 2 + 15) & ~15;
+    if (part && half == r8) return;
+    LORA_CLOCK(0);
+    const RankRows rr = {part * half, part ? r8 - half : half, part, half == r8 ? 1 : 2};
+    if (r8 <= 64) {
+        if (rr.n <= 16)
+            shrink_prefill_ksplit<1, 2, 4, 2>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+        else
+            shrink_prefill_ksplit<2, 2, 4, 2>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+    } else if (r8 <= 128)
+        shrink_prefill_rowsplit<1, 4, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+    else if (r8 <= 192)
+        shrink_prefill_rowsplit<2, 4, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
+    else
+        shrink_prefill_rowsplit<2, 2, 2, 1>(u, rr, perm, arena, x, ldx, in, v_hi, v_lo, v_f32, n_slices, slice_stride, lds, parts, sy);
     LORA_CLOCK(4);
 }
 
@@ -2840,7 +2902,10 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
     if (c.n_units <= 0) return hipSuccess;
     if (n_hi < 0 || n_hi > c.n_units) return hipErrorInvalidValue;
     const Sync sy = make_sync(sync, 0, c.scale_v);
-    if (n_hi > 0)
+    if (c.n_units <= kHeavyHalvesMaxUnits)
+        hipLaunchKernelGGL(k_shrink_halves, dim3((c.n_units + 7) / 8 * 16), dim3(kThreads), 0, stream, c.units, c.perm, c.arena, x, ldx,
+                           c.in_features, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, c.n_units, sy);
+    else if (n_hi > 0)
         hipLaunchKernelGGL(k_shrink_prefill_any, dim3(c.n_units), dim3(kThreads), 0, stream, c.units, c.perm, c.arena,
                            x, ldx, c.in_features, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, sy);
     else

@@ -104,6 +104,38 @@ def test_token_heavy_units_cut_along_k(shape, most, sizes, cut):
     dp.close()
 
 
+@pytest.mark.parametrize("slices", [1, 2, 4])
+@pytest.mark.parametrize("in_features, ranks", [
+    (4096, [8, 40, 64]), (4096, [72, 128]), (4160, [136, 192]), (4096, [200, 256]), (64, [33, 100, 255]), (1984, [16, 120, 184]),
+])
+def test_rank_halves_of_few_token_heavy_units(in_features, ranks, slices):
+    """Launches of few token-heavy units: halves of the rank rows, even and not, of units of 32 and 64 tokens, whole and cut along
+    k; the last tile of a group has 5 tokens (one counter for both halves) or 20."""
+    groups = [(384 + (5 if i % 2 else 20) + (700 if i == 0 else 0), r) for i, r in enumerate(ranks)]
+    b = _batch(in_features, 256, groups, idle=3, seed=in_features)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    cut = 0 if slices == 1 else 128 // slices * slices
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_k_cut_max_units=cut))
+    assert (L.lora_segments_export_units(seg)["shrink"][:, 0] >= 0).sum() <= 128
+    x, y = G.bits_to_dev(x_bits), G.bits_to_dev(y0)
+    ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    for _ in range(2):  # the counters are left as they were found
+        y.copy_(G.bits_to_dev(y0))
+        L.lora_apply(dp.pool, seg, x, y, ws)
+        torch.cuda.synchronize()
+        G.check_all_rows(dp, x_bits, y0, G.dev_to_bits(y))
+    v = torch.full((L.lora_segments_info(seg)["v_floats"],), float("nan"), dtype=torch.float32, device="cuda")
+    vws = torch.full((max(L.lora_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    y.copy_(G.bits_to_dev(y0))
+    L.lora_shrink(dp.pool, seg, x, v, vws)
+    L.lora_expand(dp.pool, seg, v, y)
+    torch.cuda.synchronize()
+    G.check_all_rows(dp, x_bits, y0, G.dev_to_bits(y))
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 @pytest.mark.parametrize("out_features, pad", [(8192, 0), (16384, 0), (8192, 64), (8320, 0), (8192, 2048)])
 def test_strips_of_token_heavy_expand_units_in_any_order(out_features, pad):
     """Runs of 4 KB and its multiples are walked from another strip by every tile of tokens, others (8320 columns, padded rows)
