@@ -423,9 +423,10 @@ lora_status_t lora_apply_multi(const lora_pool_t *const *pools, int32_t n_pools,
 lora_status_t lora_set_whole_k_limit(int32_t max_units);
 
 /* lora_apply is two launches (shrink units, then expand units) unless one of the single-launch forms is
- * taken (here and lora_set_decode_single_launch).  With k-slices the shrink
- * unit that completes a token tile (found through per-tile counters in the segment object's device
- * table) adds the k-slices up and leaves the tile's v for the expand units.
+ * taken (here and lora_set_decode_single_launch).  With k-slices the expand units of up to 16 tokens
+ * add the slices of their own tokens up; in batches of many such units, in lora_linear, and for
+ * token-heavy units cut along k, the shrink unit that completes a token tile (found through per-tile counters in the segment object's
+ * device table) adds them up and leaves the tile's v.
  * lora_set_fused_apply(1) selects, for batches planned with k-slices and without token-heavy groups,
  * a single launch in which shrink and expand units share the grid and the expand units poll, with a
  * bounded number of polls, until their tile's v is complete.  Applies that share one segment object

@@ -2286,6 +2286,20 @@ static bool may_be_captured(hipStream_t s)
     return true;
 }
 
+// Who adds the k-slices of v up (see the kernels).  The expand units, where the launch has few of them or its shrink launch is the
+// longer one: every one of them reads the slices of its tokens, 16 bytes an element where complete v is 4, and a shrink unit
+// saves its wait for the others once.  us per call, added up by the shrink / the expand units: batches of tokens alone,
+// 5888 -> 4608 (220 + 396 units) 14.9 / 10.2, 7936 -> 11776 (76 + 437) 12.6 / 11.1, 5056 -> 2560 (4884 + 2420) 60.7 / 56.5, but 4096 -> 14336
+// (6400 + 25200) 162.9 / 164.4, 16384 (6272 + 12544) 175.6 / 180.0; beside prompts 4096 -> 512 (1928 + 503) 30.2 / 28.0, 2112 -> 2688
+// (612 + 893) 29.0 / 28.2, but 3008 -> 3712 (198 + 523) 14.3 / 14.7, 2048 -> 8192 (732 + 3456) 48.0 / 50.0, 4096 -> 14336 (1612 + 5740) 69.9
+// / 73.7.
+static const int kExpandSlicesUnits = 512;  // two per compute unit
+static bool expand_adds_slices(const lora_segments *sg, int shrink_units, int expand_units)
+{
+    if (sg->wide) return false;
+    return expand_units < 2 * shrink_units || (!sg->has_big_units && expand_units <= kExpandSlicesUnits);
+}
+
 // The launches of one apply: `arena` is the base the units' weight offsets count from, `out` the
 // width of y that the units' columns lie in.
 // may_create: the apply may make the segment object's side stream and events at its first use.
@@ -2316,11 +2330,6 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     sa.v_lo = (uint16_t *)((char *)workspace + apply_parts_bytes(sg) + apply_packed_bytes(sg));
     sa.epoch = msg->launches + 1;  // read by the single-launch form only, which also advances it
     sa.spin_limit = opt_spin_limit(sg);
-    if (!sg->wide) {  // decode-sized groups' v in k-slices: added up by their expand units (see the kernels)
-        sa.parts = parts;
-        sa.n_slices = nsl;
-        sa.slice_stride = stride;
-    }
     const lora::LaunchCtx cs = ctx_for(arena, in, out, sg, kShrink), cp = ctx_for(arena, in, out, sg, kPrefill),
                           ce = ctx_for(arena, in, out, sg, kExpand), cb = ctx_for(arena, in, out, sg, kExpandBig);
     if (ev[0]) HIP_TRY(hipEventRecord(ev[0], s));
@@ -2336,6 +2345,11 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
                         (fused > 0 || (opt_decode_single(sg) != 0 && sg->n_active <= kSingleLaunchTokens && sg->top_rank <= kSingleLaunchRank &&
                                        cs.n_units <= kSingleLaunchShrinkUnits && cs.n_units + ce.n_units <= kSingleLaunchUnits &&
                                        !may_be_captured(s)));
+    if (single || expand_adds_slices(sg, cs.n_units + cp.n_units, ce.n_units + cb.n_units)) {
+        sa.parts = parts;
+        sa.n_slices = nsl;
+        sa.slice_stride = stride;
+    }
     if (opt_decode_single(sg) && sg->decode_fused && !may_be_captured(s)) {
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));

@@ -139,7 +139,7 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
 // A mixed batch's shrink in one launch: the token-heavy units of `heavy` (n_hi of them above rank 64),
 // then the k-slice units of `c`, which leave partial sums in `parts` and complete v through `sync` where
 // launch_shrink does.  Likewise the expand: the 64-token units of `big`, which read v from sync->v_hi / v_lo, then the
-// units of `c`, which add sync->parts up.
+// units of `c`, which add sync->parts up or, without them, read v_hi / v_lo too.
 hipError_t launch_shrink_mixed(const LaunchCtx &heavy, int n_hi, const LaunchCtx &c, const uint16_t *x, int64_t ldx,
                                int k_slice_len, float *parts, int n_slices, int64_t slice_stride,
                                const SyncArgs *sync, hipStream_t stream);

@@ -80,13 +80,14 @@ static __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __
 // arrived last adding them up, v took three trips through memory, a counter behind each.  Calls one after the other, us: one
 // token of rank 16, 4096 -> 4096, 6.7 -> 5.8; three tokens of ranks 8 to 32, 8192 -> 8192, 9.7 -> 8.4; 60 tokens of four adapters
 // of rank 16, 4096 -> 4096, 9.2 -> 8.1.)
-// In launches of their own the expand units of up to 16 tokens (k_expand_parts, k_expand_mixed) add the slices up as well, and the
+// In launches of their own the expand units of up to 16 tokens (k_expand_parts, k_expand_mixed<true>) add the slices up as well where
+// that is the shorter way (expand_adds_slices in lora_host.cpp), and the
 // shrink units of k-slices leave plain stores and end: to wait for its stores, its counter and, in the last unit of a tile, for the
 // other slices held a work group's place for longer than its products took.  Calls one after the other, us, completed in the
 // shrink launch / added up in the expand launch: 16 tokens of 10 adapters, 4096 -> 4096, 10.2 / 7.5; 100 tokens of one of rank
 // 64 12.1 / 9.1; 16 tokens of rank 256, 16384 -> 16384, 23.0 / 17.4; 500 tokens of 100 adapters of rank 256, 4096 -> 4096 (6400
 // and 3200 units), 104.9 / 82.0; of 500 adapters of ranks 8 to 128 74.8 / 73.4.
-// Only lora_linear has the k-slices completed by the shrink launch (as bf16 hi + lo, which every column tile of it reads): a unit
+// Else, and for lora_linear, the shrink launch completes them as bf16 hi + lo, which every column reads: a unit
 // bumps the arrival counter of its tile, the one whose bump completes the tile's count adds the slices up and sets the counter back
 // to zero (a launch leaves the table as it found it, so a launch replayed from a captured graph finds what the first one found).
 // Token-heavy units that are cut along k do the same (complete_tile).
@@ -1246,8 +1247,8 @@ static __device__ __forceinline__ void load_v_operand(const float *__restrict__ 
     vlo = as_bf16x8(pl);
 }
 
-// KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).  A unit may hold several blocks
-// of 16 tokens; the weights of a column pass stay in registers while the token blocks go by.
+// KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).  A unit of several blocks of 16 tokens (BIG; none is planned
+// for this body now) keeps the weights of a column pass in registers while the token blocks go by, one k step of them.
 // PARTS: v is the sum of the k-slices' partial sums (sy.parts) of the launch before.
 template <int KSTEPS, bool BIG, bool VF32, bool PARTS>
 static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t *__restrict__ perm,
@@ -1257,6 +1258,7 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
     constexpr int P = KSTEPS < 4 ? KSTEPS : 4;  // wavefronts that share one strip (each a part of the rank)
     constexpr int S = 4 / P;                    // strips per pass of the work group
     constexpr int ITEMS = KSTEPS / P;           // k steps per wavefront (1, or 2 for rank > 128)
+    static_assert(!BIG || ITEMS == 1, "the first block's second k step overwrites w");
     float(*part)[kTokTile][kPartRow] = reinterpret_cast<float(*)[kTokTile][kPartRow]>(lds);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1326,7 +1328,7 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 bk.yv[s] = zero;
                 if (c0 + s * kStrip < ncols) bk.yv[s] = ld16_stream(bk.e_y + c0 + s * kStrip);
             }
-            // (single launch) y, and up to rank 128 the weights, are on their way while v is waited for
+            // (single launch) y and the weights of the first k step are on their way while v is waited for
             if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx, u.sync_n);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
@@ -2069,6 +2071,7 @@ __global__ __launch_bounds__(kThreads, ANY ? 2 : 4) void k_shrink_mixed(
     LORA_CLOCK(4);
 }
 
+template <bool PARTS>
 __global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__restrict__ big_units, int n_big,
                                                               const Unit *__restrict__ units,
                                                               const int32_t *__restrict__ perm,
@@ -2081,7 +2084,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__rest
     if (b < n_big)
         expand_dispatch<true, false>(big_units[b], perm, arena, nullptr, y, ldy, lds, sy);
     else
-        expand_dispatch<false, false, true>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
+        expand_dispatch<false, false, PARTS>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 
@@ -2938,9 +2941,13 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_
 {
     const int total = big.n_units + c.n_units;
     if (total <= 0) return hipSuccess;
-    if (!sync || !sync->parts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_expand_mixed, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
-                       c.perm, c.arena, y, ldy, make_sync(sync, 0));
+    if (!sync) return hipErrorInvalidValue;
+    if (sync->parts)
+        hipLaunchKernelGGL(k_expand_mixed<true>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
+                           c.perm, c.arena, y, ldy, make_sync(sync, 0));
+    else
+        hipLaunchKernelGGL(k_expand_mixed<false>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
+                           c.perm, c.arena, y, ldy, make_sync(sync, 0));
     return hipGetLastError();
 }
 
