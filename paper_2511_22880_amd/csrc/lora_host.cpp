@@ -2286,18 +2286,19 @@ static bool may_be_captured(hipStream_t s)
     return true;
 }
 
-// Who adds the k-slices of v up (see the kernels).  The expand units, where the launch has few of them or its shrink launch is the
-// longer one: every one of them reads the slices of its tokens, 16 bytes an element where complete v is 4, and a shrink unit
+// Who adds the k-slices of v up (see the kernels).  The expand units, where the shrink units of a batch without token-heavy groups
+// all run at once (their waits for each other then are most of the launch), or where there are few expand units to each:
+// every one of them reads the slices of its tokens, 16 bytes an element where complete v is 4, and a shrink unit
 // saves its wait for the others once.  us per call, added up by the shrink / the expand units: batches of tokens alone,
-// 5888 -> 4608 (220 + 396 units) 14.9 / 10.2, 7936 -> 11776 (76 + 437) 12.6 / 11.1, 5056 -> 2560 (4884 + 2420) 60.7 / 56.5, but 4096 -> 14336
+// 4096 -> 16384 (192 + 768 units) 13.8 / 11.4, 16384 -> 16384 (224 + 896) 21.1 / 18.3, 8192 -> 28672 (192 + 1344) 20.0 / 18.3, 4096 -> 28672
+// (152 + 2128) 16.2 / 15.8, 5056 -> 2560 (4884 + 2420) 60.7 / 56.5, but 4096 -> 14336
 // (6400 + 25200) 162.9 / 164.4, 16384 (6272 + 12544) 175.6 / 180.0; beside prompts 4096 -> 512 (1928 + 503) 30.2 / 28.0, 2112 -> 2688
 // (612 + 893) 29.0 / 28.2, but 3008 -> 3712 (198 + 523) 14.3 / 14.7, 2048 -> 8192 (732 + 3456) 48.0 / 50.0, 4096 -> 14336 (1612 + 5740) 69.9
 // / 73.7.
-static const int kExpandSlicesUnits = 512;  // two per compute unit
 static bool expand_adds_slices(const lora_segments *sg, int shrink_units, int expand_units)
 {
     if (sg->wide) return false;
-    return expand_units < 2 * shrink_units || (!sg->has_big_units && expand_units <= kExpandSlicesUnits);
+    return expand_units < 2 * shrink_units || (!sg->has_big_units && shrink_units <= kComputeUnits);
 }
 
 // The launches of one apply: `arena` is the base the units' weight offsets count from, `out` the

@@ -332,7 +332,8 @@ def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
     ((3968, 384), [(5, 129), (33, 64), (16, 8)]),                       # three, the last of them short
     ((4096, 1152), [(1, 16)] * 24),                                     # four
     ((4096, 256), [(40, 72), (1000, 16), (3, 136), (15, 255), (31, 8)]),  # beside token-heavy groups
-    ((2048, 8192), [(1, 8)] * 40),                                      # many more expand units than shrink units: the shrink's
+    ((2048, 8192), [(1, 8)] * 40),                                      # few shrink units, many expand units
+    ((2048, 8192), [(1, 8)] * 150),                                     # many more expand units than shrink units: the shrink's
     ((2048, 4096), [(1000, 16), (40, 8)] + [(2, 24)] * 20),             # the same beside token-heavy groups
 ])
 def test_k_slices_added_up_by_the_expand_units(shape, groups):
