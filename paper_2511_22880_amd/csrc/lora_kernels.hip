@@ -80,7 +80,7 @@ static __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __
 // arrived last adding them up, v took three trips through memory, a counter behind each.  Calls one after the other, us: one
 // token of rank 16, 4096 -> 4096, 6.7 -> 5.8; three tokens of ranks 8 to 32, 8192 -> 8192, 9.7 -> 8.4; 60 tokens of four adapters
 // of rank 16, 4096 -> 4096, 9.2 -> 8.1.)
-// In launches of their own the expand units of up to 16 tokens (k_expand_parts, k_expand_mixed<true>) add the slices up as well where
+// In launches of their own the expand units of up to 16 tokens (k_expand_parts, k_expand_mixed<kSlicesByExpand>) add the slices up as well where
 // that is the shorter way (expand_adds_slices in lora_host.cpp), and the
 // shrink units of k-slices leave plain stores and end: to wait for its stores, its counter and, in the last unit of a tile, for the
 // other slices held a work group's place for longer than its products took.  Calls one after the other, us, completed in the
@@ -213,6 +213,15 @@ static __device__ __forceinline__ void split_bf16(f32x4 f0, f32x4 f1, uint4 &ph,
 }
 
 constexpr int kMaxSlices = 4;  // upper bound of the shrink's k-slices
+
+// Who adds the k-slices of v up.  A template argument of the bodies: with all three ways compiled into one, chosen by what the
+// launch was given, the expand units that read complete v paid for the others' registers and code (mixed launches, 1344 -> 4224, rank
+// 64, expand launch 17.5 us with, 16.7 without; 1984 -> 9856 28.5 / 27.9).
+enum Slices {
+    kSlicesByShrink,  // the shrink unit that completes a token tile: v_hi and v_lo are complete
+    kSlicesByExpand,  // the expand units of the next launch, each those of its own tokens
+    kSlicesByWaiting  // the same in one launch, behind the wait for the tile's shrink units
+};
 
 // sum of the k-slices' partial sums of 8 consecutive v elements, in slice order.  EARLIER: of an earlier launch, else read
 // through to memory.
@@ -1249,8 +1258,8 @@ static __device__ __forceinline__ void load_v_operand(const float *__restrict__ 
 
 // KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).  A unit of several blocks of 16 tokens (BIG; none is planned
 // for this body now) keeps the weights of a column pass in registers while the token blocks go by, one k step of them.
-// PARTS: v is the sum of the k-slices' partial sums (sy.parts) of the launch before.
-template <int KSTEPS, bool BIG, bool VF32, bool PARTS>
+// BY: where v comes from, unless it is the caller's (VF32).
+template <int KSTEPS, bool BIG, bool VF32, Slices BY>
 static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t *__restrict__ perm,
                                                    const uint16_t *__restrict__ arena,
                                                    const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
@@ -1329,16 +1338,16 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
                 if (c0 + s * kStrip < ncols) bk.yv[s] = ld16_stream(bk.e_y + c0 + s * kStrip);
             }
             // (single launch) y and the weights of the first k step are on their way while v is waited for
-            if (!BIG && !VF32 && first && sy.counters && sy.wait) wait_for(sy, u.sync_idx, u.sync_n);
+            if (BY == kSlicesByWaiting && first) wait_for(sy, u.sync_idx, u.sync_n);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 const bool ok = (n < bk.ntok) && j_ok[it];
                 const int64_t off = u.v_off + (int64_t)(ok ? t0 + n : 0) * r8 + jc[it];
                 uint4 ph, pl;
                 if (!VF32) {
-                    if (!BIG && (PARTS || sy.wait)) {
+                    if (BY != kSlicesByShrink) {
                         f32x4 f0, f1;
-                        sum_slices<PARTS>(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
+                        sum_slices<BY == kSlicesByExpand>(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
                         split_bf16(f0, f1, ph, pl);
                     } else {
                         ph = ld16(sy.v_hi + off);
@@ -1602,7 +1611,7 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
 #undef LORA_DMA_WAIT
 }
 
-template <bool BIG, bool VF32, bool PARTS = false>
+template <bool BIG, bool VF32, Slices BY = kSlicesByShrink>
 static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int32_t *__restrict__ perm,
                                                        const uint16_t *__restrict__ arena,
                                                        const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
@@ -1619,13 +1628,13 @@ static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int3
             expand_big_body<8, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
     } else {
         if (r8 <= 32)
-            expand_body<1, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<1, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 64)
-            expand_body<2, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<2, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 128)
-            expand_body<4, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<4, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
         else
-            expand_body<8, false, VF32, PARTS>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<8, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
     }
 }
 
@@ -2022,7 +2031,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_parts(const Unit *__rest
 {
     __shared__ __attribute__((aligned(16))) char lds[kExpandLds];
     LORA_CLOCK_E(0);
-    expand_dispatch<false, false, true>(units[blockIdx.x], nullptr, arena, nullptr, y, ldy, lds, sy);
+    expand_dispatch<false, false, kSlicesByExpand>(units[blockIdx.x], nullptr, arena, nullptr, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 
@@ -2042,7 +2051,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_apply_fused(const Unit *__restr
     if (b < n_shrink)
         shrink_body(shrink_units[b], arena, x, ldx, in, k_slice_len, parts, n_slices, slice_stride, lds, sy);
     else
-        expand_dispatch<false, false>(expand_units[b - n_shrink], perm, arena, nullptr, y, ldy, lds, sy);
+        expand_dispatch<false, false, kSlicesByWaiting>(expand_units[b - n_shrink], perm, arena, nullptr, y, ldy, lds, sy);
 }
 
 // A mixed batch in two launches on one queue: the token-heavy groups' units first in the grid (they
@@ -2071,7 +2080,7 @@ __global__ __launch_bounds__(kThreads, ANY ? 2 : 4) void k_shrink_mixed(
     LORA_CLOCK(4);
 }
 
-template <bool PARTS>
+template <Slices BY>
 __global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__restrict__ big_units, int n_big,
                                                               const Unit *__restrict__ units,
                                                               const int32_t *__restrict__ perm,
@@ -2084,7 +2093,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__rest
     if (b < n_big)
         expand_dispatch<true, false>(big_units[b], perm, arena, nullptr, y, ldy, lds, sy);
     else
-        expand_dispatch<false, false, PARTS>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
+        expand_dispatch<false, false, BY>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 
@@ -2943,10 +2952,10 @@ hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_
     if (total <= 0) return hipSuccess;
     if (!sync) return hipErrorInvalidValue;
     if (sync->parts)
-        hipLaunchKernelGGL(k_expand_mixed<true>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
+        hipLaunchKernelGGL(k_expand_mixed<kSlicesByExpand>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
                            c.perm, c.arena, y, ldy, make_sync(sync, 0));
     else
-        hipLaunchKernelGGL(k_expand_mixed<false>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
+        hipLaunchKernelGGL(k_expand_mixed<kSlicesByShrink>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
                            c.perm, c.arena, y, ldy, make_sync(sync, 0));
     return hipGetLastError();
 }

@@ -37,9 +37,9 @@ def test_spilled_registers(kernel, most):
     assert hits[0][".vgpr_spill_count"] <= most, hits[0][".vgpr_spill_count"]
 
 
-def _preloaded():
-    """{kernel symbol: scalar registers of arguments that are there when a wavefront starts} from the kernel descriptors."""
-    data, found, at = open(build.LIB, "rb").read(), {}, 0
+def _dynamic_symbols():
+    """(offset of the code object, its sections' headers, symbol's entry, name) of every dynamic symbol of the library's AMDGPU code."""
+    data, at = open(build.LIB, "rb").read(), 0
     num = lambda at, size: int.from_bytes(data[at:at + size], "little")
     while (at := data.find(b"\x7fELF", at)) >= 0:
         if num(at + 18, 2) == 224:  # EM_AMDGPU
@@ -50,11 +50,30 @@ def _preloaded():
                 names = at + num(sections[num(sec + 40, 4)] + 24, 8)
                 for sym in range(at + num(sec + 24, 8), at + num(sec + 24, 8) + num(sec + 32, 8), 24):
                     name = data[names + num(sym, 4):data.index(b"\0", names + num(sym, 4))].decode()
-                    if name.endswith(".kd"):
-                        home = sections[num(sym + 6, 2)]
-                        kd = at + num(home + 24, 8) + num(sym + 8, 8) - num(home + 16, 8)
-                        found[name[:-3]] = num(kd + 58, 2) & 127
+                    yield num, at, sections, sym, name
         at += 4
+
+
+def _code_bytes(kernel):
+    hits = [num(sym + 16, 8) for num, _, _, sym, name in _dynamic_symbols() if "4lora" in name and kernel in name and not name.endswith(".kd")]
+    assert len(hits) == 1
+    return hits[0]
+
+
+def test_expand_kernels_that_read_complete_v_hold_no_code_that_adds_slices_up():
+    """With it, never run, they took other registers, and a mixed launch 4 % longer."""
+    assert _code_bytes("k_expandILb0ELb0E") < _code_bytes("k_expand_partsE")
+    assert _code_bytes("k_expand_mixedILNS_6SlicesE0E") < _code_bytes("k_expand_mixedILNS_6SlicesE1E")
+
+
+def _preloaded():
+    """{kernel symbol: scalar registers of arguments that are there when a wavefront starts} from the kernel descriptors."""
+    found = {}
+    for num, at, sections, sym, name in _dynamic_symbols():
+        if name.endswith(".kd"):
+            home = sections[num(sym + 6, 2)]
+            kd = at + num(home + 24, 8) + num(sym + 8, 8) - num(home + 16, 8)
+            found[name[:-3]] = num(kd + 58, 2) & 127
     return found
 
 
