@@ -114,7 +114,6 @@ struct lora_segments {
         table_bytes;
     int top_rank;           // the largest padded rank the batch uses
     bool has_big_units;     // some unit holds more than 16 tokens (token-heavy groups)
-    bool heavy_small_expand;  // a token-heavy group above kBigExpandMaxRank (none, as the pool's ranks stand): shrunk by token-heavy units, expanded by 16-token units
     bool wide;              // decode shrink units span all of k (work groups of 16 wavefronts, no partial sums)
     int wide_slices, wide_slice_len;  // the k-slices such a work group's wavefronts divide k into
     int n_prefill_hi;       // how many of prefill_units are above rank 64
@@ -596,10 +595,9 @@ static const int kWholeKMaxIn = 18432;
 // they split the rank rows and share 64 tokens of x through LDS (A^T is then loaded once per 64
 // tokens); above rank 192, 32 tokens (the accumulators of 64 tokens x 256 rank rows do not fit the registers).
 static int heavy_tile(int r8) { return r8 <= 64 || r8 > 192 ? 32 : 64; }
-// token-heavy groups take 64-token expand units up to this padded rank (a strip's tile of B^T, 128 columns x
-// rank, must fit the kernel's 64 KiB of LDS): every rank the pool holds
-static const int kBigExpandMaxRank = 256;
-static_assert(kBigExpandMaxRank >= LORA_MAX_RANK_PADDED, "the 16-token expand units of token-heavy groups are gone");
+// Token-heavy groups take 64-token expand units, whatever their rank: 16-token ones would look for k-slices that
+// token-heavy shrink units do not leave.
+static_assert(LORA_MAX_RANK_PADDED * 128 * 2 <= 64 * 1024, "a strip's tile of B^T, 128 columns x rank, fits the kernel's 64 KiB of LDS");
 using lora::kComputeUnits;  // a whole-k launch within this many units is one round
 
 // K-slices of a launch's token-heavy shrink units: as many as keep it shortest by an estimate.  A compute unit passes
@@ -1271,7 +1269,6 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     }
     sg->n_sync = n_sync;
     sg->has_big_units = false;
-    sg->heavy_small_expand = false;
     sg->n_prefill_hi = 0;
     // (per projection, whatever the number of projections: lora_apply_multi gives the bits of separate applies)
     int heavy_k_slices = 1;
@@ -1301,7 +1298,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     // launch at few such units (it then lasts as long as one of them; see kBigRunsWorkGroupsPerComputeUnit)
     int64_t big_tiles = 0;
     for (const SegRec &r : sg->segs)
-        if (r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch && r.r8 <= kBigExpandMaxRank) big_tiles += (r.ntok + 63) / 64;
+        if (r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch) big_tiles += (r.ntok + 63) / 64;
     int big_runs = 4;
     for (int runs = 64; runs >= 8 && big_runs == 4 && !(lean && sg->opts.big_runs_max_units < 0); runs /= 2)
         if (big_tiles * std::min(runs, out / 128) * n_projections <= opt_big_runs_max_units(sg)) big_runs = runs;
@@ -1314,7 +1311,6 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
             // (heavy_k_slices > 1) a slice of it, the slices' sums meeting at the counter of the tile's
             // first 16 tokens
             sg->has_big_units = true;
-            if (r.r8 > kBigExpandMaxRank) sg->heavy_small_expand = true;
             const int tile = heavy_tile(r.r8);
             for (int tok0 = 0; tok0 < r.ntok; tok0 += tile)
                 for (int ks = 0; ks < heavy_k_slices; ++ks) {
@@ -1368,7 +1364,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         // (16 per wavefront, v kept in registers) and a quarter of the columns, at least 512, or fewer
         int cols = expand_cols_per_unit(r.r8, out);
         int etile = lora::kTokTile;
-        if (token_heavy && r.r8 <= kBigExpandMaxRank) {
+        if (token_heavy) {
             etile = 64;
             cols = std::min(out, std::max(big_runs > 4 ? 128 : 512, (out / big_runs + 127) / 128 * 128));
         }
@@ -1642,7 +1638,6 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         shift(sg->expand_units, n2, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         shift(sg->expand_big_units, n3, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         sg->n_prefill_hi += tmp->n_prefill_hi;
-        sg->heavy_small_expand = sg->heavy_small_expand || tmp->heavy_small_expand;
         sg->mpool_ids.push_back(pools[q]->id);
         sg->msegs.push_back(tmp->segs);
         sg->mepochs.push_back(tmp->seg_epoch);
@@ -2381,10 +2376,8 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
             return LORA_OK;
         }
         hipStream_t sd = s;
-        // not when a token-heavy group's v is read by 16-token expand units (groups above kBigExpandMaxRank):
-        // those would sit on the side stream, which does not wait for the token-heavy shrink launch
-        const bool split = opt_side_stream(sg) && sg->has_big_units && !sg->heavy_small_expand &&
-                           cs.n_units >= kSideStreamMinUnits && (may_create || (sg->side && sg->fork && sg->join));
+        const bool split = opt_side_stream(sg) && sg->has_big_units && cs.n_units >= kSideStreamMinUnits &&
+                           (may_create || (sg->side && sg->fork && sg->join));
         if (split) {
             if (!msg->side) HIP_TRY(hipStreamCreateWithFlags(&msg->side, hipStreamNonBlocking));
             // the two events order launches of this device among themselves and nothing reads them on

@@ -1256,18 +1256,15 @@ static __device__ __forceinline__ void load_v_operand(const float *__restrict__ 
     vlo = as_bf16x8(pl);
 }
 
-// KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).  A unit of several blocks of 16 tokens (BIG; none is planned
-// for this body now) keeps the weights of a column pass in registers while the token blocks go by, one k step of them.
+// KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).
 // BY: where v comes from, unless it is the caller's (VF32).
-template <int KSTEPS, bool BIG, bool VF32, Slices BY>
-static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t *__restrict__ perm,
-                                                   const uint16_t *__restrict__ arena,
+template <int KSTEPS, bool VF32, Slices BY>
+static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t *__restrict__ arena,
                                                    const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
 {
     constexpr int P = KSTEPS < 4 ? KSTEPS : 4;  // wavefronts that share one strip (each a part of the rank)
     constexpr int S = 4 / P;                    // strips per pass of the work group
     constexpr int ITEMS = KSTEPS / P;           // k steps per wavefront (1, or 2 for rank > 128)
-    static_assert(!BIG || ITEMS == 1, "the first block's second k step overwrites w");
     float(*part)[kTokTile][kPartRow] = reinterpret_cast<float(*)[kTokTile][kPartRow]>(lds);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1275,22 +1272,21 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
     const int n = lane & 15;
     const int kq = lane >> 4;
     const int r8 = u.r8;
-    const int ntok_all = u.ntok;
+    const int ntok = u.ntok;
     const int ncols = u.pn;
     const uint4 zero = {0u, 0u, 0u, 0u};
     const int my_strip = wave / P;
     const int my_part = wave % P;
-    const int32_t *toks = BIG ? perm + u.perm_off : u.tok;
 
-    // epilogue role of this thread: token e_tok of the block, 8 columns starting at 8*e_cg of every strip
+    // epilogue role of this thread: token e_tok, 8 columns starting at 8*e_cg of every strip
     const int e_tok = tid >> 4;
     const int e_cg = tid & 15;
+    const bool e_ok = e_tok < ntok;
     const float scale = u.scale;
-    // The row of y this thread updates in the first block of tokens, fetched before anything else: a
-    // wavefront's loads return in request order, so requested behind the weights it would come back
-    // with the last of them, and the loads of y (which need it) would only start then, a second trip
-    // to memory on the unit's critical path.
-    const int64_t first_row = toks[e_tok < min(kTokTile, ntok_all) ? e_tok : 0];
+    // The row of y this thread updates, fetched before anything else: a wavefront's loads return in request order, so
+    // requested behind the weights it would come back with the last of them, and the loads of y (which need it) would
+    // only start then, a second trip to memory on the unit's critical path.
+    const int64_t row = u.tok[e_ok ? e_tok : 0];
     __builtin_amdgcn_sched_barrier(0);
 
     int jc[ITEMS];
@@ -1301,8 +1297,8 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
         j_ok[it] = j < r8;
         jc[it] = j_ok[it] ? j : 0;
     }
-    bool first = true;
 
+#pragma unroll 1  // else its first pass is taken out of the loop: half as much code again
     for (int c0 = 0; c0 < ncols; c0 += S * kStrip) {
         const int cs = c0 + my_strip * kStrip;  // this wavefront's strip
         const bool strip_ok = cs < ncols;
@@ -1318,119 +1314,91 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const int32_t 
         // nothing that needs the row index (a wait for its load) moves up in front of these requests
         __builtin_amdgcn_sched_barrier(0);
 
-        // one block of 16 tokens: this thread's share of y and this wavefront's v operand
-        struct Blk {
-            uint4 yv[S];
-            uint4 vh[ITEMS], vl[ITEMS];
-            uint16_t *e_y;
-            int ntok;
-        };
-        auto load_blk = [&](int t0, Blk &bk) __attribute__((always_inline)) {
-            bk.ntok = min(kTokTile, ntok_all - t0);
-            const bool e_ok = e_tok < bk.ntok;
-            const int64_t row = t0 == 0 ? first_row : (int64_t)toks[e_ok ? t0 + e_tok : 0];
-            bk.e_y = y + row * ldy + u.p0 + 8 * e_cg;
+        uint16_t *e_y = y + row * ldy + u.p0 + 8 * e_cg;
+        uint4 yv[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            // no per-lane condition around the 16-byte load (it would be split into four masked
+            // 4-byte loads): threads without a token read the unit's first token's row
+            yv[s] = zero;
+            if (c0 + s * kStrip < ncols) yv[s] = ld16_stream(e_y + c0 + s * kStrip);
+        }
+        // (single launch) y and the weights of the first k step are on their way while v is waited for
+        if (BY == kSlicesByWaiting && c0 == 0) wait_for(sy, u.sync_idx, u.sync_n);
+        uint4 vh[ITEMS], vl[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const bool ok = (n < ntok) && j_ok[it];
+            const int64_t off = u.v_off + (int64_t)(ok ? n : 0) * r8 + jc[it];
+            uint4 ph, pl;
+            if (VF32) {
+                bf16x8 h, l;
+                load_v_operand(v_in + off, ok, h, l);
+                ph = __builtin_bit_cast(uint4, h);
+                pl = __builtin_bit_cast(uint4, l);
+            } else if (BY == kSlicesByShrink) {
+                ph = ld16(sy.v_hi + off);
+                pl = ld16(sy.v_lo + off);
+            } else {
+                f32x4 f0, f1;
+                sum_slices<BY == kSlicesByExpand>(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
+                split_bf16(f0, f1, ph, pl);
+            }
+            vh[it] = ok ? ph : zero;
+            vl[it] = ok ? pl : zero;
+        }
+
+        if (c0 > 0) __syncthreads();  // the previous pass's partial tiles have been consumed
+        f32x4 acc[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bf16x8 ww = as_bf16x8(j_ok[it] ? w[b] : zero);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vh[it]), ww, acc[b], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vl[it]), ww, acc[b], 0, 0, 0);
+                // ranks above 128: the second k step's operand takes the register as soon as it is free
+                if (it + 1 < ITEMS) w[b] = ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
+            }
+        }
+        if (strip_ok) {
+            // lane (n, kq) holds tokens 4*kq + e, columns 8*n + b
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int tok = 4 * kq + e;
+                if (tok < ntok) {
+                    const f32x4 lo = {acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+                    const f32x4 hi = {acc[4][e], acc[5][e], acc[6][e], acc[7][e]};
+                    *reinterpret_cast<f32x4 *>(&part[wave][tok][8 * n]) = lo;
+                    *reinterpret_cast<f32x4 *>(&part[wave][tok][8 * n + 4]) = hi;
+                }
+            }
+        }
+        __syncthreads();
+        if (e_ok) {
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                // no per-lane condition around the 16-byte load (it would be split into four masked
-                // 4-byte loads): threads without a token read the unit's first token's row
-                bk.yv[s] = zero;
-                if (c0 + s * kStrip < ncols) bk.yv[s] = ld16_stream(bk.e_y + c0 + s * kStrip);
-            }
-            // (single launch) y and the weights of the first k step are on their way while v is waited for
-            if (BY == kSlicesByWaiting && first) wait_for(sy, u.sync_idx, u.sync_n);
+                if (c0 + s * kStrip < ncols) {
+                    f32x4 d0 = *reinterpret_cast<const f32x4 *>(&part[s * P][e_tok][8 * e_cg]);
+                    f32x4 d1 = *reinterpret_cast<const f32x4 *>(&part[s * P][e_tok][8 * e_cg + 4]);
 #pragma unroll
-            for (int it = 0; it < ITEMS; ++it) {
-                const bool ok = (n < bk.ntok) && j_ok[it];
-                const int64_t off = u.v_off + (int64_t)(ok ? t0 + n : 0) * r8 + jc[it];
-                uint4 ph, pl;
-                if (!VF32) {
-                    if (BY != kSlicesByShrink) {
-                        f32x4 f0, f1;
-                        sum_slices<BY == kSlicesByExpand>(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
-                        split_bf16(f0, f1, ph, pl);
-                    } else {
-                        ph = ld16(sy.v_hi + off);
-                        pl = ld16(sy.v_lo + off);
+                    for (int p = 1; p < P; ++p) {
+                        d0 += *reinterpret_cast<const f32x4 *>(&part[s * P + p][e_tok][8 * e_cg]);
+                        d1 += *reinterpret_cast<const f32x4 *>(&part[s * P + p][e_tok][8 * e_cg + 4]);
                     }
-                } else {
-                    bf16x8 h, l;
-                    load_v_operand(v_in + off, ok, h, l);
-                    ph = __builtin_bit_cast(uint4, h);
-                    pl = __builtin_bit_cast(uint4, l);
-                }
-                bk.vh[it] = ok ? ph : zero;
-                bk.vl[it] = ok ? pl : zero;
-            }
-        };
-
-        // all of the unit's y and v go out at once (up to 4 blocks of 16 tokens), so that the HBM
-        // latency of y is paid once per column pass, not once per block
-        constexpr int NB = BIG ? 4 : 1;
-        Blk blk[NB];
-#pragma unroll
-        for (int ib = 0; ib < NB; ++ib)
-            if (ib * kTokTile < ntok_all) load_blk(ib * kTokTile, blk[ib]);
-#pragma unroll
-        for (int ib = 0; ib < NB; ++ib) {
-            if (ib * kTokTile >= ntok_all) break;
-            Blk &cur = blk[ib];
-            if (!first) __syncthreads();  // the previous block's partial tiles have been consumed
-            first = false;
-            const int ntok = cur.ntok;
-            const bool e_ok = e_tok < ntok;
-
-            f32x4 acc[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int it = 0; it < ITEMS; ++it) {
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    const bf16x8 ww = as_bf16x8(j_ok[it] ? w[b] : zero);
-                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(cur.vh[it]), ww, acc[b], 0, 0, 0);
-                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(cur.vl[it]), ww, acc[b], 0, 0, 0);
-                    // ranks above 128: the second k step's operand takes the register as soon as it is free
-                    if (it + 1 < ITEMS) w[b] = ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
-                }
-            }
-            if (strip_ok) {
-                // lane (n, kq) holds tokens 4*kq + e, columns 8*n + b
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int tok = 4 * kq + e;
-                    if (tok < ntok) {
-                        const f32x4 lo = {acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
-                        const f32x4 hi = {acc[4][e], acc[5][e], acc[6][e], acc[7][e]};
-                        *reinterpret_cast<f32x4 *>(&part[wave][tok][8 * n]) = lo;
-                        *reinterpret_cast<f32x4 *>(&part[wave][tok][8 * n + 4]) = hi;
-                    }
-                }
-            }
-            __syncthreads();
-            if (e_ok) {
-#pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    if (c0 + s * kStrip < ncols) {
-                        f32x4 d0 = *reinterpret_cast<const f32x4 *>(&part[s * P][e_tok][8 * e_cg]);
-                        f32x4 d1 = *reinterpret_cast<const f32x4 *>(&part[s * P][e_tok][8 * e_cg + 4]);
-#pragma unroll
-                        for (int p = 1; p < P; ++p) {
-                            d0 += *reinterpret_cast<const f32x4 *>(&part[s * P + p][e_tok][8 * e_cg]);
-                            d1 += *reinterpret_cast<const f32x4 *>(&part[s * P + p][e_tok][8 * e_cg + 4]);
-                        }
-                        const uint4 yy = cur.yv[s];
-                        uint4 o;
-                        o.x = pack_bf16_rne(bf16_bits_to_f32(yy.x & 0xFFFFu) + scale * d0[0],
-                                            __uint_as_float(yy.x & 0xFFFF0000u) + scale * d0[1]);
-                        o.y = pack_bf16_rne(bf16_bits_to_f32(yy.y & 0xFFFFu) + scale * d0[2],
-                                            __uint_as_float(yy.y & 0xFFFF0000u) + scale * d0[3]);
-                        o.z = pack_bf16_rne(bf16_bits_to_f32(yy.z & 0xFFFFu) + scale * d1[0],
-                                            __uint_as_float(yy.z & 0xFFFF0000u) + scale * d1[1]);
-                        o.w = pack_bf16_rne(bf16_bits_to_f32(yy.w & 0xFFFFu) + scale * d1[2],
-                                            __uint_as_float(yy.w & 0xFFFF0000u) + scale * d1[3]);
-                        st16_stream(cur.e_y + c0 + s * kStrip, o);
-                    }
+                    const uint4 yy = yv[s];
+                    uint4 o;
+                    o.x = pack_bf16_rne(bf16_bits_to_f32(yy.x & 0xFFFFu) + scale * d0[0],
+                                        __uint_as_float(yy.x & 0xFFFF0000u) + scale * d0[1]);
+                    o.y = pack_bf16_rne(bf16_bits_to_f32(yy.y & 0xFFFFu) + scale * d0[2],
+                                        __uint_as_float(yy.y & 0xFFFF0000u) + scale * d0[3]);
+                    o.z = pack_bf16_rne(bf16_bits_to_f32(yy.z & 0xFFFFu) + scale * d1[0],
+                                        __uint_as_float(yy.z & 0xFFFF0000u) + scale * d1[1]);
+                    o.w = pack_bf16_rne(bf16_bits_to_f32(yy.w & 0xFFFFu) + scale * d1[2],
+                                        __uint_as_float(yy.w & 0xFFFF0000u) + scale * d1[3]);
+                    st16_stream(e_y + c0 + s * kStrip, o);
                 }
             }
         }
@@ -1628,13 +1596,13 @@ static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int3
             expand_big_body<8, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
     } else {
         if (r8 <= 32)
-            expand_body<1, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<1, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 64)
-            expand_body<2, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<2, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 128)
-            expand_body<4, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<4, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
         else
-            expand_body<8, false, VF32, BY>(u, perm, arena, v_in, y, ldy, lds, sy);
+            expand_body<8, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
     }
 }
 
@@ -2010,7 +1978,7 @@ __global__ __launch_bounds__(kThreads) void k_shrink(const Unit *__restrict__ un
     LORA_CLOCK(4);
 }
 
-// BIG: units of up to 64 tokens (token-heavy groups), token indices from perm, the next token block's
+// BIG: units of up to 64 tokens (token-heavy groups), token indices from perm, the next strip's
 // loads in flight while the current one computes.  VF32: v is fp32 from the caller (stand-alone expand).
 template <bool BIG, bool VF32>
 __global__ __launch_bounds__(kThreads, BIG ? 2 : 4) void k_expand(const Unit *__restrict__ units,
