@@ -223,19 +223,23 @@ enum Slices {
     kSlicesByWaiting  // the same in one launch, behind the wait for the tile's shrink units
 };
 
-// sum of the k-slices' partial sums of 8 consecutive v elements, in slice order.  EARLIER: of an earlier launch, else read
-// through to memory.
-template <bool EARLIER = false>
-static __device__ __forceinline__ void sum_slices(const float *__restrict__ src, int n_slices, int64_t slice_stride,
-                                                  f32x4 &f0, f32x4 &f1)
+// the k-slices' partial sums of 8 consecutive v elements.  EARLIER: of an earlier launch, else read through to memory.
+template <bool EARLIER>
+static __device__ __forceinline__ void load_slices(const float *__restrict__ src, int n_slices, int64_t slice_stride,
+                                                   f32x4 (&p0)[kMaxSlices], f32x4 (&p1)[kMaxSlices])
 {
-    f32x4 p0[kMaxSlices], p1[kMaxSlices];
 #pragma unroll
     for (int sl = 0; sl < kMaxSlices; ++sl) {
         const int64_t off = (int64_t)(sl < n_slices ? sl : 0) * slice_stride;
         p0[sl] = EARLIER ? *reinterpret_cast<const f32x4 *>(src + off) : ld_through_f32x4(src + off);
         p1[sl] = EARLIER ? *reinterpret_cast<const f32x4 *>(src + off + 4) : ld_through_f32x4(src + off + 4);
     }
+}
+
+// their sum, in slice order
+static __device__ __forceinline__ void add_slices(const f32x4 (&p0)[kMaxSlices], const f32x4 (&p1)[kMaxSlices], int n_slices,
+                                                  f32x4 &f0, f32x4 &f1)
+{
     f0 = p0[0];
     f1 = p1[0];
 #pragma unroll
@@ -361,8 +365,9 @@ static __device__ __forceinline__ void shrink_body(const Unit &u, const uint16_t
                 const int tasks = ntok * (u.r8 >> 3);
                 const float vs = sy.scale_v ? u.scale : 1.f;
                 for (int task = lane; task < tasks; task += 64) {
-                    f32x4 f0, f1;
-                    sum_slices(v_out + tile_off + 8 * task, n_slices, slice_stride, f0, f1);
+                    f32x4 p0[kMaxSlices], p1[kMaxSlices], f0, f1;
+                    load_slices<false>(v_out + tile_off + 8 * task, n_slices, slice_stride, p0, p1);
+                    add_slices(p0, p1, n_slices, f0, f1);
                     uint4 ph, pl;
                     split_bf16(vs * f0, vs * f1, ph, pl);
                     st_through_u16x8(sy.v_hi + tile_off + 8 * task, ph);
@@ -1258,7 +1263,8 @@ static __device__ __forceinline__ void load_v_operand(const float *__restrict__ 
 
 // KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).
 // BY: where v comes from, unless it is the caller's (VF32).
-template <int KSTEPS, bool VF32, Slices BY>
+// ROOM: a kernel of two work groups per compute unit (k_expand_mixed), with registers for both k steps' weights of a rank above 128.
+template <int KSTEPS, bool VF32, Slices BY, bool ROOM>
 static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t *__restrict__ arena,
                                                    const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
 {
@@ -1297,6 +1303,10 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
         j_ok[it] = j < r8;
         jc[it] = j_ok[it] ? j : 0;
     }
+    // where this lane's piece of v begins (its token's row, k step it of the wavefront)
+    auto v_at = [&](int it) __attribute__((always_inline)) {
+        return u.v_off + (int64_t)(n < ntok && j_ok[it] ? n : 0) * r8 + jc[it];
+    };
 
 #pragma unroll 1  // else its first pass is taken out of the loop: half as much code again
     for (int c0 = 0; c0 < ncols; c0 += S * kStrip) {
@@ -1305,10 +1315,24 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
         // this lane's piece of sub-block 0, rank piece 0 of the wavefront's strip; sub-block b is
         // 16*r8 elements further, rank piece kp 128 elements further
         const uint16_t *brow = arena + u.w_off + (int64_t)(strip_ok ? cs : 0) * r8 + n * 8;
-        // weights: row (column of y) cs + 8*n + b, 16 bytes at jc, of the wavefront's first k step.  (Ranks above 128, two k
-        // steps: with both requested behind the wait for v a launch of 10 units lasted 6.6 us, now 5.7; 6076 units of 576 -> 11136,
-        // ranks 1 to 256, 52.5 -> 49.6.)
-        uint4 w[8];
+        // ROOM and slices to add up: these are requested first, so that they are added up while the rest is on its way.  (1400 tokens
+        // beside 373 decode ones, 6464 -> 1280, 32.5 -> 32.0 us; 12352 -> 1664 41.3 -> 40.9.)
+        constexpr bool kSlicesFirst = ROOM && BY == kSlicesByExpand;
+        f32x4 p0[ITEMS][kMaxSlices], p1[ITEMS][kMaxSlices];
+        if (kSlicesFirst) {
+#pragma unroll
+            for (int it = 0; it < ITEMS; ++it)
+                load_slices<true>(sy.parts + v_at(it), sy.n_slices, sy.slice_stride, p0[it], p1[it]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // weights: row (column of y) cs + 8*n + b, 16 bytes at jc, of the wavefront's first k step.  Ranks above 128, two k
+        // steps: the second's are requested behind y and v with ROOM, else as the first's registers come free.  (With both requested
+        // behind the wait for v a launch of 10 units lasted 6.6 us, now 5.7; 6076 units of 576 -> 11136, ranks 1 to 256, 52.5 -> 49.6.
+        // Mixed launches, as the registers come free / behind y and v, us per call: 576 -> 7808, 1601 tokens of ranks 1 to 256, 59.2 /
+        // 55.1; 6144 -> 14080 68.9 / 66.4; 832 -> 4480, 4417 tokens, 47.3 / 47.1; but where the units of up to 16 tokens are the fewer,
+        // 10688 -> 2688, 2116 tokens, 54.1 / 54.9, 1344 -> 1920, 3844 tokens, 39.2 / 39.7.)
+        constexpr bool kBoth = ITEMS > 1 && ROOM;
+        uint4 w[8], w2[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) w[b] = ld16_stream(brow + b * 16 * r8 + jc[0] * 16);
         // nothing that needs the row index (a wait for its load) moves up in front of these requests
@@ -1329,23 +1353,29 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
             const bool ok = (n < ntok) && j_ok[it];
-            const int64_t off = u.v_off + (int64_t)(ok ? n : 0) * r8 + jc[it];
             uint4 ph, pl;
             if (VF32) {
                 bf16x8 h, l;
-                load_v_operand(v_in + off, ok, h, l);
+                load_v_operand(v_in + v_at(it), ok, h, l);
                 ph = __builtin_bit_cast(uint4, h);
                 pl = __builtin_bit_cast(uint4, l);
             } else if (BY == kSlicesByShrink) {
-                ph = ld16(sy.v_hi + off);
-                pl = ld16(sy.v_lo + off);
+                ph = ld16(sy.v_hi + v_at(it));
+                pl = ld16(sy.v_lo + v_at(it));
             } else {
+                if (!kSlicesFirst)
+                    load_slices<BY == kSlicesByExpand>(sy.parts + v_at(it), sy.n_slices, sy.slice_stride, p0[it], p1[it]);
                 f32x4 f0, f1;
-                sum_slices<BY == kSlicesByExpand>(sy.parts + off, sy.n_slices, sy.slice_stride, f0, f1);
+                add_slices(p0[it], p1[it], sy.n_slices, f0, f1);
                 split_bf16(f0, f1, ph, pl);
             }
             vh[it] = ok ? ph : zero;
             vl[it] = ok ? pl : zero;
+        }
+        if (kBoth) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) w2[b] = ld16_stream(brow + b * 16 * r8 + jc[ITEMS - 1] * 16);
+            __builtin_amdgcn_sched_barrier(0);
         }
 
         if (c0 > 0) __syncthreads();  // the previous pass's partial tiles have been consumed
@@ -1359,8 +1389,7 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
                 const bf16x8 ww = as_bf16x8(j_ok[it] ? w[b] : zero);
                 acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vh[it]), ww, acc[b], 0, 0, 0);
                 acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vl[it]), ww, acc[b], 0, 0, 0);
-                // ranks above 128: the second k step's operand takes the register as soon as it is free
-                if (it + 1 < ITEMS) w[b] = ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
+                if (it + 1 < ITEMS) w[b] = kBoth ? w2[b] : ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
             }
         }
         if (strip_ok) {
@@ -1579,7 +1608,7 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
 #undef LORA_DMA_WAIT
 }
 
-template <bool BIG, bool VF32, Slices BY = kSlicesByShrink>
+template <bool BIG, bool VF32, Slices BY = kSlicesByShrink, bool ROOM = false>
 static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int32_t *__restrict__ perm,
                                                        const uint16_t *__restrict__ arena,
                                                        const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
@@ -1596,13 +1625,13 @@ static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int3
             expand_big_body<8, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
     } else {
         if (r8 <= 32)
-            expand_body<1, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+            expand_body<1, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 64)
-            expand_body<2, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+            expand_body<2, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
         else if (r8 <= 128)
-            expand_body<4, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+            expand_body<4, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
         else
-            expand_body<8, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+            expand_body<8, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
     }
 }
 
@@ -2061,7 +2090,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__rest
     if (b < n_big)
         expand_dispatch<true, false>(big_units[b], perm, arena, nullptr, y, ldy, lds, sy);
     else
-        expand_dispatch<false, false, BY>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
+        expand_dispatch<false, false, BY, true>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 

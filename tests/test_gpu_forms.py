@@ -335,6 +335,8 @@ def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
     ((2048, 8192), [(1, 8)] * 40),                                      # few shrink units, many expand units
     ((2048, 8192), [(1, 8)] * 150),                                     # many more expand units than shrink units: the shrink's
     ((2048, 4096), [(1000, 16), (40, 8)] + [(2, 24)] * 20),             # the same beside token-heavy groups
+    ((1152, 4096), [(1000, 16), (17, 136), (3, 255), (9, 72), (40, 200)]),  # the same with ranks above 128, several strips a unit
+    ((4096, 640), [(1000, 16), (17, 136), (3, 255), (9, 24), (40, 200), (900, 64)]),  # added up by the expand units, above 128 too
 ])
 def test_k_slices_added_up_by_the_expand_units(shape, groups):
     """Every form of the batch gives the bits of every other, and the oracle's rows: two launches, one, four, replayed."""
