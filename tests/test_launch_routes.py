@@ -314,3 +314,16 @@ def test_a_caller_s_table_without_room_for_the_faster_form(recorder, in_features
             assert b.launches(recorder, first, call) == expect
         L.lora_segments_destroy(first)
     b.close()
+
+
+# ---- the binding's own checks of arguments --------------------------------------------------------------------------
+@pytest.mark.parametrize("adapter", ["0", None, 0.0, ctypes.c_int32(0)])
+def test_an_adapter_that_is_no_whole_number_is_a_type_error(recorder, adapter):
+    """... where A and B come from device memory, which nothing else looks at the number for; any kind of whole number is taken."""
+    b = Batch(64, 128, [(1, 8)])
+    pool = b.pools[0]
+    device = torch.zeros(64, 8, dtype=torch.bfloat16), torch.zeros(8, 128, dtype=torch.bfloat16)
+    with pytest.raises(TypeError):
+        L.lora_pool_load(pool, adapter, *device)
+    L.lora_pool_load(pool, np.int64(0), *device)
+    b.close()
