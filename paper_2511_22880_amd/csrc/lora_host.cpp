@@ -117,6 +117,8 @@ struct lora_segments {
     bool wide;              // decode shrink units span all of k (work groups of 16 wavefronts, no partial sums)
     int wide_slices, wide_slice_len;  // the k-slices such a work group's wavefronts divide k into
     int n_prefill_hi;       // how many of prefill_units are above rank 64
+    int n_heavy_units;      // how many of them hold tokens (the others fill the XCDs' lists up)
+    int heavy_top_rank;     // their largest padded rank
     int heavy_k_slices;     // k-slices of the token-heavy shrink units (1: they take the whole of k)
     bool decode_fused;      // whole-k decode batch that can run as one launch (see finish_decode_fused)
     int fused_grid;         // work groups of that launch
@@ -1270,6 +1272,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     sg->n_sync = n_sync;
     sg->has_big_units = false;
     sg->n_prefill_hi = 0;
+    sg->heavy_top_rank = 0;
     // (per projection, whatever the number of projections: lora_apply_multi gives the bits of separate applies)
     int heavy_k_slices = 1;
     if (sg->n_k_slices >= 2) {
@@ -1311,6 +1314,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
             // (heavy_k_slices > 1) a slice of it, the slices' sums meeting at the counter of the tile's
             // first 16 tokens
             sg->has_big_units = true;
+            sg->heavy_top_rank = std::max(sg->heavy_top_rank, r.r8);
             const int tile = heavy_tile(r.r8);
             for (int tok0 = 0; tok0 < r.ntok; tok0 += tile)
                 for (int ks = 0; ks < heavy_k_slices; ++ks) {
@@ -1407,6 +1411,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     }
 
     order_units_by_xcd(sg->shrink_units);
+    sg->n_heavy_units = (int)sg->prefill_units.size();
     order_heavy_units_by_xcd(sg->prefill_units);
 
     finish_decode_fused(sg, want_fused, pool->in_features);
@@ -1638,6 +1643,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         shift(sg->expand_units, n2, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         shift(sg->expand_big_units, n3, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         sg->n_prefill_hi += tmp->n_prefill_hi;
+        sg->n_heavy_units += tmp->n_heavy_units;
         sg->mpool_ids.push_back(pools[q]->id);
         sg->msegs.push_back(tmp->segs);
         sg->mepochs.push_back(tmp->seg_epoch);
@@ -2094,6 +2100,8 @@ static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_f
     c.perm = (const int32_t *)(sg->dev + sg->off_perm);
     c.arena = arena;
     c.n_units = (int)list.size();
+    c.n_work = kind == kPrefill ? sg->n_heavy_units : c.n_units;
+    c.top_rank = sg->heavy_top_rank;
     c.in_features = in_features;
     c.out_features = out_features;
     c.scale_v = 0;

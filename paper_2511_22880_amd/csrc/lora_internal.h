@@ -80,6 +80,8 @@ struct LaunchCtx {
     const int32_t *perm;
     const uint16_t *arena;
     int n_units;
+    int n_work;    // of n_units, those that hold tokens (lists of token-heavy shrink units are filled up with others)
+    int top_rank;  // lists of token-heavy shrink units: the largest padded rank
     int in_features;
     int out_features;
     // shrink launches that leave v as bf16 hi + lo: store s_a v (rounded to fp32 once, then split) instead of v,
@@ -124,6 +126,17 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
 // `big`: the list holds units of up to 64 tokens (token indices through perm).
 hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16_t *y, int64_t ldy, const SyncArgs *sync,
                          hipStream_t stream);
+
+// Which launches of token-heavy shrink units alone take two work groups a unit, half of the rank rows each (see RankRows in the
+// kernels; units up to rank 32 are not halved).  Counted without the places that only fill lists up: few prompts of unlike ranks have
+// many.  Shrink launch in us, whole / halves: 93 units of ranks up to 219 in 176 places, 1344 features, 12.4 / 9.6, 89 of ranks 8 and
+// 256 in 232, 512 features, 8.9 / 6.0, 104 of ranks 8 to 128 in 152, 896 features, 10.1 / 8.4; one prompt of 2000 tokens,
+// 4096 features, rank 128 (128 units, cut along k) 15.4 / 13.1; beyond, 134 units of ranks 8 and 256, 1536 features, 13.1 / 14.2, 132 of rank
+// 256 cut along k, 3392 features, 19.8 / 21.1, 174 of ranks 8 to 128 12.9 / 14.6, though 154 of ranks 8 to 128, 960 features, 11.5 / 9.2.
+// Nothing above rank 32, in the halves' kernel all the same: 58 units of rank 8, 1536 features, 4.6 / 5.4, 123 of rank 32, 512 features,
+// 4.2 / 4.8, 102 at 2560 features 6.2 / 6.8: it runs two work groups per compute unit where their own runs four.
+constexpr int kHeavyHalvesMaxUnits = kComputeUnits / 2;
+inline bool shrink_in_halves(const LaunchCtx &c) { return c.n_work <= kHeavyHalvesMaxUnits && c.top_rank > 32; }
 
 // Shrink of token-heavy groups: one unit = (group, up to 32 tokens, all rank rows, the whole of k).
 // n_hi = how many of the units are above rank 64: with none, the launch takes the kernel that fits four

@@ -624,18 +624,16 @@ static __device__ __forceinline__ int late_thread()
     return t;
 }
 
-// The rank rows of a token-heavy shrink unit that a work group takes: all of them, or (launches of at most kHeavyHalvesMaxUnits
-// units) one of two halves.  A compute unit passes about 50 GB/s of x and A^T together, so a launch of few units lasts as long as
+// The rank rows of a token-heavy shrink unit that a work group takes: all of them, or (launches of few units, shrink_in_halves) one of
+// two halves.  A compute unit passes about 50 GB/s of x and A^T together, so a launch of few units lasts as long as
 // one of them however many compute units stand idle; halves read x twice (the second time from the L2: both run on one XCD) and every
-// row of A^T once, and nothing is added up between them.  Shrink launch in us,
-// whole / halves: one prompt of 2000 tokens, 4096 features, rank 128 (128 units, cut along k) 15.4 / 13.1, rank 192 18.3 / 16.4, 1024 tokens
-// at 14336 features 29.5 / 23.2; uncut, 1984 features, 2000 tokens (32 units) 17.2 / 14.1, 7900 tokens of rank 192 (124) 21.8 / 18.7.  From
-// more than half a unit per compute unit on: 188 units of rank 256 at 4096 features 16.9 / 18.0, 252 of rank 64 10.5 / 11.2.
+// row of A^T once, and nothing is added up between them.  Shrink launch in us, whole / halves: one prompt of 2000 tokens, 4096 features,
+// rank 128 (128 units, cut along k) 15.4 / 13.1, rank 192 18.3 / 16.4, 1024 tokens at 14336 features 29.5 / 23.2; uncut, 1984 features,
+// 2000 tokens (32 units) 17.2 / 14.1, 7900 tokens of rank 192 (124) 21.8 / 18.7.
 struct RankRows {
     int first, n;  // rank rows first .. first + n - 1 (first a multiple of 16, n of 8)
     int part, of;  // which of how many work groups
 };
-constexpr int kHeavyHalvesMaxUnits = kComputeUnits / 2;
 
 // where element quad i of those rows lies in the unit's v, in quads from its first row; i counts n / 4 quads per token
 static __device__ __forceinline__ int quad_place(const Unit &u, const RankRows &rr, int i)
@@ -2911,7 +2909,7 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
     if (c.n_units <= 0) return hipSuccess;
     if (n_hi < 0 || n_hi > c.n_units) return hipErrorInvalidValue;
     const Sync sy = make_sync(sync, 0, c.scale_v);
-    if (c.n_units <= kHeavyHalvesMaxUnits)
+    if (shrink_in_halves(c))
         hipLaunchKernelGGL(k_shrink_halves, dim3((c.n_units + 7) / 8 * 16), dim3(kThreads), 0, stream, c.units, c.perm, c.arena, x, ldx,
                            c.in_features, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, c.n_units, sy);
     else if (n_hi > 0)

@@ -6,7 +6,7 @@
 #include <cstring>
 #include <string>
 
-static std::string g_log;
+static std::string g_log, g_forms;
 static int g_capturing;
 
 static hipError_t note(const std::string &s)
@@ -14,6 +14,8 @@ static hipError_t note(const std::string &s)
     g_log += s + "\n";
     return hipSuccess;
 }
+// of a launcher that chooses between kernels, the one it takes
+static void form(const char *s) { g_forms += std::string(s) + " "; }
 static std::string num(long long v) { return " " + std::to_string(v); }
 
 extern "C" {
@@ -22,6 +24,13 @@ const char *recorder_take()
     static std::string out;
     out.swap(g_log);
     g_log.clear();
+    return out.c_str();
+}
+const char *recorder_take_forms()
+{
+    static std::string out;
+    out.swap(g_forms);
+    g_forms.clear();
     return out.c_str();
 }
 // 1: the stream captures; 2: it is the legacy stream and a blocking stream captures
@@ -61,7 +70,12 @@ namespace lora {
 hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink" + num(c.n_units)) : hipSuccess; }
 hipError_t launch_shrink_wide(const LaunchCtx &c, bool, const uint16_t *, int64_t, int, int, float *, uint16_t *, uint16_t *, hipStream_t) { return c.n_units ? note("shrink_wide" + num(c.n_units)) : hipSuccess; }
 hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note((big ? "expand_big" : "expand") + num(c.n_units)) : hipSuccess; }
-hipError_t launch_shrink_prefill(const LaunchCtx &c, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int n_slices, int64_t, float *, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink_prefill" + num(c.n_units) + num(n_slices)) : hipSuccess; }
+hipError_t launch_shrink_prefill(const LaunchCtx &c, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int n_slices, int64_t, float *, const SyncArgs *, hipStream_t)
+{
+    if (!c.n_units) return hipSuccess;
+    form(shrink_in_halves(c) ? "halves" : "whole");
+    return note("shrink_prefill" + num(c.n_units) + num(n_slices));
+}
 hipError_t launch_shrink_mixed(const LaunchCtx &h, int, const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return note("shrink_mixed" + num(h.n_units) + num(c.n_units)); }
 hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("expand_mixed" + num(b.n_units) + num(c.n_units)); }
 hipError_t launch_apply_fused(const LaunchCtx &s, const LaunchCtx &e, const uint16_t *, int64_t, int, float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("apply_fused" + num(s.n_units) + num(e.n_units)); }

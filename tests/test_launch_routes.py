@@ -30,7 +30,7 @@ def recorder(tmp_path_factory):
     path, loaded = L.LIB_PATH, L._lib
     L.LIB_PATH, L._lib = so, None
     lib = L.lib()
-    lib.recorder_take.restype = ctypes.c_char_p
+    lib.recorder_take.restype = lib.recorder_take_forms.restype = ctypes.c_char_p
     yield lib
     L.LIB_PATH, L._lib = path, loaded
 
@@ -220,6 +220,33 @@ def test_token_heavy_shrink_units_are_cut_where_that_is_shorter(recorder, in_fea
     # the units' cut does not depend on how many projections share the launch: their sums are the same bits
     b = Batch(in_features, [512, 128, 128], groups)
     assert _heavy_slices(b)[0] == slices
+    b.close()
+
+
+# ---- kernels that a launcher chooses between ----------------------------------------------------------------------
+def _forms(b, lib, call="apply", options=None):
+    seg = b.build(options)
+    lib.recorder_take_forms()
+    b.launches(lib, seg, call)
+    L.lora_segments_destroy(seg)
+    return lib.recorder_take_forms().decode().split()
+
+
+@pytest.mark.parametrize("groups, form", [
+    ([(2048, 40)] * 2, "halves"),                       # 128 units of 32 tokens
+    ([(2048, 40)] * 2 + [(32, 40)], "whole"),           # 129
+    ([(8192, 128)], "halves"),                          # 128 of 64 tokens
+    ([(8192, 128), (64, 128)], "whole"),
+    ([(2048, 32)] * 2, "whole"),                        # nothing above rank 32
+    ([(2048, 32)] + [(2016, 16), (32, 33)], "halves"),
+    ([(3000, 8), (1000, 256)], "halves"),               # 126 units; the XCDs' lists, of equal bytes, are filled up to 320 places
+    ([(3000, 8), (1100, 256)], "whole"),                # 129
+])
+def test_few_token_heavy_shrink_units_as_two_work_groups_each(recorder, groups, form):
+    b = Batch(1984, 128, groups)
+    for call in ("apply", "static", "shrink", "linear"):
+        forms = _forms(b, recorder, call, L.plan_options(heavy_k_cut_max_units=0))
+        assert forms[0] == form
     b.close()
 
 
