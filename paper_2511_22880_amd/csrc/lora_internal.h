@@ -183,6 +183,23 @@ hipError_t launch_decode_fused(const LaunchCtx &shrink, const LaunchCtx &expand,
 // Synchronises the stream.
 hipError_t probe_xcc(unsigned *host_out, int n_work_groups, hipStream_t stream);
 
+// The tiles of lora_linear's batches that take no large ones, 16 rb rows x 16 cb columns: the largest that still make a work group per
+// compute unit.  4096 -> 4096, us per layer of tokens without adapter (eight weights in rotation), tiles of 64 x 64 / 32 x 64 / 32 x 32
+// / 16 x 32: 16 tokens 14.8 / 12.0 / 9.4 / 8.5, 64 tokens 17.7 / 13.1 / 10.8 / 13.0, 128 tokens 18.7 / 14.2 / 18.2 / 23.8, 256 tokens 19.4
+// / 23.1, 512 tokens 36.2 / 48.0 (256 x 256 tiles: 65 to 69 for each of them).
+struct LinSmallTiles {
+    int rb, cb;
+    int64_t n;  // of them
+    int grid() const { return (int)(8 * ((n + 7) / 8)); }  // an eighth of them per XCD
+    bool pairs() const { return grid() > kComputeUnits; }  // k_linear_rounds, two work groups per compute unit
+};
+inline LinSmallTiles linear_small_tiles(int n_places, int out)
+{
+    auto tiles = [&](int rb, int cb) { return LinSmallTiles{rb, cb, (int64_t)((n_places + 16 * rb - 1) / (16 * rb)) * (out / (16 * cb))}; };
+    auto fits = [&](int rb, int cb) { return (n_places + 15) / 16 >= rb && tiles(rb, cb).n >= kComputeUnits; };
+    return fits(4, 4) ? tiles(4, 4) : fits(2, 4) ? tiles(2, 4) : fits(2, 2) ? tiles(2, 2) : tiles(1, 2);
+}
+
 // The adapted layer in one pass over y: y[row] = bf16(x[row] W + s_a v[row] B_a), W in operand order
 // (launch_pack_weight), s_a v as bf16 hi + lo from a shrink launch with scale_v.  n_places places in use;
 // rows[m] = batch row of place m, -1 for none and from n_places to the next multiple of kLinTileM.

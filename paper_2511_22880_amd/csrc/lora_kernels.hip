@@ -2677,14 +2677,14 @@ __global__ __launch_bounds__(kLinThreads, 1) void k_linear_lora(
 }
 
 template <int RB, int CB, int D>
-static void launch_linear_small(const int32_t *rows, const int32_t *start, const LinPiece *pieces, int n_places,
+static void launch_linear_small(const LinSmallTiles &t, const int32_t *rows, const int32_t *start, const LinPiece *pieces, int n_places,
                                 const uint16_t *arena, const uint16_t *w_packed, const uint16_t *x, int64_t ldx, int in,
                                 int out, const uint16_t *v_hi, const uint16_t *v_lo, uint16_t *y, int64_t ldy,
                                 hipStream_t stream)
 {
     const int m_tiles = (n_places + 16 * RB - 1) / (16 * RB);
-    const int grid = 8 * ((m_tiles * (out / (16 * CB)) + 7) / 8);  // an eighth of the tiles per XCD
-    if (grid > kComputeUnits)
+    const int grid = t.grid();
+    if (t.pairs())
         hipLaunchKernelGGL((k_linear_rounds<RB, CB, D>), dim3((unsigned)grid), dim3(64 * kLinRoundsWaves), 0, stream, rows, start,
                            pieces, m_tiles, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy);
     else
@@ -2968,22 +2968,17 @@ hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n
     const int m_big = std::min(blocks->big_tiles, (n_places + kLinTileM - 1) / kLinTileM);
     if (m_big < 0) return hipErrorInvalidValue;
     if (m_big == 0) {
-        // small tiles only: the largest that still make a work group per compute unit.  4096 -> 4096, us per layer
-        // of tokens without adapter (eight weights in rotation), tiles of 64 x 64 / 32 x 64 / 32 x 32 / 16 x 32: 16 tokens 14.8 /
-        // 12.0 / 9.4 / 8.5, 64 tokens 17.7 / 13.1 / 10.8 / 13.0, 128 tokens 18.7 / 14.2 / 18.2 / 23.8, 256 tokens 19.4 / 23.1, 512
-        // tokens 36.2 / 48.0 (256 x 256 tiles: 65 to 69 for each of them).
-        auto tiles = [&](int rb, int cb) { return (int64_t)((n_places + 16 * rb - 1) / (16 * rb)) * (out / (16 * cb)); };
-        auto fits = [&](int rb, int cb) { return (n_places + 15) / 16 >= rb && tiles(rb, cb) >= kComputeUnits; };
+        const LinSmallTiles t = linear_small_tiles(n_places, out);
         auto go = [&](auto rb, auto cb, auto d) {
             launch_linear_small<decltype(rb)::value, decltype(cb)::value, decltype(d)::value>(
-                rows, start, pieces, n_places, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy, stream);
+                t, rows, start, pieces, n_places, arena, w_packed, x, ldx, in, out, v_hi, v_lo, y, ldy, stream);
         };
         using std::integral_constant;
-        if (fits(4, 4))
+        if (t.rb == 4)
             go(integral_constant<int, 4>{}, integral_constant<int, 4>{}, integral_constant<int, 2>{});
-        else if (fits(2, 4))
+        else if (t.cb == 4)
             go(integral_constant<int, 2>{}, integral_constant<int, 4>{}, integral_constant<int, 2>{});
-        else if (fits(2, 2))
+        else if (t.rb == 2)
             go(integral_constant<int, 2>{}, integral_constant<int, 2>{}, integral_constant<int, 3>{});
         else
             go(integral_constant<int, 1>{}, integral_constant<int, 2>{}, integral_constant<int, 4>{});

@@ -67,22 +67,48 @@ const char *hipGetErrorString(hipError_t) { return "error"; }
 }
 
 namespace lora {
-hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note("shrink" + num(c.n_units)) : hipSuccess; }
+static void slices_form(const SyncArgs *sync) { form(!sync ? "callers" : sync->parts ? "by_expand" : "by_shrink"); }
+hipError_t launch_shrink(const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *sync, hipStream_t)
+{
+    if (!c.n_units) return hipSuccess;
+    slices_form(sync);
+    return note("shrink" + num(c.n_units));
+}
 hipError_t launch_shrink_wide(const LaunchCtx &c, bool, const uint16_t *, int64_t, int, int, float *, uint16_t *, uint16_t *, hipStream_t) { return c.n_units ? note("shrink_wide" + num(c.n_units)) : hipSuccess; }
-hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return c.n_units ? note((big ? "expand_big" : "expand") + num(c.n_units)) : hipSuccess; }
+hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, uint16_t *, int64_t, const SyncArgs *sync, hipStream_t)
+{
+    if (!c.n_units) return hipSuccess;
+    if (!big) slices_form(sync);
+    return note((big ? "expand_big" : "expand") + num(c.n_units));
+}
 hipError_t launch_shrink_prefill(const LaunchCtx &c, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int n_slices, int64_t, float *, const SyncArgs *, hipStream_t)
 {
     if (!c.n_units) return hipSuccess;
     form(shrink_in_halves(c) ? "halves" : "whole");
     return note("shrink_prefill" + num(c.n_units) + num(n_slices));
 }
-hipError_t launch_shrink_mixed(const LaunchCtx &h, int, const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *, hipStream_t) { return note("shrink_mixed" + num(h.n_units) + num(c.n_units)); }
-hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("expand_mixed" + num(b.n_units) + num(c.n_units)); }
+hipError_t launch_shrink_mixed(const LaunchCtx &h, int, const LaunchCtx &c, const uint16_t *, int64_t, int, float *, int, int64_t, const SyncArgs *sync, hipStream_t)
+{
+    slices_form(sync);
+    return note("shrink_mixed" + num(h.n_units) + num(c.n_units));
+}
+hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, uint16_t *, int64_t, const SyncArgs *sync, hipStream_t)
+{
+    slices_form(sync);
+    return note("expand_mixed" + num(b.n_units) + num(c.n_units));
+}
 hipError_t launch_apply_fused(const LaunchCtx &s, const LaunchCtx &e, const uint16_t *, int64_t, int, float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("apply_fused" + num(s.n_units) + num(e.n_units)); }
 hipError_t launch_decode_fused(const LaunchCtx &, const LaunchCtx &, int grid, const uint16_t *, int64_t, int, int, uint16_t *, int64_t, unsigned, const SyncArgs *, hipStream_t) { return note("decode_fused" + num(grid)); }
 hipError_t launch_reduce_slices(const float *, int n, int64_t, float *, int64_t, hipStream_t) { return note("reduce_slices" + num(n)); }
 hipError_t launch_pack_adapter(const uint16_t *, const uint16_t *, int, int, int, int, uint16_t *, uint16_t *, hipStream_t) { return hipSuccess; }
-hipError_t launch_linear_lora(const int32_t *, const LinBlock *b, int n_places, const uint16_t *, const uint16_t *, const uint16_t *, int64_t, int, int, const uint16_t *, const uint16_t *, uint16_t *, int64_t, hipStream_t) { return note("linear" + num(n_places) + num(b->big_tiles)); }
+hipError_t launch_linear_lora(const int32_t *, const LinBlock *b, int n_places, const uint16_t *, const uint16_t *, const uint16_t *, int64_t, int, int out, const uint16_t *, const uint16_t *, uint16_t *, int64_t, hipStream_t)
+{
+    if (b->big_tiles == 0) {
+        const LinSmallTiles t = linear_small_tiles(n_places, out);
+        g_forms += std::to_string(16 * t.rb) + "x" + std::to_string(16 * t.cb) + (t.pairs() ? "_in_pairs " : " ");
+    }
+    return note("linear" + num(n_places) + num(b->big_tiles));
+}
 hipError_t launch_pack_weight(const uint16_t *, int, int, uint16_t *, hipStream_t) { return hipSuccess; }
 hipError_t probe_xcc(unsigned *x, int n, hipStream_t)
 {

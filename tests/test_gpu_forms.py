@@ -8,7 +8,8 @@ from paper_2511_22880_amd import workloads as wl
 
 import gpu_util as G
 from test_gpu_parity import _linear_case
-from test_launch_routes import LARGE_TILES, LARGE_TILES_MEETING, LARGE_TILES_PADDED, LINEAR_ORDERS
+from test_launch_routes import (HALVES, LARGE_TILES, LARGE_TILES_MEETING, LARGE_TILES_PADDED, LINEAR_ORDERS, SLICES, TILES_IN_PAIRS,
+                                halves_groups, halves_options)
 
 pytestmark = pytest.mark.gpu
 
@@ -104,20 +105,17 @@ def test_token_heavy_units_cut_along_k(shape, most, sizes, cut):
     dp.close()
 
 
-@pytest.mark.parametrize("slices", [1, 2, 4])
-@pytest.mark.parametrize("in_features, ranks", [
-    (4096, [8, 40, 64]), (4096, [72, 128]), (4160, [136, 192]), (4096, [200, 256]), (64, [33, 100, 255]), (1984, [16, 120, 184]),
-])
+@pytest.mark.parametrize("in_features, ranks, slices", HALVES)
 def test_rank_halves_of_few_token_heavy_units(in_features, ranks, slices):
     """Launches of few token-heavy units: halves of the rank rows, even and not, of units of 32 and 64 tokens, whole and cut along
-    k; the last tile of a group has 5 tokens (one counter for both halves) or 20."""
-    groups = [(384 + (5 if i % 2 else 20) + (700 if i == 0 else 0), r) for i, r in enumerate(ranks)]
-    b = _batch(in_features, 256, groups, idle=3, seed=in_features)
+    k; the last tile of a group has 5 tokens (one counter for both halves) or 20.  (That they take the halves is tested in
+    test_launch_routes.py.)"""
+    b = _batch(in_features, 256, halves_groups(ranks), idle=3, seed=in_features)
     dp = G.DevicePool(b)
     x_bits, y0 = b.x_bits(), b.y0_bits("small")
-    cut = 0 if slices == 1 else 128 // slices * slices
-    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_k_cut_max_units=cut))
-    assert (L.lora_segments_export_units(seg)["shrink"][:, 0] >= 0).sum() <= 128
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=halves_options(ranks, slices))
+    u = L.lora_segments_export_units(seg)["shrink"]
+    assert {int(k) for k in u[u[:, 0] >= 0][:, 5]} == set(range(slices))
     x, y = G.bits_to_dev(x_bits), G.bits_to_dev(y0)
     ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
     for _ in range(2):  # the counters are left as they were found
@@ -275,13 +273,8 @@ def test_linear_large_and_small_tiles_together(case):
 
 
 @pytest.mark.parametrize("in_features", [64, 320, 1024])  # 64-wide pieces of k: fewer than a work group's four wavefronts, 5, 16
-@pytest.mark.parametrize("out_features, groups", [
-    (8192, [(70, 24), (1, 256), (40, 8), (19, 130)]),   # 384 tiles of 64 x 64
-    (8064, [(33, 64), (29, 9), (3, 200)]),              # 378 of 32 x 64
-    (4224, [(9, 16), (23, 72)]),                        # 264 of 32 x 32
-    (8320, [(7, 40), (6, 255)]),                        # 260 of 16 x 32
-])
-def test_linear_small_tiles_beyond_one_per_compute_unit(in_features, out_features, groups):
+@pytest.mark.parametrize("tile, out_features, groups", TILES_IN_PAIRS)
+def test_linear_small_tiles_beyond_one_per_compute_unit(in_features, tile, out_features, groups):
     _linear_case(_batch(in_features, out_features, groups, idle=1, seed=out_features), 0.02, seed=9)
 
 
@@ -326,20 +319,10 @@ def test_linear_keeps_what_an_adapter_holds_to_its_own_tokens():
 
 
 # ---- k-slice units: what the shrink launch leaves, the expand launch adds up -------------------------------------------
-@pytest.mark.parametrize("shape, groups", [
-    ((64, 128), [(1, 1), (17, 8)]),                                     # one slice
-    ((2048, 640), [(16, 24), (17, 33), (1, 256)]),                      # two
-    ((3968, 384), [(5, 129), (33, 64), (16, 8)]),                       # three, the last of them short
-    ((4096, 1152), [(1, 16)] * 24),                                     # four
-    ((4096, 256), [(40, 72), (1000, 16), (3, 136), (15, 255), (31, 8)]),  # beside token-heavy groups
-    ((2048, 8192), [(1, 8)] * 40),                                      # few shrink units, many expand units
-    ((2048, 8192), [(1, 8)] * 150),                                     # many more expand units than shrink units: the shrink's
-    ((2048, 4096), [(1000, 16), (40, 8)] + [(2, 24)] * 20),             # the same beside token-heavy groups
-    ((1152, 4096), [(1000, 16), (17, 136), (3, 255), (9, 72), (40, 200)]),  # the same with ranks above 128, several strips a unit
-    ((4096, 640), [(1000, 16), (17, 136), (3, 255), (9, 24), (40, 200), (900, 64)]),  # added up by the expand units, above 128 too
-])
-def test_k_slices_added_up_by_the_expand_units(shape, groups):
-    """Every form of the batch gives the bits of every other, and the oracle's rows: two launches, one, four, replayed."""
+@pytest.mark.parametrize("shape, groups, by", SLICES)
+def test_k_slices_added_up_by_the_expand_units(shape, groups, by):
+    """Every form of the batch gives the bits of every other, and the oracle's rows: two launches, one, four, each twice.  (Which
+    side adds them up in two is tested in test_launch_routes.py.)"""
     b = _batch(*shape, groups, idle=3)
     dp = G.DevicePool(b)
     x_bits, y0 = b.x_bits(), b.y0_bits("small")

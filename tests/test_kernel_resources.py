@@ -29,6 +29,11 @@ def _kernels():
     ("k_decode_fusedE", 0),
     # 254 of 256 registers; its waits count memory operations, and a spill's are among them
     ("k_linear_loraE", 0),
+    ("k_shrink_halvesE", 0),
+    ("k_expand_partsE", 0),
+    ("k_expand_mixedILNS_6SlicesE0E", 0),
+    ("k_expand_mixedILNS_6SlicesE1E", 0),
+    ("k_linear_roundsILi4ELi4ELi2E", 0),  # 244 of 256
 ])
 def test_spilled_registers(kernel, most):
     """A register spilled in a unit's k loop is a trip to memory in every pass of it."""

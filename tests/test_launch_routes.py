@@ -250,6 +250,72 @@ def test_few_token_heavy_shrink_units_as_two_work_groups_each(recorder, groups, 
     b.close()
 
 
+# (shape, groups, who adds the k-slices up) of batches that have them; test_gpu_forms.py runs them
+SLICES = [
+    ((64, 128), [(1, 1), (17, 8)], "by_expand"),                                     # one slice
+    ((2048, 640), [(16, 24), (17, 33), (1, 256)], "by_expand"),                      # two
+    ((3968, 384), [(5, 129), (33, 64), (16, 8)], "by_expand"),                       # three, the last of them short
+    ((4096, 1152), [(1, 16)] * 24, "by_expand"),                                     # four
+    ((4096, 256), [(40, 72), (1000, 16), (3, 136), (15, 255), (31, 8)], "by_expand"),  # beside token-heavy groups
+    ((2048, 8192), [(1, 8)] * 40, "by_expand"),                                      # few shrink units, many expand units
+    # 256 shrink units at most, or fewer expand units than twice as many
+    ((2048, 4096), [(1, 8)] * 128, "by_expand"),                                     # 256 and 1024
+    ((2048, 4096), [(1, 8)] * 129, "by_shrink"),
+    ((2048, 1536), [(1, 8)] * 129, "by_expand"),                                     # 258 and 387
+    ((2048, 2048), [(1, 8)] * 129, "by_shrink"),                                     # 258 and 516
+    ((2048, 8192), [(1, 8)] * 150, "by_shrink"),
+    ((2048, 4096), [(1000, 16), (40, 8)] + [(2, 24)] * 20, "by_shrink"),             # the same beside token-heavy groups
+    ((1152, 4096), [(1000, 16), (17, 136), (3, 255), (9, 72), (40, 200)], "by_shrink"),  # the same above rank 128, several strips a unit
+    ((4096, 640), [(1000, 16), (17, 136), (3, 255), (9, 24), (40, 200), (900, 64)], "by_expand"),
+]
+
+
+@pytest.mark.parametrize("case", SLICES)
+def test_who_adds_the_k_slices_up(recorder, case):
+    shape, groups, by = case
+    b = Batch(*shape, groups, 3)
+    two = dict(whole_k_limit=0, heavy_k_cut_max_units=0, fused_apply=0)
+    assert _forms(b, recorder, "apply", L.plan_options(**two)) == [by] * 2
+    assert _forms(b, recorder, "static", L.plan_options(**two)) == [by] * 2
+    apart = L.plan_options(merged_launches=0, **two)  # the token-heavy groups' launches by themselves
+    assert [f for f in _forms(b, recorder, "apply", apart) if f not in ("halves", "whole")] == [by] * 2
+    assert "by_expand" not in _forms(b, recorder, "linear", L.plan_options(**two))
+    assert "callers" in _forms(b, recorder, "shrink", L.plan_options(**two))
+    b.close()
+
+
+# (in, ranks, k-slices) of batches of few token-heavy units, each rank in a group that ends in a tile of 5 tokens and in one that ends
+# in a tile of 20; test_gpu_forms.py runs them
+HALVES = [(n, ranks, slices) for ranks in ([8, 40, 64], [72, 128], [136, 192], [200, 256], [33, 100, 255])
+          for n, slices in ((64, 1), (4160, 1), (4096, 2), (3072, 3), (4160, 4))]
+
+
+def halves_groups(ranks):
+    tile = lambda r: 64 if 64 < (r + 7) // 8 * 8 <= 192 else 32
+    return [g for r in ranks for g in ((2 * tile(r) + 5, r), (tile(r) + 20, r))]
+
+
+def halves_options(ranks, slices):
+    # five tiles a rank: twice as many slices would be beyond the limit
+    return L.plan_options(heavy_min_batch=64, heavy_k_cut_max_units=5 * len(ranks) * slices if slices > 1 else 0)
+
+
+@pytest.mark.parametrize("case", HALVES)
+def test_batches_that_are_halves_only(recorder, case):
+    in_features, ranks, slices = case
+    b = Batch(in_features, 256, halves_groups(ranks), 3)
+    seg = b.build(halves_options(ranks, slices))
+    u = L.lora_segments_export_units(seg)["shrink"]
+    assert {int(k) for k in u[u[:, 0] >= 0][:, 5]} == set(range(slices)) and (u[:, 0] >= 0).sum() == 5 * len(ranks) * slices
+    for call in ("apply", "shrink"):
+        recorder.recorder_take_forms()
+        launches = b.launches(recorder, seg, call)
+        assert recorder.recorder_take_forms() == b"halves "
+        assert all(name in ("shrink_prefill", "expand_big", "reduce_slices") for name, *_ in launches)
+    L.lora_segments_destroy(seg)
+    b.close()
+
+
 # ---- the adapted layer's row order and tiles ---------------------------------------------------------------------
 # (in, out, groups, idle tokens, every group in blocks of its own, row tiles of 256 places as large tiles, of how many);
 # test_gpu_forms.py runs them
@@ -285,6 +351,29 @@ def test_row_order_and_tiles_of_the_adapted_layer(recorder, case):
     assert places <= sum((n + 15) // 16 * 16 for n, _ in groups) + idle + 16 if padded else places == len(b.ta)
     assert (places > len(b.ta)) == padded
     L.lora_segments_destroy(seg)
+    b.close()
+
+
+# (small tiles, out, groups) of more than a tile per compute unit: two work groups of four wavefronts share one; test_gpu_forms.py runs them
+TILES_IN_PAIRS = [
+    ("64x64", 8192, [(70, 24), (1, 256), (40, 8), (19, 130)]),  # 384 tiles
+    ("32x64", 8064, [(33, 64), (29, 9), (3, 200)]),             # 378
+    ("32x32", 4224, [(9, 16), (23, 72)]),                       # 264
+    ("16x32", 8320, [(7, 40), (6, 255)]),                       # 260
+]
+
+
+@pytest.mark.parametrize("in_features", [64, 320, 1024])
+@pytest.mark.parametrize("tiles, out, groups, pairs", [case + (True,) for case in TILES_IN_PAIRS] + [
+    ("64x64", 4096, [(256, 8)], False),   # 256
+    ("64x64", 8320, [(128, 8)], True),    # 260
+    ("32x32", 4096, [(33, 8)], False),    # 256
+    ("16x32", 8192, [(16, 8)], False),    # 256
+    ("16x32", 8320, [(16, 8)], True),     # 260
+])
+def test_small_tiles_of_the_adapted_layer(recorder, in_features, tiles, out, groups, pairs):
+    b = Batch(in_features, out, groups, 1 if (tiles, out, groups) in TILES_IN_PAIRS else 0)
+    assert _forms(b, recorder, "linear")[-1] == tiles + ("_in_pairs" if pairs else "")
     b.close()
 
 
