@@ -424,9 +424,9 @@ lora_status_t lora_set_whole_k_limit(int32_t max_units);
 
 /* lora_apply is two launches (shrink units, then expand units) unless one of the single-launch forms is
  * taken (here and lora_set_decode_single_launch).  With k-slices the expand units of up to 16 tokens
- * add the slices of their own tokens up; in batches of many such units, in lora_linear, and for
- * token-heavy units cut along k, the shrink unit that completes a token tile (found through per-tile counters in the segment object's
- * device table) adds them up and leaves the tile's v.
+ * add the slices of their own tokens up; where there are at least twice as many expand units as shrink units (unless the latter are at
+ * most 256 and none is token-heavy), in lora_linear, and for token-heavy units cut along k, the shrink unit that completes a token
+ * tile (found through per-tile counters in the segment object's device table) adds them up and leaves the tile's v.
  * lora_set_fused_apply(1) selects, for batches planned with k-slices and without token-heavy groups,
  * a single launch in which shrink and expand units share the grid and the expand units poll, with a
  * bounded number of polls, until their tile's v is complete.  Applies that share one segment object

@@ -576,22 +576,24 @@ static int expand_cols_per_unit(int r8, int out)
 // longer than a whole decode-sized launch lasts.
 static const int kPrefillMinTokens = 32;
 static const int kPrefillMinBatch = 1024;
-// Between kWholeKMin and this many whole-k shrink units (four rounds of one work group per compute
-// unit of the chip) the decode shrink runs without k-slices; measured on the rank-skew batches, 442
-// and 544 such units beat their 4 x as many k-slice units by 8 %, 32 units lose 9 % to their 128.
+// Between kWholeKMin and this many whole-k shrink units (four rounds of one work group per compute unit of the chip) the decode
+// shrink runs without k-slices.  Us per call, whole-k / k-slices, one token per adapter of rank 16: lora_apply 4096 -> 4096, 64 units
+// 8.8 / 8.1, 96 9.9 / 11.1, 256 17.4 / 19.4, 442 27.9 / 30.4, 1000 56.1 / 59.5, 1300 72.8 / 75.1; lora_linear, and shrink and expand apart, take
+// whole-k from 64 on: 64 units 18.5 / 19.4 and 8.6 / 9.7, 256 33.5 / 35.1 and 17.2 / 19.5.  Just above a round of work groups
+// k-slices are ahead where k is long, in every call: 8192 -> 2048, 260 units 22.9 / 20.4, 320 24.7 / 22.9 (442 28.7 / 29.8); 14336 -> 4096, 260
+// units 38.4 / 34.7, 544 65.2 / 64.4 (768 82.7 / 87.6).  The rank-skew batches at 8192 features: 272 units 32.5 / 31.0, 425 45.1 / 49.2, 544
+// 54.0 / 56.0.
 static std::atomic<int> g_whole_k_limit{1024};
 // Mixed batches (token-heavy groups beside decode-sized ones) in two launches that hold both kinds of
 // unit: the decode-sized groups are then planned in k-slices, whose work groups have the size of the
 // token-heavy ones'.
 static std::atomic<int> g_merged_mixed{1};
 static const int kSplitRowsFloor = 1;   // fewest tokens of a whole-k unit that may be cut into 8-row halves
-static const int kWholeKMin = 64;  // below this, k-slices are what spreads the batch over the chip
-// A wavefront of a whole-k unit walks in_features / 16 of k in passes of 256, one trip to memory each:
-// beyond this many input features the k-slice units win.  cfg1's routing, ms per step of 32 projections,
-// whole-k (one launch per apply) against k-slices (two launches): 0.663 / 0.744 at 8192 input features,
-// 0.668 / 0.769 at 8256, 0.942 / 0.963 at 14336, 1.002 / 1.041 at 16384, 1.038 / 1.079 at 16448, 1.290 /
-// 1.228 at 20480, 1.442 / 1.380 at 24576, 1.592 / 1.533 at 28672; the rank-skew batch at 28672: 1.024 /
-// 0.951.  (Before the one-launch form the shrink launches alone crossed at 8192.)
+static const int kWholeKMin = 64;  // below this, k-slices are what spreads the batch over the chip (from about there on lora_linear loses by them)
+// A wavefront of a whole-k unit walks in_features / 16 of k in passes of 256, one trip to memory each: beyond this many input
+// features k-slices win where the whole-k plan is two launches.  The rank-skew batch (544 whole-k units, 8192 columns), us per apply,
+// whole-k / k-slices: 57.2 / 57.7 at 8192 input features, 75.9 / 74.7 at 14336, 118 / 112 at 28672.  cfg1's routing (199 units, one launch)
+// has no such end: 17.8 / 20.6 at 8192, 27.2 / 30.0 at 16384, 32.2 / 34.7 at 20480, 41.3 / 43.8 at 28672.
 static const int kWholeKMaxIn = 18432;
 // Tokens of a token-heavy shrink unit: up to rank 64 the wavefronts split k and hold 32 tokens; above,
 // they split the rank rows and share 64 tokens of x through LDS (A^T is then loaded once per 64
@@ -613,7 +615,7 @@ using lora::kComputeUnits;  // a whole-k launch within this many units is one ro
 // (takes 2); 10112, 372 units 63 / 57 / 57 (takes 1).  Over 269 random batches of 2048 .. 16384 features and up to 600
 // such units the choice is 2.6 % from the best of 1 to 4 slices in the mean and 31 % at most; with 50 GB/s, no account of
 // v and limits of 448 to 750 cut units it was 5.2 % and 48 %.  Beyond kHeavyCutMaxUnits cut units the estimate no longer
-// holds.
+// holds.  It prices whole units also where the launch takes two work groups a unit (shrink_in_halves).
 static const int kHeavyCutMaxUnits = 900;
 static const double kHeavyRowsPerUs = 34000.0;  // rows of one input feature that a compute unit passes per us
 struct HeavyShrink {
@@ -791,15 +793,14 @@ static const int kXcds = 8;         // XCDs of the chip, each with an L2 of its 
 static std::atomic<int> g_decode_single_launch{-1};  // 1: wherever it can be, 0: never, -1: where it is the faster form
 static std::atomic<int> g_side_stream{1};
 static std::atomic<int> g_fused_apply{-1};  // 1: always where it can be, 0: never, -1: batches of few units
-// Batches of at most this many units and this rank on the k-slice plan run as one launch: it lasts 6 to 10 us, two
-// launches about as long as the host takes to issue them, but the units that wait and poll slow those they wait for.  260
-// random batches within the other two limits at 512 .. 16384 features, called from Python one after the other, one launch
-// against two by shrink units: up to 8 10 % faster in the mean, none slower; 9 .. 15 5 % faster; 17 .. 24 level, from 6 % faster
-// to 9 % slower; 25 .. 32 3 % slower in the mean, 12 % at most (2816 -> 7552, one token of rank 256, (32, 59) 13.2 / 11.7 us);
-// within all four limits 8.5 % faster in the mean, 5 % slower at most but for one of 11 %.  By rank: up to 64 9 % faster,
-// 128 level, above 2 % slower.  More units or tokens: 4096 -> 4096 (96, 104) 12.5 /
-// 10.1, 3008 -> 1920 (46, 51) 11.8 / 10.9; 126 tokens of 2 adapters, 4096 -> 4096 (32, 64) 11.2 / 9.6, 8192 -> 2048 (32, 32)
-// 12.2 / 11.1.
+// Batches of at most this many units and this rank on the k-slice plan run as one launch: it lasts 5 to 8 us, two
+// launches about as long as the host takes to issue them, but the units that wait and poll slow those they wait for.  200 random
+// batches at 512 .. 16384 features, called from Python one after the other, one launch against two: within all four limits 20 % faster in
+// the mean, none slower; by shrink units, up to 8 22 %, 9 .. 16 15 %, 17 .. 24 9 % faster, none slower; 25 .. 32 7 % faster in the mean,
+// 9 % slower at most; 33 .. 40 level.  By rank, of 16 shrink units at most: up to 128 20 % faster, above 7 %.  More units or tokens: 4096 -> 4096
+// (96, 192) 9.1 / 8.4, 3008 -> 1920 (60, 80) 8.9 / 8.5, 2816 -> 7552, one token of rank 256, (32, 59) 9.1 / 9.0; 126 tokens of 2 adapters, 4096 ->
+// 4096 (36, 72) 8.2 / 8.4, 8192 -> 2048 (36, 36) 8.8 / 9.7.  (The limits were drawn when the one launch completed v before its expand
+// units read it: then 17 .. 24 was level and 25 .. 32 3 % slower.)
 static const int kSingleLaunchShrinkUnits = 16;
 static const int kSingleLaunchRank = 128;
 static const int kSingleLaunchUnits = 96;
@@ -822,8 +823,9 @@ static int opt_decode_single(const lora_segments *sg) { return sg->opts.decode_s
 // 14.5, 1024 -> 3456 (233, 946) 11.8 / 12.6, 2304 -> 4224 (208, 998) 15.1 / 14.6, 1728 -> 896 (205, 217) 11.2 / 10.0, 2496 ->
 // 4096 (112, 448) 14.3 / 12.4, 7552 -> 1024 (104, 104) 19.4 / 15.1; ranks up to 256: 12928 -> 2176 (208, 221) 32.3 / 24.6,
 // 8704 -> 640 (222, 93) 28.0 / 20.6, 1408 -> 8064 (206, 980) 21.5 / 17.8, 7808 -> 14208 (64, 694) 32.2 / 18.0.  The line below
-// is 0.2 % from the better form of each batch in the mean and 7 % at most (1216 -> 4736 (91, 910) 10.9 / 11.6); always one launch
-// 11 % and 79 %.  A line at 192 shrink units and 8192 features in and out together, 0.5 % and 36 %.
+// was 0.2 % from the better form of each batch in the mean and 7 % at most.  The expand launch of the two has become shorter since: over
+// 160 such batches it is 0.4 % in the mean and 15 % at most (3072 -> 2944 (232, 667) 14.9 / 13.0; 16000 -> 2048 (208, 416) 25.2 / 28.5);
+// always one launch 17 % and 82 %, always two 0.3 % and 13 %.
 static bool decode_single_pays(int opt, int64_t whole_k_units, int64_t expand_units, int top_rank)
 {
     return opt > 0 || (opt < 0 && top_rank <= 128 && 6 * whole_k_units + expand_units >= 8 * (int64_t)kComputeUnits);
@@ -2291,13 +2293,14 @@ static bool may_be_captured(hipStream_t s)
 
 // Who adds the k-slices of v up (see the kernels).  The expand units, where the shrink units of a batch without token-heavy groups
 // all run at once (their waits for each other then are most of the launch), or where there are few expand units to each:
-// every one of them reads the slices of its tokens, 16 bytes an element where complete v is 4, and a shrink unit
-// saves its wait for the others once.  us per call, added up by the shrink / the expand units: batches of tokens alone,
-// 4096 -> 16384 (192 + 768 units) 13.8 / 11.4, 16384 -> 16384 (224 + 896) 21.1 / 18.3, 8192 -> 28672 (192 + 1344) 20.0 / 18.3, 4096 -> 28672
-// (152 + 2128) 16.2 / 15.8, 5056 -> 2560 (4884 + 2420) 60.7 / 56.5, but 4096 -> 14336
-// (6400 + 25200) 162.9 / 164.4, 16384 (6272 + 12544) 175.6 / 180.0; beside prompts 4096 -> 512 (1928 + 503) 30.2 / 28.0, 2112 -> 2688
-// (612 + 893) 29.0 / 28.2, but 3008 -> 3712 (198 + 523) 14.3 / 14.7, 2048 -> 8192 (732 + 3456) 48.0 / 50.0, 4096 -> 14336 (1612 + 5740) 69.9
-// / 73.7.
+// every one of them reads the slices of its tokens, of four slices 16 bytes an element where complete v is 4, and a shrink unit
+// saves its wait for the others once.  Both counted as the launches' work groups, places that fill an XCD's list up included.  us per
+// call, added up by the shrink / the expand units: batches of tokens alone,
+// 4096 -> 16384 (192 + 768 units) 12.9 / 11.3, 16384 -> 16384 (224 + 896) 21.2 / 18.2, 8192 -> 28672 (192 + 1344) 20.3 / 18.0, 4096 -> 28672
+// (152 + 2128) 16.0 / 15.9, 5056 -> 2560 (9848 + 4845) 100.4 / 97.9, 4096 -> 4096 (6400 + 3200) 77.3 / 76.5, but 4096 -> 14336
+// (6400 + 25200) 158.8 / 162.4, 16384 (6272 + 12544) 176.7 / 178.8; beside prompts 4096 -> 512 (2260 + 502) 31.8 / 29.4, 2112 -> 2688
+// (660 + 1016) 27.6 / 27.3, 4032 -> 6656 (1067 + 1755) 49.5 / 48.9, but 2048 -> 8192 (732 + 3456) 47.3 / 48.0, 4096 -> 14336 (1612 +
+// 5740) 68.9 / 70.5; level 3008 -> 3712 (318 + 652) 13.7 / 13.5.  Of one slice 896 -> 1920 (514 + 1366) 24.1 / 24.5.
 static bool expand_adds_slices(const lora_segments *sg, int shrink_units, int expand_units)
 {
     if (sg->wide) return false;

@@ -72,9 +72,9 @@ static __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __
 // ------------------------------------------------------------------------------------------------
 // Hand-over of v between the two halves of a fused launch.  The L2 caches of the chip's eight XCDs
 // are not coherent with each other, and a device-scope fence (write back / invalidate a whole L2)
-// costs far more than the data is worth.  So the partial sums of v never live in a cache: they are
-// stored and loaded with device-scope relaxed atomics (64 bits at a time), which go through to
-// memory.  In the single-launch form a shrink work group waits until its stores have completed, then
+// costs far more than the data is worth.  So partial sums of v that work groups of the same launch read never
+// live in a cache: they are stored and loaded with device-scope relaxed atomics (64 bits at a time), which go
+// through to memory.  In the single-launch form a shrink work group waits until its stores have completed, then
 // bumps the ready counter of its (group, token tile), and the expand work groups add the k-slices up
 // themselves, each for its own tokens, behind a wait for all of the tile's bumps.  (With the shrink unit that
 // arrived last adding them up, v took three trips through memory, a counter behind each.  Calls one after the other, us: one
@@ -83,10 +83,9 @@ static __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __
 // In launches of their own the expand units of up to 16 tokens (k_expand_parts, k_expand_mixed<kSlicesByExpand>) add the slices up as well where
 // that is the shorter way (expand_adds_slices in lora_host.cpp), and the
 // shrink units of k-slices leave plain stores and end: to wait for its stores, its counter and, in the last unit of a tile, for the
-// other slices held a work group's place for longer than its products took.  Calls one after the other, us, completed in the
-// shrink launch / added up in the expand launch: 16 tokens of 10 adapters, 4096 -> 4096, 10.2 / 7.5; 100 tokens of one of rank
-// 64 12.1 / 9.1; 16 tokens of rank 256, 16384 -> 16384, 23.0 / 17.4; 500 tokens of 100 adapters of rank 256, 4096 -> 4096 (6400
-// and 3200 units), 104.9 / 82.0; of 500 adapters of ranks 8 to 128 74.8 / 73.4.
+// other slices hold a work group's place for longer than its products take.  Calls one after the other, us, completed in the
+// shrink launch / added up in the expand launch: 16 tokens of 10 adapters, 4096 -> 4096, 10.0 / 8.0; 80 tokens of four of rank 128,
+// 16384 -> 16384, 21.2 / 18.2; 500 tokens of 100 adapters of rank 256, 4096 -> 4096 (6400 and 3200 units), 77.3 / 76.5.
 // Else, and for lora_linear, the shrink launch completes them as bf16 hi + lo, which every column reads: a unit
 // bumps the arrival counter of its tile, the one whose bump completes the tile's count adds the slices up and sets the counter back
 // to zero (a launch leaves the table as it found it, so a launch replayed from a captured graph finds what the first one found).
@@ -1503,10 +1502,10 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
     const uint4 *gtile = reinterpret_cast<const uint4 *>(arena + u.w_off);  // strip s starts tile_pieces * s further
     uint4 *ltile = reinterpret_cast<uint4 *>(lds);
     const int nstrips = ncols / kStrip;
-    // The order of the strips: from the first one, or (runs and rows of whole multiples of 4 KB) every tile of tokens from another
-    // one.  All units of a launch walk their runs at about the same pace; where the runs' starts and the rows differ by multiples of
+    // The order of the strips: from the first one, or (runs and rows of whole multiples of 4 KB) every tile of tokens of a group from
+    // another one.  All units of a launch walk their runs at about the same pace; where the runs' starts and the rows differ by multiples of
     // 4 KB they otherwise ask a part of the memory's channels for y at any one time.  Expand launch of 19,675 tokens of ranks 8 to
-    // 128, us from the first strip / each from another: 8192 columns 166 / 138; rank 8 167 / 133, rank 128 184 /
+    // 128, in us, from the first strip / in turn: 8192 columns 166 / 138; rank 8 167 / 133, rank 128 184 /
     // 167; 16384 columns, 10,082 tokens 179 / 161; 4096 columns (runs of 2 KB) 75.1 / 75.5, 14336 (runs of 7 KB) 138.5 / 141.7.
     const int turn = (ncols * 2) % 4096 == 0 && (ldy * 2) % 4096 == 0 ? (u.tok0 >> 6) * 5 % nstrips : 0;
     auto strip_at = [&](int i) __attribute__((always_inline)) { return i + turn < nstrips ? i + turn : i + turn - nstrips; };
@@ -2460,7 +2459,7 @@ static __device__ __forceinline__ void linear_big_body(
 constexpr int kLinSmallWaves = kLinThreads / 64;
 // Where there are more tiles than compute units, a tile takes a work group of half as many wavefronts and two work groups share a
 // compute unit: what a tile waits for (its rows, the first operands, v and B^T, the sums) then passes beside another's products, and
-// there are no rounds.  k_linear_small -> k_linear_rounds, us per layer: 576 -> 8192, 208 tokens (512 tiles) 24.9 -> 19.2; 832 -> 4864, 544
+// up to 512 tiles are one round.  k_linear_small -> k_linear_rounds, us per layer: 576 -> 8192, 208 tokens (512 tiles) 24.9 -> 19.2; 832 -> 4864, 544
 // tokens (688) 32.3 -> 27.9; 1728 -> 5120, 630 tokens (800) 49.0 -> 43.3; 8192 -> 2432, 1068 tokens (648) 109 -> 101; 32 x 64 tiles, 7168 -> 640,
 // 1428 tokens (456) 57.4 -> 55.2; 16 x 32, 1536 -> 2688, 81 tokens (504) 15.7 -> 14.6, 8192 -> 4224, 28 tokens (264) 34.9 -> 33.8.
 constexpr int kLinRoundsWaves = kLinSmallWaves / 2;
