@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from operator import index
 from typing import Optional, Sequence
 
 import numpy as np
@@ -256,7 +257,7 @@ def lora_pool_load(pool: Pool, adapter: int, A, B, src_is_device: Optional[bool]
         a, b = A.data_ptr(), B.data_ptr()
     except AttributeError:
         a, b = _addr(A), _addr(B)
-    status = (_lib or lib()).lora_pool_load(pool.handle, ctypes.c_int32(adapter), a, b, 1 if src_is_device else 0,
+    status = (_lib or lib()).lora_pool_load(pool.handle, index(adapter), a, b, 1 if src_is_device else 0,
                                             None if stream is None else _queue(stream))
     if status:
         _check(status)
