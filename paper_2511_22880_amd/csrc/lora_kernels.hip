@@ -601,6 +601,22 @@ struct Through {
     }
 };
 
+// An adapter's rows of A^T in 16-byte loads whose address is a lane's element offset, a register's, and a wavefront's, a scalar: the
+// loads of a k loop then need no 64-bit addition per lane and no registers for its results.  22,532 tokens, us a call with an address
+// per load / this way: rank 64 4096 -> 4096 113.0 / 111.1, 14336 -> 1024 177.3 / 172.7, rank 256 250.4 / 247.3 and 418.9 / 407.9; ranks up to
+// 32 level; k_shrink_prefill no longer spills its one register.  base is wavefront-uniform.
+struct Rows {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Rows(const uint16_t *base, int elements)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (int)(2u * (unsigned)elements), 0x00020000)) {}
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    __device__ __forceinline__ uint4 ld(int lane, int wave) const
+    {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(2u * (unsigned)lane), (int)(2u * (unsigned)wave), 0);
+        return uint4{v.x, v.y, v.z, v.w};
+    }
+};
+
 // four elements of v, at element index `at`, as bf16 hi + lo
 static __device__ __forceinline__ void store_v4(f32x4 f, int64_t at, uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo)
 {
@@ -746,7 +762,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
     // The caller picks JB from the rank; telling the compiler so removes the branches around the row
     // blocks that always exist (with a branch per block the same loop ran 2.4 times slower).
     __builtin_assume(r8 <= 16 * JB && (JB == 1 ? r8 >= 8 : r8 > 8 * JB));
-    const uint16_t *wbase = arena + u.w_off + (int64_t)rr.first * in;
+    const Rows wa(arena + u.w_off + (int64_t)rr.first * in, r8 * in);
     int woff[JB];  // element offset of this lane's 16-byte piece in k step 0 of row block jb
     int wh[JB];    // rows in block jb (16, or 8 for the last block of a padded rank that is 8 mod 16)
     // The loop below has no branch: a block beyond the padded rank (ranks 33..48 of the bucket up to 64) is
@@ -793,7 +809,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
             for (int t = 0; t < NL; ++t) xq[t] = ld16_stream(xrow[t] + kx);
         };
         auto w_step = [&](int k, int jb) __attribute__((always_inline)) {
-            return ld16(wbase + woff[jb] + (int64_t)min(k, in - 32) * wh[jb]);
+            return wa.ld(woff[jb], min(k, in - 32) * wh[jb]);
         };
         auto stage = [&](const uint4(&xq)[NL]) __attribute__((always_inline)) {
 #pragma unroll
@@ -931,7 +947,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
 
     // A wavefront whose row blocks lie beyond the padded rank (ranks that are not multiples of 64) works on
     // the last block that exists instead: its sums are never stored, and the loop needs no branch for it.
-    const uint16_t *wbase = arena + u.w_off + (int64_t)rr.first * in;
+    const Rows wa(arena + u.w_off + (int64_t)rr.first * in, r8 * in);
     const int nblk = (r8 + 15) >> 4;
     int woff[JBW], wh[JBW];
 #pragma unroll
@@ -967,7 +983,7 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
         for (int i = 0; i < TB; ++i) xs[i] = ld16_stream(xrow[i] + kx);
     };
     auto w_step = [&](int k, int j) __attribute__((always_inline)) {
-        return ld16(wbase + woff[j] + (int64_t)min(k, in - 32) * wh[j]);
+        return wa.ld(woff[j], min(k, in - 32) * wh[j]);
     };
     auto stage = [&](int base, const uint4(&xs)[TB]) __attribute__((always_inline)) {
 #pragma unroll
