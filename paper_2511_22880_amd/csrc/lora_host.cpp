@@ -119,6 +119,7 @@ struct lora_segments {
     int n_prefill_hi;       // how many of prefill_units are above rank 64
     int n_heavy_units;      // how many of them hold tokens (the others fill the XCDs' lists up)
     int heavy_top_rank;     // their largest padded rank
+    std::vector<lora::BigSection> big_sections;  // expand_big_units in runs of equally wide ones: one per projection, or fewer
     int heavy_k_slices;     // k-slices of the token-heavy shrink units (1: they take the whole of k)
     bool decode_fused;      // whole-k decode batch that can run as one launch (see finish_decode_fused)
     int fused_grid;         // work groups of that launch
@@ -1275,6 +1276,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     sg->has_big_units = false;
     sg->n_prefill_hi = 0;
     sg->heavy_top_rank = 0;
+    sg->big_sections.clear();
     // (per projection, whatever the number of projections: lora_apply_multi gives the bits of separate applies)
     int heavy_k_slices = 1;
     if (sg->n_k_slices >= 2) {
@@ -1304,7 +1306,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     int64_t big_tiles = 0;
     for (const SegRec &r : sg->segs)
         if (r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch) big_tiles += (r.ntok + 63) / 64;
-    int big_runs = 4;
+    int big_runs = 4, big_cols = 0;
     for (int runs = 64; runs >= 8 && big_runs == 4 && !(lean && sg->opts.big_runs_max_units < 0); runs /= 2)
         if (big_tiles * std::min(runs, out / 128) * n_projections <= opt_big_runs_max_units(sg)) big_runs = runs;
     for (int32_t si : order) {
@@ -1373,6 +1375,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         if (token_heavy) {
             etile = 64;
             cols = std::min(out, std::max(big_runs > 4 ? 128 : 512, (out / big_runs + 127) / 128 * 128));
+            big_cols = cols;
         }
         auto emit = [&](int c0, int tok0) {
             Unit u;
@@ -1412,6 +1415,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         }
     }
 
+    if (!sg->expand_big_units.empty()) sg->big_sections.push_back({(int)sg->expand_big_units.size(), big_cols});
     order_units_by_xcd(sg->shrink_units);
     sg->n_heavy_units = (int)sg->prefill_units.size();
     order_heavy_units_by_xcd(sg->prefill_units);
@@ -1646,6 +1650,12 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         shift(sg->expand_big_units, n3, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         sg->n_prefill_hi += tmp->n_prefill_hi;
         sg->n_heavy_units += tmp->n_heavy_units;
+        for (const lora::BigSection &b : tmp->big_sections) {
+            if (!sg->big_sections.empty() && sg->big_sections.back().cols == b.cols)
+                sg->big_sections.back().n_units += b.n_units;
+            else
+                sg->big_sections.push_back(b);
+        }
         sg->mpool_ids.push_back(pools[q]->id);
         sg->msegs.push_back(tmp->segs);
         sg->mepochs.push_back(tmp->seg_epoch);
@@ -2104,6 +2114,8 @@ static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_f
     c.n_units = (int)list.size();
     c.n_work = kind == kPrefill ? sg->n_heavy_units : c.n_units;
     c.top_rank = sg->heavy_top_rank;
+    c.sections = sg->big_sections.data();
+    c.n_sections = (int)sg->big_sections.size();
     c.in_features = in_features;
     c.out_features = out_features;
     c.scale_v = 0;

@@ -75,6 +75,12 @@ constexpr int kTokTile = 16;   // tokens per MFMA tile (the N of a 16x16x32 MFMA
 constexpr int kRowTile = 16;   // rank rows / output columns per MFMA tile (the M)
 constexpr int kThreads = 256;  // 4 wavefronts per work group
 
+// Consecutive 64-token expand units of the same number of columns, but for those at the end of a row of y.
+struct BigSection {
+    int n_units, cols;
+};
+constexpr int kMaxBigSections = 8;  // one per projection at most
+
 struct LaunchCtx {
     const Unit *units;
     const int32_t *perm;
@@ -82,6 +88,9 @@ struct LaunchCtx {
     int n_units;
     int n_work;    // of n_units, those that hold tokens (lists of token-heavy shrink units are filled up with others)
     int top_rank;  // lists of token-heavy shrink units: the largest padded rank
+    // lists of 64-token expand units: in which runs of equally wide ones (host memory)
+    const BigSection *sections;
+    int n_sections;
     int in_features;
     int out_features;
     // shrink launches that leave v as bf16 hi + lo: store s_a v (rounded to fp32 once, then split) instead of v,

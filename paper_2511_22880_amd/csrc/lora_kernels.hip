@@ -650,18 +650,34 @@ struct RankRows {
     int part, of;  // which of how many work groups
 };
 
-// where element quad i of those rows lies in the unit's v, in quads from its first row; i counts n / 4 quads per token
-static __device__ __forceinline__ int quad_place(const Unit &u, const RankRows &rr, int i)
+// How token-heavy units leave v, whole or as slices of its sums.  In rows as everyone's v lies (for lora_shrink's caller and
+// lora_linear), or, for the 64-token expand units (`tiled`), in the order in which an MFMA takes it: 16 tokens at a time, element (token
+// n, rank row j) of h tokens at (j / 8 * h + n) * 8 + j % 8.  A wavefront's load of an operand is then 1 KB of consecutive bytes instead
+// of 64 bytes of each of 16 rows, which cost a compute unit's address path 3.7 times as long, and so are the stores straight from
+// the registers that the MFMAs left.
+static __device__ __forceinline__ int tiled_quad(int r8, int ntok, int tok, int j4)
+{
+    const int b = tok >> 4, h = min(16, ntok - 16 * b);
+    return 4 * b * r8 + ((j4 >> 1) * h + (tok & 15)) * 2 + (j4 & 1);
+}
+
+// where element quad i of those rows lies in the unit's v, in quads from its first element; i counts n / 4 quads per token
+static __device__ __forceinline__ int quad_place(const Unit &u, const RankRows &rr, int i, bool tiled)
 {
     if (rr.of == 1) return i;
-    const int quads = rr.n >> 2, tok = i / quads;
+    const int quads = rr.n >> 2;
+    if (tiled) {
+        const int b = i / (16 * quads), h = min(16, u.ntok - 16 * b);
+        return i + 4 * b * (u.r8 - rr.n) + (rr.first >> 2) * h;
+    }
+    const int tok = i / quads;
     return tok * (u.r8 >> 2) + (rr.first >> 2) + (i - tok * quads);
 }
 
 // The end of a token-heavy shrink unit, by all threads of its work group: rows row0 .. row0 + rows - 1 of the unit's
-// v are one run of memory (or, of half the rank rows, a run per token), which goes out in 16-byte pieces, neighbouring threads side by
-// side; quad(i) = the sums of its elements 4 i .. 4 i + 3.  (Straight from the MFMA registers a wavefront's stores were 8 bytes of each of 64
-// pieces of lines; written through to memory those were most of a cut unit's time: 2000 tokens of rank 128 at
+// v are one run of memory (or, of half the rank rows, a run per token or 16), which goes out in 16-byte pieces, neighbouring threads side by
+// side; quad(i) = the sums of its elements 4 i .. 4 i + 3.  (Straight from the MFMA registers a wavefront's stores to rows were 8 bytes of
+// each of 64 pieces of lines; written through to memory those were most of a cut unit's time: 2000 tokens of rank 128 at
 // 4096 features, 128 units, shrink launch 20.4 -> 15.2 us.)
 // Whole units write v.  Units cut along k leave their sums in slice u.ks of the fp32 partial sums: plainly for the
 // stand-alone shrink (v_f32: the caller adds the slices up, and slice 0's unit clears those this group does not
@@ -670,22 +686,22 @@ template <class Quad>
 static __device__ __forceinline__ void store_heavy_rows(const Unit &u, const RankRows &rr, int n_ks, int row0, int rows, Quad quad,
                                                         uint16_t *__restrict__ v_hi, uint16_t *__restrict__ v_lo,
                                                         float *__restrict__ v_f32, int n_slices, int64_t slice_stride,
-                                                        float *__restrict__ parts, float vs)
+                                                        float *__restrict__ parts, float vs, bool tiled)
 {
     const int n = rows * (rr.n >> 2);
     const int64_t at = u.v_off + (int64_t)row0 * u.r8;
     if (n_ks > 1 && !v_f32) {
         const Through slice(parts + (int64_t)u.ks * slice_stride + at, rows * u.r8);
-        for (int i = late_thread(); i < n; i += kThreads) slice.st(quad_place(u, rr, i), quad(i));
+        for (int i = late_thread(); i < n; i += kThreads) slice.st(quad_place(u, rr, i, tiled), quad(i));
     } else if (v_f32) {
         float *dst = v_f32 + (int64_t)u.ks * slice_stride + at;
-        for (int i = late_thread(); i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[quad_place(u, rr, i)] = quad(i);
+        for (int i = late_thread(); i < n; i += kThreads) reinterpret_cast<f32x4 *>(dst)[quad_place(u, rr, i, false)] = quad(i);
         if (n_ks > 1 && u.ks == 0)
             for (int sl = n_ks; sl < n_slices; ++sl)
                 for (int i = late_thread(); i < n; i += kThreads)
-                    reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride)[quad_place(u, rr, i)] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    reinterpret_cast<f32x4 *>(dst + (int64_t)sl * slice_stride)[quad_place(u, rr, i, false)] = f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
-        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * quad_place(u, rr, i), v_hi, v_lo);
+        for (int i = late_thread(); i < n; i += kThreads) store_v4(vs * quad(i), at + 4 * quad_place(u, rr, i, tiled), v_hi, v_lo);
     }
 }
 
@@ -694,7 +710,7 @@ static __device__ __forceinline__ void store_heavy_rows(const Unit &u, const Ran
 // (it has one per 16 tokens), else the last of all completes all rows.  `word`: an LDS word that nothing else uses any more.
 static __device__ __forceinline__ void complete_tile(const Unit &u, const RankRows &rr, int n_ks, int64_t slice_stride,
                                                      float *__restrict__ parts, uint16_t *__restrict__ v_hi,
-                                                     uint16_t *__restrict__ v_lo, float vs, const Sync &sy, unsigned *word)
+                                                     uint16_t *__restrict__ v_lo, float vs, bool tiled, const Sync &sy, unsigned *word)
 {
     stores_done();
     __syncthreads();  // every wavefront's partial sums are out
@@ -711,7 +727,7 @@ static __device__ __forceinline__ void complete_tile(const Unit &u, const RankRo
     if (n_ks <= 2) {
 #pragma unroll 4
         for (int i = late_thread(); i < n; i += kThreads) {
-            const int q = quad_place(u, all, i);
+            const int q = quad_place(u, all, i, tiled);
             store_v4(vs * (s0.ld(q) + s1.ld(q)), u.v_off + 4 * q, v_hi, v_lo);
         }
     } else {
@@ -719,7 +735,7 @@ static __device__ __forceinline__ void complete_tile(const Unit &u, const RankRo
         const Through s3(parts + u.v_off + (n_ks > 3 ? 3 : 2) * slice_stride, len);
 #pragma unroll 4
         for (int i = late_thread(); i < n; i += kThreads) {
-            const int q = quad_place(u, all, i);
+            const int q = quad_place(u, all, i, tiled);
             f32x4 f = s0.ld(q) + s1.ld(q);
             f += s2.ld(q);
             const f32x4 f3 = s3.ld(q);
@@ -740,7 +756,7 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
 {
     constexpr int NT = JB * TB;
     constexpr int NL = 4 * TB;  // x loads of a wavefront per pass: 4 tokens each
-    static_assert(16 * TB <= kPfTokens, "tokens of a unit");
+    static_assert(TB <= 2 && 16 * TB <= kPfTokens, "tokens of a unit");
     static_assert(4 * NT * 64 * 16 + 4 <= kPrefillLds, "the wavefronts' partial tiles and a word fit the LDS");
     static_assert(WD == 1 || WD == 2 || WD == 4, "the weight ring must divide the 4 steps of a pass");
     const int lane = threadIdx.x & 63;
@@ -894,16 +910,26 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         for (int tb = 0; tb < TB; ++tb) red[wave][jb * TB + tb][lane] = acc[jb][tb];
     __syncthreads();
     const float vs = sy.scale_v ? u.scale : 1.f;
+    const bool tiled = !v_f32 && !sy.scale_v;
     const int quads = r8 >> 2;
     // lane (n, kq) of tile (jb, tb) holds v[token 16 tb + n][16 jb + 4 kq + e]
     auto quad = [&](int i) __attribute__((always_inline)) {
-        const int tok = i / quads, j4 = i - tok * quads;
+        int tok, j4;
+        if (tiled) {
+            const int b = TB > 1 && i >= 16 * quads ? 1 : 0, h2 = 2 * min(16, ntok - 16 * b), k = i - 16 * b * quads;
+            const int kp = ntok == 16 * TB ? k >> 5 : (int)((unsigned)k / (unsigned)h2);
+            tok = 16 * b + ((k - kp * h2) >> 1);
+            j4 = 2 * kp + (k & 1);
+        } else {
+            tok = i / quads;
+            j4 = i - tok * quads;
+        }
         const int t = (j4 >> 2) * TB + (tok >> 4), l = (j4 & 3) * 16 + (tok & 15);
         return (red[0][t][l] + red[2][t][l]) + (red[1][t][l] + red[3][t][l]);
     };
-    store_heavy_rows(u, rr, n_ks, 0, ntok, quad, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, vs);
+    store_heavy_rows(u, rr, n_ks, 0, ntok, quad, v_hi, v_lo, v_f32, n_slices, slice_stride, parts, vs, tiled);
     if (n_ks == 1 || v_f32) return;
-    complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + 4 * NT * 64 * 16));
+    complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, tiled, sy, reinterpret_cast<unsigned *>(lds + 4 * NT * 64 * 16));
 }
 
 // Token-heavy units above rank 64: 16 * TB tokens, all rank rows, all of k or a slice of it.  Here the
@@ -913,7 +939,8 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
 // one barrier per pass).  With k split over the wavefronts as above, a unit of 32 tokens loads all of
 // A^T for 32 tokens' worth of x: at rank 128 four times the bytes of x, which made the compute units'
 // vector caches, not memory, the bound (uniform rank 128 on cfg2's routing: 78 us against 35 us at
-// rank 8; 62 us with this body).  No sums cross wavefronts: each puts the rows of v it owns into LDS, from where they leave.  (Up to
+// rank 8; 62 us with this body).  No sums cross wavefronts: each stores the rows of v it owns straight
+// from its registers (tiled), or puts them into LDS, from where they leave in rows.  (Up to
 // rank 64 the k-split body of 32 tokens stayed as fast or faster: 50 us at uniform rank 64 either way.
 // Ranks 129..192 take three row blocks per wavefront and 64 tokens, ranks 193..256 four and 32 tokens, the
 // accumulators of 64 not fitting the registers: against units of 16 tokens with k split, the shrink
@@ -1072,8 +1099,28 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     LORA_CLOCK(2);
 #endif
     const float vs = sy.scale_v ? u.scale : 1.f;
-    // lane (n, kq) holds, for token block tb and its row block j, v[token 16 tb + n][16 jb + 4 kq + e]: the rows
-    // meet in LDS as they lie in v, all of the unit's tokens at once where they fit, else half of them
+    const bool tiled = !v_f32 && !sy.scale_v;
+    // lane (n, kq) holds, for token block tb and its row block j, v[token 16 tb + n][16 jb + 4 kq + e]
+    if (tiled) {
+        const Through slice(parts + (int64_t)(n_ks > 1 ? u.ks : 0) * slice_stride + u.v_off, ntok * u.r8);
+        const int late = late_thread(), ln = late & 15, lk = (late >> 4) & 3;
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+            for (int j = 0; j < JBW; ++j) {
+                const int j4 = 4 * (wave * JBW + j) + lk;
+                if (j4 < (r8 >> 2) && 16 * tb + ln < ntok) {
+                    const int q = tiled_quad(u.r8, ntok, 16 * tb + ln, (rr.first >> 2) + j4);
+                    if (n_ks > 1)
+                        slice.st(q, acc[j][tb]);
+                    else
+                        store_v4(acc[j][tb], u.v_off + 4 * q, v_hi, v_lo);
+                }
+            }
+        if (n_ks > 1) complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, true, sy, reinterpret_cast<unsigned *>(lds + kPrefillLds - 16));
+        return;
+    }
+    // rows: they meet in LDS as they lie in v, all of the unit's tokens at once where they fit, else half of them
     constexpr int GO = 16 * TB * 64 * JBW * 4 + 16 <= kPrefillLds ? TB : TB / 2;
     static_assert(16 * GO * 64 * JBW * 4 + 16 <= kPrefillLds, "the rows in LDS");
     f32x4 *rows = reinterpret_cast<f32x4 *>(lds);
@@ -1091,10 +1138,10 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
         __syncthreads();
         if (16 * g < ntok)
             store_heavy_rows(u, rr, n_ks, 16 * g, min(16 * GO, ntok - 16 * g), [&](int i) { return rows[i]; }, v_hi, v_lo, v_f32,
-                             n_slices, slice_stride, parts, vs);
+                             n_slices, slice_stride, parts, vs, false);
     }
     if (n_ks == 1 || v_f32) return;
-    complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, sy, reinterpret_cast<unsigned *>(lds + kPrefillLds - 16));
+    complete_tile(u, rr, n_ks, slice_stride, parts, v_hi, v_lo, vs, false, sy, reinterpret_cast<unsigned *>(lds + kPrefillLds - 16));
 }
 
 // One wavefront copies 1 KB from memory into LDS without passing through registers: lane l's 16 bytes
@@ -1276,8 +1323,7 @@ static __device__ __forceinline__ void load_v_operand(const float *__restrict__ 
 
 // KSTEPS: 32-wide steps that cover the padded rank (1, 2, 4 or 8).
 // BY: where v comes from, unless it is the caller's (VF32).
-// ROOM: a kernel of two work groups per compute unit (k_expand_mixed), with registers for both k steps' weights of a rank above 128.
-template <int KSTEPS, bool VF32, Slices BY, bool ROOM>
+template <int KSTEPS, bool VF32, Slices BY>
 static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t *__restrict__ arena,
                                                    const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
 {
@@ -1328,24 +1374,10 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
         // this lane's piece of sub-block 0, rank piece 0 of the wavefront's strip; sub-block b is
         // 16*r8 elements further, rank piece kp 128 elements further
         const uint16_t *brow = arena + u.w_off + (int64_t)(strip_ok ? cs : 0) * r8 + n * 8;
-        // ROOM and slices to add up: these are requested first, so that they are added up while the rest is on its way.  (1400 tokens
-        // beside 373 decode ones, 6464 -> 1280, 32.5 -> 32.0 us; 12352 -> 1664 41.3 -> 40.9.)
-        constexpr bool kSlicesFirst = ROOM && BY == kSlicesByExpand;
-        f32x4 p0[ITEMS][kMaxSlices], p1[ITEMS][kMaxSlices];
-        if (kSlicesFirst) {
-#pragma unroll
-            for (int it = 0; it < ITEMS; ++it)
-                load_slices<true>(sy.parts + v_at(it), sy.n_slices, sy.slice_stride, p0[it], p1[it]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
         // weights: row (column of y) cs + 8*n + b, 16 bytes at jc, of the wavefront's first k step.  Ranks above 128, two k
-        // steps: the second's are requested behind y and v with ROOM, else as the first's registers come free.  (With both requested
-        // behind the wait for v a launch of 10 units lasted 6.6 us, now 5.7; 6076 units of 576 -> 11136, ranks 1 to 256, 52.5 -> 49.6.
-        // Mixed launches, as the registers come free / behind y and v, us per call: 576 -> 7808, 1601 tokens of ranks 1 to 256, 59.2 /
-        // 55.1; 6144 -> 14080 68.9 / 66.4; 832 -> 4480, 4417 tokens, 47.3 / 47.1; but where the units of up to 16 tokens are the fewer,
-        // 10688 -> 2688, 2116 tokens, 54.1 / 54.9, 1344 -> 1920, 3844 tokens, 39.2 / 39.7.)
-        constexpr bool kBoth = ITEMS > 1 && ROOM;
-        uint4 w[8], w2[8];
+        // steps: the second's are requested as the first's registers come free.  (With both requested behind the wait for v a launch
+        // of 10 units lasted 6.6 us, now 5.7; 6076 units of 576 -> 11136, ranks 1 to 256, 52.5 -> 49.6.)
+        uint4 w[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) w[b] = ld16_stream(brow + b * 16 * r8 + jc[0] * 16);
         // nothing that needs the row index (a wait for its load) moves up in front of these requests
@@ -1376,19 +1408,13 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
                 ph = ld16(sy.v_hi + v_at(it));
                 pl = ld16(sy.v_lo + v_at(it));
             } else {
-                if (!kSlicesFirst)
-                    load_slices<BY == kSlicesByExpand>(sy.parts + v_at(it), sy.n_slices, sy.slice_stride, p0[it], p1[it]);
-                f32x4 f0, f1;
-                add_slices(p0[it], p1[it], sy.n_slices, f0, f1);
+                f32x4 p0[kMaxSlices], p1[kMaxSlices], f0, f1;
+                load_slices<BY == kSlicesByExpand>(sy.parts + v_at(it), sy.n_slices, sy.slice_stride, p0, p1);
+                add_slices(p0, p1, sy.n_slices, f0, f1);
                 split_bf16(f0, f1, ph, pl);
             }
             vh[it] = ok ? ph : zero;
             vl[it] = ok ? pl : zero;
-        }
-        if (kBoth) {
-#pragma unroll
-            for (int b = 0; b < 8; ++b) w2[b] = ld16_stream(brow + b * 16 * r8 + jc[ITEMS - 1] * 16);
-            __builtin_amdgcn_sched_barrier(0);
         }
 
         if (c0 > 0) __syncthreads();  // the previous pass's partial tiles have been consumed
@@ -1402,7 +1428,7 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
                 const bf16x8 ww = as_bf16x8(j_ok[it] ? w[b] : zero);
                 acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vh[it]), ww, acc[b], 0, 0, 0);
                 acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vl[it]), ww, acc[b], 0, 0, 0);
-                if (it + 1 < ITEMS) w[b] = kBoth ? w2[b] : ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
+                if (it + 1 < ITEMS) w[b] = ld16_stream(brow + b * 16 * r8 + jc[it + 1] * 16);
             }
         }
         if (strip_ok) {
@@ -1448,130 +1474,126 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
 }
 
 // ------------------------------------------------------------------------------------------------
-// expand of token-heavy groups: one unit = (group, up to 64 tokens, a run of 128-column strips).
-// Each wavefront owns 16 of the tokens for the whole unit and all of the rank, so nothing is summed
-// across wavefronts and there is no barrier per token block: its v operands (bf16 hi + lo, every
-// k step) are loaded once and stay in registers; a strip's B^T tile (128 columns x rank, one
-// contiguous piece of the pool) is copied into LDS once per work group and read from there by the
-// four wavefronts; the MFMA result (token x column, lane n holding 8 consecutive columns of 4
-// tokens) goes straight to the y update, 16 bytes per lane, four 256-byte row pieces per store.
-// While a strip computes, the next strip's B^T tile and this lane's y pieces are already on their
-// way (the tile waits in registers, then goes into the other half of the LDS buffer).
+// expand of token-heavy groups: one unit = (group, up to 64 tokens, a run of 128-column strips), a work group takes two of the
+// strips.  Each wavefront owns 16 of the tokens and all of the rank, so nothing is summed across wavefronts; a strip's B^T tile
+// (128 columns x rank, one contiguous piece of the pool) is copied into LDS once per work group and read from there by the four
+// wavefronts; the MFMA result (token x column, lane n holding 8 consecutive columns of 4 tokens) goes straight to the y update,
+// 16 bytes per lane, four 256-byte row pieces per store.
+// y, read and written once, is nearly all the bytes, and what the memory gives for it depends on how much of it is asked for at a
+// time and where: a kernel that only adds to 161 MB in place takes 51 us (6.4 TB/s) in the order of the addresses, 51 to 54 with 64
+// rows x 512 bytes per work group, neighbours along the row, 56 with 64 x 256, 60 to 63 with a work group that walks 2 KB of its
+// rows in steps of 256 bytes, 67 with 8 KB.  So a work group takes 64 tokens x 256 columns and ends, and the work groups of a row of
+// units are neighbours in the launch.  19,675 tokens, 4096 / 8192 / 14336 columns, expand launch in us, a run of 8 to 28 strips walked by
+// each work group / as here: rank 16 63.7 / 54.4, 136 / 106, 233 / 191; rank 64 68.4 / 58.9, 141 / 114, 242 / 203; rank 128 81.6 / 69.9,
+// 165 / 132, 280 / 235; rank 256 130 / 105, 288 / 208, 521 / 390.  (The tiles in another order, or rows known to be consecutive without
+// a look at perm: level.)
+// That asks for v and B^T oftener, which therefore come in whole KB of operand order (tiled_quad; B^T as the pool holds it), and for
+// 128 registers and 32 KB of LDS, four work groups on a compute unit: the low ranks' tiles of both strips, or one strip's up to rank
+// 128, or half of one's.  Up to rank 128 launches of their own ask for 16 KB of LDS more, so that three run there: less of y is under way at a
+// time (rank 16 56.6 / 54.4, rank 64 61.8 / 58.9, rank 128 70.9 / 69.9; two per compute unit 61.5, 64.0, 80.9), while above the fourth hides more of the
+// copies (rank 256 106 / 109).  Beside units of up to 16 tokens (k_expand_mixed) four are as fast as three or up to 3 % faster.
 // ------------------------------------------------------------------------------------------------
-constexpr int kBigLds = 64 * 1024;
+constexpr int kBigStrips = 2;                 // strips of a work group
+constexpr int kBigTile = 32 * 1024;           // bytes of B^T in LDS at a time
+constexpr int kBigSpread = 16 * 1024;         // LDS that a launch asks for beside it up to rank 128
+constexpr int kBigSpreadMaxRank = 128;
 
-template <int KSTEPS, bool VF32>
-static __device__ __forceinline__ void expand_big_body(const Unit &u, const int32_t *__restrict__ perm,
+// KSTEPS: 32-wide steps of a chunk of the rank (1, 2 or 4); CHUNKS of 128 of it.
+template <int KSTEPS, int CHUNKS, bool VF32>
+static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, const int32_t *__restrict__ perm,
                                                        const uint16_t *__restrict__ arena,
                                                        const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
 {
-    // the tile of one strip is 128 * r8 * 2 bytes: <= 32 KiB up to rank 128, two buffers of 32 KiB; above,
-    // one buffer of 64 KiB, filled between two strips
-    static_assert(KSTEPS <= 8, "token-heavy expand units exist up to rank 256");
-    constexpr bool DB = KSTEPS <= 4;
-    constexpr int WREG = 2 * KSTEPS;  // 16-byte pieces of a tile per thread (256 threads): 128*32*KSTEPS*2 / 4096
+    static_assert(CHUNKS == 1 || KSTEPS == 4, "a chunk is 128 of the rank");
+    constexpr int HELD = KSTEPS <= 2 ? kBigStrips : 1;  // strips whose tiles the LDS holds at a time
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15;
     const int kq = lane >> 4;
     const int r8 = u.r8;
     const int ntok_all = u.ntok;
-    const int ncols = u.pn;
+    const int nstrips = min(kBigStrips, (u.pn - c0) / kStrip);
     const uint4 zero = {0u, 0u, 0u, 0u};
-    const int32_t *toks = perm + u.perm_off;
     const float scale = u.scale;
     const int tile_pieces = 16 * r8;  // 16-byte pieces in one strip's tile (128 * r8 * 2 / 16)
-
-    // this wavefront's 16 tokens: v operands for every k step
     const int nt = min(kTokTile, ntok_all - kTokTile * wave);  // may be <= 0: the wavefront only helps copying
-    uint4 vh[KSTEPS], vl[KSTEPS];
-    bool j_ok[KSTEPS];
-#pragma unroll
-    for (int st = 0; st < KSTEPS; ++st) {
-        const int j = 32 * st + 8 * kq;
-        j_ok[st] = j < r8;
-        const bool ok = (n < nt) && j_ok[st];
-        const int64_t off = u.v_off + (int64_t)(ok ? kTokTile * wave + n : 0) * r8 + (j_ok[st] ? j : 0);
-        uint4 ph, pl;
-        if (!VF32) {
-            ph = ld16(sy.v_hi + off);
-            pl = ld16(sy.v_lo + off);
-        } else {
-            bf16x8 h, l;
-            load_v_operand(v_in + off, ok, h, l);
-            ph = __builtin_bit_cast(uint4, h);
-            pl = __builtin_bit_cast(uint4, l);
-        }
-        vh[st] = ok ? ph : zero;
-        vl[st] = ok ? pl : zero;
-    }
-    // the MFMA leaves tokens 4*kq + e (e = 0..3), columns 8*n .. 8*n+7 of the strip in this lane
-    uint16_t *yrow[4];
-    bool y_ok[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        y_ok[e] = 4 * kq + e < nt;
-        yrow[e] = y + (int64_t)toks[y_ok[e] ? kTokTile * wave + 4 * kq + e : 0] * ldy + u.p0 + 8 * n;
-    }
-
-    const uint4 *gtile = reinterpret_cast<const uint4 *>(arena + u.w_off);  // strip s starts tile_pieces * s further
     uint4 *ltile = reinterpret_cast<uint4 *>(lds);
-    const int nstrips = ncols / kStrip;
-    // The order of the strips: from the first one, or (runs and rows of whole multiples of 4 KB) every tile of tokens of a group from
-    // another one.  All units of a launch walk their runs at about the same pace; where the runs' starts and the rows differ by multiples of
-    // 4 KB they otherwise ask a part of the memory's channels for y at any one time.  Expand launch of 19,675 tokens of ranks 8 to
-    // 128, in us, from the first strip / in turn: 8192 columns 166 / 138; rank 8 167 / 133, rank 128 184 /
-    // 167; 16384 columns, 10,082 tokens 179 / 161; 4096 columns (runs of 2 KB) 75.1 / 75.5, 14336 (runs of 7 KB) 138.5 / 141.7.
-    const int turn = (ncols * 2) % 4096 == 0 && (ldy * 2) % 4096 == 0 ? (u.tok0 >> 6) * 5 % nstrips : 0;
-    auto strip_at = [&](int i) __attribute__((always_inline)) { return i + turn < nstrips ? i + turn : i + turn - nstrips; };
+    const uint4 *gtile = reinterpret_cast<const uint4 *>(arena + u.w_off + (int64_t)c0 * r8);
 
-    // Copy of strip S_'s tile from the pool into LDS buffer BUF_ with loads that write LDS directly
-    // (no registers in between, so the copy runs while the MFMAs of the current strip do): every
-    // wavefront moves 1 KB pieces, lane l's 16 bytes landing at the piece's LDS base + 16*l.  The
-    // tile is 16*r8 pieces of 16 bytes, a multiple of 64, so a wavefront's piece is whole or absent.
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-#define LORA_DMA_TILE(BUF_, S_)                                                                         \
-    _Pragma("unroll") for (int q = 0; q < WREG; ++q) {                                                  \
-        const int piece0 = 64 * wave_u + kThreads * q;                                                  \
-        if (piece0 < tile_pieces)                                                                       \
-            dma16_to_lds(gtile + (int64_t)(S_) * tile_pieces + piece0 + lane, ltile + (BUF_) * 2048 + piece0); \
-    }
-    // the copies (and everything else this wavefront has in flight) have landed
-#define LORA_DMA_WAIT()                       \
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);  \
-    __builtin_amdgcn_s_waitcnt(kWaitcntVmcnt0); \
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    uint4 ya[4], yb[4];
-    auto fetch_y = [&](int s, uint4 (&yv)[4]) __attribute__((always_inline)) {
+    // batch rows of the wavefront's tokens, through the scalar cache
+    const int32_t *toks = perm + u.perm_off;
+    int row[kTokTile];
 #pragma unroll
-        // unconditional: rows of absent tokens point at the unit's first token (a per-lane condition
-        // around a 16-byte load makes the compiler split it into four masked 4-byte loads)
-        for (int e = 0; e < 4; ++e) yv[e] = ld16_stream(yrow[e] + s * kStrip);
-    };
-    auto compute = [&](int s, int buf, const uint4 (&yv)[4]) __attribute__((always_inline)) {
-        if (nt <= 0) return;
-        const uint4 *t = ltile + buf * 2048;
-        f32x4 acc[8];
+    for (int i = 0; i < kTokTile; ++i) row[i] = toks[max(0, min(kTokTile * wave + i, ntok_all - 1))];
+
+    // Chunk c of the tile of strip s into LDS (HELD > 1: of all strips), 1 KB per wavefront and step, nothing through registers: sub-block
+    // b and k step st take 64 pieces in operand order whatever the rank, so that the reads' addresses differ by constants.  Rank
+    // pieces beyond the padded rank are copies of the first one.
+    auto copy_tile = [&](int s, int c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int h = 0; h < HELD; ++h) {
+            if (h > 0 && h >= nstrips) break;
 #pragma unroll
             for (int st = 0; st < KSTEPS; ++st) {
-                if (32 * st < r8) {  // uniform
-                    // piece (sub-block b, rank piece 4*st + kq, column slot n).  Lanes whose rank piece
-                    // lies beyond the padded rank read piece 0 instead (their v operand is zero): an
-                    // unconditional 16-byte read stays one instruction, a conditional one becomes four
-                    const uint4 wv = t[(b * (r8 >> 3) + (j_ok[st] ? 4 * st + kq : 0)) * 16 + n];
+                if (128 * c + 32 * st < r8) {
+                    int kp = 16 * c + 4 * st + kq;
+                    kp = 8 * kp < r8 ? kp : 0;
+#pragma unroll
+                    for (int bb = 0; bb < 2; ++bb) {
+                        const int b = 2 * wave + bb;
+                        dma16_to_lds(gtile + (int64_t)(s + h) * tile_pieces + (b * (r8 >> 3) + kp) * 16 + n,
+                                     ltile + ((h * 8 + b) * KSTEPS + st) * 64);
+                    }
+                }
+            }
+        }
+    };
+    uint4 vh[KSTEPS], vl[KSTEPS];
+    auto load_v = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int st = 0; st < KSTEPS; ++st) {
+            const int j = 128 * c + 32 * st + 8 * kq;
+            const bool ok = n < nt && j < r8;
+            uint4 ph, pl;
+            if (!VF32) {
+                const int64_t off = u.v_off + 16 * wave * r8 + (j < r8 ? j : 0) * nt + 8 * min(n, nt - 1);
+                ph = ld16(sy.v_hi + off);
+                pl = ld16(sy.v_lo + off);
+            } else {
+                bf16x8 h, l;
+                load_v_operand(v_in + u.v_off + (int64_t)(ok ? kTokTile * wave + n : 0) * r8 + (j < r8 ? j : 0), ok, h, l);
+                ph = __builtin_bit_cast(uint4, h);
+                pl = __builtin_bit_cast(uint4, l);
+            }
+            vh[st] = ok ? ph : zero;
+            vl[st] = ok ? pl : zero;
+        }
+    };
+    f32x4 acc[8];
+    auto compute = [&](int held, int c) __attribute__((always_inline)) {
+        const uint4 *t = ltile + lane;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            if (c == 0) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int st = 0; st < KSTEPS; ++st) {
+                if (128 * c + 32 * st < r8) {  // uniform
+                    const uint4 wv = t[((held * 8 + b) * KSTEPS + st) * 64];
                     acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vh[st]), as_bf16x8(wv), acc[b], 0, 0, 0);
                     acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vl[st]), as_bf16x8(wv), acc[b], 0, 0, 0);
                 }
             }
         }
+    };
+    // the MFMA leaves tokens 4*kq + e (e = 0..3), columns 8*n .. 8*n+7 of the strip in this lane
+    uint16_t *yrow[4];
+    uint4 yv[kBigStrips][4];
+    auto update = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (y_ok[e]) {
-                const uint4 yy = yv[e];
+            if (4 * kq + e < nt) {
+                const uint4 yy = yv[s][e];
                 uint4 o;
                 o.x = pack_bf16_rne(bf16_bits_to_f32(yy.x & 0xFFFFu) + scale * acc[0][e],
                                     __uint_as_float(yy.x & 0xFFFF0000u) + scale * acc[1][e]);
@@ -1586,66 +1608,137 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, const int3
         }
     };
 
-    LORA_DMA_TILE(0, strip_at(0))
-    fetch_y(strip_at(0), ya);
-    LORA_DMA_WAIT()
-    __syncthreads();
-    for (int s = 0; s < nstrips; s += 2) {
-        // even strips from buffer 0, odd strips from buffer 1 (a single buffer above rank 128)
-        if (s + 1 < nstrips) {
-            if (DB) { LORA_DMA_TILE(1, strip_at(s + 1)) }
-            fetch_y(strip_at(s + 1), yb);
+    // unconditional (rows of absent tokens are the last token's: a per-lane condition around a 16-byte load makes the compiler split it
+    // into four masked 4-byte loads)
+    auto fetch_y = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) yv[s][e] = ld16_stream(yrow[e] + s * kStrip);
+    };
+    copy_tile(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (nt > 0) {
+        load_v(0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = kq == 0 ? row[e] : kq == 1 ? row[4 + e] : kq == 2 ? row[8 + e] : row[12 + e];
+            yrow[e] = y + (int64_t)r * ldy + u.p0 + c0 + 8 * n;
         }
-        compute(strip_at(s), 0, ya);
-        if (s + 1 >= nstrips) break;
-        if (!DB) {
-            __syncthreads();  // single buffer: everyone has finished reading strip s
-            LORA_DMA_TILE(0, strip_at(s + 1))
+        fetch_y(0);
+        if (HELD > 1 && nstrips > 1) {
+            fetch_y(1);
+            wait_vm<8>();  // all but the rows of y: the copies have landed
+        } else {
+            wait_vm<4>();
         }
-        LORA_DMA_WAIT()
-        __syncthreads();
-        if (s + 2 < nstrips) {
-            if (DB) { LORA_DMA_TILE(0, strip_at(s + 2)) }
-            fetch_y(strip_at(s + 2), ya);
-        }
-        compute(strip_at(s + 1), DB ? 1 : 0, yb);
-        if (s + 2 >= nstrips) break;
-        if (!DB) {
-            __syncthreads();
-            LORA_DMA_TILE(0, strip_at(s + 2))
-        }
-        LORA_DMA_WAIT()
-        __syncthreads();
+    } else {
+        wait_vm<0>();
     }
-#undef LORA_DMA_TILE
-#undef LORA_DMA_WAIT
+    __syncthreads();
+    if (HELD > 1) {
+        if (nt <= 0) return;
+#pragma unroll
+        for (int s = 0; s < kBigStrips; ++s)
+            if (s < nstrips) {
+                compute(s, 0);
+                update(s);
+            }
+    } else {
+        static_assert(kBigStrips == 2, "two strips, one after the other");
+        auto multiply = [&](int s) __attribute__((always_inline)) {
+            if (nt > 0) compute(0, 0);
+            if (CHUNKS > 1) {
+                __syncthreads();  // everyone has read the chunk
+                copy_tile(s, 1);
+                if (nt > 0) load_v(1);
+                wait_vm<0>();
+                __syncthreads();
+                if (nt > 0) compute(0, 1);
+            }
+        };
+        multiply(0);
+        if (nstrips > 1) {
+            __syncthreads();
+            copy_tile(1, 0);
+            if (nt > 0) {
+                if (CHUNKS > 1) load_v(0);
+                fetch_y(1);
+                update(0);
+            }
+            // behind the copies: four rows of y, and a full wavefront's four stores
+            if (nt == kTokTile)
+                wait_vm<8>();
+            else if (nt > 0)
+                wait_vm<4>();
+            else
+                wait_vm<0>();
+            __syncthreads();
+            multiply(1);
+            if (nt > 0) update(1);
+        } else if (nt > 0) {
+            update(0);
+        }
+    }
 }
 
-template <bool BIG, bool VF32, Slices BY = kSlicesByShrink, bool ROOM = false>
-static __device__ __forceinline__ void expand_dispatch(const Unit &u, const int32_t *__restrict__ perm,
-                                                       const uint16_t *__restrict__ arena,
+template <bool VF32>
+static __device__ __forceinline__ void expand_big_dispatch(const Unit &u, int c0, const int32_t *__restrict__ perm,
+                                                           const uint16_t *__restrict__ arena,
+                                                           const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
+{
+    const int r8 = u.r8;
+    if (r8 <= 32)
+        expand_big_body<1, 1, VF32>(u, c0, perm, arena, v_in, y, ldy, lds, sy);
+    else if (r8 <= 64)
+        expand_big_body<2, 1, VF32>(u, c0, perm, arena, v_in, y, ldy, lds, sy);
+    else if (r8 <= 128)
+        expand_big_body<4, 1, VF32>(u, c0, perm, arena, v_in, y, ldy, lds, sy);
+    else
+        expand_big_body<4, 2, VF32>(u, c0, perm, arena, v_in, y, ldy, lds, sy);
+}
+
+// Which unit and which of its strips work group b of a launch of 64-token units takes: a row of 8 units takes 8 * subs work groups,
+// each unit's on places of one residue mod 8, i.e. on one XCD.  subs = how many work groups a unit of the list has; lists of several
+// projections of unlike width have sections behind the first one.  (With the widest projection's subs for all of them, work groups
+// without columns returning at once, q|k|v of 9,100 tokens took 55.5 us, 52.5 without those.)
+struct BigMore {
+    int n;                                                                       // sections behind the first
+    int first_place[kMaxBigSections], first_unit[kMaxBigSections], subs[kMaxBigSections];  // the end in [n], n < kMaxBigSections
+};
+struct BigPlace {
+    int unit, c0;  // unit < 0: none
+    __device__ __forceinline__ BigPlace(int b, int n_first, int subs, const BigMore &more)
+    {
+        int from = 0, to = n_first;
+        const int rows = (n_first + 7) >> 3;
+        if (b >= 8 * rows * subs) {
+            int s = 0;
+            while (s + 1 < more.n && b >= more.first_place[s + 1]) ++s;
+            b -= more.first_place[s];
+            from = more.first_unit[s];
+            to = more.first_unit[s + 1];
+            subs = more.subs[s];
+        }
+        const int t = b >> 3, q = (int)((unsigned)t / (unsigned)subs);
+        unit = from + 8 * q + (b & 7);
+        if (unit >= to) unit = -1;
+        c0 = (t - q * subs) * (kBigStrips * kStrip);
+    }
+};
+
+template <bool VF32, Slices BY = kSlicesByShrink>
+static __device__ __forceinline__ void expand_dispatch(const Unit &u, const uint16_t *__restrict__ arena,
                                                        const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy, char *lds, const Sync &sy)
 {
     const int r8 = u.r8;
-    if (BIG) {
-        if (r8 <= 32)
-            expand_big_body<1, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
-        else if (r8 <= 64)
-            expand_big_body<2, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
-        else if (r8 <= 128)
-            expand_big_body<4, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
-        else
-            expand_big_body<8, VF32>(u, perm, arena, v_in, y, ldy, lds, sy);
-    } else {
-        if (r8 <= 32)
-            expand_body<1, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
-        else if (r8 <= 64)
-            expand_body<2, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
-        else if (r8 <= 128)
-            expand_body<4, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
-        else
-            expand_body<8, VF32, BY, ROOM>(u, arena, v_in, y, ldy, lds, sy);
-    }
+    if (r8 <= 32)
+        expand_body<1, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+    else if (r8 <= 64)
+        expand_body<2, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+    else if (r8 <= 128)
+        expand_body<4, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
+    else
+        expand_body<8, VF32, BY>(u, arena, v_in, y, ldy, lds, sy);
 }
 
 
@@ -2020,18 +2113,33 @@ __global__ __launch_bounds__(kThreads) void k_shrink(const Unit *__restrict__ un
     LORA_CLOCK(4);
 }
 
-// BIG: units of up to 64 tokens (token-heavy groups), token indices from perm, the next strip's
-// loads in flight while the current one computes.  VF32: v is fp32 from the caller (stand-alone expand).
+// Units of up to 16 tokens (BIG is false: those of 64 run in k_expand_big), whose token indices are their own.  VF32: v is fp32 from
+// the caller (stand-alone expand).
 template <bool BIG, bool VF32>
-__global__ __launch_bounds__(kThreads, BIG ? 2 : 4) void k_expand(const Unit *__restrict__ units,
-                                                                  const int32_t *__restrict__ perm,
-                                                                  const uint16_t *__restrict__ arena,
-                                                                  const float *__restrict__ v_in,
-                                                                  uint16_t *__restrict__ y, int64_t ldy, Sync sy)
+__global__ __launch_bounds__(kThreads, 4) void k_expand(const Unit *__restrict__ units, const int32_t *__restrict__ /* perm */,
+                                                        const uint16_t *__restrict__ arena, const float *__restrict__ v_in,
+                                                        uint16_t *__restrict__ y, int64_t ldy, Sync sy)
 {
-    __shared__ __attribute__((aligned(16))) char lds[BIG ? kBigLds : kExpandLds];
+    static_assert(!BIG, "units of up to 16 tokens");
+    __shared__ __attribute__((aligned(16))) char lds[kExpandLds];
     LORA_CLOCK_E(0);
-    expand_dispatch<BIG, VF32>(units[blockIdx.x], perm, arena, v_in, y, ldy, lds, sy);
+    expand_dispatch<VF32>(units[blockIdx.x], arena, v_in, y, ldy, lds, sy);
+    LORA_CLOCK_E(4);
+}
+
+// Units of up to 64 tokens (token-heavy groups), token indices from perm, `subs` work groups a unit.
+template <bool VF32>
+__global__ __launch_bounds__(kThreads, 4) void k_expand_big(const Unit *__restrict__ units, int n_first, int subs,
+                                                            const int32_t *__restrict__ perm,
+                                                            const uint16_t *__restrict__ arena,
+                                                            const float *__restrict__ v_in, uint16_t *__restrict__ y,
+                                                            int64_t ldy, Sync sy, BigMore more)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kBigTile];
+    const BigPlace p(blockIdx.x, n_first, subs, more);
+    if (p.unit < 0 || p.c0 >= units[p.unit].pn) return;
+    LORA_CLOCK_E(0);
+    expand_big_dispatch<VF32>(units[p.unit], p.c0, perm, arena, v_in, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 
@@ -2041,7 +2149,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_parts(const Unit *__rest
 {
     __shared__ __attribute__((aligned(16))) char lds[kExpandLds];
     LORA_CLOCK_E(0);
-    expand_dispatch<false, false, kSlicesByExpand>(units[blockIdx.x], nullptr, arena, nullptr, y, ldy, lds, sy);
+    expand_dispatch<false, kSlicesByExpand>(units[blockIdx.x], arena, nullptr, y, ldy, lds, sy);
     LORA_CLOCK_E(4);
 }
 
@@ -2049,7 +2157,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_parts(const Unit *__rest
 // for their tokens' v through the counters.
 __global__ __launch_bounds__(kThreads, 4) void k_apply_fused(const Unit *__restrict__ shrink_units, int n_shrink,
                                                           const Unit *__restrict__ expand_units,
-                                                          const int32_t *__restrict__ perm,
+                                                          const int32_t *__restrict__ /* perm */,
                                                           const uint16_t *__restrict__ arena,
                                                           const uint16_t *__restrict__ x, int64_t ldx, int in,
                                                           int k_slice_len, float *__restrict__ parts, int n_slices,
@@ -2061,7 +2169,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_apply_fused(const Unit *__restr
     if (b < n_shrink)
         shrink_body(shrink_units[b], arena, x, ldx, in, k_slice_len, parts, n_slices, slice_stride, lds, sy);
     else
-        expand_dispatch<false, false, kSlicesByWaiting>(expand_units[b - n_shrink], perm, arena, nullptr, y, ldy, lds, sy);
+        expand_dispatch<false, kSlicesByWaiting>(expand_units[b - n_shrink], arena, nullptr, y, ldy, lds, sy);
 }
 
 // A mixed batch in two launches on one queue: the token-heavy groups' units first in the grid (they
@@ -2070,7 +2178,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_apply_fused(const Unit *__restr
 // units write v complete as bf16 hi + lo, the k-slice units leave partial sums and the one that
 // completes a token tile writes its hi + lo; both kinds of expand unit read v from there.
 constexpr int kMixedShrinkLds = kPrefillLds > kShrinkLds ? kPrefillLds : kShrinkLds;
-constexpr int kMixedExpandLds = kBigLds > kExpandLds ? kBigLds : kExpandLds;
+constexpr int kMixedExpandLds = kBigTile > kExpandLds ? kBigTile : kExpandLds;
 
 template <bool ANY>
 __global__ __launch_bounds__(kThreads, ANY ? 2 : 4) void k_shrink_mixed(
@@ -2091,19 +2199,21 @@ __global__ __launch_bounds__(kThreads, ANY ? 2 : 4) void k_shrink_mixed(
 }
 
 template <Slices BY>
-__global__ __launch_bounds__(kThreads, 2) void k_expand_mixed(const Unit *__restrict__ big_units, int n_big,
+__global__ __launch_bounds__(kThreads, 4) void k_expand_mixed(const Unit *__restrict__ big_units, int n_first, int subs, int big_grid,
                                                               const Unit *__restrict__ units,
-                                                              const int32_t *__restrict__ perm,
-                                                              const uint16_t *__restrict__ arena,
-                                                              uint16_t *__restrict__ y, int64_t ldy, Sync sy)
+                                                              const uint16_t *__restrict__ arena, const int32_t *__restrict__ perm,
+                                                              uint16_t *__restrict__ y, int64_t ldy, Sync sy, BigMore more)
 {
     __shared__ __attribute__((aligned(16))) char lds[kMixedExpandLds];
     const int b = blockIdx.x;
     LORA_CLOCK_E(0);
-    if (b < n_big)
-        expand_dispatch<true, false>(big_units[b], perm, arena, nullptr, y, ldy, lds, sy);
-    else
-        expand_dispatch<false, false, BY, true>(units[b - n_big], perm, arena, nullptr, y, ldy, lds, sy);
+    if (b < big_grid) {
+        const BigPlace p(b, n_first, subs, more);
+        if (p.unit < 0 || p.c0 >= big_units[p.unit].pn) return;
+        expand_big_dispatch<false>(big_units[p.unit], p.c0, perm, arena, nullptr, y, ldy, lds, sy);
+    } else {
+        expand_dispatch<false, BY>(units[b - big_grid], arena, nullptr, y, ldy, lds, sy);
+    }
     LORA_CLOCK_E(4);
 }
 
@@ -2853,6 +2963,31 @@ hipError_t launch_shrink_wide(const LaunchCtx &c, bool more_than_one_round, cons
     return hipGetLastError();
 }
 
+// The places of a launch of 64-token expand units, section by section.
+struct BigGrid {
+    int n_first = 0, subs = 1;
+    int64_t places = 0;
+    BigMore more = {};
+    explicit BigGrid(const LaunchCtx &c)
+    {
+        int unit = 0;
+        for (int i = 0; i < c.n_sections; ++i) {
+            const int per_unit = (c.sections[i].cols + kBigStrips * kStrip - 1) / (kBigStrips * kStrip);
+            if (i == 0) {
+                n_first = c.sections[0].n_units;
+                subs = per_unit;
+            } else {
+                more.first_place[more.n] = (int)std::min<int64_t>(places, 0x7FFFFFFF);
+                more.first_unit[more.n] = unit;
+                more.subs[more.n] = per_unit;
+                more.first_unit[++more.n] = unit + c.sections[i].n_units;
+            }
+            unit += c.sections[i].n_units;
+            places += (int64_t)(c.sections[i].n_units + 7) / 8 * 8 * per_unit;
+        }
+    }
+};
+
 hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16_t *y, int64_t ldy, const SyncArgs *sync,
                          hipStream_t stream)
 {
@@ -2860,12 +2995,20 @@ hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16
     if (!sync && !v_in) return hipErrorInvalidValue;
     const Sync sy = make_sync(sync, 0);
     const dim3 g(c.n_units), b(kThreads);
-    if (!big && sync && sync->parts)
+    if (big) {
+        if (c.n_sections > kMaxBigSections) return hipErrorInvalidValue;
+        const BigGrid bg(c);
+        if (bg.places > 0x7FFFFFFF) return hipErrorInvalidValue;
+        const dim3 gb((unsigned)bg.places);
+        const unsigned more_lds = c.top_rank <= kBigSpreadMaxRank ? kBigSpread : 0;
+        if (sync)
+            hipLaunchKernelGGL(k_expand_big<false>, gb, b, more_lds, stream, c.units, bg.n_first, bg.subs, c.perm, c.arena, v_in, y, ldy,
+                               sy, bg.more);
+        else
+            hipLaunchKernelGGL(k_expand_big<true>, gb, b, more_lds, stream, c.units, bg.n_first, bg.subs, c.perm, c.arena, v_in, y, ldy,
+                               sy, bg.more);
+    } else if (sync && sync->parts)
         hipLaunchKernelGGL(k_expand_parts, g, b, 0, stream, c.units, c.arena, y, ldy, sy);
-    else if (big && sync)
-        hipLaunchKernelGGL((k_expand<true, false>), g, b, 0, stream, c.units, c.perm, c.arena, v_in, y, ldy, sy);
-    else if (big)
-        hipLaunchKernelGGL((k_expand<true, true>), g, b, 0, stream, c.units, c.perm, c.arena, v_in, y, ldy, sy);
     else if (sync)
         hipLaunchKernelGGL((k_expand<false, false>), g, b, 0, stream, c.units, c.perm, c.arena, v_in, y, ldy, sy);
     else
@@ -2958,15 +3101,17 @@ hipError_t launch_shrink_mixed(const LaunchCtx &heavy, int n_hi, const LaunchCtx
 hipError_t launch_expand_mixed(const LaunchCtx &big, const LaunchCtx &c, uint16_t *y, int64_t ldy, const SyncArgs *sync,
                                hipStream_t stream)
 {
-    const int total = big.n_units + c.n_units;
+    if (big.n_sections > kMaxBigSections) return hipErrorInvalidValue;
+    const BigGrid bg(big);
+    const int64_t total = bg.places + c.n_units;
     if (total <= 0) return hipSuccess;
-    if (!sync) return hipErrorInvalidValue;
+    if (!sync || total > 0x7FFFFFFF) return hipErrorInvalidValue;
     if (sync->parts)
-        hipLaunchKernelGGL(k_expand_mixed<kSlicesByExpand>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
-                           c.perm, c.arena, y, ldy, make_sync(sync, 0));
+        hipLaunchKernelGGL(k_expand_mixed<kSlicesByExpand>, dim3((unsigned)total), dim3(kThreads), 0, stream, big.units, bg.n_first,
+                           bg.subs, (int)bg.places, c.units, c.arena, c.perm, y, ldy, make_sync(sync, 0), bg.more);
     else
-        hipLaunchKernelGGL(k_expand_mixed<kSlicesByShrink>, dim3(total), dim3(kThreads), 0, stream, big.units, big.n_units, c.units,
-                           c.perm, c.arena, y, ldy, make_sync(sync, 0));
+        hipLaunchKernelGGL(k_expand_mixed<kSlicesByShrink>, dim3((unsigned)total), dim3(kThreads), 0, stream, big.units, bg.n_first,
+                           bg.subs, (int)bg.places, c.units, c.arena, c.perm, y, ldy, make_sync(sync, 0), bg.more);
     return hipGetLastError();
 }
 

@@ -154,6 +154,42 @@ def test_strips_of_token_heavy_expand_units_in_any_order(out_features, pad):
     dp.close()
 
 
+@pytest.mark.parametrize("decode", [[], [(3, 40), (1, 200)]], ids=["alone", "beside decode"])
+@pytest.mark.parametrize("outs", [
+    [384], [1408],             # runs of 3 strips, of 4 and of 3: a work group with one strip
+    [1152, 128, 640, 2176],    # projections of unlike widths: 2, 1, 2 and 3 work groups a unit
+    [256, 256, 4224],          # and of like ones, then a wider one
+])
+def test_work_groups_of_64_token_expand_units(outs, decode):
+    """Two strips of a unit per work group, at every number of rank steps and chunks, whole and partial; tiles of 64 tokens with one
+    wavefront's worth, one token more, one less; lists whose length is no multiple of 8."""
+    groups = [(64, 8), (33, 24), (65, 32), (49, 40), (47, 64), (128, 72), (63, 128), (79, 136), (100, 200), (32, 256), (129, 16)]
+    b = _batch(192, outs[0], groups + decode, idle=3, seed=len(outs))
+    others = [_batch(192, o, groups + decode, idle=3, seed=len(outs)) for o in outs[1:]]
+    dps = [G.DevicePool(q) for q in [b] + others]
+    pools = [dp.pool for dp in dps]
+    opts = L.plan_options(heavy_min_batch=64, big_runs_max_units=0)
+    seg = (L.lora_segments_build_multi(pools, b.token_adapter, options=opts) if len(pools) > 1
+           else L.lora_segments_build(pools[0], b.token_adapter, options=opts))
+    x_bits = b.x_bits()
+    y0 = np.concatenate([q.y0_bits("small") for q in [b] + others], axis=1)
+    y = G.bits_to_dev(y0)
+    ws = torch.full((max(L.lora_apply_workspace_bytes(pools[0], seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    if len(pools) > 1:
+        L.lora_apply_multi(pools, seg, G.bits_to_dev(x_bits), y, ws)
+    else:
+        L.lora_apply(pools[0], seg, G.bits_to_dev(x_bits), y, ws)
+    torch.cuda.synchronize()
+    got, at = G.dev_to_bits(y), 0
+    for dp, q in zip(dps, [b] + others):
+        part = slice(at, at + q.out_features)
+        G.check_all_rows(dp, x_bits, np.ascontiguousarray(y0[:, part]), np.ascontiguousarray(got[:, part]))
+        at += q.out_features
+    L.lora_segments_destroy(seg)
+    for dp in dps:
+        dp.close()
+
+
 # ---- batches of few units: one launch by themselves, two under capture ------------------------------------------
 @pytest.mark.parametrize("case", [
     # (which of them take the one launch is tested in test_launch_routes.py)
