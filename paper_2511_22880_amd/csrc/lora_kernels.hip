@@ -745,6 +745,9 @@ static __device__ __forceinline__ void complete_tile(const Unit &u, const RankRo
     }
 }
 
+// which of n passes along k the i-th tile of tokens of a group begins with, where they begin in turn: i modulo the power of two in n
+static __device__ __forceinline__ int first_pass(int i, int n) { return n > 0 ? i & ((1 << (31 - __builtin_clz(n))) - 1) : 0; }
+
 template <int JB, int TB, int WD, int XD = 1>
 static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, const RankRows &rr, const int32_t *__restrict__ perm,
                                                              const uint16_t *__restrict__ arena,
@@ -819,6 +822,17 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         // ahead included, so that every pass of 128 of k took a whole trip to memory.
         const int npass = kend > kbeg ? (kend - kbeg + kPfPassK - 1) / kPfPassK : 0;
         const int nfull = kend > kbeg ? (kend - kbeg) / kPfPassK : 0;
+        // The passes in order, but from another one in every tile of tokens of a group where rows of x and the wavefronts' quarters lie
+        // whole multiples of 4 KB apart: all units of a launch walk k at about the same pace, and would ask a part of the memory's
+        // channels at any one time.  Not where the rank rows are more than 1 MB, which the units of an XCD then share less of.  A call
+        // in us, in order / by 3 passes a tile: 19,675 tokens, 8192 -> 1024, rank 8 82 / 72, rank 32 91 / 85.6, rank 64 107 / 104.6;
+        // 10,082 tokens, 16384 -> 1024, rank 8 79 / 68.9, rank 32 89.7 / 82.6, but rank 64 110 / 118.  In rows of 8 KB and 28 KB it gains
+        // nothing, and few prompts pay for it: two of 900 tokens, 3712 -> 640, 11.4 / 11.7, four of 700, 8192 -> 1024, 16.7 / 16.8.
+        const bool turns = kquarter * 2 % 4096 == 0 && ldx * 2 % 4096 == 0 && (int64_t)r8 * in <= 512 * 1024;
+        const int turn = turns ? first_pass(3 * (u.tok0 / kPfTokens), nfull) : 0;
+        auto pass_k = [&](int i) __attribute__((always_inline)) {
+            return kbeg + kPfPassK * (i < nfull ? (i + turn < nfull ? i + turn : i + turn - nfull) : i);
+        };
         auto x_all = [&](int k0, uint4(&xq)[NL]) __attribute__((always_inline)) {
             const int kx = min(k0 + 8 * n, in - 8);
 #pragma unroll
@@ -853,24 +867,28 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         // XD passes of x and WD k steps of A^T are in flight per wavefront (registers)
         uint4 xq[XD][NL], w[WD][JB];
 #pragma unroll
-        for (int q = 0; q < XD; ++q) x_all(kbeg + min(q, max(npass - 1, 0)) * kPfPassK, xq[q]);
+        for (int q = 0; q < XD; ++q) x_all(pass_k(min(q, max(npass - 1, 0))), xq[q]);
 #pragma unroll
         for (int d = 0; d < WD; ++d)
 #pragma unroll
-            for (int jb = 0; jb < JB; ++jb) w[d][jb] = w_step(kbeg + 32 * d, jb);
-        int i0 = 0;
+            for (int jb = 0; jb < JB; ++jb) w[d][jb] = w_step(pass_k(0) + 32 * d, jb);
+        int i0 = 0, k1 = pass_k(0), kx = pass_k(XD);
+        const int kturn = kbeg + kPfPassK * nfull;  // behind the last whole pass comes the first
         for (; i0 + 2 * XD <= nfull; i0 += XD) {
 #pragma unroll
             for (int q = 0; q < XD; ++q) {
-                const int k0 = kbeg + (i0 + q) * kPfPassK;
+                const int k0 = k1;
+                k1 = k1 + kPfPassK < kturn ? k1 + kPfPassK : kbeg;
                 stage(xq[q]);
-                x_all(k0 + XD * kPfPassK, xq[q]);
+                x_all(kx, xq[q]);
+                kx = kx + kPfPassK < kturn ? kx + kPfPassK : kbeg;
                 wave_sync();
 #pragma unroll
                 for (int d = 0; d < kPfPassK / 32; ++d) {
                     k_step(d, w[d % WD]);
 #pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) w[d % WD][jb] = w_step(k0 + 32 * (d + WD), jb);
+                    for (int jb = 0; jb < JB; ++jb)
+                        w[d % WD][jb] = w_step(d + WD < 4 ? k0 + 32 * (d + WD) : k1 + 32 * (d + WD - 4), jb);
                 }
                 wave_sync();
             }
@@ -881,18 +899,19 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         for (int q = 0; q < XD; ++q) {
             const int i = i0 + q;
             if (i < npass) {
-                const int k0 = kbeg + i * kPfPassK;
+                const int k0 = pass_k(i), k1 = pass_k(i + 1);
                 stage(xq[q]);
-                if (i + XD < npass) x_all(k0 + XD * kPfPassK, xq[q]);
+                if (i + XD < npass) x_all(pass_k(i + XD), xq[q]);
                 wave_sync();
 #pragma unroll
                 for (int d = 0; d < kPfPassK / 32; ++d) {
                     const int k = k0 + 32 * d;
                     if (k < kend) {
                         k_step(d, w[d % WD]);
-                        if (k + 32 * WD < kend) {
+                        if (d + WD < 4 || i + 1 < npass) {
 #pragma unroll
-                            for (int jb = 0; jb < JB; ++jb) w[d % WD][jb] = w_step(k + 32 * WD, jb);
+                            for (int jb = 0; jb < JB; ++jb)
+                                w[d % WD][jb] = w_step(d + WD < 4 ? k + 32 * WD : k1 + 32 * (d + WD - 4), jb);
                         }
                     }
                 }
@@ -999,6 +1018,14 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     const int kend = min(in, kbeg + ks_len);
     const int npass = (kend - kbeg + kPfPassK - 1) / kPfPassK;
     const int nfull = (kend - kbeg) / kPfPassK;  // passes that hold 128 of k (in is a multiple of 64: the last may hold 64)
+    // The passes in order, but one further in every tile of tokens of a group, for the same reason as above.  A call in us, in order /
+    // in turn: rank 256 14336 -> 1024 394 / 372, 8192 -> 2048 260 / 252, 4096 -> 4096 214 / 211; rank 192 14336 -> 1024 256 / 245; rank 128
+    // 8192 -> 2048 151 / 148, 4096 -> 4096 127.9 / 126.7.  By 3 passes a tile, whose rows of A^T the units of an XCD no longer share, rank 256
+    // 525, 328 and 221.
+    const int turn = first_pass(u.tok0 / TOK, nfull);
+    auto pass_k = [&](int i) __attribute__((always_inline)) {
+        return kbeg + kPfPassK * (i < nfull ? (i + turn < nfull ? i + turn : i + turn - nfull) : i);
+    };
 
     // Loads without conditions (rows of tokens beyond ntok are the last token's, see xrow; a chunk beyond
     // the row is fetched from the row's last chunk and a k step beyond kend from the last step, neither
@@ -1039,28 +1066,29 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     uint4 xs[PD][TB], w[WP][SP][JBW];
 #pragma unroll
     for (int q = 0; q < PD; ++q) {
-        x_pass(kbeg + min(q, max(npass - 1, 0)) * kPfPassK, xs[q]);
+        x_pass(pass_k(min(q, max(npass - 1, 0))), xs[q]);
         if (q < WP) {
 #pragma unroll
             for (int d = 0; d < SP; ++d)
 #pragma unroll
-                for (int j = 0; j < JBW; ++j) w[q][d][j] = w_step(kbeg + q * kPfPassK + 32 * d, j);
+                for (int j = 0; j < JBW; ++j) w[q][d][j] = w_step(pass_k(q) + 32 * d, j);
         }
     }
 #ifdef LORA_WG_CLOCKS
     unsigned long long c_wait = 0;  // from the top of a pass to the barrier's exit, summed over the passes
 #endif
-    int i0 = 0;
+    int i0 = 0, kw = pass_k(WP), kx = pass_k(PD);
+    const int kturn = kbeg + kPfPassK * nfull;  // behind the last whole pass comes the first
     for (; i0 + 2 * PD <= nfull; i0 += PD) {
 #pragma unroll
         for (int q = 0; q < PD; ++q) {
-            const int k0 = kbeg + (i0 + q) * kPfPassK;
             const int base = (q & 1) * TOK;
 #ifdef LORA_WG_CLOCKS
             const unsigned long long c_top = wall_clock64();
 #endif
             stage(base, xs[q]);
-            x_pass(k0 + PD * kPfPassK, xs[q]);
+            x_pass(kx, xs[q]);
+            kx = kx + kPfPassK < kturn ? kx + kPfPassK : kbeg;
             __syncthreads();
 #ifdef LORA_WG_CLOCKS
             c_wait += wall_clock64() - c_top;
@@ -1069,8 +1097,9 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
             for (int d = 0; d < SP; ++d) {
                 k_step(base, d, w[q % WP][d]);
 #pragma unroll
-                for (int j = 0; j < JBW; ++j) w[q % WP][d][j] = w_step(k0 + WP * kPfPassK + 32 * d, j);
+                for (int j = 0; j < JBW; ++j) w[q % WP][d][j] = w_step(kw + 32 * d, j);
             }
+            kw = kw + kPfPassK < kturn ? kw + kPfPassK : kbeg;
         }
     }
     // the last passes (fewer than 2 PD, the last maybe 64 of k): the same, with every request and every k
@@ -1079,17 +1108,17 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     for (int q = 0; q < 2 * PD; ++q) {
         const int i = i0 + q;
         if (i < npass) {
-            const int k0 = kbeg + i * kPfPassK;
+            const int k0 = pass_k(i), kw = pass_k(i + WP);
             const int base = (q & 1) * TOK;
             stage(base, xs[q % PD]);
-            if (i + PD < npass) x_pass(k0 + PD * kPfPassK, xs[q % PD]);
+            if (i + PD < npass) x_pass(pass_k(i + PD), xs[q % PD]);
             __syncthreads();
 #pragma unroll
             for (int d = 0; d < SP; ++d) {
                 if (k0 + 32 * d < kend) k_step(base, d, w[q % WP][d]);
                 if (i + WP < npass) {
 #pragma unroll
-                    for (int j = 0; j < JBW; ++j) w[q % WP][d][j] = w_step(k0 + WP * kPfPassK + 32 * d, j);
+                    for (int j = 0; j < JBW; ++j) w[q % WP][d][j] = w_step(kw + 32 * d, j);
                 }
             }
         }

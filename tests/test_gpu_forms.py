@@ -105,6 +105,28 @@ def test_token_heavy_units_cut_along_k(shape, most, sizes, cut):
     dp.close()
 
 
+@pytest.mark.parametrize("pad", [0, 64])
+@pytest.mark.parametrize("in_features", [8192, 16384, 24576, 8256])
+@pytest.mark.parametrize("cut", [0, 1 << 20])
+def test_token_heavy_tiles_that_begin_with_another_pass(in_features, pad, cut):
+    """Rows and quarters of whole multiples of 4 KB (8192, 16384 and, uncut, 24576 features; not 8256, nor padded rows), in more tiles than a
+    walk has passes, up to rank 64 by the size of the rank rows and above always."""
+    b = _batch(in_features, 128, [(300, 8), (33, 24), (600, 32), (200, 64), (130, 72), (200, 160), (100, 256)], idle=2, seed=in_features)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_k_cut_max_units=cut))
+    x = torch.full((b.T, in_features + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    x[:, :in_features] = G.bits_to_dev(x_bits)
+    y = G.bits_to_dev(y0)
+    ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    L.lora_apply(dp.pool, seg, x[:, :in_features], y, ws)
+    torch.cuda.synchronize()
+    rows = np.arange(0, b.T, 7)
+    G.check_parity(G.dev_to_bits(y), G.oracle_apply(dp, x_bits, y0, rows=rows), y0, b.token_adapter, rows=rows)
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 @pytest.mark.parametrize("in_features, ranks, slices", HALVES)
 def test_rank_halves_of_few_token_heavy_units(in_features, ranks, slices):
     """Launches of few token-heavy units: halves of the rank rows, even and not, of units of 32 and 64 tokens, whole and cut along
