@@ -207,7 +207,8 @@ typedef struct {
      * order of fp32 sums. */
     int32_t whole_k_max_in;        /* largest in_features planned without k-slices (built in: 18432)      */
     int32_t heavy_min_tokens;      /* a group of at least this many tokens is token-heavy (32) ...        */
-    int32_t heavy_min_batch;       /* ... in a batch of at least this many active tokens (1024)           */
+    int32_t heavy_min_batch;       /* ... in a batch of at least this many active tokens (1024, or fewer  *
+                                    * where an estimate from ranks, tokens and in_features says so)       */
     int32_t heavy_k_cut_max_units; /* token-heavy shrink units are cut along k while the cut units stay    *
                                     * within this count (built in: 1 to 4 slices by estimated time)        */
     int32_t big_runs_max_units;    /* 64-token expand units take their columns in 8 runs or more, not 4, while *

@@ -573,8 +573,8 @@ static int expand_cols_per_unit(int r8, int out)
 
 // Groups with at least this many tokens are token-heavy: their shrink runs on token tiles that read x
 // once (instead of once per 16 rank rows), their expand units hold up to 64 tokens and several column passes.
-// Only in batches of at least kPrefillMinBatch tokens: a 128-token tile streams about 1 MB of x, far
-// longer than a whole decode-sized launch lasts.
+// Only in batches of at least kPrefillMinBatch tokens, or where an estimate says so (small_batch_token_heavy): a 128-token tile streams
+// about 1 MB of x, far longer than a whole decode-sized launch lasts.
 static const int kPrefillMinTokens = 32;
 static const int kPrefillMinBatch = 1024;
 // Between kWholeKMin and this many whole-k shrink units (four rounds of one work group per compute unit of the chip) the decode
@@ -834,6 +834,34 @@ static bool decode_single_pays(int opt, int64_t whole_k_units, int64_t expand_un
 static int opt_whole_k_max_in(const lora_segments *sg) { return sg->opts.whole_k_max_in >= 0 ? sg->opts.whole_k_max_in : kWholeKMaxIn; }
 static int opt_heavy_min_tokens(const lora_segments *sg) { return sg->opts.heavy_min_tokens >= 0 ? sg->opts.heavy_min_tokens : kPrefillMinTokens; }
 static int opt_heavy_min_batch(const lora_segments *sg) { return sg->opts.heavy_min_batch >= 0 ? sg->opts.heavy_min_batch : kPrefillMinBatch; }
+// Batches of fewer than kPrefillMinBatch tokens whose groups take token-heavy units all the same: those of only such groups, where
+// units of 16 tokens would fetch the adapters so often that it takes longer than a launch of few token-heavy units, which lasts as long as
+// one of these walks k.  Estimated from the shrink half alone, so that every projection of one x decides alike, whatever its columns.
+// us per call by units of 16 tokens / token-heavy ones: one prompt of 900 tokens, 4096 -> 4096, rank 64 16.1 / 12.9, rank 256 43.9 / 20.2;
+// 512 tokens there, rank 64 12.6 / 11.7 (left), rank 256 26.2 / 18.6; 256 tokens, rank 256 16.9 / 18.4; 14336 -> 4096, 900 tokens, rank 64
+// 31.6 / 19.7, rank 256 93.6 / 32.9, 256 tokens, rank 256 27.9 / 30.1; above rank 64 the token-heavy units' walk is longer: 646 tokens of rank 128,
+// 1600 -> 2304, 14.0 / 17.7, 726 tokens, 4032 -> 512, 16.6 / 20.2, 700 tokens, 9024 -> 1536, 31.2 / 22.8.  Over 150 random batches the
+// median of those behind the line gains 40 % (lora_apply, lora_apply_multi and the halves apart; 167 % at most), in lora_linear, which uses the
+// shrink half only, -1 to 27 %.  The halves apart lose up to 6 % at small widths just beyond 8192 features, rank 64 (8256 -> 640, 800 tokens,
+// 15.4 / 16.4), and had lost more where other groups are small, which then take launches of their own (803 tokens of 16 prompts there 16.9 / 27.6).
+static bool small_batch_token_heavy(const lora_segments *sg, const lora_pool *pool, const std::vector<int32_t> &count, int n_active,
+                                    int heavy_min_tokens)
+{
+    if (sg->opts.heavy_min_batch >= 0 || n_active >= kPrefillMinBatch) return false;
+    int top_rank = 0;
+    int64_t rows = 0;  // rank rows that units of 16 tokens fetch
+    for (size_t a = 0; a < count.size(); ++a) {
+        if (!count[a]) continue;
+        if (count[a] < heavy_min_tokens) return false;
+        top_rank = std::max(top_rank, pool->r8[a]);
+        rows += (int64_t)((count[a] + lora::kTokTile - 1) / lora::kTokTile) * pool->r8[a];
+    }
+    const double in = pool->in_features;
+    const double by_16 = 3.0 + 2e-6 * (double)rows * in / 7.0;  // us: the rank rows' bytes at 7 TB/s
+    const double heavy = 3.5 + 0.009 * top_rank + in / 1024 * (0.34 + 0.0032 * top_rank) +
+                         (top_rank > 192 ? 2.0 : top_rank > 64 ? 4.0 : 0.0);
+    return by_16 > heavy;
+}
 static int opt_big_runs_max_units(const lora_segments *sg);
 static unsigned opt_spin_limit(const lora_segments *sg) { return sg->opts.fused_wait_limit ? sg->opts.fused_wait_limit : g_spin_limit.load(); }
 
@@ -1143,7 +1171,9 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         ++count[a];
         ++n_active;
     }
-    const int heavy_min_tokens = opt_heavy_min_tokens(sg), heavy_min_batch = opt_heavy_min_batch(sg);
+    const int heavy_min_tokens = opt_heavy_min_tokens(sg);
+    const int heavy_min_batch =
+        !lean && small_batch_token_heavy(sg, pool, count, n_active, heavy_min_tokens) ? 1 : opt_heavy_min_batch(sg);
     sg->pool = pool;
     sg->pool_id = pool->id;
     sg->layout_in = pool->in_features;

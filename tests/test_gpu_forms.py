@@ -127,6 +127,34 @@ def test_token_heavy_tiles_that_begin_with_another_pass(in_features, pad, cut):
     dp.close()
 
 
+@pytest.mark.parametrize("in_features, groups", [(4096, [(900, 64)]), (4096, [(128, 256)] * 4), (9024, [(65, 128)] * 11)])
+def test_small_batches_of_token_heavy_units(in_features, groups):
+    """Fewer than 1024 tokens: the whole apply, the halves apart, the adapted layer's shrink (that they are token-heavy is tested in
+    test_launch_routes.py)."""
+    b = _batch(in_features, 384, groups, idle=3, seed=in_features)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    x = G.bits_to_dev(x_bits)
+    seg = L.lora_segments_build(dp.pool, b.token_adapter)
+    ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    vws = torch.full((max(L.lora_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    v = torch.full((L.lora_segments_info(seg)["v_floats"],), float("nan"), dtype=torch.float32, device="cuda")
+    y, apart, none = (G.bits_to_dev(y0) for _ in range(3))
+    L.lora_apply(dp.pool, seg, x, y, ws)
+    L.lora_shrink(dp.pool, seg, x, v, vws)
+    L.lora_expand(dp.pool, seg, v, apart)
+    w = torch.empty(in_features * 384, dtype=torch.bfloat16, device="cuda")
+    L.lora_linear_pack_weight(torch.zeros(384, in_features, dtype=torch.bfloat16, device="cuda"), in_features, 384, w)
+    ws.fill_(0xFF)
+    L.lora_linear(dp.pool, seg, x, w, none, ws)
+    torch.cuda.synchronize()
+    rows = np.arange(0, b.T, 3)
+    for got, start in ((y, y0), (apart, y0), (none, np.zeros_like(y0))):
+        G.check_parity(G.dev_to_bits(got), G.oracle_apply(dp, x_bits, start, rows=rows), start, b.token_adapter, rows=rows)
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 @pytest.mark.parametrize("in_features, ranks, slices", HALVES)
 def test_rank_halves_of_few_token_heavy_units(in_features, ranks, slices):
     """Launches of few token-heavy units: halves of the rank rows, even and not, of units of 32 and 64 tokens, whole and cut along

@@ -432,6 +432,33 @@ def test_a_caller_s_table_without_room_for_the_faster_form(recorder, in_features
     b.close()
 
 
+# ---- batches of fewer than 1024 tokens that take token-heavy units all the same ------------------------------------------
+@pytest.mark.parametrize("in_features, groups, heavy", [
+    (4096, [(900, 64)], True), (4096, [(512, 64)], False),                      # up to rank 64: by the rank rows fetched again
+    (4096, [(512, 256)], True), (4096, [(256, 256)], False),
+    (14336, [(900, 256)], True), (14336, [(256, 256)], False),                  # ... and by the length of the walk along k
+    (4096, [(128, 256)] * 4, True), (4096, [(128, 256)] * 3 + [(31, 8)], False),  # one group of fewer than 32 tokens
+    (1600, [(646, 128)], False), (9024, [(700, 128)], True),
+])
+def test_small_batches_of_token_heavy_units(recorder, in_features, groups, heavy):
+    """Every projection of one x decides alike, whatever its columns; an option, a table without room for it, or both halves' own calls
+    are as for larger batches."""
+    for outs in (128, 14336, [256, 14336]):
+        b = Batch(in_features, outs, groups, idle=5)
+        seg = b.build()
+        names = _names(b.launches(recorder, seg))
+        assert names == (["shrink_prefill", "expand_big"] if heavy else names) and ("expand_big" in names) == heavy
+        if outs == 128:
+            assert ("shrink_prefill" in _names(b.launches(recorder, seg, "shrink"))) == heavy
+            assert ("shrink_prefill" in _names(b.launches(recorder, seg, "linear"))) == heavy
+            assert _names(b.launches(recorder, seg, "static")) == names
+        L.lora_segments_destroy(seg)
+        seg = b.build(L.plan_options(heavy_min_batch=1024))
+        assert "expand_big" not in _names(b.launches(recorder, seg))
+        L.lora_segments_destroy(seg)
+        b.close()
+
+
 # ---- the binding's own checks of arguments --------------------------------------------------------------------------
 @pytest.mark.parametrize("adapter", ["0", None, 0.0, ctypes.c_int32(0)])
 def test_an_adapter_that_is_no_whole_number_is_a_type_error(recorder, adapter):
