@@ -440,6 +440,11 @@ try {
 }
 API_CATCH
 
+// Adapters of up to this many bytes come from pinned memory by a kernel (lora::launch_copy_in), larger ones by the copy engine, which
+// is a little faster once it runs.  us per adapter, two copies / the kernel: 4096 -> 4096 rank 8 (0.13 MB) 33.4 / 7.9, rank 64 49.5 / 28.1,
+// rank 128 (2.1 MB) 68.6 / 53.4; 4096 -> 14336 rank 128 (4.7 MB) 114.4 / 114.5; 14336 -> 4096 rank 256 (9.4 MB) 199 / 215.
+static const size_t kLoadByKernelMax = (size_t)4 << 20;
+
 extern "C" lora_status_t lora_pool_load_staged(lora_pool_t *pool, int32_t adapter, const void *A, const void *B,
                                                void *dev_staging, size_t staging_bytes, void *stream)
 try {
@@ -456,8 +461,14 @@ try {
     hipStream_t s = (hipStream_t)stream;
     if (pool->live && (st = live_place(pool, adapter)) != LORA_OK) return st;
     uint16_t *tmp = (uint16_t *)dev_staging;
-    HIP_TRY(hipMemcpyAsync(tmp, A, nA * 2, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(tmp + nA, B, nB * 2, hipMemcpyHostToDevice, s));
+    if (lora::launch_copy_in && ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && (nA + nB) * 2 <= kLoadByKernelMax && lora::device_reads(A) &&
+        lora::device_reads(B)) {
+        // pinned: one kernel in front of the pack kernel instead of two copies, each of which the queue would wait for
+        HIP_TRY(lora::launch_copy_in(A, nA * 2, B, nB * 2, tmp, s));
+    } else {
+        HIP_TRY(hipMemcpyAsync(tmp, A, nA * 2, hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync(tmp + nA, B, nB * 2, hipMemcpyHostToDevice, s));
+    }
     HIP_TRY(lora::launch_pack_adapter(tmp, tmp + nA, in, out, r, r8, pool->arena + pool->a_off[adapter],
                                       pool->arena + pool->b_off[adapter], s));
     pool->resident[adapter] = 1;
@@ -1813,7 +1824,7 @@ static lora_status_t upload_table(lora_segments *sg, hipStream_t s)
             sg->staging = nullptr;
             sg->staging_capacity = 0;
             const size_t cap = round_up_sz(sg->table_bytes * 2, 4096);
-            HIP_TRY(hipHostMalloc((void **)&sg->staging, cap, hipHostMallocDefault));
+            HIP_TRY(hipHostMalloc((void **)&sg->staging, cap, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
             sg->staging_capacity = cap;
         }
         if (sg->table_bytes > sg->dev_capacity) {
@@ -1845,7 +1856,11 @@ static lora_status_t upload_table(lora_segments *sg, hipStream_t s)
         memcpy(sg->staging + sg->off_lin_pieces, sg->lin_pieces.data(), sg->lin_pieces.size() * sizeof(LinPiece));
     memset(sg->staging + sg->off_sync, 0, sg->table_bytes - sg->off_sync);
     sg->launches = 0;
-    if (sg->table_bytes) HIP_TRY(hipMemcpyAsync(sg->dev, sg->staging, sg->table_bytes, hipMemcpyHostToDevice, s));
+    // (a caller's staging may be any host memory, and the question costs more than it is asked for to save)
+    if (sg->table_bytes && sg->table_bytes < (size_t)1 << 31 && !sg->caller_memory && lora::launch_copy_in)
+        HIP_TRY(lora::launch_copy_in(sg->staging, sg->table_bytes, nullptr, 0, sg->dev, s));
+    else if (sg->table_bytes)
+        HIP_TRY(hipMemcpyAsync(sg->dev, sg->staging, sg->table_bytes, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(sg->copied, s));
     sg->uploaded = true;
     return LORA_OK;

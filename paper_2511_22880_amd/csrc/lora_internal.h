@@ -222,6 +222,11 @@ hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n
 // (kq, n) holding k = 32 step + 8 kq .. +7 of column 128 strip + 8 n + b.
 hipError_t launch_pack_weight(const uint16_t *wt, int in, int out, uint16_t *dst, hipStream_t stream);
 
+// Copies pinned host memory that the device can read, a_bytes from `a` and behind them b_bytes from `b` (multiples of 16, less than 2 GiB),
+// to dev by a kernel.  Weak, like the question whether host memory is of that kind: the planner also links without the kernels.
+hipError_t launch_copy_in(const void *a, size_t a_bytes, const void *b, size_t b_bytes, void *dev, hipStream_t stream) __attribute__((weak));
+bool device_reads(const void *host) __attribute__((weak));
+
 // v[i] = sum over slices, in slice order.
 hipError_t launch_reduce_slices(const float *parts, int n_slices, int64_t slice_stride, float *v,
                                 int64_t n, hipStream_t stream);

@@ -65,6 +65,33 @@ def test_packed_adapter_is_the_documented_layout(rank, shape, offset):
     L.lora_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("kind", ["pinned", "pinned, 2 bytes on", "pageable"])
+@pytest.mark.parametrize("rank, n_in, n_out", [(1, 64, 128), (24, 320, 384), (255, 2048, 6144), (256, 4160, 4096)])  # 4 MB in between
+def test_staged_loads_by_kernel_and_by_copies(kind, rank, n_in, n_out):
+    """Pinned sources at 16-byte addresses up to 4 MB are read by a kernel, others copied: the same bytes, also where the host memory
+    changes between two loads."""
+    rng = np.random.default_rng([rank, n_in])
+    r8 = (rank + 7) // 8 * 8
+    ranks = np.array([rank], dtype=np.int32)
+    arena = torch.zeros(L.lora_pool_bytes(n_in, n_out, ranks, np.ones(1, dtype=np.float32)), dtype=torch.uint8, device="cuda")
+    pool = L.lora_pool_create(n_in, n_out, ranks, np.ones(1, dtype=np.float32), arena)
+    staging = torch.empty(L.lora_pool_load_staging_bytes(pool, 0), dtype=torch.uint8, device="cuda")
+    off = 1 if kind == "pinned, 2 bytes on" else 0
+    host = [torch.empty(n + off, dtype=torch.int16, pin_memory=kind != "pageable")[off:] for n in (n_in * rank, rank * n_out)]
+    for _ in range(2):
+        A, B = (rng.integers(0, 1 << 16, size=s).astype(np.uint16) for s in ((n_in, rank), (rank, n_out)))
+        for t, m in zip(host, (A, B)):
+            t.copy_(torch.from_numpy(m.reshape(-1).view(np.int16)))
+        L.lora_pool_load_staged(pool, 0, host[0], host[1], staging)
+        torch.cuda.synchronize()
+        info = L.lora_pool_adapter_info(pool, 0)
+        got = arena.view(torch.int16).cpu().numpy().view(np.uint16)
+        a, b = _packed(A, B, r8)
+        assert np.array_equal(got[info["a_offset"]:info["a_offset"] + a.size], a)
+        assert np.array_equal(got[info["b_offset"]:info["b_offset"] + b.size], b)
+    L.lora_pool_destroy(pool)
+
+
 # ---- token-heavy groups: units cut along k, column runs down to one strip, the two halves apart -----------------
 @pytest.mark.parametrize("shape, most", [((64, 128), 1), ((2112, 640), 2), ((3072, 1152), 3), ((4160, 4224), 4)])
 @pytest.mark.parametrize("sizes", [
