@@ -30,18 +30,21 @@ namespace lora {
 #ifdef LORA_WG_CLOCKS
 __device__ unsigned long long *g_clock_buf = nullptr;
 __device__ unsigned g_clock_slots = 0;
-#define LORA_CLOCK_AT(base, point)                                                                     \
+#define LORA_CLOCK_SLOT(slot, point)                                                                   \
     do {                                                                                               \
-        if (g_clock_buf && threadIdx.x == 0 && (base) + blockIdx.x < g_clock_slots)                    \
-            g_clock_buf[((size_t)(base) + blockIdx.x) * 8 + (point)] = wall_clock64();                 \
+        if (g_clock_buf && threadIdx.x == 0 && (slot) < g_clock_slots)                                 \
+            g_clock_buf[(size_t)(slot) * 8 + (point)] = wall_clock64();                                \
     } while (0)
 #else
-#define LORA_CLOCK_AT(base, point) do { } while (0)
+#define LORA_CLOCK_SLOT(slot, point) do { } while (0)
 #endif
+#define LORA_CLOCK_AT(base, point) LORA_CLOCK_SLOT((base) + blockIdx.x, point)
 #define LORA_CLOCK(point) LORA_CLOCK_AT(0, point)
 // expand launches keep their clocks behind those of the shrink launch of the same apply
 [[maybe_unused]] constexpr unsigned kClockExpandBase = 32768;
 #define LORA_CLOCK_E(point) LORA_CLOCK_AT(kClockExpandBase, point)
+// by unit where a unit has several work groups: those of its first one
+#define LORA_CLOCK_E_UNIT(unit, point) LORA_CLOCK_SLOT(kClockExpandBase + (unsigned)(unit), point)
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -2167,9 +2170,9 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_big(const Unit *__restri
     __shared__ __attribute__((aligned(16))) char lds[kBigTile];
     const BigPlace p(blockIdx.x, n_first, subs, more);
     if (p.unit < 0 || p.c0 >= units[p.unit].pn) return;
-    LORA_CLOCK_E(0);
+    if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 0);
     expand_big_dispatch<VF32>(units[p.unit], p.c0, perm, arena, v_in, y, ldy, lds, sy);
-    LORA_CLOCK_E(4);
+    if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 4);
 }
 
 // Units of up to 16 tokens whose v the launch before left as k-slices' partial sums.
@@ -2235,15 +2238,18 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_mixed(const Unit *__rest
 {
     __shared__ __attribute__((aligned(16))) char lds[kMixedExpandLds];
     const int b = blockIdx.x;
-    LORA_CLOCK_E(0);
     if (b < big_grid) {
         const BigPlace p(b, n_first, subs, more);
         if (p.unit < 0 || p.c0 >= big_units[p.unit].pn) return;
+        if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 0);
         expand_big_dispatch<false>(big_units[p.unit], p.c0, perm, arena, nullptr, y, ldy, lds, sy);
+        if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 4);
     } else {
+        [[maybe_unused]] const int n_big = more.n ? more.first_unit[more.n] : n_first;
+        LORA_CLOCK_E_UNIT(n_big + b - big_grid, 0);
         expand_dispatch<false, BY>(units[b - big_grid], arena, nullptr, y, ldy, lds, sy);
+        LORA_CLOCK_E_UNIT(n_big + b - big_grid, 4);
     }
-    LORA_CLOCK_E(4);
 }
 
 __global__ __launch_bounds__(256) void k_reduce_slices(const float *__restrict__ parts, int n_slices,
