@@ -316,6 +316,13 @@ def lora_pool_load_staging_bytes(pool: Pool, adapter: int) -> int:
 
 def lora_pool_load_staged(pool: Pool, adapter: int, A, B, dev_staging, stream=None) -> None:
     """A, B: host arrays (numpy uint16 or pinned torch tensors); dev_staging: device tensor of the caller's."""
+    n = ctypes.c_int32(adapter).value
+    if 0 <= n < pool.n_adapters:
+        r = int(pool.ranks[n])
+        for name, obj, features in (("A", A, pool.in_features), ("B", B, pool.out_features)):
+            have = getattr(obj, "nbytes", None)  # (an address states no size)
+            if have is not None and have < 2 * r * features:
+                raise ValueError(f"adapter {n}: {name} of {have} bytes is shorter than rank {r} x {features} bf16 values")
     _check(lib().lora_pool_load_staged(pool.handle, ctypes.c_int32(adapter), _addr(A), _addr(B), _addr(dev_staging), _nbytes(dev_staging),
                                        _queue(stream)))
 

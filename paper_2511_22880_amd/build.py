@@ -12,7 +12,7 @@ LIB = os.path.join(PKG, "liblora_gfx950.so")
 # measurement build: the same library with per-work-group device clocks compiled in (-DLORA_WG_CLOCKS)
 LIB_CLOCKS = os.path.join(PKG, "liblora_gfx950_clocks.so")
 SOURCES = [os.path.join(CSRC, "lora_host.cpp"), os.path.join(CSRC, "lora_place.cpp"),
-           os.path.join(CSRC, "lora_kernels.hip")]
+           os.path.join(CSRC, "lora_memory.cpp"), os.path.join(CSRC, "lora_kernels.hip")]
 HEADERS = [os.path.join(CSRC, "lora_internal.h"), os.path.join(ROOT, "include", "lora.h"),
            os.path.join(ROOT, "include", "lora_placement.h")]
 

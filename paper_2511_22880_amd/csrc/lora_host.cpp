@@ -461,8 +461,9 @@ try {
     hipStream_t s = (hipStream_t)stream;
     if (pool->live && (st = live_place(pool, adapter)) != LORA_OK) return st;
     uint16_t *tmp = (uint16_t *)dev_staging;
-    if (lora::launch_copy_in && ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && (nA + nB) * 2 <= kLoadByKernelMax && lora::device_reads(A) &&
-        lora::device_reads(B)) {
+    // (memory that is shorter than the adapter, or that HIP does not know, is left to the copies, which refuse what exceeds its allocation)
+    if (lora::launch_copy_in && ((uintptr_t)A | (uintptr_t)B) % 16 == 0 && (nA + nB) * 2 <= kLoadByKernelMax &&
+        lora::pinned_holds(A, nA * 2) && lora::pinned_holds(B, nB * 2) && lora::allocation_holds(tmp, (nA + nB) * 2)) {
         // pinned: one kernel in front of the pack kernel instead of two copies, each of which the queue would wait for
         HIP_TRY(lora::launch_copy_in(A, nA * 2, B, nB * 2, tmp, s));
     } else {

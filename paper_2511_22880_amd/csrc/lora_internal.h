@@ -223,9 +223,13 @@ hipError_t launch_linear_lora(const int32_t *rows, const LinBlock *blocks, int n
 hipError_t launch_pack_weight(const uint16_t *wt, int in, int out, uint16_t *dst, hipStream_t stream);
 
 // Copies pinned host memory that the device can read, a_bytes from `a` and behind them b_bytes from `b` (multiples of 16, less than 2 GiB),
-// to dev by a kernel.  Weak, like the question whether host memory is of that kind: the planner also links without the kernels.
+// to dev by a kernel, which reads and writes that many bytes whatever the memory holds: the caller has made sure that it holds them.
+// Weak, like the two questions below: the planner also links without the kernels.
 hipError_t launch_copy_in(const void *a, size_t a_bytes, const void *b, size_t b_bytes, void *dev, hipStream_t stream) __attribute__((weak));
-bool device_reads(const void *host) __attribute__((weak));
+// Whether `bytes` from p on lie in one allocation that HIP knows (a copy asks this too, and refuses what exceeds one) ...
+bool allocation_holds(const void *p, size_t bytes) __attribute__((weak));
+// ... of pinned host memory that a kernel on the current device reads at the same address.
+bool pinned_holds(const void *host, size_t bytes) __attribute__((weak));
 
 // v[i] = sum over slices, in slice order.
 hipError_t launch_reduce_slices(const float *parts, int n_slices, int64_t slice_stride, float *v,

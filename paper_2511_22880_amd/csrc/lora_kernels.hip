@@ -2999,18 +2999,6 @@ static Sync make_sync(const SyncArgs *a, int wait, int scale_v = 0)
     return sy;
 }
 
-bool device_reads(const void *host)
-{
-    hipPointerAttribute_t at;
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, host) != hipSuccess) {
-        (void)hipGetLastError();  // memory that HIP does not know: not an error of the caller's
-        return false;
-    }
-    // pinned for this device (another's pinned memory need not be mapped here), at the same address
-    return at.type == hipMemoryTypeHost && at.devicePointer == host && at.device == dev;
-}
-
 hipError_t launch_copy_in(const void *a, size_t a_bytes, const void *b, size_t b_bytes, void *dev, hipStream_t stream)
 {
     const size_t bytes = a_bytes + b_bytes;

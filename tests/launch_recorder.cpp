@@ -8,6 +8,8 @@
 
 static std::string g_log, g_forms;
 static int g_capturing;
+static struct Memory { uintptr_t from; size_t bytes; hipMemoryType type; } g_memory[8];  // what this runtime knows of, besides what it gave out
+static int g_n_memory;
 
 static hipError_t note(const std::string &s)
 {
@@ -35,6 +37,35 @@ const char *recorder_take_forms()
 }
 // 1: the stream captures; 2: it is the legacy stream and a blocking stream captures
 void recorder_capture(int on) { g_capturing = on; }
+
+// memory of a caller's as this runtime knows it: an allocation of pinned host memory, or of the device's
+void recorder_memory(void *p, size_t bytes, int pinned)
+{
+    g_memory[g_n_memory++ % 8] = {(uintptr_t)p, bytes, pinned ? hipMemoryTypeHost : hipMemoryTypeDevice};
+}
+static const Memory *known(const void *p)
+{
+    for (const Memory &m : g_memory)
+        if ((uintptr_t)p >= m.from && (uintptr_t)p - m.from < m.bytes) return &m;
+    return nullptr;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *p)
+{
+    const Memory *m = known(p);
+    if (!m) return hipErrorInvalidValue;
+    memset(at, 0, sizeof *at);
+    at->type = m->type;
+    at->devicePointer = const_cast<void *>(p);
+    return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *bytes, hipDeviceptr_t p)
+{
+    const Memory *m = known(p);
+    if (!m) return hipErrorNotFound;
+    *base = (hipDeviceptr_t)m->from;
+    *bytes = m->bytes;
+    return hipSuccess;
+}
 
 hipError_t hipMalloc(void **p, size_t n) { return (*p = aligned_alloc(4096, (n + 4095) / 4096 * 4096)) ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void *p) { free(p); return hipSuccess; }
@@ -100,6 +131,12 @@ hipError_t launch_expand_mixed(const LaunchCtx &b, const LaunchCtx &c, uint16_t 
 hipError_t launch_apply_fused(const LaunchCtx &s, const LaunchCtx &e, const uint16_t *, int64_t, int, float *, int, int64_t, uint16_t *, int64_t, const SyncArgs *, hipStream_t) { return note("apply_fused" + num(s.n_units) + num(e.n_units)); }
 hipError_t launch_decode_fused(const LaunchCtx &, const LaunchCtx &, int grid, const uint16_t *, int64_t, int, int, uint16_t *, int64_t, unsigned, const SyncArgs *, hipStream_t) { return note("decode_fused" + num(grid)); }
 hipError_t launch_reduce_slices(const float *, int n, int64_t, float *, int64_t, hipStream_t) { return note("reduce_slices" + num(n)); }
+hipError_t launch_copy_in(const void *a, size_t a_bytes, const void *b, size_t b_bytes, void *dev, hipStream_t)
+{
+    memmove(dev, a, a_bytes);
+    if (b_bytes) memmove((char *)dev + a_bytes, b, b_bytes);
+    return note("copy_in" + num((long long)a_bytes) + num((long long)b_bytes));
+}
 hipError_t launch_pack_adapter(const uint16_t *, const uint16_t *, int, int, int, int, uint16_t *, uint16_t *, hipStream_t) { return hipSuccess; }
 hipError_t launch_linear_lora(const int32_t *, const LinBlock *b, int n_places, const uint16_t *, const uint16_t *, const uint16_t *, int64_t, int, int out, const uint16_t *, const uint16_t *, uint16_t *, int64_t, hipStream_t)
 {

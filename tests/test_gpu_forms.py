@@ -1,4 +1,6 @@
 """Forms of a launch that a rule on sizes, types or alignment chooses: each at the sizes where it can go wrong."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -90,6 +92,21 @@ def test_staged_loads_by_kernel_and_by_copies(kind, rank, n_in, n_out):
         assert np.array_equal(got[info["a_offset"]:info["a_offset"] + a.size], a)
         assert np.array_equal(got[info["b_offset"]:info["b_offset"] + b.size], b)
     L.lora_pool_destroy(pool)
+
+
+def test_what_memory_a_kernel_may_read():
+    """The questions asked before a kernel takes the place of copies, about memory as the runtime knows it (nothing reads it)."""
+    lib = L.lib()
+    pinned_holds, allocation_holds = lib._ZN4lora12pinned_holdsEPKvm, lib._ZN4lora16allocation_holdsEPKvm
+    for f in (pinned_holds, allocation_holds):
+        f.argtypes, f.restype = (ctypes.c_void_p, ctypes.c_size_t), ctypes.c_bool
+    n, beyond = 1 << 20, 1 << 40
+    pinned, pageable = torch.empty(n, dtype=torch.uint8, pin_memory=True), np.empty(n, dtype=np.uint8)
+    device = torch.empty(n, dtype=torch.uint8, device="cuda")
+    h, d = pinned.data_ptr(), device.data_ptr()
+    assert pinned_holds(h, n) and pinned_holds(h + 16, n - 16) and not pinned_holds(h, beyond) and not pinned_holds(h + 16, beyond)
+    assert allocation_holds(d, n) and allocation_holds(d + 256, n - 256) and not allocation_holds(d, beyond)
+    assert not pinned_holds(d, n) and not pinned_holds(pageable.ctypes.data, n)
 
 
 # ---- token-heavy groups: units cut along k, column runs down to one strip, the two halves apart -----------------

@@ -24,7 +24,7 @@ def recorder(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("recorder") / "liblora_recorder.so")
     cmd = ["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I" + HIP_INCLUDE,
            "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-o", so, os.path.join(ROOT, "tests", "launch_recorder.cpp"),
-           os.path.join(CSRC, "lora_host.cpp"), os.path.join(CSRC, "lora_place.cpp")]
+           os.path.join(CSRC, "lora_host.cpp"), os.path.join(CSRC, "lora_place.cpp"), os.path.join(CSRC, "lora_memory.cpp")]
     build = subprocess.run(cmd, capture_output=True, text=True)
     assert build.returncode == 0, build.stderr[-2000:]
     path, loaded = L.LIB_PATH, L._lib
@@ -469,4 +469,55 @@ def test_an_adapter_that_is_no_whole_number_is_a_type_error(recorder, adapter):
     with pytest.raises(TypeError):
         L.lora_pool_load(pool, adapter, *device)
     L.lora_pool_load(pool, np.int64(0), *device)
+    b.close()
+
+
+# ---- staged loads: what may be read by a kernel ------------------------------------------------------------------------
+@pytest.fixture
+def staged(recorder):
+    """A pool of one adapter (rank 8, 128 -> 256), and pinned sources and a staging buffer as the runtime knows them."""
+    ranks, n = np.array([8], dtype=np.int32), [128 * 8 * 2, 8 * 256 * 2]
+    arena = np.zeros(L.lora_pool_bytes(128, 256, ranks, np.ones(1, dtype=np.float32)), dtype=np.uint8)
+    pool = L.lora_pool_create(128, 256, ranks, np.ones(1, dtype=np.float32), arena.ctypes.data // 256 * 256, arena_bytes=arena.size)
+    host = torch.empty(1 << 14, dtype=torch.uint8)
+    at = [(host.data_ptr() + 255) // 256 * 256 + q * 4096 for q in range(3)]  # A, B and the staging, 4 KB apart
+    recorder.recorder_memory.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+
+    def load(bytes_a=n[0], bytes_b=n[1], bytes_staging=sum(n), shift=0, pinned=1):
+        for p, size, kind in zip(at, (bytes_a, bytes_b, bytes_staging), (pinned, pinned, 0)):
+            recorder.recorder_memory(p, size, kind)
+        for q in range(5):
+            recorder.recorder_memory(None, 0, 0)  # (the oldest are forgotten)
+        recorder.recorder_take()
+        L._check(L.lib().lora_pool_load_staged(pool.handle, 0, at[0] + shift, at[1], at[2], sum(n), None))
+        return recorder.recorder_take().decode().split()
+
+    yield load
+    L.lora_pool_destroy(pool)
+
+
+def test_staged_loads_go_by_kernel_where_all_of_the_memory_is_known(staged):
+    """The kernel reads and writes the adapter's size whatever is there; a copy refuses what exceeds an allocation."""
+    by_kernel = ["copy_in", "2048", "4096"]
+    assert staged() == staged(bytes_a=4096, bytes_b=4096) == by_kernel
+    assert staged(bytes_a=2047) == [] and staged(bytes_b=4095) == []     # the first byte is pinned, the last is not
+    assert staged(bytes_a=2063, shift=16) == [] and staged(bytes_a=2064, shift=16) == by_kernel
+    assert staged(bytes_staging=6143) == []
+    assert staged(pinned=0) == []
+
+
+@pytest.mark.parametrize("make", [lambda n: np.zeros(n, dtype=np.uint16), lambda n: torch.zeros(n, dtype=torch.bfloat16)])
+def test_staged_loads_refuse_sources_shorter_than_the_adapter(recorder, make):
+    b = Batch(64, 128, [(1, 8)])
+    pool, staging = b.pools[0], torch.empty(1 << 12, dtype=torch.uint8)
+    for a, c in ((64 * 8 - 1, 8 * 128), (64 * 8, 8 * 128 - 1)):
+        with pytest.raises(ValueError, match="shorter than rank 8"):
+            L.lora_pool_load_staged(pool, 0, make(a), make(c), staging)
+    L.lora_pool_load_staged(pool, 0, make(64 * 8), make(8 * 128 + 5), staging)
+    L.lora_pool_load_staged(pool, np.int64(0), make(64 * 8), make(8 * 128), staging)
+    for adapter in (-1, 1):
+        with pytest.raises(L.LoraError):
+            L.lora_pool_load_staged(pool, adapter, make(1), make(1), staging)
+    with pytest.raises(L.LoraError):
+        L.lora_pool_load_staged(pool, 0, None, make(8 * 128), staging)
     b.close()
