@@ -2964,24 +2964,31 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_adapter(const uint16_t *_
 // queue instead of the copy engine, which the queue waits for and which waits for the queue, about 10 us each way round: a batch
 // planned anew in front of every launch of it, us per step: 256 tokens through 32 layers 494 -> 480, through eight layers of seven
 // projections, four objects, 1086 -> 1053, 31 tokens of 92 adapters through one projection, 4928 -> 2048, 33 -> 24 (the rest is
-// the host's; where the host plans for longer than the device works a launch costs it 1 or 2 us more than a copy, four objects of 500
-// tokens 222 -> 230).  The loads have system scope: the host's memory serves them, whatever a cache holds of what was read there before.
+// the host's).  Where the host plans for longer than the device works, a launch costs it about 0.7 us more than a copy, and of five arguments
+// 0.5 us more than of one struct: four objects of 500 tokens, copies / five arguments / a struct 228.6 / 232.0 / 230.0, of 256 tokens
+// 152.5 / 157.9 / 155.7, one of 500 tokens 34.9 / 35.7 / 35.4.
+// The loads have system scope: the host's memory serves them, whatever a cache holds of what was read there before.
 // They are 16 bytes wide: with 8 (atomic) loads the link gives half of its 47 GB/s.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_copy_in(const uint4 *a, unsigned n_a, const uint4 *b, unsigned n, uint4 *__restrict__ dst)
+struct CopyIn {
+    const uint4 *a, *b;
+    uint4 *dst;
+    unsigned n_a, n;  // pieces of a, and in all
+};
+__global__ __launch_bounds__(256) void k_copy_in(CopyIn c)
 {
     const unsigned at = blockIdx.x * 256 + threadIdx.x;
-    if (at >= n) return;
+    if (at >= c.n) return;
     typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
     constexpr int kSystem = 17;  // sc0 sc1
     u32x4 v;
-    if (at < n_a)
-        v = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(a), 0, (int)(16u * n_a), 0x00020000),
+    if (at < c.n_a)
+        v = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(c.a), 0, (int)(16u * c.n_a), 0x00020000),
                                                   (int)(16u * at), 0, kSystem);
     else
-        v = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(b), 0, (int)(16u * (n - n_a)), 0x00020000),
-                                                  (int)(16u * (at - n_a)), 0, kSystem);
-    dst[at] = uint4{v.x, v.y, v.z, v.w};
+        v = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(c.b), 0, (int)(16u * (c.n - c.n_a)), 0x00020000),
+                                                  (int)(16u * (at - c.n_a)), 0, kSystem);
+    c.dst[at] = uint4{v.x, v.y, v.z, v.w};
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -3006,8 +3013,8 @@ hipError_t launch_copy_in(const void *a, size_t a_bytes, const void *b, size_t b
     if (a_bytes % 16 || b_bytes % 16 || bytes >= (size_t)1 << 31 || ((uintptr_t)a | (uintptr_t)b | (uintptr_t)dev) % 16)
         return hipErrorInvalidValue;
     const unsigned n = (unsigned)(bytes / 16);
-    hipLaunchKernelGGL(k_copy_in, dim3((n + 255) / 256), dim3(256), 0, stream, (const uint4 *)a, (unsigned)(a_bytes / 16),
-                       (const uint4 *)b, n, (uint4 *)dev);
+    const CopyIn c = {(const uint4 *)a, (const uint4 *)b, (uint4 *)dev, (unsigned)(a_bytes / 16), n};
+    hipLaunchKernelGGL(k_copy_in, dim3((n + 255) / 256), dim3(256), 0, stream, c);
     return hipGetLastError();
 }
 
