@@ -247,7 +247,11 @@ lora_status_t lora_segments_upload(lora_segments_t *seg, void *stream);
  * on, for lora_segments_rebuild too (a later batch that they have no room for is planned without the
  * forms that take more table for speed alone; LORA_ERR_OOM, with the sizes, if that needs more too), and
  * never frees them; the caller keeps them alive as long as the object and leaves them alone while
- * launches that use the object may run.  No allocation is made. */
+ * launches that use the object may run.  No allocation is made.
+ * Tables do not grow with the batch alone: units of 64 tokens take fewer records than units of 16.  For a
+ * batch of fewer than lora_plan_options_t.heavy_min_batch tokens lora_segments_table_bytes is therefore
+ * never less than for units of 16 tokens, which a smaller batch may take; a batch of more tokens than that
+ * may need less than a smaller one. */
 lora_status_t lora_segments_table_bytes(const lora_segments_t *seg, size_t *bytes);
 lora_status_t lora_segments_upload_to(lora_segments_t *seg, void *dev_table, size_t dev_bytes, void *host_staging,
                                       size_t staging_bytes, void *stream);

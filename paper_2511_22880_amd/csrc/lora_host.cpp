@@ -121,6 +121,7 @@ struct lora_segments {
     int heavy_top_rank;     // their largest padded rank
     std::vector<lora::BigSection> big_sections;  // expand_big_units in runs of equally wide ones: one per projection, or fewer
     int heavy_k_slices;     // k-slices of the token-heavy shrink units (1: they take the whole of k)
+    bool small_heavy;       // token-heavy units in a batch of fewer than kPrefillMinBatch tokens (see small_batch_token_heavy)
     bool decode_fused;      // whole-k decode batch that can run as one launch (see finish_decode_fused)
     int fused_grid;         // work groups of that launch
     int n_sync;             // counters: one per (group, token tile), then the time-out flag
@@ -1168,10 +1169,17 @@ static void order_linear_rows(lora_segments *sg, const int32_t *ta, int32_t T, i
     for (size_t b = 1; b <= places / 16; ++b) start[b] += start[b - 1];
 }
 
+// How a batch is planned where memory of the caller's has no room for the planner's first choice.
+struct PlanForm {
+    bool lean = false;         // its own choices give way where they take more table
+    bool units_of_16 = false;  // a small batch keeps units of 16 tokens (see small_batch_token_heavy)
+};
+
 static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const int32_t *ta, int32_t T,
                                int n_projections = 1,  // projections whose units share the launches
-                               bool lean = false)      // the planner's own choices give way where they take more table
+                               PlanForm form = PlanForm())
 {
+    const bool lean = form.lean;
     const int N = pool->n_adapters;
     std::vector<int32_t> count(N, 0);
     int32_t n_active = 0;
@@ -1184,8 +1192,8 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
         ++n_active;
     }
     const int heavy_min_tokens = opt_heavy_min_tokens(sg);
-    const int heavy_min_batch =
-        !lean && small_batch_token_heavy(sg, pool, count, n_active, heavy_min_tokens) ? 1 : opt_heavy_min_batch(sg);
+    sg->small_heavy = !form.units_of_16 && small_batch_token_heavy(sg, pool, count, n_active, heavy_min_tokens);
+    const int heavy_min_batch = sg->small_heavy ? 1 : opt_heavy_min_batch(sg);
     sg->pool = pool;
     sg->pool_id = pool->id;
     sg->layout_in = pool->in_features;
@@ -1482,6 +1490,7 @@ static lora_segments *new_segments()
     sg->fork = sg->join = nullptr;
     sg->uploaded = false;
     sg->n_sync = 0;
+    sg->small_heavy = false;
     sg->launches = 0;
     sg->caller_memory = false;
     sg->opts = kDefaultOptions;
@@ -1631,7 +1640,7 @@ static void interleave_heavy_units(std::vector<Unit> &units, size_t P)
 
 // Plans every projection on its own, then strings the unit lists together.
 static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const lora_pool *> &pools,
-                                     const int32_t *ta, int32_t T, bool lean = false)
+                                     const int32_t *ta, int32_t T, PlanForm form = PlanForm())
 {
     const lora_pool *p0 = pools[0];
     const uint16_t *base = p0->arena;
@@ -1641,7 +1650,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         if (((uintptr_t)q->arena - (uintptr_t)p0->arena) % 2) return fail(LORA_ERR_INVALID_ARG, "arena alignment");
         base = std::min(base, (const uint16_t *)q->arena);
     }
-    lora_status_t st = plan_into(sg, p0, ta, T, (int)pools.size(), lean);
+    lora_status_t st = plan_into(sg, p0, ta, T, (int)pools.size(), form);
     if (st != LORA_OK) return st;
     sg->mpools = pools;
     sg->mpool_ids.clear();
@@ -1676,7 +1685,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
     if (!tmp) return fail(LORA_ERR_OOM, "host allocation failed");
     tmp->opts = sg->opts;
     for (size_t q = 1; q < pools.size(); ++q) {
-        st = plan_into(tmp, pools[q], ta, T, (int)pools.size(), lean);
+        st = plan_into(tmp, pools[q], ta, T, (int)pools.size(), form);
         if (st != LORA_OK) break;
         const uint64_t delta = (uint64_t)(((uintptr_t)pools[q]->arena - (uintptr_t)base) / 2);
         const size_t n0 = sg->shrink_units.size(), n1 = sg->prefill_units.size(), n2 = sg->expand_units.size(),
@@ -1874,11 +1883,31 @@ try {
 }
 API_CATCH
 
+// The room that a caller's table needs for the batch.  Token-heavy units of a small batch take a table far smaller than its units of 16
+// tokens (900 tokens of rank 256, 4096 -> 4096, 90 KB and 363 KB), while a batch of fewer tokens may take the latter (400 of these
+// 161 KB): a table made for the largest of such batches has to hold the others, so the room is never less than for units of 16 tokens.
+static size_t table_room(const lora_segments *sg)
+{
+    if (!sg->small_heavy || !pool_is(sg->pool, sg->pool_id)) return sg->table_bytes;
+    for (size_t q = 0; q < sg->mpools.size(); ++q)
+        if (!pool_is(sg->mpools[q], sg->mpool_ids[q])) return sg->table_bytes;
+    std::vector<int32_t> ta((size_t)sg->T, -1);
+    for (size_t i = 0; i < sg->seg_adapter.size(); ++i)
+        for (int32_t p = sg->seg_start[i]; p < sg->seg_start[i + 1]; ++p) ta[sg->perm[p]] = sg->seg_adapter[i];
+    lora_segments other{};  // host lists only
+    other.opts = sg->opts;
+    PlanForm form;
+    form.units_of_16 = true;
+    const lora_status_t st = sg->mpools.empty() ? plan_into(&other, sg->pool, ta.data(), sg->T, 1, form)
+                                                : plan_multi_into(&other, sg->mpools, ta.data(), sg->T, form);
+    return st == LORA_OK ? std::max(sg->table_bytes, other.table_bytes) : sg->table_bytes;  // (an adapter has left: no launch either)
+}
+
 extern "C" lora_status_t lora_segments_table_bytes(const lora_segments_t *sg, size_t *bytes)
 try {
     if (!seg_ok(sg)) return fail(LORA_ERR_INVALID_ARG, "seg is NULL or not a segment object");
     if (!bytes) return fail(LORA_ERR_INVALID_ARG, "bytes is NULL");
-    *bytes = sg->table_bytes;
+    *bytes = table_room(sg);
     return LORA_OK;
 }
 API_CATCH
@@ -1889,9 +1918,10 @@ try {
     if (!seg_ok(sg)) return fail(LORA_ERR_INVALID_ARG, "seg is NULL or not a segment object");
     if (!dev_table || ((uintptr_t)dev_table) % 256) return fail(LORA_ERR_INVALID_ARG, "dev_table is NULL or not 256-byte aligned");
     if (!host_staging || ((uintptr_t)host_staging) % 16) return fail(LORA_ERR_INVALID_ARG, "host_staging is NULL or not 16-byte aligned");
-    if (dev_bytes < sg->table_bytes || staging_bytes < sg->table_bytes)
+    const size_t room = table_room(sg);
+    if (dev_bytes < room || staging_bytes < room)
         return fail(LORA_ERR_OOM, "the batch's table needs %zu bytes (lora_segments_table_bytes); dev_table holds %zu, host_staging %zu",
-                    sg->table_bytes, dev_bytes, staging_bytes);
+                    room, dev_bytes, staging_bytes);
     if (sg->copied) HIP_TRY(hipEventSynchronize(sg->copied));  // an upload from the library's own staging may be in flight
     if (!sg->caller_memory) {
         if (sg->dev) HIP_TRY(hipFree(sg->dev));
@@ -1978,13 +2008,22 @@ try {
     for (size_t q = 0; q < pools.size(); ++q)
         if (!pool_is(pools[q], sg->mpool_ids[q]))
             return fail(LORA_ERR_STALE_SEGMENTS, "a pool this segment object was built for no longer exists");
-    auto plan = [&](bool lean) {
-        return pools.empty() ? plan_into(sg, sg->pool, ta, T, 1, lean) : plan_multi_into(sg, pools, ta, T, lean);
+    auto plan = [&](bool lean, bool units_of_16) {
+        PlanForm form;
+        form.lean = lean;
+        form.units_of_16 = units_of_16;
+        return pools.empty() ? plan_into(sg, sg->pool, ta, T, 1, form) : plan_multi_into(sg, pools, ta, T, form);
     };
-    lora_status_t st = plan(false);
+    auto no_room = [&] { return sg->caller_memory && sg->table_bytes > std::min(sg->dev_capacity, sg->staging_capacity); };
+    lora_status_t st = plan(false, false);
     // memory of the caller's that has no room for k-slices, short column runs, the one launch's lists or padded rows, but for the
-    // batch without them (tables of the two plans over 600 random batches: up to 1.8 to 1)
-    if (st == LORA_OK && sg->caller_memory && sg->table_bytes > std::min(sg->dev_capacity, sg->staging_capacity)) st = plan(true);
+    // batch without them (tables of the two plans over 600 random batches: up to 1.8 to 1); and for token-heavy units of a small batch
+    // that has room for its units of 16 tokens all the same
+    if (st == LORA_OK && no_room()) st = plan(true, false);
+    if (st == LORA_OK && no_room() && sg->small_heavy) {
+        st = plan(false, true);
+        if (st == LORA_OK && no_room()) st = plan(true, true);
+    }
     if (st != LORA_OK) {
         sg->uploaded = false;
         return st;

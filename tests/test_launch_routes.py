@@ -459,6 +459,63 @@ def test_small_batches_of_token_heavy_units(recorder, in_features, groups, heavy
         b.close()
 
 
+def _in_a_table_of(b, size, tokens):
+    """An object of b's pools whose table and staging hold `size` bytes, as planned for the first `tokens` tokens."""
+    seg = L.lora_segments_plan_multi(b.pools, b.ta[:tokens]) if len(b.pools) > 1 else L.lora_segments_plan(b.pools[0], b.ta[:tokens])
+    dev, staging = (m[-m.data_ptr() % 256:][:size] for m in (torch.zeros(size + 256, dtype=torch.uint8) for _ in range(2)))
+    L.lora_segments_upload_to(seg, dev, staging)
+    return seg
+
+
+def _room(b, options=None):
+    seg = L.lora_segments_plan(b.pools[0], b.ta, options) if len(b.pools) == 1 else L.lora_segments_plan_multi(b.pools, b.ta, options)
+    n = L.lora_segments_table_bytes(seg)
+    L.lora_segments_destroy(seg)
+    return n
+
+
+@pytest.mark.parametrize("in_features, outs, rank, tokens", [
+    (4096, 4096, 256, (900, 400, 256, 31, 1)), (4096, 4096, 64, (900, 512, 100)), (8192, 8192, 128, (900, 200)),
+    (4096, [1024, 4096], 256, (1023, 400, 256)), (14336, 128, 256, (700, 256)),
+])
+def test_a_table_made_for_the_largest_small_batch_holds_the_smaller_ones(recorder, in_features, outs, rank, tokens):
+    """Token-heavy units take a smaller table than the units of 16 tokens that a batch of fewer tokens goes back to."""
+    b = Batch(in_features, outs, [(tokens[0], rank)])
+    room = _room(b)
+    assert room >= _room(b, L.plan_options(heavy_min_batch=1024)) > _room(b, L.plan_options(heavy_min_batch=1))
+    seg = _in_a_table_of(b, room, tokens[0])
+    for n in tokens:
+        L.lora_segments_rebuild(seg, b.ta[:n])
+        names = _names(b.launches(recorder, seg))
+        assert ("expand_big" in names) == (n == tokens[0])
+    L.lora_segments_destroy(seg)
+    with pytest.raises(L.LoraError, match="OOM"):
+        _in_a_table_of(b, room - 256, tokens[0])
+    b.close()
+
+
+@pytest.mark.parametrize("outs", [4096, [4096, 1024]])
+def test_a_table_without_room_for_the_cuts_of_a_small_batch_s_token_heavy_units(recorder, outs):
+    """They lose their cuts along k and their short column runs, not their 64 tokens; units of 16 tokens would need more."""
+    b = Batch(4096, outs, [(900, 256)])
+    full = _room(b, L.plan_options(heavy_min_batch=1))
+    plain = _room(b, L.plan_options(heavy_min_batch=1, heavy_k_cut_max_units=0, big_runs_max_units=0))
+    assert plain < full - 256
+    made = {}
+    for size in (full, full - 256, plain):
+        seg = _in_a_table_of(b, size, 1)
+        L.lora_segments_rebuild(seg, b.ta)
+        made[size] = b.launches(recorder, seg)
+        assert _names(made[size]) == ["shrink_prefill", "expand_big"]
+        L.lora_segments_destroy(seg)
+    assert made[full][0][1] > made[plain][0][1] and made[full - 256] == made[plain]
+    seg = _in_a_table_of(b, plain - 256, 1)
+    with pytest.raises(L.LoraError, match="OOM"):
+        L.lora_segments_rebuild(seg, b.ta)
+    L.lora_segments_destroy(seg)
+    b.close()
+
+
 # ---- the binding's own checks of arguments --------------------------------------------------------------------------
 @pytest.mark.parametrize("adapter", ["0", None, 0.0, ctypes.c_int32(0)])
 def test_an_adapter_that_is_no_whole_number_is_a_type_error(recorder, adapter):
