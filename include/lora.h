@@ -317,7 +317,10 @@ lora_status_t lora_segments_destroy(lora_segments_t *seg);
 /* ---- the hot path ---- */
 
 /* Bytes of device workspace lora_shrink / lora_apply need for this batch (split-K partial sums of
- * v; 0 is possible).  The workspace must be 256-byte aligned. */
+ * v; 0 is possible).  The workspace must be 256-byte aligned.  A batch of fewer than
+ * lora_plan_options_t.heavy_min_batch tokens on token-heavy units is stated what its fastest form needs, and
+ * runs in what its units of 16 tokens would need too (a workspace made for another batch of few tokens): without
+ * cuts along k then, the sums of v in another order. */
 lora_status_t lora_workspace_bytes(const lora_pool_t *pool, const lora_segments_t *seg, size_t *bytes);
 
 /* A segment object can be launched on the pool it was built for, and on any other pool with the same

@@ -110,7 +110,7 @@ struct lora_segments {
     size_t dev_capacity;
     char *staging;  // pinned host copy of the table
     size_t staging_capacity;
-    size_t off_perm, off_shrink, off_prefill, off_expand, off_expand_big, off_fused_shrink, off_fused_expand, off_sync,
+    size_t off_perm, off_shrink, off_prefill, off_uncut, off_expand, off_expand_big, off_fused_shrink, off_fused_expand, off_sync,
         table_bytes;
     int top_rank;           // the largest padded rank the batch uses
     bool has_big_units;     // some unit holds more than 16 tokens (token-heavy groups)
@@ -122,6 +122,9 @@ struct lora_segments {
     std::vector<lora::BigSection> big_sections;  // expand_big_units in runs of equally wide ones: one per projection, or fewer
     int heavy_k_slices;     // k-slices of the token-heavy shrink units (1: they take the whole of k)
     bool small_heavy;       // token-heavy units in a batch of fewer than kPrefillMinBatch tokens (see small_batch_token_heavy)
+    bool small_whole_k;     // ... whose units of 16 tokens would take the whole of k
+    std::vector<Unit> uncut_units;  // and whose own ones are cut along k: the same uncut (see slices_in), places that hold no work among them
+    int n_uncut_work;               // how many of these hold tokens
     bool decode_fused;      // whole-k decode batch that can run as one launch (see finish_decode_fused)
     int fused_grid;         // work groups of that launch
     int n_sync;             // counters: one per (group, token tile), then the time-out flag
@@ -884,7 +887,8 @@ static void layout_table(lora_segments *sg)
     sg->off_perm = 0;
     sg->off_shrink = round_up_sz(sg->perm.size() * sizeof(int32_t), 256);
     sg->off_prefill = round_up_sz(sg->off_shrink + sg->shrink_units.size() * sizeof(Unit), 256);
-    sg->off_expand = round_up_sz(sg->off_prefill + sg->prefill_units.size() * sizeof(Unit), 256);
+    sg->off_uncut = round_up_sz(sg->off_prefill + sg->prefill_units.size() * sizeof(Unit), 256);
+    sg->off_expand = round_up_sz(sg->off_uncut + sg->uncut_units.size() * sizeof(Unit), 256);
     sg->off_expand_big = round_up_sz(sg->off_expand + sg->expand_units.size() * sizeof(Unit), 256);
     sg->off_fused_shrink = round_up_sz(sg->off_expand_big + sg->expand_big_units.size() * sizeof(Unit), 256);
     sg->off_fused_expand = round_up_sz(sg->off_fused_shrink + sg->fused_shrink.size() * sizeof(Unit), 256);
@@ -1212,8 +1216,16 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     }
     bool heavy_groups = false;
     for (int a = 0; a < N; ++a) heavy_groups |= count[a] >= heavy_min_tokens && n_active >= heavy_min_batch;
-    sg->wide = whole_k_units >= kWholeKMin && whole_k_units <= opt_whole_k_limit(sg) &&
-               pool->in_features <= opt_whole_k_max_in(sg) && !(opt_merged(sg) && heavy_groups);
+    auto takes_whole_k = [&](int64_t units) {
+        return units >= kWholeKMin && units <= opt_whole_k_limit(sg) && pool->in_features <= opt_whole_k_max_in(sg);
+    };
+    sg->wide = takes_whole_k(whole_k_units) && !(opt_merged(sg) && heavy_groups);
+    int64_t units_of_16 = 0;
+    if (sg->small_heavy)
+        for (int a = 0; a < N; ++a)
+            units_of_16 += (int64_t)((pool->r8[a] + lora::kRowTile - 1) / lora::kRowTile) *
+                           ((count[a] + lora::kTokTile - 1) / lora::kTokTile);
+    sg->small_whole_k = takes_whole_k(units_of_16);
     choose_k_slices(pool->in_features, &sg->wide_slices, &sg->wide_slice_len);
     // Whole-k units of many tokens pass up to twice the bytes of the others through their compute unit
     // (x beside A^T) and end the launch.  While the launch stays at one work group per compute unit,
@@ -1468,7 +1480,16 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     if (!sg->expand_big_units.empty()) sg->big_sections.push_back({(int)sg->expand_big_units.size(), big_cols});
     order_units_by_xcd(sg->shrink_units);
     sg->n_heavy_units = (int)sg->prefill_units.size();
+    sg->uncut_units.clear();
+    if (sg->small_whole_k && heavy_k_slices > 1)
+        for (const Unit &u : sg->prefill_units)
+            if (u.ks == 0) {
+                sg->uncut_units.push_back(u);
+                sg->uncut_units.back().sync_n = 1;
+            }
+    sg->n_uncut_work = (int)sg->uncut_units.size();
     order_heavy_units_by_xcd(sg->prefill_units);
+    order_heavy_units_by_xcd(sg->uncut_units);
 
     finish_decode_fused(sg, want_fused, pool->in_features);
     order_linear_rows(sg, ta, n_projections == 1 ? T : 0, pool->in_features, out, !lean);
@@ -1490,7 +1511,7 @@ static lora_segments *new_segments()
     sg->fork = sg->join = nullptr;
     sg->uploaded = false;
     sg->n_sync = 0;
-    sg->small_heavy = false;
+    sg->small_heavy = sg->small_whole_k = false;
     sg->launches = 0;
     sg->caller_memory = false;
     sg->opts = kDefaultOptions;
@@ -1671,6 +1692,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
     const uint64_t delta0 = (uint64_t)(((uintptr_t)p0->arena - (uintptr_t)base) / 2);
     shift(sg->shrink_units, 0, delta0, 0, 0, 0);
     shift(sg->prefill_units, 0, delta0, 0, 0, 0);
+    shift(sg->uncut_units, 0, delta0, 0, 0, 0);
     shift(sg->expand_units, 0, delta0, 0, 0, 0);
     shift(sg->expand_big_units, 0, delta0, 0, 0, 0);
     sg->mpool_ids.push_back(p0->id);
@@ -1689,18 +1711,21 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         if (st != LORA_OK) break;
         const uint64_t delta = (uint64_t)(((uintptr_t)pools[q]->arena - (uintptr_t)base) / 2);
         const size_t n0 = sg->shrink_units.size(), n1 = sg->prefill_units.size(), n2 = sg->expand_units.size(),
-                     n3 = sg->expand_big_units.size();
+                     n3 = sg->expand_big_units.size(), n4 = sg->uncut_units.size();
         sg->shrink_units.insert(sg->shrink_units.end(), tmp->shrink_units.begin(), tmp->shrink_units.end());
         sg->prefill_units.insert(sg->prefill_units.end(), tmp->prefill_units.begin(), tmp->prefill_units.end());
+        sg->uncut_units.insert(sg->uncut_units.end(), tmp->uncut_units.begin(), tmp->uncut_units.end());
         sg->expand_units.insert(sg->expand_units.end(), tmp->expand_units.begin(), tmp->expand_units.end());
         sg->expand_big_units.insert(sg->expand_big_units.end(), tmp->expand_big_units.begin(),
                                     tmp->expand_big_units.end());
         shift(sg->shrink_units, n0, delta, (int64_t)q * v_one, (int)q * sync_one, 0);
         shift(sg->prefill_units, n1, delta, (int64_t)q * v_one, (int)q * sync_one, 0);
+        shift(sg->uncut_units, n4, delta, (int64_t)q * v_one, (int)q * sync_one, 0);
         shift(sg->expand_units, n2, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         shift(sg->expand_big_units, n3, delta, (int64_t)q * v_one, (int)q * sync_one, col);
         sg->n_prefill_hi += tmp->n_prefill_hi;
         sg->n_heavy_units += tmp->n_heavy_units;
+        sg->n_uncut_work += tmp->n_uncut_work;
         for (const lora::BigSection &b : tmp->big_sections) {
             if (!sg->big_sections.empty() && sg->big_sections.back().cols == b.cols)
                 sg->big_sections.back().n_units += b.n_units;
@@ -1717,6 +1742,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
     }
     if (st != LORA_OK) return st;
     interleave_heavy_units(sg->prefill_units, pools.size());
+    interleave_heavy_units(sg->uncut_units, pools.size());
     sg->out_total = col;
     sg->v_floats = v_one * (int64_t)pools.size();
     sg->n_sync = sync_one * (int)pools.size();
@@ -1852,6 +1878,8 @@ static lora_status_t upload_table(lora_segments *sg, hipStream_t s)
                sg->expand_big_units.size() * sizeof(Unit));
     if (!sg->prefill_units.empty())
         memcpy(sg->staging + sg->off_prefill, sg->prefill_units.data(), sg->prefill_units.size() * sizeof(Unit));
+    if (!sg->uncut_units.empty())
+        memcpy(sg->staging + sg->off_uncut, sg->uncut_units.data(), sg->uncut_units.size() * sizeof(Unit));
     if (!sg->shrink_units.empty())
         memcpy(sg->staging + sg->off_shrink, sg->shrink_units.data(), sg->shrink_units.size() * sizeof(Unit));
     if (!sg->expand_units.empty())
@@ -2169,13 +2197,28 @@ static size_t partial_bytes(const lora_segments *sg)
 }
 
 // lora_apply's workspace: [k-slices' fp32 partial sums of v | v as bf16 hi | v as bf16 lo]
-static size_t apply_parts_bytes(const lora_segments *sg)
+static size_t apply_parts_bytes(const lora_segments *sg, int n_slices)
 {
-    return round_up_sz((size_t)std::max(1, sg->n_k_slices) * (size_t)sg->v_floats * 4, 256);
+    return round_up_sz((size_t)n_slices * (size_t)sg->v_floats * 4, 256);
 }
 static size_t apply_packed_bytes(const lora_segments *sg) { return round_up_sz((size_t)sg->v_floats * 2, 256); }
+static size_t apply_bytes(const lora_segments *sg, int n_slices) { return apply_parts_bytes(sg, n_slices) + 2 * apply_packed_bytes(sg); }
 
-enum UnitKind { kShrink, kPrefill, kExpand, kExpandBig, kFusedShrink, kFusedExpand };
+// The slices that an apply makes.  A small batch on token-heavy units states a workspace for slices of v where its units of 16 tokens
+// would have taken the whole of k (20 bytes an element of v, not 8; the halves apart 16, not 0).  A caller's workspace that is only large
+// enough for the latter, made for another batch of such units, is enough all the same: without slices, by the list of uncut units if
+// the planned ones are cut.  (A list of its own, since a question in the kernels whether to take the cut cost launches of few units 0.1 to
+// 0.2 us: 1024 -> 1024, 16 prompts of 128 tokens, 9.1 / 9.3.)
+static int slices_in(const lora_segments *sg, size_t ws_bytes)
+{
+    const int n = std::max(1, sg->n_k_slices);
+    return sg->small_whole_k && ws_bytes < apply_bytes(sg, n) ? 1 : n;
+}
+
+enum UnitKind { kShrink, kPrefill, kPrefillUncut, kExpand, kExpandBig, kFusedShrink, kFusedExpand };
+static UnitKind heavy_list(const lora_segments *sg, int n_slices) { return n_slices == 1 && sg->heavy_k_slices > 1 ? kPrefillUncut : kPrefill; }
+// how many of a list's units are above rank 64 (an uncut list is the shorter; the launch asks whether there are any)
+static int above_64(const lora_segments *sg, const lora::LaunchCtx &c) { return std::min(sg->n_prefill_hi, c.n_units); }
 
 static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_features, const lora_segments *sg,
                                 UnitKind kind)
@@ -2183,12 +2226,14 @@ static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_f
     lora::LaunchCtx c;
     const size_t off = kind == kShrink        ? sg->off_shrink
                        : kind == kPrefill     ? sg->off_prefill
+                       : kind == kPrefillUncut ? sg->off_uncut
                        : kind == kExpand      ? sg->off_expand
                        : kind == kExpandBig   ? sg->off_expand_big
                        : kind == kFusedShrink ? sg->off_fused_shrink
                                               : sg->off_fused_expand;
     const std::vector<Unit> &list = kind == kShrink        ? sg->shrink_units
                                     : kind == kPrefill     ? sg->prefill_units
+                                    : kind == kPrefillUncut ? sg->uncut_units
                                     : kind == kExpand      ? sg->expand_units
                                     : kind == kExpandBig   ? sg->expand_big_units
                                     : kind == kFusedShrink ? sg->fused_shrink
@@ -2197,7 +2242,7 @@ static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_f
     c.perm = (const int32_t *)(sg->dev + sg->off_perm);
     c.arena = arena;
     c.n_units = (int)list.size();
-    c.n_work = kind == kPrefill ? sg->n_heavy_units : c.n_units;
+    c.n_work = kind == kPrefill ? sg->n_heavy_units : kind == kPrefillUncut ? sg->n_uncut_work : c.n_units;
     c.top_rank = sg->heavy_top_rank;
     c.sections = sg->big_sections.data();
     c.n_sections = (int)sg->big_sections.size();
@@ -2227,7 +2272,7 @@ try {
     if (!pool_ok(pool)) return fail(LORA_ERR_INVALID_ARG, "pool is NULL or not a pool");
     if (!seg_ok(sg)) return fail(LORA_ERR_INVALID_ARG, "seg is NULL or not a segment object");
     if (!bytes) return fail(LORA_ERR_INVALID_ARG, "bytes is NULL");
-    *bytes = apply_parts_bytes(sg) + 2 * apply_packed_bytes(sg);
+    *bytes = apply_bytes(sg, std::max(1, sg->n_k_slices));
     return LORA_OK;
 }
 API_CATCH
@@ -2249,33 +2294,35 @@ try {
     if (sg->n_active == 0) return LORA_OK;
     if ((st = check_matrix(x, ldx, pool->in_features, "x")) != LORA_OK) return st;
     if (!v || ((uintptr_t)v) % 16) return fail(LORA_ERR_INVALID_ARG, "v is NULL or not 16-byte aligned");
-    if ((st = check_workspace(workspace, ws_bytes, partial_bytes(sg))) != LORA_OK) return st;
+    // (see slices_in; units of 16 tokens would not look at the workspace at all)
+    const bool uncut = sg->small_whole_k && (!workspace || (uintptr_t)workspace % 256 || ws_bytes < partial_bytes(sg));
+    if (!uncut && (st = check_workspace(workspace, ws_bytes, partial_bytes(sg))) != LORA_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const lora::LaunchCtx c = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, kPrefill);
+    const lora::LaunchCtx c = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, heavy_list(sg, uncut ? 1 : sg->n_k_slices));
     if (sg->wide) {
         HIP_TRY(lora::launch_shrink_wide(c, c.n_units > kComputeUnits, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, v, nullptr,
                                          nullptr, s));
-        HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
+        HIP_TRY(lora::launch_shrink_prefill(cp, above_64(sg, cp), (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
                                             nullptr, s));
     } else if (sg->n_k_slices <= 1) {
         HIP_TRY(lora::launch_shrink(c, (const uint16_t *)x, ldx, sg->k_slice_len, v, 1, 0, nullptr, s));
-        HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
+        HIP_TRY(lora::launch_shrink_prefill(cp, above_64(sg, cp), (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
                                             nullptr, s));
     } else {
         // Token-heavy units that were not cut along k leave v themselves, behind the addition of the others' slices
         // (which passes over their rows too).  Uncut and alone, nothing is added up: 19,675 tokens at 4096 features,
         // shrink and expand 141 -> 112 us against slices of zeros and their addition.
         float *parts = (float *)workspace;
-        const bool cut = sg->heavy_k_slices > 1;
-        const int n_add = c.n_units > 0 ? sg->n_k_slices : sg->heavy_k_slices;
+        const bool cut = sg->heavy_k_slices > 1 && !uncut;
+        const int n_add = uncut ? 1 : c.n_units > 0 ? sg->n_k_slices : sg->heavy_k_slices;
         HIP_TRY(lora::launch_shrink(c, (const uint16_t *)x, ldx, sg->k_slice_len, parts, sg->n_k_slices,
                                     sg->v_floats, nullptr, s));
         if (cut)
-            HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, nullptr, nullptr, parts, n_add,
+            HIP_TRY(lora::launch_shrink_prefill(cp, above_64(sg, cp), (const uint16_t *)x, ldx, nullptr, nullptr, parts, n_add,
                                                 sg->v_floats, nullptr, nullptr, s));
         if (n_add > 1) HIP_TRY(lora::launch_reduce_slices(parts, n_add, sg->v_floats, v, sg->v_floats, s));
         if (!cut)
-            HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
+            HIP_TRY(lora::launch_shrink_prefill(cp, above_64(sg, cp), (const uint16_t *)x, ldx, nullptr, nullptr, v, 1, 0, nullptr,
                                                 nullptr, s));
     }
     return LORA_OK;
@@ -2414,11 +2461,10 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     lora_status_t st;
     if ((st = check_matrix(x, ldx, in, "x")) != LORA_OK) return st;
     if ((st = check_matrix(y, ldy, out, "y")) != LORA_OK) return st;
-    const size_t need = apply_parts_bytes(sg) + 2 * apply_packed_bytes(sg);
-    if ((st = check_workspace(workspace, ws_bytes, need)) != LORA_OK) return st;
+    const int nsl = slices_in(sg, ws_bytes);
+    if ((st = check_workspace(workspace, ws_bytes, apply_bytes(sg, nsl))) != LORA_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     float *parts = (float *)workspace;
-    const int nsl = std::max(1, sg->n_k_slices);
     const int64_t stride = nsl > 1 ? sg->v_floats : 0;
     hipEvent_t ev[3] = {g_prof[0], g_prof[1], g_prof[2]};
     g_prof[0] = g_prof[1] = g_prof[2] = nullptr;
@@ -2430,11 +2476,11 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
     sa.counters = (unsigned *)(sg->dev + sg->off_sync);
     sa.ready = sa.counters + sg->n_sync;
     sa.timeout_flag = sa.counters + 2 * sg->n_sync;
-    sa.v_hi = (uint16_t *)((char *)workspace + apply_parts_bytes(sg));
-    sa.v_lo = (uint16_t *)((char *)workspace + apply_parts_bytes(sg) + apply_packed_bytes(sg));
+    sa.v_hi = (uint16_t *)((char *)workspace + apply_parts_bytes(sg, nsl));
+    sa.v_lo = (uint16_t *)((char *)workspace + apply_parts_bytes(sg, nsl) + apply_packed_bytes(sg));
     sa.epoch = msg->launches + 1;  // read by the single-launch form only, which also advances it
     sa.spin_limit = opt_spin_limit(sg);
-    const lora::LaunchCtx cs = ctx_for(arena, in, out, sg, kShrink), cp = ctx_for(arena, in, out, sg, kPrefill),
+    const lora::LaunchCtx cs = ctx_for(arena, in, out, sg, kShrink), cp = ctx_for(arena, in, out, sg, heavy_list(sg, nsl)),
                           ce = ctx_for(arena, in, out, sg, kExpand), cb = ctx_for(arena, in, out, sg, kExpandBig);
     if (ev[0]) HIP_TRY(hipEventRecord(ev[0], s));
     // units of more than 16 tokens span several counters, and whole-k shrink units are work groups of
@@ -2498,7 +2544,7 @@ static lora_status_t run_apply(const uint16_t *arena, int in, int out, const lor
             HIP_TRY(hipEventRecord(msg->fork, s));
             HIP_TRY(hipStreamWaitEvent(sd, msg->fork, 0));
         }
-        HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, sa.v_hi, sa.v_lo, nullptr,
+        HIP_TRY(lora::launch_shrink_prefill(cp, above_64(sg, cp), (const uint16_t *)x, ldx, sa.v_hi, sa.v_lo, nullptr,
                                             nsl, stride, parts, &sa, s));
         if (sg->wide)
             HIP_TRY(lora::launch_shrink_wide(cs, cs.n_units > kComputeUnits, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, nullptr,
@@ -2554,29 +2600,28 @@ try {
     const int in = pool->in_features, out = pool->out_features;
     if ((st = check_matrix(x, ldx, in, "x")) != LORA_OK) return st;
     if ((st = check_matrix(y, ldy, out, "y")) != LORA_OK) return st;
-    const size_t need = apply_parts_bytes(sg) + 2 * apply_packed_bytes(sg);
-    if (sg->n_active > 0 && (st = check_workspace(workspace, ws_bytes, need)) != LORA_OK) return st;
+    const int nsl = slices_in(sg, ws_bytes);
+    if (sg->n_active > 0 && (st = check_workspace(workspace, ws_bytes, apply_bytes(sg, nsl))) != LORA_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     float *parts = (float *)workspace;
-    const int nsl = std::max(1, sg->n_k_slices);
     const int64_t stride = nsl > 1 ? sg->v_floats : 0;
     lora::SyncArgs sa;
     sa.counters = (unsigned *)(sg->dev + sg->off_sync);
     sa.ready = sa.counters + sg->n_sync;
     sa.timeout_flag = sa.counters + 2 * sg->n_sync;
-    sa.v_hi = (uint16_t *)((char *)workspace + apply_parts_bytes(sg));
-    sa.v_lo = (uint16_t *)((char *)workspace + apply_parts_bytes(sg) + apply_packed_bytes(sg));
+    sa.v_hi = (uint16_t *)((char *)workspace + apply_parts_bytes(sg, nsl));
+    sa.v_lo = (uint16_t *)((char *)workspace + apply_parts_bytes(sg, nsl) + apply_packed_bytes(sg));
     sa.epoch = 0;
     sa.spin_limit = opt_spin_limit(sg);
     if (sg->n_active > 0) {
         // the shrink half of lora_apply's separate-launch forms: s_a v complete as bf16 hi + lo in the workspace
-        lora::LaunchCtx cs = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, kPrefill);
+        lora::LaunchCtx cs = ctx_for(pool, sg, kShrink), cp = ctx_for(pool, sg, heavy_list(sg, nsl));
         cs.scale_v = cp.scale_v = 1;
         if (opt_merged(sg) && sg->has_big_units && !sg->wide && cs.n_units > 0) {
             HIP_TRY(lora::launch_shrink_mixed(cp, sg->n_prefill_hi, cs, (const uint16_t *)x, ldx, sg->k_slice_len, parts, nsl,
                                               stride, &sa, s));
         } else {
-            HIP_TRY(lora::launch_shrink_prefill(cp, sg->n_prefill_hi, (const uint16_t *)x, ldx, sa.v_hi, sa.v_lo, nullptr, nsl,
+            HIP_TRY(lora::launch_shrink_prefill(cp, above_64(sg, cp), (const uint16_t *)x, ldx, sa.v_hi, sa.v_lo, nullptr, nsl,
                                                 stride, parts, &sa, s));
             if (sg->wide)
                 HIP_TRY(lora::launch_shrink_wide(cs, cs.n_units > kComputeUnits, (const uint16_t *)x, ldx, sg->wide_slice_len, sg->wide_slices, nullptr,
@@ -2604,7 +2649,7 @@ try {
     lora_status_t st = check_launchable(pool, sg);
     if (st != LORA_OK) return st;
     if (sg->n_active == 0) return LORA_OK;
-    const size_t need = apply_parts_bytes(sg) + 2 * apply_packed_bytes(sg);
+    const size_t need = apply_bytes(sg, std::max(1, sg->n_k_slices));
     if (need > lora::kStaticScratchBytes)
         return fail(LORA_ERR_WORKSPACE,
                     "this batch needs a workspace of %zu bytes, the library's own holds LORA_STATIC_WORKSPACE_BYTES = "

@@ -199,6 +199,46 @@ def test_small_batches_of_token_heavy_units(in_features, groups):
     dp.close()
 
 
+@pytest.mark.parametrize("in_features, groups", [
+    (4096, [(900, 64)]),                            # two work groups a unit
+    (4096, [(530, 256), (33, 24), (70, 72)]),       # more than one list of units, partial tiles
+    (9024, [(64, 128)] * 11 + [(47, 192), (33, 8)]),
+    (4160, [(1000, 248)]),
+])
+def test_cut_token_heavy_units_without_memory_for_their_slices(in_features, groups):
+    """A small batch in the workspace that its units of 16 tokens would take: the first of a tile's cut units does all of k.  The bytes
+    behind that workspace stay as they are."""
+    b = _batch(in_features, 384, groups, idle=3, seed=in_features)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    x = G.bits_to_dev(x_bits)
+    seg = L.lora_segments_build(dp.pool, b.token_adapter)
+    of_16 = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_min_batch=1024))
+    n, stated = (L.lora_apply_workspace_bytes(dp.pool, s) for s in (of_16, seg))
+    assert n < stated and L.lora_workspace_bytes(dp.pool, of_16) == 0
+    w = torch.empty(in_features * 384, dtype=torch.bfloat16, device="cuda")
+    L.lora_linear_pack_weight(torch.zeros(384, in_features, dtype=torch.bfloat16, device="cuda"), in_features, 384, w)
+    v = torch.full((L.lora_segments_info(seg)["v_floats"],), float("nan"), dtype=torch.float32, device="cuda")
+    y, apart, none = (G.bits_to_dev(y0) for _ in range(3))
+    ws = torch.full((stated,), 0xFF, dtype=torch.uint8, device="cuda")
+    for _ in range(2):  # (the counters too are as a cut launch would leave them)
+        y.copy_(G.bits_to_dev(y0))
+        L.lora_apply(dp.pool, seg, x, y, ws[:n])
+    L.lora_shrink(dp.pool, seg, x, v, None)
+    L.lora_expand(dp.pool, seg, v, apart)
+    L.lora_linear(dp.pool, seg, x, w, none, ws[:n])
+    cut = G.bits_to_dev(y0)
+    assert (ws[n:] == 0xFF).all()
+    L.lora_apply(dp.pool, seg, x, cut, ws)
+    torch.cuda.synchronize()
+    rows = np.arange(0, b.T, 3)
+    for got, start in ((y, y0), (apart, y0), (cut, y0), (none, np.zeros_like(y0))):
+        G.check_parity(G.dev_to_bits(got), G.oracle_apply(dp, x_bits, start, rows=rows), start, b.token_adapter, rows=rows)
+    L.lora_segments_destroy(seg)
+    L.lora_segments_destroy(of_16)
+    dp.close()
+
+
 @pytest.mark.parametrize("in_features, ranks, slices", HALVES)
 def test_rank_halves_of_few_token_heavy_units(in_features, ranks, slices):
     """Launches of few token-heavy units: halves of the rank rows, even and not, of units of 32 and 64 tokens, whole and cut along

@@ -66,10 +66,10 @@ class Batch:
             return L.lora_segments_build_multi(self.pools, self.ta, options=options)
         return L.lora_segments_build(self.pools[0], self.ta, options=options)
 
-    def launches(self, lib, seg, call="apply"):
-        """[(kernel, numbers ...), ...] of one call."""
+    def launches(self, lib, seg, call="apply", n=1 << 40, ws=1 << 47):
+        """[(kernel, numbers ...), ...] of one call with n bytes of workspace."""
         lib.recorder_take()
-        x, y, v, ws, n = 1 << 44, 1 << 45, 1 << 46, 1 << 47, 1 << 40
+        x, y, v = 1 << 44, 1 << 45, 1 << 46
         if call == "apply" and len(self.pools) > 1:
             L.lora_apply_multi(self.pools, seg, x, y, ws, ldx=self.in_features, ldy=self.out, ws_bytes=n)
         elif call == "apply":
@@ -498,21 +498,52 @@ def test_a_table_made_for_the_largest_small_batch_holds_the_smaller_ones(recorde
 def test_a_table_without_room_for_the_cuts_of_a_small_batch_s_token_heavy_units(recorder, outs):
     """They lose their cuts along k and their short column runs, not their 64 tokens; units of 16 tokens would need more."""
     b = Batch(4096, outs, [(900, 256)])
-    full = _room(b, L.plan_options(heavy_min_batch=1))
+    room = _room(b)
+    cut = _room(b, L.plan_options(heavy_min_batch=1))  # (without the list of uncut units, for a workspace without slices)
     plain = _room(b, L.plan_options(heavy_min_batch=1, heavy_k_cut_max_units=0, big_runs_max_units=0))
-    assert plain < full - 256
+    assert plain < cut < room
     made = {}
-    for size in (full, full - 256, plain):
+    for size in (room, cut, plain):
         seg = _in_a_table_of(b, size, 1)
         L.lora_segments_rebuild(seg, b.ta)
         made[size] = b.launches(recorder, seg)
         assert _names(made[size]) == ["shrink_prefill", "expand_big"]
         L.lora_segments_destroy(seg)
-    assert made[full][0][1] > made[plain][0][1] and made[full - 256] == made[plain]
+    assert made[room][0][1] > made[plain][0][1] and made[cut] == made[plain]
     seg = _in_a_table_of(b, plain - 256, 1)
     with pytest.raises(L.LoraError, match="OOM"):
         L.lora_segments_rebuild(seg, b.ta)
     L.lora_segments_destroy(seg)
+    b.close()
+
+
+@pytest.mark.parametrize("in_features, outs, groups, whole_k", [
+    (4096, 512, [(900, 64)], True), (9024, 384, [(700, 128)], True), (4096, [512, 128, 128], [(900, 64)], True),
+    (4096, 512, [(512, 256)], True), (4096, 512, [(1023, 256)], True),                # 512 and 1024 units of 16 tokens,
+    (4096, 512, [(980, 256), (43, 256)], False), (28672, 512, [(512, 64)], False),    # 1040; beyond the longest whole k
+])
+def test_the_workspace_of_units_of_16_tokens_is_enough_for_a_small_batch(recorder, in_features, outs, groups, whole_k):
+    """A workspace that units of 16 tokens over the whole of k fit, made for another batch, stays one that this batch can use:
+    token-heavy units then run without their cuts.  One byte less is refused, as is less than stated where the units of 16 tokens
+    would be cut too."""
+    b = Batch(in_features, outs, groups)
+    seg, of_16 = b.build(), b.build(L.plan_options(heavy_min_batch=1024))
+    for call in ["apply"] + ["shrink", "linear"] * (len(b.pools) == 1):
+        def shrinks(n, ws=1 << 47):  # (kernel, slices) of the launches in front of the expand or the product
+            return [(k[0], k[-1]) for k in b.launches(recorder, seg, call, n, ws) if k[0] not in ("expand_big", "linear")]
+
+        size = L.lora_workspace_bytes if call == "shrink" else L.lora_apply_workspace_bytes
+        stated, enough = size(b.pools[0], seg), size(b.pools[0], of_16)
+        assert (enough < stated) == whole_k and shrinks(stated)[0][0] == "shrink_prefill" and shrinks(stated)[0][1] > 1
+        if whole_k:
+            assert shrinks(enough) == [("shrink_prefill", 1)]
+        if whole_k and call == "shrink":  # these do not look at the workspace
+            assert enough == 0 and shrinks(0, 0) == shrinks(stated, (1 << 47) + 16) == [("shrink_prefill", 1)]
+        else:
+            with pytest.raises(L.LoraError, match="WORKSPACE"):
+                shrinks(enough - 1)
+    L.lora_segments_destroy(seg)
+    L.lora_segments_destroy(of_16)
     b.close()
 
 
