@@ -1398,6 +1398,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
                     u.v_off = r.v_off + (int64_t)tok0 * r.r8;
                     u.sync_idx = sync_base[si] + tok0 / lora::kTokTile;
                     u.sync_n = heavy_k_slices;
+                    u.turn = sg->seg_adapter[si];
                     fill_tokens(u, r);
                     sg->prefill_units.push_back(u);
                     if (r.r8 > 64) ++sg->n_prefill_hi;

@@ -39,7 +39,7 @@ struct Unit {
     int32_t sync_idx; // counter of this unit's (group, token tile) in a fused launch
     int32_t sync_n;   // shrink units that feed that counter per launch
     int32_t perm_off; // position of the unit's first token in the device copy of perm
-    int32_t pad[1];
+    int32_t turn;     // token-heavy shrink units: the adapter, by which they begin their walk along k with another pass
     int32_t tok[16];  // batch row index of each token; entries >= ntok repeat tok[0] (units of <= 16
                       // tokens; larger units read perm[perm_off + i])
 };

@@ -748,7 +748,7 @@ static __device__ __forceinline__ void complete_tile(const Unit &u, const RankRo
     }
 }
 
-// which of n passes along k the i-th tile of tokens of a group begins with, where they begin in turn: i modulo the power of two in n
+// which of n passes along k adapter i's units begin with, where they begin in turn: i modulo the largest power of two up to n
 static __device__ __forceinline__ int first_pass(int i, int n) { return n > 0 ? i & ((1 << (31 - __builtin_clz(n))) - 1) : 0; }
 
 template <int JB, int TB, int WD, int XD = 1>
@@ -825,14 +825,13 @@ static __device__ __forceinline__ void shrink_prefill_ksplit(const Unit &u, cons
         // ahead included, so that every pass of 128 of k took a whole trip to memory.
         const int npass = kend > kbeg ? (kend - kbeg + kPfPassK - 1) / kPfPassK : 0;
         const int nfull = kend > kbeg ? (kend - kbeg) / kPfPassK : 0;
-        // The passes in order, but from another one in every tile of tokens of a group where rows of x and the wavefronts' quarters lie
-        // whole multiples of 4 KB apart: all units of a launch walk k at about the same pace, and would ask a part of the memory's
-        // channels at any one time.  Not where the rank rows are more than 1 MB, which the units of an XCD then share less of.  A call
-        // in us, in order / by 3 passes a tile: 19,675 tokens, 8192 -> 1024, rank 8 82 / 72, rank 32 91 / 85.6, rank 64 107 / 104.6;
-        // 10,082 tokens, 16384 -> 1024, rank 8 79 / 68.9, rank 32 89.7 / 82.6, but rank 64 110 / 118.  In rows of 8 KB and 28 KB it gains
-        // nothing, and few prompts pay for it: two of 900 tokens, 3712 -> 640, 11.4 / 11.7, four of 700, 8192 -> 1024, 16.7 / 16.8.
-        const bool turns = kquarter * 2 % 4096 == 0 && ldx * 2 % 4096 == 0 && (int64_t)r8 * in <= 512 * 1024;
-        const int turn = turns ? first_pass(3 * (u.tok0 / kPfTokens), nfull) : 0;
+        // The passes in order, but from another one for every adapter where the wavefronts' quarters lie whole multiples of 4 KB apart: all
+        // units of a launch walk k at about the same pace, and would ask a part of the memory's channels at any one time.  By adapter
+        // and not by tile, so that a row's sums come in one order wherever its token sits in the group, and the tiles of a group still
+        // share its rows of A^T.  A call in us, in order / by tile / by adapter: 19,675 tokens of 32 adapters, 8192 -> 1024, rank 8 80.6 / 72.2 /
+        // 71.8, rank 32 92.8 / 85.8 / 84.9, rank 64 107.7 / 107.7 / 102; 10,082 tokens, 16384 -> 1024, rank 8 76.9 / 71.2 / 68.6, rank 32 86.3 / 82.5 /
+        // 81.8, rank 64 105 / 107 / 101.  Few prompts level: four of 700, 8192 -> 1024, 21.6 / 21.4 / 21.4.
+        const int turn = kquarter * 2 % 4096 == 0 ? first_pass(u.turn, nfull) : 0;
         auto pass_k = [&](int i) __attribute__((always_inline)) {
             return kbeg + kPfPassK * (i < nfull ? (i + turn < nfull ? i + turn : i + turn - nfull) : i);
         };
@@ -1021,11 +1020,10 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
     const int kend = min(in, kbeg + ks_len);
     const int npass = (kend - kbeg + kPfPassK - 1) / kPfPassK;
     const int nfull = (kend - kbeg) / kPfPassK;  // passes that hold 128 of k (in is a multiple of 64: the last may hold 64)
-    // The passes in order, but one further in every tile of tokens of a group, for the same reason as above.  A call in us, in order /
-    // in turn: rank 256 14336 -> 1024 394 / 372, 8192 -> 2048 260 / 252, 4096 -> 4096 214 / 211; rank 192 14336 -> 1024 256 / 245; rank 128
-    // 8192 -> 2048 151 / 148, 4096 -> 4096 127.9 / 126.7.  By 3 passes a tile, whose rows of A^T the units of an XCD no longer share, rank 256
-    // 525, 328 and 221.
-    const int turn = first_pass(u.tok0 / TOK, nfull);
+    // The passes in order, but one further for every adapter, as above.  A call in us, in order / by adapter: rank 256 14336 -> 1024 394 / 386,
+    // 8192 -> 2048 264 / 260, 4096 -> 4096 216 / 211; rank 192 14336 -> 1024 255 / 250; rank 128 8192 -> 2048 152.9 / 150.7.  (One further for
+    // every tile of a group 370, 253, 211, 241 and 151, but a row's sums then come in an order that depends on where its token sits.)
+    const int turn = first_pass(u.turn, nfull);
     auto pass_k = [&](int i) __attribute__((always_inline)) {
         return kbeg + kPfPassK * (i < nfull ? (i + turn < nfull ? i + turn : i + turn - nfull) : i);
     };

@@ -153,8 +153,8 @@ def test_token_heavy_units_cut_along_k(shape, most, sizes, cut):
 @pytest.mark.parametrize("in_features", [8192, 16384, 24576, 8256])
 @pytest.mark.parametrize("cut", [0, 1 << 20])
 def test_token_heavy_tiles_that_begin_with_another_pass(in_features, pad, cut):
-    """Rows and quarters of whole multiples of 4 KB (8192, 16384 and, uncut, 24576 features; not 8256, nor padded rows), in more tiles than a
-    walk has passes, up to rank 64 by the size of the rank rows and above always."""
+    """Quarters of whole multiples of 4 KB (8192, 16384 and, uncut, 24576 features; not 8256) up to rank 64, and above always: adapters 0 to 6
+    begin with different passes."""
     b = _batch(in_features, 128, [(300, 8), (33, 24), (600, 32), (200, 64), (130, 72), (200, 160), (100, 256)], idle=2, seed=in_features)
     dp = G.DevicePool(b)
     x_bits, y0 = b.x_bits(), b.y0_bits("small")
@@ -168,6 +168,38 @@ def test_token_heavy_tiles_that_begin_with_another_pass(in_features, pad, cut):
     rows = np.arange(0, b.T, 7)
     G.check_parity(G.dev_to_bits(y), G.oracle_apply(dp, x_bits, y0, rows=rows), y0, b.token_adapter, rows=rows)
     L.lora_segments_destroy(seg)
+    dp.close()
+
+
+@pytest.mark.parametrize("groups", [
+    [(300, 8), (33, 24), (600, 32), (200, 64), (130, 72), (200, 128), (200, 160), (100, 256)],  # whole
+    [(200, 64), (130, 72), (200, 128), (200, 160), (500, 256)],                               # few units: rank halves
+    [(300, 32), (130, 64), (900, 8)],
+], ids=["many", "halves", "low"])
+@pytest.mark.parametrize("in_features", [8192, 16384, 4096])
+@pytest.mark.parametrize("cut", [0, 1 << 20])
+def test_a_row_has_the_same_bits_wherever_its_token_sits(in_features, groups, cut):
+    """Any order of the tokens, those of one group among themselves too, and padded rows of x: adapters' units begin with different passes
+    along k, tiles of one adapter do not."""
+    b = _batch(in_features, 128, groups, idle=2, seed=in_features)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+
+    def apply(order, pad):
+        seg = L.lora_segments_build(dp.pool, b.token_adapter[order], options=L.plan_options(heavy_k_cut_max_units=cut))
+        x = torch.full((b.T, in_features + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+        x[:, :in_features] = G.bits_to_dev(x_bits[order])
+        y = G.bits_to_dev(y0[order])
+        ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+        L.lora_apply(dp.pool, seg, x[:, :in_features], y, ws)
+        torch.cuda.synchronize()
+        L.lora_segments_destroy(seg)
+        return G.dev_to_bits(y)
+
+    want = apply(np.arange(b.T), 0)
+    order = np.random.default_rng(1).permutation(b.T)
+    assert np.array_equal(apply(order, 0), want[order])
+    assert np.array_equal(apply(np.arange(b.T), 64), want)
     dp.close()
 
 
