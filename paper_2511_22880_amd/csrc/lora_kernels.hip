@@ -1178,8 +1178,9 @@ static __device__ __forceinline__ void shrink_prefill_rowsplit(const Unit &u, co
 // at gptr (per lane) land at lds_piece + 16*l (lds_piece wave-uniform).  Written as an instruction the
 // compiler does not look into: for its own form of this load it waits until the copy has landed
 // before the wavefront may issue anything else that touches LDS or the registers involved, which
-// leaves nothing of the overlap the copy exists for.  The caller waits (vmcnt(0)) and synchronises
-// the work group before anyone reads the destination.
+// leaves nothing of the overlap the copy exists for.  The caller waits and synchronises the work group before anyone
+// reads the destination: for all of the wavefront's memory operations (vmcnt(0)), or for all but the last N, if at least N that the compiler
+// knows of are issued behind the copies on every way to the wait: a branch or a scheduling barrier between keeps them there.
 static __device__ __forceinline__ void dma16_to_lds(const uint4 *gptr, const uint4 *lds_piece)
 {
     const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(
@@ -1645,7 +1646,7 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
         for (int e = 0; e < 4; ++e) yv[s][e] = ld16_stream(yrow[e] + s * kStrip);
     };
     copy_tile(0, 0);
-    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_sched_barrier(0);  // the rows of y behind the copies: the wait below counts them
     if (nt > 0) {
         load_v(0);
         __builtin_amdgcn_sched_barrier(0);
@@ -1690,6 +1691,8 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
         if (nstrips > 1) {
             __syncthreads();
             copy_tile(1, 0);
+            // (the rows of y stand in a block of their own behind the copies; a scheduling barrier here made ranks up to 64, which do not
+            // come this way, 2 to 4 % slower by other registers)
             if (nt > 0) {
                 if (CHUNKS > 1) load_v(0);
                 fetch_y(1);
