@@ -158,6 +158,22 @@ hipError_t launch_shrink_prefill(const LaunchCtx &c, int n_hi, const uint16_t *x
                                  uint16_t *v_lo, float *v_f32, int n_slices, int64_t slice_stride, float *parts,
                                  const SyncArgs *sync, hipStream_t stream);
 
+// The work groups of a launch of 64-token expand units: rows of 8 units, each unit in pieces of kBigCols columns.
+constexpr int kBigCols = 256;
+inline int64_t big_places(const LaunchCtx &c)
+{
+    int64_t places = 0;
+    for (int i = 0; i < c.n_sections; ++i)
+        places += (int64_t)(c.sections[i].n_units + 7) / 8 * 8 * ((c.sections[i].cols + kBigCols - 1) / kBigCols);
+    return places;
+}
+// Whether such a launch, of its own, asks for so much LDS that three work groups run on a compute unit and not four: up to rank 128, where
+// less of y is under way at a time (see the kernel), but not where four hold all of it and a fourth of it would wait for the others to end.
+// us a call, 512 features, three / four a compute unit, 769 to 1024 work groups: 4096 columns, 4096 tokens, rank 16 19.0 / 18.4, rank 128 26.1 /
+// 24.7; 8192, two prompts of 900, rank 16 18.3 / 17.4, rank 128 25.7 / 24.2; 14336, 1024 tokens, rank 16 17.9 / 17.7, two of 512, rank 128 25.2 /
+// 24.3, but rank 64 19.6 / 20.2; 1800 tokens, 8192, rank 64 18.7 / 19.0; over 160 such batches 2 % faster.
+inline bool big_spread(const LaunchCtx &c) { return c.top_rank <= 128 && big_places(c) > 4 * kComputeUnits; }
+
 // A mixed batch's shrink in one launch: the token-heavy units of `heavy` (n_hi of them above rank 64),
 // then the k-slice units of `c`, which leave partial sums in `parts` and complete v through `sync` where
 // launch_shrink does.  Likewise the expand: the 64-token units of `big`, which read v from sync->v_hi / v_lo, then the

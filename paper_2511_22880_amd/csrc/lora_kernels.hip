@@ -1520,14 +1520,15 @@ static __device__ __forceinline__ void expand_body(const Unit &u, const uint16_t
 // a look at perm: level.)
 // That asks for v and B^T oftener, which therefore come in whole KB of operand order (tiled_quad; B^T as the pool holds it), and for
 // 128 registers and 32 KB of LDS, four work groups on a compute unit: the low ranks' tiles of both strips, or one strip's up to rank
-// 128, or half of one's.  Up to rank 128 launches of their own ask for 16 KB of LDS more, so that three run there: less of y is under way at a
-// time (rank 16 56.6 / 54.4, rank 64 61.8 / 58.9, rank 128 70.9 / 69.9; two per compute unit 61.5, 64.0, 80.9), while above the fourth hides more of the
-// copies (rank 256 106 / 109).  Beside units of up to 16 tokens (k_expand_mixed) four are as fast as three or up to 3 % faster.
+// 128, or half of one's.  Up to rank 128 launches of their own and of more than those four (big_spread) ask for 16 KB of LDS more, so that
+// three run there: less of y is under way at a time (rank 16 56.6 / 54.4, rank 64 61.8 / 58.9, rank 128 70.9 / 69.9; two per compute unit 61.5,
+// 64.0, 80.9), while above the fourth hides more of the copies (rank 256 106 / 109).  Beside units of up to 16 tokens (k_expand_mixed) four
+// are as fast as three or up to 3 % faster.
 // ------------------------------------------------------------------------------------------------
 constexpr int kBigStrips = 2;                 // strips of a work group
 constexpr int kBigTile = 32 * 1024;           // bytes of B^T in LDS at a time
-constexpr int kBigSpread = 16 * 1024;         // LDS that a launch asks for beside it up to rank 128
-constexpr int kBigSpreadMaxRank = 128;
+constexpr int kBigSpread = 16 * 1024;         // LDS that a launch asks for beside it where big_spread says so
+static_assert(kBigStrips * kStrip == kBigCols, "columns of a work group");
 
 // KSTEPS: 32-wide steps of a chunk of the rank (1, 2 or 4); CHUNKS of 128 of it.
 template <int KSTEPS, int CHUNKS, bool VF32>
@@ -3052,7 +3053,7 @@ struct BigGrid {
     {
         int unit = 0;
         for (int i = 0; i < c.n_sections; ++i) {
-            const int per_unit = (c.sections[i].cols + kBigStrips * kStrip - 1) / (kBigStrips * kStrip);
+            const int per_unit = (c.sections[i].cols + kBigCols - 1) / kBigCols;
             if (i == 0) {
                 n_first = c.sections[0].n_units;
                 subs = per_unit;
@@ -3080,7 +3081,7 @@ hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16
         const BigGrid bg(c);
         if (bg.places > 0x7FFFFFFF) return hipErrorInvalidValue;
         const dim3 gb((unsigned)bg.places);
-        const unsigned more_lds = c.top_rank <= kBigSpreadMaxRank ? kBigSpread : 0;
+        const unsigned more_lds = big_spread(c) ? kBigSpread : 0;
         if (sync)
             hipLaunchKernelGGL(k_expand_big<false>, gb, b, more_lds, stream, c.units, bg.n_first, bg.subs, c.perm, c.arena, v_in, y, ldy,
                                sy, bg.more);

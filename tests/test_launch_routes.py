@@ -547,6 +547,22 @@ def test_the_workspace_of_units_of_16_tokens_is_enough_for_a_small_batch(recorde
     b.close()
 
 
+# ---- 64-token expand units: work groups per compute unit, runs of columns, order -----------------------------------------
+@pytest.mark.parametrize("outs, groups, three", [
+    (4096, [(4096, 128)], False), (4096, [(4097, 128)], True),       # 64 tiles of 16 work groups, all on the chip at four; one more tile
+    (4096, [(4097, 8)], True), (4096, [(4097, 136)], False),         # above rank 128 four hide the copies
+    ([4096, 1024], [(3200, 64)], False), ([4096, 1024], [(3300, 64)], True), (128, [(3000, 16)], False),
+])
+def test_work_groups_per_compute_unit_of_64_token_expand_units(recorder, outs, groups, three):
+    """Three only where four would not hold the launch at once."""
+    b = Batch(512, outs, groups)
+    seg = b.build()
+    b.launches(recorder, seg)
+    assert recorder.recorder_big_spread() == three
+    L.lora_segments_destroy(seg)
+    b.close()
+
+
 # ---- the binding's own checks of arguments --------------------------------------------------------------------------
 @pytest.mark.parametrize("adapter", ["0", None, 0.0, ctypes.c_int32(0)])
 def test_an_adapter_that_is_no_whole_number_is_a_type_error(recorder, adapter):
