@@ -618,7 +618,7 @@ static const int kWholeKMaxIn = 18432;
 static int heavy_tile(int r8) { return r8 <= 64 || r8 > 192 ? 32 : 64; }
 // Token-heavy groups take 64-token expand units, whatever their rank: 16-token ones would look for k-slices that
 // token-heavy shrink units do not leave.
-static_assert(LORA_MAX_RANK_PADDED * 128 * 2 <= 64 * 1024, "a strip's tile of B^T, 128 columns x rank, fits the kernel's 64 KiB of LDS");
+static_assert(LORA_MAX_RANK_PADDED <= 256, "a strip's tile of B^T, 128 columns x rank, fits the kernel's 32 KiB of LDS in two pieces");
 using lora::kComputeUnits;  // a whole-k launch within this many units is one round
 
 // K-slices of a launch's token-heavy shrink units: as many as keep it shortest by an estimate.  A compute unit passes
@@ -666,13 +666,16 @@ static int choose_heavy_k_slices(HeavyShrink &h, int in, int max_slices)
     }
     return best;
 }
-// 64-token expand units take a group's columns in 8, 16, .. runs instead of 4 (down to one strip of 128 columns
-// each), the most that keep the launch within one round of work groups (two per compute unit): it then
-// lasts as long as one unit, a strip after the other.  Expand launch in us by units allowed, 4 runs / 256 / 512 /
-// 1024 units; 4096 columns, rank 128: 16 tiles of 64 tokens 20.1 / 8.9 / 8.6 / 8.8, 32 tiles 21.0 / 13.0 / 10.6 /
-// 15.0, 63 tiles 22.5 / 22.5 / 18.4 / 20.7, 125 tiles 32.0 / 32.6 / 32.5 / 35.1; rank 16: 16 tiles 11.7 / 5.8 / 5.6 /
-// 5.9, 63 tiles 15.8 / 15.8 / 14.1 / 14.6; rank 256: 32 tiles 35.8 / 22.5 / 19.0 / 24.5; 1024 columns, rank 128, 16
-// tiles 11.7 / 6.3 / 6.2 / 6.4; 14336 columns, rank 256, 32 tiles 114 / 63 / 44 / 52.
+// 64-token expand units take a group's columns in 8, 16, .. runs instead of 4 (down to one strip of 128 columns each), the most that
+// keep the launch within 512 units.  A work group takes 256 columns of a unit, so runs of more than that only order the launch and change
+// the length of its unit list; what they gain is runs of one strip in launches of few tiles of 64 tokens.  us a call, 512 features, 4 runs /
+// limits of 256 / 512 / 1024 units: 4096 columns, rank 256, 8 tiles 16.4 / 13.5 / 13.3 / 13.4, 16 tiles 17.7 / 18.3 / 15.1 / 14.9, 32 tiles 21.2 /
+// 21.7 / 21.7 / 20.9, 63 tiles 32.9 / 32.7 / 34.6 / 34.8; rank 128, 16 tiles 14.2 / 14.3 / 13.4 / 13.5, 63 tiles 25.2 / 25.1 / 25.6 / 25.7; rank 16, 16
+// tiles 10.5 / 10.5 / 10.1 / 10.3, 63 tiles 18.4 throughout; 1024 columns, rank 256, 16 tiles 16.6 / 14.5 / 14.4 / 14.3, 63 tiles 20.4 / 20.4 / 21.6 /
+// 21.6, 125 tiles 27.8 / 27.7 / 27.7 / 32.3.
+// Runs of 3, 5, .. strips are passed over: the last work group of each would take half of its columns.  With / without them, 512 features:
+// 3072 columns, 62 tiles, rank 16 17.1 / 15.3, rank 256 35.6 / 28.8; 5120 columns, 32 tiles, rank 128 22.4 / 19.8; 14336 columns, 32 tiles, rank 128
+// 37.4 / 34.5; 11008 columns, 50 tiles, rank 256 57.5 / 55.5; but 5632 columns, 24 tiles, rank 128, one round of work groups either way, 18.7 / 19.3.
 static const int kBigRunsWorkGroupsPerComputeUnit = 2;
 
 extern "C" lora_status_t lora_set_whole_k_limit(int32_t max_units)
@@ -1364,13 +1367,16 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     }
     sg->heavy_k_slices = heavy_k_slices;
     // The 64-token expand units: a group's columns in 4 runs, or in more and shorter ones while that keeps the
-    // launch at few such units (it then lasts as long as one of them; see kBigRunsWorkGroupsPerComputeUnit)
+    // launch at few such units (see kBigRunsWorkGroupsPerComputeUnit)
     int64_t big_tiles = 0;
     for (const SegRec &r : sg->segs)
         if (r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch) big_tiles += (r.ntok + 63) / 64;
     int big_runs = 4, big_cols = 0;
+    auto run_cols = [&](int runs) { return std::min(out, std::max(runs > 4 ? 128 : 512, (out / runs + 127) / 128 * 128)); };
     for (int runs = 64; runs >= 8 && big_runs == 4 && !(lean && sg->opts.big_runs_max_units < 0); runs /= 2)
-        if (big_tiles * std::min(runs, out / 128) * n_projections <= opt_big_runs_max_units(sg)) big_runs = runs;
+        if (big_tiles * std::min(runs, out / 128) * n_projections <= opt_big_runs_max_units(sg) &&
+            (run_cols(runs) == 128 || run_cols(runs) % lora::kBigCols == 0))
+            big_runs = runs;
     for (int32_t si : order) {
         const SegRec &r = sg->segs[si];
         const bool token_heavy = r.ntok >= heavy_min_tokens && n_active >= heavy_min_batch;
@@ -1431,13 +1437,13 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
                         }
                     }
         }
-        // expand: small groups one column pass and <= 16 tokens per unit; token-heavy groups 64 tokens
-        // (16 per wavefront, v kept in registers) and a quarter of the columns, at least 512, or fewer
+        // expand: small groups one column pass and <= 16 tokens per unit; token-heavy groups 64 tokens (16 per
+        // wavefront) and a run of columns, of which each of the unit's work groups takes 256
         int cols = expand_cols_per_unit(r.r8, out);
         int etile = lora::kTokTile;
         if (token_heavy) {
             etile = 64;
-            cols = std::min(out, std::max(big_runs > 4 ? 128 : 512, (out / big_runs + 127) / 128 * 128));
+            cols = run_cols(big_runs);
             big_cols = cols;
         }
         auto emit = [&](int c0, int tok0) {
