@@ -1530,6 +1530,27 @@ constexpr int kBigTile = 32 * 1024;           // bytes of B^T in LDS at a time
 constexpr int kBigSpread = 16 * 1024;         // LDS that a launch asks for beside it where big_spread says so
 static_assert(kBigStrips * kStrip == kBigCols, "columns of a work group");
 
+typedef __attribute__((ext_vector_type(16), aligned(4))) int i32x16;
+
+// mine[e] = v[4 * (lane / 16) + e], of scalars: a quarter of the wavefront at a time, all lanes of which run here.  (The compiler makes branches
+// of it, or takes registers that spill.)
+static __device__ __forceinline__ void rows_by_quarter(const i32x16 &v, int (&mine)[4])
+{
+    unsigned long long all;
+    asm volatile("s_mov_b64 %4, exec\n\ts_mov_b32 exec_lo, 0xffff\n\ts_mov_b32 exec_hi, 0\n\t"
+        "v_mov_b32 %0, %5\n\tv_mov_b32 %1, %6\n\tv_mov_b32 %2, %7\n\tv_mov_b32 %3, %8\n\t"
+        "s_mov_b32 exec_lo, 0xffff0000\n\t"
+        "v_mov_b32 %0, %9\n\tv_mov_b32 %1, %10\n\tv_mov_b32 %2, %11\n\tv_mov_b32 %3, %12\n\t"
+        "s_mov_b32 exec_lo, 0\n\ts_mov_b32 exec_hi, 0xffff\n\t"
+        "v_mov_b32 %0, %13\n\tv_mov_b32 %1, %14\n\tv_mov_b32 %2, %15\n\tv_mov_b32 %3, %16\n\t"
+        "s_mov_b32 exec_hi, 0xffff0000\n\t"
+        "v_mov_b32 %0, %17\n\tv_mov_b32 %1, %18\n\tv_mov_b32 %2, %19\n\tv_mov_b32 %3, %20\n\t"
+        "s_mov_b64 exec, %4"
+        : "=&v"(mine[0]), "=&v"(mine[1]), "=&v"(mine[2]), "=&v"(mine[3]), "=&s"(all)
+        : "s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]), "s"(v[5]), "s"(v[6]), "s"(v[7]), "s"(v[8]), "s"(v[9]), "s"(v[10]),
+          "s"(v[11]), "s"(v[12]), "s"(v[13]), "s"(v[14]), "s"(v[15]));
+}
+
 // KSTEPS: 32-wide steps of a chunk of the rank (1, 2 or 4); CHUNKS of 128 of it.
 template <int KSTEPS, int CHUNKS, bool VF32>
 static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, const int32_t *__restrict__ perm,
@@ -1553,11 +1574,13 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
     uint4 *ltile = reinterpret_cast<uint4 *>(lds);
     const uint4 *gtile = reinterpret_cast<const uint4 *>(arena + u.w_off + (int64_t)c0 * r8);
 
-    // batch rows of the wavefront's tokens, through the scalar cache
-    const int32_t *toks = perm + u.perm_off;
-    int row[kTokTile];
-#pragma unroll
-    for (int i = 0; i < kTokTile; ++i) row[i] = toks[max(0, min(kTokTile * wave + i, ntok_all - 1))];
+    // Batch rows of the wavefront's tokens, through the scalar cache in one load.  Behind the group's last token it brings other groups', or
+    // what lies behind perm in the table, where the unit list alone is longer than 60 bytes; none of those is used.  (One load a
+    // token, each at an address of its own, and a choice by branches stood in front of the requests: launches of one round of work groups of
+    // ranks up to 32 lasted longer than those of the units that walked their strips.  us a call, such units / a load a token / this way, 4096
+    // columns: 17 tiles, rank 16 10.9 / 11.6 / 10.7, 32 tiles 12.3 / 12.5 / 11.7; 4096 features, 24 tiles, rank 8 14.1 / 14.4 / 13.8.  Ranks up to 32
+    // of many tokens, where the memory is busy anyhow, lose by it: 19,600 tokens, rank 16, 4096 columns 75.3 / 73.5 / 74.3, 8192 145 / 136.4 / 136.9.)
+    const i32x16 row = *reinterpret_cast<const i32x16 *>(perm + u.perm_off + (nt > 0 ? kTokTile * wave : 0));
 
     // Chunk c of the tile of strip s into LDS (HELD > 1: of all strips), 1 KB per wavefront and step, nothing through registers: sub-block
     // b and k step st take 64 pieces in operand order whatever the rank, so that the reads' addresses differ by constants.  Rank
@@ -1573,7 +1596,11 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
                     kp = 8 * kp < r8 ? kp : 0;
 #pragma unroll
                     for (int bb = 0; bb < 2; ++bb) {
-                        const int b = 2 * wave + bb;
+                        // Ranks of 65 to 128, where half of the tile is asked for at a time and in front of the products: the tiles of tokens
+                        // begin with different sub-blocks, not all of an XCD's work groups with the same lines of its L2.  us a call, 512 features,
+                        // rank 128, in order / in turn: 4096 columns, 32 tiles 18.0 / 17.6, 19,600 tokens 87.7 / 85.9; 14336 columns 258.5 / 255.0; above
+                        // rank 128 level, up to rank 64 1 % slower.
+                        const int b = (2 * wave + bb + (KSTEPS == 4 && CHUNKS == 1 ? u.tok0 >> 6 : 0)) & 7;
                         dma16_to_lds(gtile + (int64_t)(s + h) * tile_pieces + (b * (r8 >> 3) + kp) * 16 + n,
                                      ltile + ((h * 8 + b) * KSTEPS + st) * 64);
                     }
@@ -1640,7 +1667,7 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
         }
     };
 
-    // unconditional (rows of absent tokens are the last token's: a per-lane condition around a 16-byte load makes the compiler split it
+    // unconditional (rows of absent tokens are the wavefront's first token's: a per-lane condition around a 16-byte load makes the compiler split it
     // into four masked 4-byte loads)
     auto fetch_y = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
@@ -1651,9 +1678,11 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
     if (nt > 0) {
         load_v(0);
         __builtin_amdgcn_sched_barrier(0);
+        int mine[4];
+        rows_by_quarter(row, mine);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int r = kq == 0 ? row[e] : kq == 1 ? row[4 + e] : kq == 2 ? row[8 + e] : row[12 + e];
+            const int r = 4 * kq + e < nt ? mine[e] : row[0];
             yrow[e] = y + (int64_t)r * ldy + u.p0 + c0 + 8 * n;
         }
         fetch_y(0);
@@ -1715,6 +1744,12 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
     }
 }
 
+// All of a unit that its work groups use, in one trip to the scalar cache and not field by field where each is first needed.
+static __device__ __forceinline__ void load_big_unit(const Unit &u)
+{
+    asm volatile("" ::"s"(u.w_off), "s"(u.v_off), "s"(u.r8), "s"(u.ntok), "s"(u.p0), "s"(u.pn), "s"(u.scale), "s"(u.perm_off), "s"(u.tok0));
+}
+
 template <bool VF32>
 static __device__ __forceinline__ void expand_big_dispatch(const Unit &u, int c0, const int32_t *__restrict__ perm,
                                                            const uint16_t *__restrict__ arena,
@@ -1753,7 +1788,8 @@ struct BigPlace {
             to = more.first_unit[s + 1];
             subs = more.subs[s];
         }
-        const int t = b >> 3, q = (int)((unsigned)t / (unsigned)subs);
+        const int t = b >> 3;
+        const int q = (subs & (subs - 1)) ? (int)((unsigned)t / (unsigned)subs) : t >> __builtin_ctz(subs);
         unit = from + 8 * q + (b & 7);
         if (unit >= to) unit = -1;
         c0 = (t - q * subs) * (kBigStrips * kStrip);
@@ -2171,9 +2207,12 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_big(const Unit *__restri
 {
     __shared__ __attribute__((aligned(16))) char lds[kBigTile];
     const BigPlace p(blockIdx.x, n_first, subs, more);
-    if (p.unit < 0 || p.c0 >= units[p.unit].pn) return;
+    if (p.unit < 0) return;
+    const Unit &u = units[p.unit];
+    load_big_unit(u);
+    if (p.c0 >= u.pn) return;
     if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 0);
-    expand_big_dispatch<VF32>(units[p.unit], p.c0, perm, arena, v_in, y, ldy, lds, sy);
+    expand_big_dispatch<VF32>(u, p.c0, perm, arena, v_in, y, ldy, lds, sy);
     if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 4);
 }
 
@@ -2242,9 +2281,12 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_mixed(const Unit *__rest
     const int b = blockIdx.x;
     if (b < big_grid) {
         const BigPlace p(b, n_first, subs, more);
-        if (p.unit < 0 || p.c0 >= big_units[p.unit].pn) return;
+        if (p.unit < 0) return;
+        const Unit &u = big_units[p.unit];
+        load_big_unit(u);
+        if (p.c0 >= u.pn) return;
         if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 0);
-        expand_big_dispatch<false>(big_units[p.unit], p.c0, perm, arena, nullptr, y, ldy, lds, sy);
+        expand_big_dispatch<false>(u, p.c0, perm, arena, nullptr, y, ldy, lds, sy);
         if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 4);
     } else {
         [[maybe_unused]] const int n_big = more.n ? more.first_unit[more.n] : n_first;

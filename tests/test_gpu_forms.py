@@ -203,6 +203,34 @@ def test_a_row_has_the_same_bits_wherever_its_token_sits(in_features, groups, cu
     dp.close()
 
 
+@pytest.mark.parametrize("n_out", [128, 384, 640])
+@pytest.mark.parametrize("groups", [
+    [(33, 16)], [(47, 64)], [(64, 128)], [(65, 256)],               # the list of token indices ends within a wavefront's 16, or with them
+    [(81, 8), (40, 32), (35, 72), (113, 200)],                      # other groups' tokens follow
+    [(600, 128), (577, 96)],                                        # more tiles of 64 tokens than a tile of B^T has sub-blocks
+], ids=lambda g: "-".join(f"{n}x{r}" for n, r in g))
+def test_rows_of_64_token_expand_units(groups, n_out):
+    """A wavefront reads its tokens' indices 16 at a time, also where the group has fewer; rows of absent tokens stay as they are."""
+    b = _batch(192, n_out, groups, idle=0, seed=n_out)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(heavy_min_batch=1))
+    ws = torch.full((max(L.lora_apply_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    v = torch.full((L.lora_segments_info(seg)["v_floats"],), float("nan"), dtype=torch.float32, device="cuda")
+    x, apart = G.bits_to_dev(x_bits), G.bits_to_dev(y0)
+    y = torch.cat([G.bits_to_dev(y0), torch.zeros(16, n_out, dtype=torch.bfloat16, device="cuda")])
+    L.lora_apply(dp.pool, seg, x, y[:b.T], ws)
+    L.lora_shrink(dp.pool, seg, x, v, ws)
+    L.lora_expand(dp.pool, seg, v, apart)
+    torch.cuda.synchronize()
+    assert (y[b.T:] == 0).all()
+    want = G.oracle_apply(dp, x_bits, y0)
+    for got in (y[:b.T], apart):
+        G.check_parity(G.dev_to_bits(got), want, y0, b.token_adapter)
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 @pytest.mark.parametrize("in_features, groups", [(4096, [(900, 64)]), (4096, [(128, 256)] * 4), (9024, [(65, 128)] * 11)])
 def test_small_batches_of_token_heavy_units(in_features, groups):
     """Fewer than 1024 tokens: the whole apply, the halves apart, the adapted layer's shrink (that they are token-heavy is tested in
