@@ -212,8 +212,8 @@ typedef struct {
     int32_t heavy_k_cut_max_units; /* token-heavy shrink units are cut along k while the cut units stay    *
                                     * within this count (built in: 1 to 4 slices by estimated time)        */
     int32_t big_runs_max_units;    /* 64-token expand units take their columns in 8 runs or more, not 4, while *
-                                    * the launch stays within this many of them (512) and the runs are of 1, *
-                                    * 2, 4, 6, .. strips of 128 columns                                      */
+                                    * the launch stays within this many of them (512) and the runs are not    *
+                                    * of 3, 5 or 7 strips of 128 columns                                     */
 } lora_plan_options_t;
 #define LORA_PLAN_OPTIONS_DEFAULT {-1, -1, -1, -1, -1, 0u, -1, -1, -1, -1, -1}
 

@@ -673,9 +673,11 @@ static int choose_heavy_k_slices(HeavyShrink &h, int in, int max_slices)
 // 21.7 / 21.7 / 20.9, 63 tiles 32.9 / 32.7 / 34.6 / 34.8; rank 128, 16 tiles 14.2 / 14.3 / 13.4 / 13.5, 63 tiles 25.2 / 25.1 / 25.6 / 25.7; rank 16, 16
 // tiles 10.5 / 10.5 / 10.1 / 10.3, 63 tiles 18.4 throughout; 1024 columns, rank 256, 16 tiles 16.6 / 14.5 / 14.4 / 14.3, 63 tiles 20.4 / 20.4 / 21.6 /
 // 21.6, 125 tiles 27.8 / 27.7 / 27.7 / 32.3.
-// Runs of 3, 5, .. strips are passed over: the last work group of each would take half of its columns.  With / without them, 512 features:
+// Runs of 3, 5 or 7 strips are passed over: the last work group of each would take half of its columns.  With / without them, 512 features:
 // 3072 columns, 62 tiles, rank 16 17.1 / 15.3, rank 256 35.6 / 28.8; 5120 columns, 32 tiles, rank 128 22.4 / 19.8; 14336 columns, 32 tiles, rank 128
-// 37.4 / 34.5; 11008 columns, 50 tiles, rank 256 57.5 / 55.5; but 5632 columns, 24 tiles, rank 128, one round of work groups either way, 18.7 / 19.3.
+// 37.4 / 34.5; but 5632 columns, 24 tiles, rank 128, one round of work groups either way, 18.7 / 19.3.  Beside decode-sized units the same with
+// less of a difference.  Of longer ones the half is less than the order is worth: by 50 to 56 tiles in groups of 1 or 4, with and without
+// decode-sized units, runs of 11 strips (11008 columns) 0.4 % faster than runs of 22, of 13 (13056 columns) 1.5 %.
 static const int kBigRunsWorkGroupsPerComputeUnit = 2;
 
 extern "C" lora_status_t lora_set_whole_k_limit(int32_t max_units)
@@ -1375,7 +1377,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     auto run_cols = [&](int runs) { return std::min(out, std::max(runs > 4 ? 128 : 512, (out / runs + 127) / 128 * 128)); };
     for (int runs = 64; runs >= 8 && big_runs == 4 && !(lean && sg->opts.big_runs_max_units < 0); runs /= 2)
         if (big_tiles * std::min(runs, out / 128) * n_projections <= opt_big_runs_max_units(sg) &&
-            (run_cols(runs) == 128 || run_cols(runs) % lora::kBigCols == 0))
+            (run_cols(runs) == 128 || run_cols(runs) % lora::kBigCols == 0 || run_cols(runs) > 7 * 128))
             big_runs = runs;
     for (int32_t si : order) {
         const SegRec &r = sg->segs[si];

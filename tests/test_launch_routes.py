@@ -566,9 +566,10 @@ def test_work_groups_per_compute_unit_of_64_token_expand_units(recorder, outs, g
 @pytest.mark.parametrize("out, tiles, units", [
     (14336, 32, 32 * 8), (3072, 63, 63 * 4), (5632, 32, 32 * 8), (5120, 24, 24 * 4),  # 16 runs would have 7 strips, 8 have 3, 16 3, 16 3 and 8 5
     (14336, 16, 16 * 28), (4096, 32, 32 * 16), (1024, 63, 63 * 8),                    # runs of 4 strips, 2 and one
+    (9216, 62, 62 * 8), (11008, 50, 50 * 8),                                          # of 9 and 11
 ])
 def test_runs_of_columns_hold_whole_work_groups(recorder, out, tiles, units):
-    """A work group of 64-token expand units takes two strips of 128 columns: runs of more and an odd number of strips are passed over."""
+    """A work group of 64-token expand units takes two strips of 128 columns: runs of 3, 5 or 7 are passed over."""
     b = Batch(512, out, [(64 * tiles, 64)])
     seg = b.build()
     assert b.launches(recorder, seg)[-1] == ("expand_big", units)
