@@ -2230,7 +2230,6 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_parts(const Unit *__rest
 // for their tokens' v through the counters.
 __global__ __launch_bounds__(kThreads, 4) void k_apply_fused(const Unit *__restrict__ shrink_units, int n_shrink,
                                                           const Unit *__restrict__ expand_units,
-                                                          const int32_t *__restrict__ /* perm */,
                                                           const uint16_t *__restrict__ arena,
                                                           const uint16_t *__restrict__ x, int64_t ldx, int in,
                                                           int k_slice_len, float *__restrict__ parts, int n_slices,
@@ -3147,7 +3146,7 @@ hipError_t launch_apply_fused(const LaunchCtx &cs, const LaunchCtx &ce, const ui
     if (total <= 0) return hipSuccess;
     if (!sync || !sync->parts) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_apply_fused, dim3(total), dim3(kThreads), 0, stream, cs.units, cs.n_units, ce.units,
-                       ce.perm, cs.arena, x, ldx, cs.in_features, k_slice_len, parts, n_slices, slice_stride, y, ldy,
+                       cs.arena, x, ldx, cs.in_features, k_slice_len, parts, n_slices, slice_stride, y, ldy,
                        make_sync(sync, 1));
     return hipGetLastError();
 }
