@@ -1,5 +1,7 @@
 """Registers of the built kernels, from the metadata the compiler leaves in the library's code object; when it is out of date."""
+import json
 import os
+import subprocess
 
 import msgpack
 import pytest
@@ -31,6 +33,9 @@ def _kernels():
     ("k_linear_loraE", 0),
     ("k_shrink_halvesE", 0),
     ("k_expand_partsE", 0),
+    # up to 126 of the 128 that four work groups on a compute unit leave; their waits count memory operations too
+    ("k_expand_bigILb0E", 0),
+    ("k_expand_bigILb1E", 0),
     ("k_expand_mixedILNS_6SlicesE0E", 0),
     ("k_expand_mixedILNS_6SlicesE1E", 0),
     ("k_linear_roundsILi4ELi4ELi2E", 0),  # 244 of 256
@@ -69,6 +74,14 @@ def test_expand_kernels_that_read_complete_v_hold_no_code_that_adds_slices_up():
     """With it, never run, they took other registers, and a mixed launch 4 % longer."""
     assert _code_bytes("k_expandILb0ELb0E") < _code_bytes("k_expand_partsE")
     assert _code_bytes("k_expand_mixedILNS_6SlicesE0E") < _code_bytes("k_expand_mixedILNS_6SlicesE1E")
+
+
+def test_kernels_whose_profiles_are_quoted_exist():
+    """bench.py names the kernel of a phase from profiles/measured.json."""
+    with open(os.path.join(build.ROOT, "profiles", "measured.json")) as f:
+        quoted = json.load(f)["phase_kernels"].values()
+    names = subprocess.run(["c++filt", *_kernels()], capture_output=True, text=True, check=True).stdout.splitlines()
+    assert set(quoted) <= {name.removeprefix("void ").split("(")[0] for name in names}
 
 
 def _preloaded():
