@@ -863,8 +863,8 @@ static int opt_heavy_min_batch(const lora_segments *sg) { return sg->opts.heavy_
 // 31.6 / 19.7, rank 256 93.6 / 32.9, 256 tokens, rank 256 27.9 / 30.1; above rank 64 the token-heavy units' walk is longer: 646 tokens of rank 128,
 // 1600 -> 2304, 14.0 / 17.7, 726 tokens, 4032 -> 512, 16.6 / 20.2, 700 tokens, 9024 -> 1536, 31.2 / 22.8.  Over 150 random batches the
 // median of those behind the line gains 40 % (lora_apply, lora_apply_multi and the halves apart; 167 % at most), in lora_linear, which uses the
-// shrink half only, -1 to 27 %.  The halves apart lose up to 6 % at small widths just beyond 8192 features, rank 64 (8256 -> 640, 800 tokens,
-// 15.4 / 16.4), and had lost more where other groups are small, which then take launches of their own (803 tokens of 16 prompts there 16.9 / 27.6).
+// shrink half only, -3 to 27 %.  Just beyond 8192 features, rank 64, the halves apart gain least (8256 -> 640, 800 tokens, 18.0 / 14.6), and had
+// lost where other groups are small, which then take launches of their own (803 tokens of 16 prompts there 16.9 / 27.6).
 static bool small_batch_token_heavy(const lora_segments *sg, const lora_pool *pool, const std::vector<int32_t> &count, int n_active,
                                     int heavy_min_tokens)
 {
