@@ -119,6 +119,7 @@ struct lora_segments {
     int n_prefill_hi;       // how many of prefill_units are above rank 64
     int n_heavy_units;      // how many of them hold tokens (the others fill the XCDs' lists up)
     int heavy_top_rank;     // their largest padded rank
+    int n_big_hi;           // how many of expand_big_units are above rank 128
     std::vector<lora::BigSection> big_sections;  // expand_big_units in runs of equally wide ones: one per projection, or fewer
     int heavy_k_slices;     // k-slices of the token-heavy shrink units (1: they take the whole of k)
     bool small_heavy;       // token-heavy units in a batch of fewer than kPrefillMinBatch tokens (see small_batch_token_heavy)
@@ -1343,6 +1344,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
     sg->has_big_units = false;
     sg->n_prefill_hi = 0;
     sg->heavy_top_rank = 0;
+    sg->n_big_hi = 0;
     sg->big_sections.clear();
     // (per projection, whatever the number of projections: lora_apply_multi gives the bits of separate applies)
     int heavy_k_slices = 1;
@@ -1464,6 +1466,7 @@ static lora_status_t plan_into(lora_segments *sg, const lora_pool *pool, const i
             u.sync_n = sync_n;
             fill_tokens(u, r);
             (etile > lora::kTokTile ? sg->expand_big_units : sg->expand_units).push_back(u);
+            if (etile > lora::kTokTile && r.r8 > 128) ++sg->n_big_hi;
         };
         const int ncb = (out + cols - 1) / cols;
         if (etile > lora::kTokTile && ncb % 8 == 0) {
@@ -1735,6 +1738,7 @@ static lora_status_t plan_multi_into(lora_segments *sg, const std::vector<const 
         sg->n_prefill_hi += tmp->n_prefill_hi;
         sg->n_heavy_units += tmp->n_heavy_units;
         sg->n_uncut_work += tmp->n_uncut_work;
+        sg->n_big_hi += tmp->n_big_hi;
         for (const lora::BigSection &b : tmp->big_sections) {
             if (!sg->big_sections.empty() && sg->big_sections.back().cols == b.cols)
                 sg->big_sections.back().n_units += b.n_units;
@@ -2253,6 +2257,7 @@ static lora::LaunchCtx ctx_for(const uint16_t *arena, int in_features, int out_f
     c.n_units = (int)list.size();
     c.n_work = kind == kPrefill ? sg->n_heavy_units : kind == kPrefillUncut ? sg->n_uncut_work : c.n_units;
     c.top_rank = sg->heavy_top_rank;
+    c.n_high = sg->n_big_hi;
     c.sections = sg->big_sections.data();
     c.n_sections = (int)sg->big_sections.size();
     c.in_features = in_features;

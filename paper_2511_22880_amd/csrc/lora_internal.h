@@ -88,6 +88,7 @@ struct LaunchCtx {
     int n_units;
     int n_work;    // of n_units, those that hold tokens (lists of token-heavy shrink units are filled up with others)
     int top_rank;  // lists of token-heavy shrink units: the largest padded rank
+    int n_high;    // lists of 64-token expand units: how many are above rank 128
     // lists of 64-token expand units: in which runs of equally wide ones (host memory)
     const BigSection *sections;
     int n_sections;
@@ -173,6 +174,28 @@ inline int64_t big_places(const LaunchCtx &c)
 // 24.7; 8192, two prompts of 900, rank 16 18.3 / 17.4, rank 128 25.7 / 24.2; 14336, 1024 tokens, rank 16 17.9 / 17.7, two of 512, rank 128 25.2 /
 // 24.3, but rank 64 19.6 / 20.2; 1800 tokens, 8192, rank 64 18.7 / 19.0; over 160 such batches 2 % faster.
 inline bool big_spread(const LaunchCtx &c) { return c.top_rank <= 128 && big_places(c) > 4 * kComputeUnits; }
+// lora_expand's launches of these units, v as the caller has it (fp32 in rows): whether work groups walk up to `walk_strips` strips of their unit
+// and load v once (k_expand_walk, two on a compute unit) or take 256 columns as elsewhere.  The latter load v twice a strip above rank 128, the
+// former fill the chip only with enough units; where most units are above rank 128 an estimate decides (in us at rank 256; other ranks differ by
+// a factor common to both).  lora_expand alone, us, 256 columns a work group / walks: 4096 columns, rank 256, 31 tiles of 64 tokens 16.0 / 16.3, 48 23.7 /
+// 25.3, 63 30.1 / 26.1, 125 53.6 / 43.7, 300 119 / 114; 1024 columns, 63 tiles 10.0 / 12.4, 300 36.6 / 43.1; 2048 columns, 31 tiles 9.2 / 11.9; 8064 columns, rank
+// 192, 17 tiles 19.2 / 20.7, 125 87 / 67; 14336 columns, rank 160, 125 tiles 139 / 105.  Half of the units at rank 8 and half at 256 level; one group of
+// eight above rank 128 the walks 38 % slower; up to rank 128 (one chunk, v once a strip) level or slower (4096 columns, 125 tiles 31.2 / 29.4; 8064 columns,
+// 63 tiles, rank 96 29.3 / 29.9).
+inline int walk_strips(const LaunchCtx &c)
+{
+    const int most = c.sections[0].cols / 128, parts = most < 2 * kComputeUnits / c.n_units ? most : 2 * kComputeUnits / c.n_units;
+    return parts > 1 ? (most + parts - 1) / parts : most;
+}
+inline bool expand_walks(const LaunchCtx &c)
+{
+    if (c.n_sections != 1 || 2 * c.n_high <= c.n_units) return false;
+    const int most = c.sections[0].cols / 128, strips = walk_strips(c);
+    const int64_t walks = (int64_t)c.n_units * ((most + strips - 1) / strips), round = 2 * kComputeUnits;
+    const double rounds = walks <= round ? 1.0 : 0.5 * ((double)((walks + round - 1) / round) + (double)walks / round);
+    const double by_256 = 1.5 + (most == 1 ? 3.7 : 6.9) * (double)((big_places(c) + kComputeUnits - 1) / kComputeUnits);
+    return rounds * (6.5 + 4.7 * strips) < 1.06 * by_256;
+}
 
 // A mixed batch's shrink in one launch: the token-heavy units of `heavy` (n_hi of them above rank 64),
 // then the k-slice units of `c`, which leave partial sums in `parts` and complete v through `sync` where

@@ -1551,6 +1551,17 @@ static __device__ __forceinline__ void rows_by_quarter(const i32x16 &v, int (&mi
           "s"(v[11]), "s"(v[12]), "s"(v[13]), "s"(v[14]), "s"(v[15]));
 }
 
+// eight columns of y, plus scale times element e of the sums of each
+static __device__ __forceinline__ uint4 add_scaled(uint4 yy, float scale, const f32x4 (&acc)[8], int e)
+{
+    uint4 o;
+    o.x = pack_bf16_rne(bf16_bits_to_f32(yy.x & 0xFFFFu) + scale * acc[0][e], __uint_as_float(yy.x & 0xFFFF0000u) + scale * acc[1][e]);
+    o.y = pack_bf16_rne(bf16_bits_to_f32(yy.y & 0xFFFFu) + scale * acc[2][e], __uint_as_float(yy.y & 0xFFFF0000u) + scale * acc[3][e]);
+    o.z = pack_bf16_rne(bf16_bits_to_f32(yy.z & 0xFFFFu) + scale * acc[4][e], __uint_as_float(yy.z & 0xFFFF0000u) + scale * acc[5][e]);
+    o.w = pack_bf16_rne(bf16_bits_to_f32(yy.w & 0xFFFFu) + scale * acc[6][e], __uint_as_float(yy.w & 0xFFFF0000u) + scale * acc[7][e]);
+    return o;
+}
+
 // KSTEPS: 32-wide steps of a chunk of the rank (1, 2 or 4); CHUNKS of 128 of it.
 template <int KSTEPS, int CHUNKS, bool VF32>
 static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, const int32_t *__restrict__ perm,
@@ -1651,19 +1662,7 @@ static __device__ __forceinline__ void expand_big_body(const Unit &u, int c0, co
     auto update = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (4 * kq + e < nt) {
-                const uint4 yy = yv[s][e];
-                uint4 o;
-                o.x = pack_bf16_rne(bf16_bits_to_f32(yy.x & 0xFFFFu) + scale * acc[0][e],
-                                    __uint_as_float(yy.x & 0xFFFF0000u) + scale * acc[1][e]);
-                o.y = pack_bf16_rne(bf16_bits_to_f32(yy.y & 0xFFFFu) + scale * acc[2][e],
-                                    __uint_as_float(yy.y & 0xFFFF0000u) + scale * acc[3][e]);
-                o.z = pack_bf16_rne(bf16_bits_to_f32(yy.z & 0xFFFFu) + scale * acc[4][e],
-                                    __uint_as_float(yy.z & 0xFFFF0000u) + scale * acc[5][e]);
-                o.w = pack_bf16_rne(bf16_bits_to_f32(yy.w & 0xFFFFu) + scale * acc[6][e],
-                                    __uint_as_float(yy.w & 0xFFFF0000u) + scale * acc[7][e]);
-                st16_stream(yrow[e] + s * kStrip, o);
-            }
+            if (4 * kq + e < nt) st16_stream(yrow[e] + s * kStrip, add_scaled(yv[s][e], scale, acc, e));
         }
     };
 
@@ -1764,6 +1763,129 @@ static __device__ __forceinline__ void expand_big_dispatch(const Unit &u, int c0
         expand_big_body<4, 1, VF32>(u, c0, perm, arena, v_in, y, ldy, lds, sy);
     else
         expand_big_body<4, 2, VF32>(u, c0, perm, arena, v_in, y, ldy, lds, sy);
+}
+
+// ------------------------------------------------------------------------------------------------
+// The same units with v as the caller of lora_expand has it, fp32 in rows, in launches mostly of ranks above 128 (expand_walks): a work group walks
+// strips of its unit and each wavefront loads its tokens' v once, as bf16 hi + lo of every k step in registers.  There v is more bytes than
+// a strip's rows of y, 32 of each of 16 rows at a time, and work groups of two strips and two chunks of the rank load it four times.
+// A launch of few units takes several work groups a unit, as many as stay within two per compute unit.
+// The tile of a strip is 128 * r8 * 2 bytes: two buffers of 32 KB up to rank 128, above one of 64 KB, filled between two strips; while a
+// strip computes, the next one's rows of y (and tile) are on their way.
+// ------------------------------------------------------------------------------------------------
+constexpr int kWalkTile = 64 * 1024;
+
+template <int KSTEPS>
+static __device__ __forceinline__ void expand_walk_body(const Unit &u, int c0, int nstrips, const int32_t *__restrict__ perm,
+                                                        const uint16_t *__restrict__ arena, const float *__restrict__ v_in,
+                                                        uint16_t *__restrict__ y, int64_t ldy, char *lds)
+{
+    static_assert(KSTEPS <= 8, "ranks up to 256");
+    constexpr bool TWO = KSTEPS <= 4;  // buffers
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6, wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int n = lane & 15;
+    const int kq = lane >> 4;
+    const int r8 = u.r8;
+    const uint4 zero = {0u, 0u, 0u, 0u};
+    const int32_t *toks = perm + u.perm_off;
+    const float scale = u.scale;
+    const int tile_pieces = 16 * r8;  // 16-byte pieces in one strip's tile
+    const int nt = min(kTokTile, u.ntok - kTokTile * wave);  // may be <= 0: the wavefront only helps copying
+    uint4 vh[KSTEPS], vl[KSTEPS];
+    bool j_ok[KSTEPS];
+#pragma unroll
+    for (int st = 0; st < KSTEPS; ++st) {
+        const int j = 32 * st + 8 * kq;
+        j_ok[st] = j < r8;
+        const bool ok = n < nt && j_ok[st];
+        bf16x8 h, l;
+        load_v_operand(v_in + u.v_off + (int64_t)(ok ? kTokTile * wave + n : 0) * r8 + (j_ok[st] ? j : 0), ok, h, l);
+        vh[st] = ok ? __builtin_bit_cast(uint4, h) : zero;
+        vl[st] = ok ? __builtin_bit_cast(uint4, l) : zero;
+    }
+    // the MFMA leaves tokens 4*kq + e (e = 0..3), columns 8*n .. 8*n+7 of the strip in this lane
+    uint16_t *yrow[4];
+    bool y_ok[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        y_ok[e] = 4 * kq + e < nt;
+        yrow[e] = y + (int64_t)toks[y_ok[e] ? kTokTile * wave + 4 * kq + e : 0] * ldy + u.p0 + c0 + 8 * n;
+    }
+    const uint4 *gtile = reinterpret_cast<const uint4 *>(arena + u.w_off + (int64_t)c0 * r8);  // strip s starts tile_pieces * s further
+    uint4 *ltile = reinterpret_cast<uint4 *>(lds);
+    // From the first strip on, or (walks and rows of whole multiples of 4 KB) every tile of tokens of a group from another one: all units walk at
+    // about the same pace and would ask a part of the memory's channels for y at any one time.  (19,675 tokens, rank 128, 8192 columns 184 / 167 us.)
+    const int turn = nstrips * kStrip * 2 % 4096 == 0 && (ldy * 2) % 4096 == 0 ? (u.tok0 >> 6) * 5 % nstrips : 0;
+    auto strip_at = [&](int i) __attribute__((always_inline)) { return i + turn < nstrips ? i + turn : i + turn - nstrips; };
+    // 1 KB per wavefront and step, nothing through registers; the tile is a multiple of 64 pieces, so a wavefront's is whole or absent
+    auto copy_tile = [&](int buf, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 2 * KSTEPS; ++q) {
+            const int piece0 = 64 * wave_u + kThreads * q;
+            if (piece0 < tile_pieces) dma16_to_lds(gtile + (int64_t)s * tile_pieces + piece0 + lane, ltile + buf * 2048 + piece0);
+        }
+    };
+    uint4 ya[4], yb[4];
+    auto fetch_y = [&](int s, uint4(&yv)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) yv[e] = ld16_stream(yrow[e] + s * kStrip);  // unconditional, as above
+    };
+    auto compute = [&](int s, int buf, const uint4(&yv)[4]) __attribute__((always_inline)) {
+        if (nt <= 0) return;
+        const uint4 *t = ltile + buf * 2048;
+        f32x4 acc[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int st = 0; st < KSTEPS; ++st) {
+                if (32 * st < r8) {  // uniform
+                    // (sub-block b, rank piece 4*st + kq, column slot n; lanes beyond the padded rank read piece 0, their v is zero)
+                    const uint4 wv = t[(b * (r8 >> 3) + (j_ok[st] ? 4 * st + kq : 0)) * 16 + n];
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vh[st]), as_bf16x8(wv), acc[b], 0, 0, 0);
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vl[st]), as_bf16x8(wv), acc[b], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (y_ok[e]) st16_stream(yrow[e] + s * kStrip, add_scaled(yv[e], scale, acc, e));
+    };
+
+    // (stores_done waits by the builtin, so the compiler knows that y is there; behind wait_vm<0> it waits once more, for what has been asked
+    // for since: rank 192, 14336 columns, 63 tiles 58.8 / 62.2 us)
+    copy_tile(0, strip_at(0));
+    fetch_y(strip_at(0), ya);
+    stores_done();
+    __syncthreads();
+    for (int s = 0; s < nstrips; s += 2) {
+        // even strips from buffer 0, odd strips from buffer 1 (above rank 128 all from the one buffer, when everyone has read the strip before)
+        if (s + 1 < nstrips) {
+            if (TWO) copy_tile(1, strip_at(s + 1));
+            fetch_y(strip_at(s + 1), yb);
+        }
+        compute(strip_at(s), 0, ya);
+        if (s + 1 >= nstrips) break;
+        if (!TWO) {
+            __syncthreads();
+            copy_tile(0, strip_at(s + 1));
+        }
+        stores_done();
+        __syncthreads();
+        if (s + 2 < nstrips) {
+            if (TWO) copy_tile(0, strip_at(s + 2));
+            fetch_y(strip_at(s + 2), ya);
+        }
+        compute(strip_at(s + 1), TWO ? 1 : 0, yb);
+        if (s + 2 >= nstrips) break;
+        if (!TWO) {
+            __syncthreads();
+            copy_tile(0, strip_at(s + 2));
+        }
+        stores_done();
+        __syncthreads();
+    }
 }
 
 // Which unit and which of its strips work group b of a launch of 64-token units takes: a row of 8 units takes 8 * subs work groups,
@@ -2214,6 +2336,29 @@ __global__ __launch_bounds__(kThreads, 4) void k_expand_big(const Unit *__restri
     if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 0);
     expand_big_dispatch<VF32>(u, p.c0, perm, arena, v_in, y, ldy, lds, sy);
     if (p.c0 == 0) LORA_CLOCK_E_UNIT(p.unit, 4);
+}
+
+// ... and with v from the caller in launches mostly of ranks above 128: a work group walks `strips` of its unit's.
+__global__ __launch_bounds__(kThreads, 2) void k_expand_walk(const Unit *__restrict__ units, int n_units, int strips,
+                                                             const int32_t *__restrict__ perm, const uint16_t *__restrict__ arena,
+                                                             const float *__restrict__ v_in, uint16_t *__restrict__ y, int64_t ldy)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kWalkTile];
+    const int part = (int)(blockIdx.x / (unsigned)n_units), unit = (int)blockIdx.x - part * n_units;
+    const Unit &u = units[unit];
+    const int r8 = u.r8, c0 = part * strips * kStrip;
+    if (c0 >= u.pn) return;
+    const int n = min(strips, (u.pn - c0) / kStrip);
+    if (c0 == 0) LORA_CLOCK_E_UNIT(unit, 0);
+    if (r8 <= 32)
+        expand_walk_body<1>(u, c0, n, perm, arena, v_in, y, ldy, lds);
+    else if (r8 <= 64)
+        expand_walk_body<2>(u, c0, n, perm, arena, v_in, y, ldy, lds);
+    else if (r8 <= 128)
+        expand_walk_body<4>(u, c0, n, perm, arena, v_in, y, ldy, lds);
+    else
+        expand_walk_body<8>(u, c0, n, perm, arena, v_in, y, ldy, lds);
+    if (c0 == 0) LORA_CLOCK_E_UNIT(unit, 4);
 }
 
 // Units of up to 16 tokens whose v the launch before left as k-slices' partial sums.
@@ -3117,7 +3262,12 @@ hipError_t launch_expand(const LaunchCtx &c, bool big, const float *v_in, uint16
     if (!sync && !v_in) return hipErrorInvalidValue;
     const Sync sy = make_sync(sync, 0);
     const dim3 g(c.n_units), b(kThreads);
-    if (big) {
+    if (big && !sync && expand_walks(c)) {
+        const int most = c.sections[0].cols / kStrip, strips = walk_strips(c);
+        const int64_t grid = (int64_t)c.n_units * ((most + strips - 1) / strips);
+        if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_expand_walk, dim3((unsigned)grid), b, 0, stream, c.units, c.n_units, strips, c.perm, c.arena, v_in, y, ldy);
+    } else if (big) {
         if (c.n_sections > kMaxBigSections) return hipErrorInvalidValue;
         const BigGrid bg(c);
         if (bg.places > 0x7FFFFFFF) return hipErrorInvalidValue;

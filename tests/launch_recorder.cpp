@@ -7,7 +7,7 @@
 #include <string>
 
 static std::string g_log, g_forms;
-static int g_capturing, g_big_spread;
+static int g_capturing, g_big_spread, g_walks;
 static struct Memory { uintptr_t from; size_t bytes; hipMemoryType type; } g_memory[8];  // what this runtime knows of, besides what it gave out
 static int g_n_memory;
 
@@ -37,6 +37,8 @@ const char *recorder_take_forms()
 }
 // whether the last launch of 64-token expand units asked for three work groups per compute unit
 int recorder_big_spread() { return g_big_spread; }
+// ... and how many strips of their unit its work groups walk (0: they take 256 columns)
+int recorder_walks() { return g_walks; }
 // 1: the stream captures; 2: it is the legacy stream and a blocking stream captures
 void recorder_capture(int on) { g_capturing = on; }
 
@@ -112,7 +114,7 @@ hipError_t launch_expand(const LaunchCtx &c, bool big, const float *, uint16_t *
 {
     if (!c.n_units) return hipSuccess;
     if (!big) slices_form(sync);
-    else g_big_spread = big_spread(c);
+    else g_big_spread = big_spread(c), g_walks = !sync && expand_walks(c) ? walk_strips(c) : 0;
     return note((big ? "expand_big" : "expand") + num(c.n_units));
 }
 hipError_t launch_shrink_prefill(const LaunchCtx &c, int, const uint16_t *, int64_t, uint16_t *, uint16_t *, float *, int n_slices, int64_t, float *, const SyncArgs *, hipStream_t)

@@ -231,6 +231,31 @@ def test_rows_of_64_token_expand_units(groups, n_out):
     dp.close()
 
 
+@pytest.mark.parametrize("n_out, runs", [(128, -1), (1152, -1), (2176, 0), (4096, -1), (8192, 0), (12928, -1)])
+@pytest.mark.parametrize("groups", [
+    [(1024, 256)], [(1089, 136)], [(33, 8), (33, 32), (65, 64), (40, 128), (300, 192), (900, 249)], [(64, 160)] * 20, [(63 * 64, 200)],
+], ids=lambda g: f"{len(g)}of{g[-1][0]}x{g[-1][1]}")
+def test_expand_alone_of_ranks_above_128(groups, n_out, runs):
+    """lora_expand in work groups that walk their units, whole or a part, or take 256 columns, by the number of units and their width: one
+    strip, odd numbers of them, strips in turn (runs and rows of whole multiples of 4 KB), units of every rank beside, partial tiles, rows
+    behind the batch."""
+    b = _batch(64, n_out, groups, idle=3, seed=n_out)
+    dp = G.DevicePool(b)
+    x_bits, y0 = b.x_bits(), b.y0_bits("small")
+    seg = L.lora_segments_build(dp.pool, b.token_adapter, options=L.plan_options(big_runs_max_units=runs))
+    v = torch.full((L.lora_segments_info(seg)["v_floats"],), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.full((max(L.lora_workspace_bytes(dp.pool, seg), 256),), 0xFF, dtype=torch.uint8, device="cuda")
+    y = torch.cat([G.bits_to_dev(y0), torch.zeros(16, n_out, dtype=torch.bfloat16, device="cuda")])
+    L.lora_shrink(dp.pool, seg, G.bits_to_dev(x_bits), v, ws)
+    L.lora_expand(dp.pool, seg, v, y[:b.T])
+    torch.cuda.synchronize()
+    assert (y[b.T:] == 0).all()
+    rows = np.unique(np.concatenate([np.arange(0, b.T, 5), np.arange(b.T - 3, b.T)]))
+    G.check_parity(G.dev_to_bits(y[:b.T]), G.oracle_apply(dp, x_bits, y0, rows=rows), y0, b.token_adapter, rows=rows)
+    L.lora_segments_destroy(seg)
+    dp.close()
+
+
 @pytest.mark.parametrize("in_features, groups", [(4096, [(900, 64)]), (4096, [(128, 256)] * 4), (9024, [(65, 128)] * 11)])
 def test_small_batches_of_token_heavy_units(in_features, groups):
     """Fewer than 1024 tokens: the whole apply, the halves apart, the adapted layer's shrink (that they are token-heavy is tested in

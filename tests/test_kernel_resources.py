@@ -36,6 +36,7 @@ def _kernels():
     # up to 126 of the 128 that four work groups on a compute unit leave; their waits count memory operations too
     ("k_expand_bigILb0E", 0),
     ("k_expand_bigILb1E", 0),
+    ("k_expand_walkE", 0),  # 245 of 256
     ("k_expand_mixedILNS_6SlicesE0E", 0),
     ("k_expand_mixedILNS_6SlicesE1E", 0),
     ("k_linear_roundsILi4ELi4ELi2E", 0),  # 244 of 256

@@ -78,6 +78,8 @@ class Batch:
             L.lora_apply_static(self.pools[0], seg, x, y, ldx=self.in_features, ldy=self.out)
         elif call == "shrink":
             L.lora_shrink(self.pools[0], seg, x, v, ws, ldx=self.in_features, ws_bytes=n)
+        elif call == "expand":
+            L.lora_expand(self.pools[0], seg, v, y, ldy=self.out)
         else:
             L.lora_linear(self.pools[0], seg, x, 1 << 43, y, ws, ldx=self.in_features, ldy=self.out, ws_bytes=n)
         return [tuple(int(w) if w.lstrip("-").isdigit() else w for w in line.split())
@@ -572,6 +574,23 @@ def test_runs_of_columns_hold_whole_work_groups(recorder, out, tiles, units):
     b = Batch(512, out, [(64 * tiles, 64)])
     seg = b.build()
     assert b.launches(recorder, seg)[-1] == ("expand_big", units)
+    L.lora_segments_destroy(seg)
+    b.close()
+
+
+@pytest.mark.parametrize("out, groups, strips", [
+    (4096, [(63 * 64, 256)], 4), (14336, [(17 * 64, 160)], 5), (4096, [(300 * 64, 192)], 8),  # whole units, a third of one, several rounds
+    (1024, [(300 * 64, 256)], 0), (2048, [(31 * 64, 256)], 0), (8064, [(17 * 64, 192)], 0),   # narrow; one strip a unit; too few to walk 4
+    (4096, [(63 * 64, 128)], 0), (14336, [(125 * 64, 64)], 0),                              # one chunk of the rank
+    (8064, [(1000, 8), (1000, 256)] * 4, 0), (8064, [(1000, 8), (1100, 256)] * 4, 16),      # half of the units, and more
+])
+def test_expand_alone_walks_units_above_rank_128(recorder, out, groups, strips):
+    """lora_expand's v is fp32 in rows: work groups that load it once, where they fill the chip; lora_apply's launches never."""
+    b = Batch(512, out, groups)
+    seg = b.build()
+    assert _names(b.launches(recorder, seg, "expand")) == ["expand_big"] and recorder.recorder_walks() == strips
+    b.launches(recorder, seg)
+    assert recorder.recorder_walks() == 0
     L.lora_segments_destroy(seg)
     b.close()
 
