@@ -582,7 +582,8 @@ def test_runs_of_columns_hold_whole_work_groups(recorder, out, tiles, units):
     (4096, [(63 * 64, 256)], 4), (14336, [(17 * 64, 160)], 5), (4096, [(300 * 64, 192)], 8),  # whole units, a third of one, several rounds
     (1024, [(300 * 64, 256)], 0), (2048, [(31 * 64, 256)], 0), (8064, [(17 * 64, 192)], 0),   # narrow; one strip a unit; too few to walk 4
     (4096, [(63 * 64, 128)], 0), (14336, [(125 * 64, 64)], 0),                              # one chunk of the rank
-    (8064, [(1000, 8), (1000, 256)] * 4, 0), (8064, [(1000, 8), (1100, 256)] * 4, 16),      # half of the units, and more
+    (8064, [(1000, 8), (1000, 256)] * 4, 0), (8064, [(1000, 8)] * 2 + [(1000, 256)] * 6, 16),  # half of the units, and three quarters
+    (4736, [(130 * 64, 192)], 0),                                                           # a second round of few walks
 ])
 def test_expand_alone_walks_units_above_rank_128(recorder, out, groups, strips):
     """lora_expand's v is fp32 in rows: work groups that load it once, where they fill the chip; lora_apply's launches never."""
