@@ -178,10 +178,10 @@ inline bool big_spread(const LaunchCtx &c) { return c.top_rank <= 128 && big_pla
 // and load v once (k_expand_walk, two on a compute unit) or take 256 columns as elsewhere.  The latter load v twice a strip above rank 128, the
 // former fill the chip only with enough units; where most units are above rank 128 an estimate decides (in us at rank 256; other ranks differ by
 // a factor common to both).  lora_expand alone, us, 256 columns a work group / walks: 4096 columns, rank 256, 31 tiles of 64 tokens 16.0 / 16.3, 48 23.7 /
-// 25.3, 63 30.1 / 26.1, 125 53.6 / 43.7, 300 119 / 114; 1024 columns, 63 tiles 10.0 / 12.4, 300 36.6 / 43.1; 2048 columns, 31 tiles 9.2 / 11.9; 8064 columns, rank
-// 192, 17 tiles 19.2 / 20.7, 125 87 / 67; 4736 columns, 130 tiles, 8 of 520 walks in a second round, 88 / 110; 14336 columns, rank 160, 125 tiles 139 / 105.  Half of the units at rank 8 and half at 256 level; one group of
-// eight above rank 128 the walks 38 % slower; up to rank 128 (one chunk, v once a strip) level or slower (4096 columns, 125 tiles 31.2 / 29.4; 8064 columns,
-// 63 tiles, rank 96 29.3 / 29.9).
+// 25.3, 63 30.1 / 26.1, 125 53.6 / 43.7, 300 119 / 114; 1024 columns, 63 tiles 10.0 / 12.4, 300 36.6 / 43.1; 2048 columns, 31 tiles 9.2 / 11.9; 8064
+// columns, rank 192, 17 tiles 19.2 / 20.7, 125 87 / 67; 4736 columns, 130 tiles, 8 of 520 walks in a second round, 88 / 110; 14336 columns, rank
+// 160, 125 tiles 139 / 105.  Half of the units at rank 8 and half at 256 level; one group of eight above rank 128 the walks 38 % slower; up to
+// rank 128 (one chunk, v once a strip) level or slower (8064 columns, 63 tiles, rank 96 29.3 / 29.9; but 4096 columns, 125 tiles, rank 128 31.2 / 29.4).
 inline int walk_strips(const LaunchCtx &c)
 {
     const int most = c.sections[0].cols / 128, parts = most < 2 * kComputeUnits / c.n_units ? most : 2 * kComputeUnits / c.n_units;
